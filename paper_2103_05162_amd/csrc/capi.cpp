@@ -92,9 +92,7 @@ Plan make_plan(int64_t n, int dim, int algo, int num_clouds) {
     p.prim_hi = take(N * 16);
     p.prim_key = take(N * 8);
     p.dense_list = take(N * 4);
-    // the cell boxes are dead once the primitives are written: the isolated-point
-    // test keeps its occupancy words there
-    p.map_bytes = static_cast<int64_t>(p.cell_hi + N * 16 - p.cell_lo);
+    p.super_cap = static_cast<int64_t>((p.rope - p.node_a) / sizeof(uint4));
   }
   p.cl_lo = p.cl_scale = p.cl_eps2 = p.cl_minpts = p.cl_root = p.cl_end = p.cl_flags = p.cl_ord = 0;
   if (num_clouds > 0) {
@@ -455,6 +453,26 @@ T* at(void* base, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(base) + off);
 }
 
+// The grid's index lives in the hierarchy's buffers (a call builds one of the two)
+// and its bricks in the cell boxes', which are dead once the primitives are written.
+// cell_prim's n + 1 entries run on from `other` into `gamma`.
+fdb::CellIndex cell_index(const fdb::Plan& p, void* ws) {
+  fdb::CellIndex ix{};
+  ix.plan = at<fdb::GridPlan>(ws, p.gplan);
+  ix.supers = at<uint4>(ws, p.node_a);
+  ix.super_cap = p.super_cap;
+  ix.brick_base = at<int>(ws, p.rope);
+  ix.cell_code = at<uint8_t>(ws, p.leaf_rope);
+  ix.cell_prim = at<int>(ws, p.other);
+  ix.bricks = at<uint4>(ws, p.cell_lo);
+  if (p.num_clouds > 0) {
+    ix.cl_lo = at<float4>(ws, p.cl_lo);
+    ix.cl_scale = at<float4>(ws, p.cl_scale);
+    ix.cl_grid = at<int4>(ws, p.cl_ord);  // over the clouds' bounds
+  }
+  return ix;
+}
+
 }  // namespace
 
 extern "C" {
@@ -791,7 +809,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
 
   // DenseBox sizes its grid on the device (k_grid_plan): nothing waits for the GPU
   GridPlan* gplan = at<GridPlan>(ws, plan.gplan);
-  if (densebox) launch_grid_plan(bounds, dim, eps, n, plan.map_bytes, gplan, h->d_info, s);
+  if (densebox) launch_grid_plan(bounds, dim, eps, plan.super_cap, gplan, h->d_info, s);
 
   int cur = 0;
   const uint32_t* perm = nullptr;
@@ -815,9 +833,11 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   ta.t.leaf_size = leaf;
 
   if (densebox) {
+    const CellIndex ix = cell_index(plan, ws);
+    ta.ix = ix;
     st.mark("cell_keys");
-    launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist), s,
-                    false);
+    launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist),
+                    ix.supers, s, false);
     st.mark("sort");
     radix_sort_planned(keys[0], keys[1], vals[0], vals[1], n, gplan, at<uint32_t>(ws, plan.hist),
                        at<uint32_t>(ws, plan.digoff), at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status),
@@ -832,8 +852,8 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
                    at<float4>(ws, plan.cell_lo), at<float4>(ws, plan.cell_hi), at<int>(ws, plan.pflag),
                    at<int>(ws, plan.prim_start), at<int>(ws, plan.prim_cnt),
                    at<float4>(ws, plan.prim_lo), at<float4>(ws, plan.prim_hi), at<uint64_t>(ws, plan.prim_key),
-                   at<int>(ws, plan.dense_list), lab, core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, 0,
-                   nullptr, nullptr, at<int>(ws, plan.ends), at<int>(ws, plan.minorig));
+                   at<int>(ws, plan.dense_list), lab, core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, ix, 0,
+                   nullptr, nullptr, 0, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
   }
   h->last_densebox = densebox;
   if (densebox) {
@@ -842,7 +862,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s,
-               at<float4>(ws, plan.cut), misc + kMiscCut, true);
+               at<float4>(ws, plan.cut), misc + kMiscCut, true, kCutDiv, &gplan->grid_on);
     ta.t.m_cap = static_cast<int>(n);
     ta.t.d_m = misc + kMiscNumPrims;
     ta.t.cut = at<float4>(ws, plan.cut);
@@ -864,7 +884,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     perm = vals[cur];
     st.mark("permute");
     launch_permute(points, n, dim, perm, xs, h->d_info, s);
-    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig));
+    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
     st.mark("lbvh");
     build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
@@ -879,24 +899,11 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   const bool all_core = min_pts <= 2;
   ta.lone = all_core ? nullptr : at<uint8_t>(ws, plan.lone);
   ta.qborder = at<int>(ws, plan.qborder);
-  ta.qborder_n = misc + kMiscBorderQ;
+  ta.border_n = at<int>(ws, plan.hist);
   ta.brec_i = at<int>(ws, plan.brec_i);
   ta.brec_nb = at<int>(ws, plan.brec_nb);
-  ta.brec_n = misc + kMiscBorderRec;
-  ta.brec_cap = static_cast<int>(plan.brec_cap);
+  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per XCD
   if (!all_core) {
-    // (the border counters are misc slots, cleared at the start of the call)
-    // isolated points first, when the plan says the occupancy map fits the (now
-    // free) cell-box buffers and its brick table the pflag buffer; otherwise these
-    // kernels leave at once and the core pass walks every primitive
-    if (densebox) {
-      st.mark("isolated");
-      ta.core_list = at<int>(ws, plan.cid);  // cid is free until the canonical ids
-      ta.core_qn = misc + kMiscCoreQ;
-      ta.lone_on = &gplan->lone_on;
-      launch_lone_filter(ta, dim, at<uint64_t>(ws, plan.prim_key), gplan, at<uint32_t>(ws, plan.pflag),
-                         at<uint64_t>(ws, plan.cell_lo), bounds, at<int>(ws, plan.cid), misc + kMiscCoreQ, s);
-    }
     st.mark("core");
     launch_core(ta, dim, densebox, s);
   }
@@ -1064,12 +1071,18 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   st.mark("clouds");
   fill_u32(h->d_info, 0, 2, s);  // info bits and the forest check's count
   fill_u32(reinterpret_cast<uint32_t*>(misc), 0, kMiscCount, s);
+  GridPlan* gplan = at<GridPlan>(ws, plan.gplan);
+  const CellIndex ix = densebox ? cell_index(plan, ws) : CellIndex{};
+  if (densebox) {  // no supers yet, and the grid on until a cloud says otherwise
+    fill_u32(reinterpret_cast<uint32_t*>(gplan), 0, sizeof(GridPlan) / 4, s);
+    fill_u32(reinterpret_cast<uint32_t*>(&gplan->grid_on), 1, 1, s);
+  }
   int* cl_flags = at<int>(ws, plan.cl_flags);
   batch_prep(points, offsets, num_clouds, n, dim, eps, min_pts, bpd, densebox, at<uint32_t>(ws, plan.cl_ord), cl_lo,
-             cl_scale, cl_eps2, cl_minpts, cl_flags, h->d_info, s);
+             cl_scale, cl_eps2, cl_minpts, cl_flags, h->d_info, gplan, plan.super_cap, s);
   st.mark("keys");
   batch_keys(points, offsets, num_clouds, n, dim, cl_lo, cl_scale, bpd, shift, static_cast<uint64_t*>(keys[0]),
-             vals[0], shift + cb, at<uint32_t>(ws, plan.hist), s);
+             vals[0], shift + cb, at<uint32_t>(ws, plan.hist), ix.supers, gplan, s);
   st.mark("sort");
   const int cur = radix_sort(keys[0], keys[1], vals[0], vals[1], n, true, shift + cb, at<uint32_t>(ws, plan.hist), true,
                              at<uint32_t>(ws, plan.digoff), at<uint32_t>(ws, plan.tilectr),
@@ -1113,16 +1126,17 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
                    at<float4>(ws, plan.cell_hi), at<int>(ws, plan.pflag),
                    at<int>(ws, plan.prim_start), at<int>(ws, plan.prim_cnt), at<float4>(ws, plan.prim_lo),
                    at<float4>(ws, plan.prim_hi), at<uint64_t>(ws, plan.prim_key), at<int>(ws, plan.dense_list), lab,
-                   core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, shift, cl_minpts, cl_eps2,
-                   at<int>(ws, plan.ends), at<int>(ws, plan.minorig));
+                   core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, ix, shift, cl_minpts,
+                   cl_eps2, num_clouds, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
     st.mark("lbvh");
     build_lbvh(at<void>(ws, plan.prim_key), true, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s, nullptr,
-               nullptr, true);
+               nullptr, true, kCutDiv, &gplan->grid_on);
     batch_roots(offsets, num_clouds, n, at<int>(ws, plan.cand), misc + kMiscNumPrims, at<int>(ws, plan.other),
-                cl_root, cl_end, h->d_info, s);
+                cl_root, cl_end, h->d_info, &gplan->grid_on, s);
+    ta.ix = ix;
     ta.t.d_m = misc + kMiscNumPrims;
     ta.prim_start = at<int>(ws, plan.prim_start);
     ta.prim_cnt = at<int>(ws, plan.prim_cnt);
@@ -1131,23 +1145,23 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
     ta.dense_list = at<int>(ws, plan.dense_list);
     ta.d_ndense = misc + kMiscNumDense;
   } else {
-    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig));
+    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
     st.mark("lbvh");
     build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
                at<int>(ws, plan.ends), at<int>(ws, plan.other), at<int>(ws, plan.gamma),
                nullptr, h->d_info, s, nullptr, nullptr, true);
-    batch_roots(offsets, num_clouds, n, nullptr, nullptr, at<int>(ws, plan.other), cl_root, cl_end, h->d_info, s);
+    batch_roots(offsets, num_clouds, n, nullptr, nullptr, at<int>(ws, plan.other), cl_root, cl_end, h->d_info,
+                nullptr, s);
     ta.t.d_m = nullptr;
   }
   st.mark("core");
   ta.lone = at<uint8_t>(ws, plan.lone);
   ta.qborder = at<int>(ws, plan.qborder);
-  ta.qborder_n = misc + kMiscBorderQ;
+  ta.border_n = at<int>(ws, plan.hist);
   ta.brec_i = at<int>(ws, plan.brec_i);
   ta.brec_nb = at<int>(ws, plan.brec_nb);
-  ta.brec_n = misc + kMiscBorderRec;
-  ta.brec_cap = static_cast<int>(plan.brec_cap);
+  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per XCD
   launch_core(ta, dim, densebox, s);
   if (densebox) {
     st.mark("main_cells");

@@ -87,6 +87,13 @@ __device__ __forceinline__ float boxbox_dist2(const float* alo, const float* ahi
   return s;
 }
 
+// Ends the optimiser's knowledge of v. For a value that lanes leave a divergent loop
+// with, before it is tested: this compiler reuses the condition register that the
+// loop's own exit test left, which only holds the lanes of the last iteration (seen
+// with a count that a loop both stopped at and was tested for after: lanes that had
+// left earlier read 0).
+__device__ __forceinline__ void settle(int& v) { asm volatile("" : "+v"(v)); }
+
 // ---- agent-scope atomics -----------------------------------------------------
 // On gfx950 each XCD has its own L2; agent-scope atomic loads and stores bypass it
 // (sc1), so values written by a workgroup on another XCD are seen within the
@@ -188,12 +195,18 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
   return x * per + (x < rem ? x : rem) + k;
 }
 
+// Indices per XCD when [0, m) is split into 8 contiguous chunks of whole workgroups
+// of bdim threads.
+__device__ __forceinline__ int64_t xcd_share(int64_t m, int bdim) {
+  return ((m + kNumXcd - 1) / kNumXcd + bdim - 1) / bdim * bdim;
+}
+
 // Index of thread `tid` of workgroup b (of blocks of `bdim` threads) when the
 // active range [0, m) is split into 8 contiguous chunks, one per XCD (chunks are
 // whole workgroups); -1 for threads past their chunk. A grid of
 // 8 * ceil(ceil(n/8)/bdim) workgroups, for any n >= m, covers [0, m).
 __device__ __forceinline__ int64_t xcd_spread(int b, int bdim, int tid, int64_t m) {
-  const int64_t chunk = ((m + kNumXcd - 1) / kNumXcd + bdim - 1) / bdim * bdim;
+  const int64_t chunk = xcd_share(m, bdim);
   const int64_t off = static_cast<int64_t>(b / kNumXcd) * bdim;
   if (off >= chunk) return -1;
   return (b % kNumXcd) * chunk + off + tid;

@@ -20,6 +20,7 @@ constexpr int kScanItems = 16;                 // items per thread in the device
 constexpr int kScanTile = 256 * kScanItems;
 constexpr int64_t kMaxPoints = (int64_t(1) << 30) - 1;
 constexpr int kRecNb = 8;  // neighbouring primitives recorded per non-core point
+constexpr int kBorderCounters = 32 * 17;  // words of TravArgs::border_n (they fit the digit histograms)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -45,7 +46,7 @@ struct Plan {
   int num_clouds = 0;
   size_t cl_lo, cl_scale, cl_eps2, cl_minpts, cl_root, cl_end, cl_flags, cl_ord;
   int64_t sort_tiles = 0, scan_blocks = 0;
-  int64_t map_bytes = 0;  // DenseBox: bytes from cell_lo to the end of cell_hi (free after the primitives)
+  int64_t super_cap = 0;  // DenseBox: supers that the node records' buffer holds
 };
 
 Plan make_plan(int64_t n, int dim, int algo, int num_clouds = 0);
@@ -57,17 +58,14 @@ enum MiscSlot : int {
   kMiscNumCand = 2,      // DenseBox: cells with >= minPts points
   kMiscNumPrims = 3,     // DenseBox: m = dense cells + points outside them
   kMiscNumDense = 4,     // DenseBox: dense cells
-  kMiscBorderQ = 5,      // entries of the border query list (filled by the core pass)
-  kMiscBorderRec = 6,    // border neighbour records asked for by the core pass
   kMiscCut = 7,          // entries of the hierarchy's cut (TreeView::cut)
-  kMiscCoreQ = 8,        // DenseBox: point primitives left for the core pass by the isolated-point test,
-                         // one count per XCD segment (slots 8 .. 15)
+  kMiscNumBricks = 8,    // DenseBox: occupied bricks
   kMiscCount = 16
 };
 
 // DenseBox grid of one cloud (Section 4.2: cells of side eps/sqrt(d)), sized on
 // the device from the scene bounds by k_grid_plan, so no value goes back to the
-// host mid-call. The key, sort, dense-cell and isolated-point kernels read it.
+// host mid-call. The key, sort and dense-cell kernels and the walks read it.
 // When the eps/sqrt(d) grid needs more cells per axis than a 64-bit key holds
 // (21 bits per axis in 3D, 31 in 2D), the cells are widened to fit (coarse = 1,
 // FDB_INFO_DENSEBOX_FALLBACK): density is still decided by the exact guard, so
@@ -79,10 +77,28 @@ struct GridPlan {
   int32_t key64;       // 1: d * bits > 32, keys are stored as 64-bit words, else 32-bit
   int32_t passes;      // 8-bit radix passes over the d * bits key bits
   int32_t start;       // key buffer (0/1) the key kernel fills: the sort then ends in buffer 1
-  int32_t lone_on;     // the isolated-point test runs (32-bit keys, its map and table fit their buffers)
   int32_t coarse;      // cells widened to fit 64-bit keys
-  int64_t lone_words;  // the test's 64-bit occupancy words, one per brick of 64 grid cells
-  float reach;         // eps / side plus rounding slack, in cell units (< 2)
+  int32_t grid_on;     // neighbours are searched through the grid (CellIndex), else through the hierarchy
+  float reach;         // eps / side plus rounding slack, in cell units
+  float lo[3];         // the scene's low corner
+  uint64_t supers;     // supers of the grid (a batch: of all its grids)
+};
+
+// The occupied cells as a three-level index (fdb_cells.hpp): supers (16 bytes each:
+// occupancy word, first brick), bricks (occupancy word, first cell) and each cell's
+// first primitive. A batch has a grid per cloud: its corner in cl_lo, 1 / side and
+// reach in cl_scale (x, w), and in cl_grid[2 c] its cells per axis and first super.
+struct CellIndex {
+  const GridPlan* plan;
+  uint4* supers;
+  uint4* bricks;
+  int* cell_prim;   // first primitive of each cell, complemented for a dense cell; then the number of primitives
+  int* brick_base;  // first cell of each brick (while the index is built)
+  uint8_t* cell_code;  // low 6 key bits of each cell (while the index is built)
+  int64_t super_cap;   // supers the table holds
+  const float4* cl_lo;
+  const float4* cl_scale;
+  const int4* cl_grid;
 };
 
 // Node records are interleaved: node k's two halves sit at node_a[kNodeStride * k]
@@ -152,12 +168,13 @@ void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds,
 // launch_bounds; eps is the caller's), then the cell keys go to key buffer
 // plan->start as 32- or 64-bit words with the identity permutation, and their
 // digits are counted for the sort (hist: 8 x 256 words, cleared here unless the
-// caller has, hist_clear = false).
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t n, int64_t map_bytes, GridPlan* plan,
-                      uint32_t* info, hipStream_t s);
+// caller has, hist_clear = false). The key kernel also clears the super table that
+// the grid's index is built into (plan->supers entries, when plan->grid_on).
+void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,
+                      hipStream_t s);
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
-                     void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, hipStream_t s,
-                     bool hist_clear = true);
+                     void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
+                     hipStream_t s, bool hist_clear = true);
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
                     hipStream_t s);
 
@@ -185,24 +202,28 @@ int64_t planned_status_words(int64_t n);
 // the sorted points); see TravArgs. ends: m words of scratch; other / gamma:
 // each internal node's other range end and split (m - 1 words each). cut / cut_n:
 // the cut of TreeView (kCutMax pairs, and a counter the caller zeroed), or null.
+// d_skip (device, optional): nonzero = no hierarchy is needed, the kernels leave.
 void build_lbvh(const void* keys, bool key64, int m, int dim, const float* xs, int64_t n_pts,
                 const float4* prim_lo, const float4* prim_hi, float4* node_a, float4* node_b, int* rope,
                 int* leaf_rope, int* ends, int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s,
-                float4* cut = nullptr, int* cut_n = nullptr, bool ends_ready = false, int cut_div = kCutDiv);
+                float4* cut = nullptr, int* cut_n = nullptr, bool ends_ready = false, int cut_div = kCutDiv,
+                const int* d_skip = nullptr);
 
 // k_dense.hip
 // sorted_keys are 64-bit words when key64 (or, with d_key64 set, when *d_key64 on
 // the device says so), else 32-bit; prim_key receives each primitive's key as a
 // 64-bit word. ends / minorig (optional): set to -1 per primitive and to INT_MAX
 // per point, the starting values of build_lbvh's exchange words (pass
-// ends_ready) and of launch_finalize's minorig.
+// ends_ready) and of launch_finalize's minorig; border_n (optional): the core pass'
+// counters, cleared. The grid's index ix is built over
+// the cells (its words and bricks only when ix.plan->grid_on).
 void densebox_cells(const void* sorted_keys, bool key64, const int* d_key64, int64_t n, int dim, const float* xs,
                     float eps2, int min_pts, int* cell_id, int* cell_start, int* cand, uint8_t* cell_dense,
                     float4* cell_lo, float4* cell_hi, int* pflag, int* prim_start, int* prim_cnt, float4* prim_lo,
                     float4* prim_hi, uint64_t* prim_key, int* dense_list, int* labels, uint8_t* core, int* misc,
-                    int* bsums, int64_t scan_blocks, hipStream_t s, int key_shift = 0,
-                    const int* cl_minpts = nullptr, const float* cl_eps2 = nullptr, int* ends = nullptr,
-                    int* minorig = nullptr);
+                    int* bsums, int64_t scan_blocks, hipStream_t s, const CellIndex& ix, int key_shift = 0,
+                    const int* cl_minpts = nullptr, const float* cl_eps2 = nullptr, int num_clouds = 0,
+                    int* ends = nullptr, int* minorig = nullptr, int* border_n = nullptr);
 
 // k_trav.hip
 struct TravArgs {
@@ -218,27 +239,22 @@ struct TravArgs {
   uint8_t* lone;  // set by the core pass (or the isolated-point test before it): 1 = not core and no
                   // neighbour but itself (noise); NULL if no core pass
   // Border work left by the core pass for non-core points with some neighbour
-  // other than themselves. Up to kRecNb neighbouring primitives of such a point
-  // (the point itself, or a dense cell's first point) are recorded, so the
-  // border pass needs no walk: record k is point brec_i[k] with neighbours
-  // brec_nb[k * kRecNb + t] (-1 = none); *brec_n counts the records asked for,
-  // of which the first brec_cap are stored. Points with more neighbouring
-  // primitives, or past the capacity, are listed in qborder (DenseBox: their
-  // primitive indices) and walk the tree again.
+  // other than themselves, kept per XCD that found it (kNumXcd of each list). Up to
+  // kRecNb neighbouring primitives of such a point (the point itself, or a dense
+  // cell's first point) are recorded, so the border pass needs no walk: record k of
+  // XCD x, at r = x * brec_cap + k, is point brec_i[r] with neighbours
+  // brec_nb[r * kRecNb + t] (-1 = none); the first brec_cap asked for are stored.
+  // Points with more neighbouring primitives, or past the capacity, are listed in
+  // qborder (DenseBox: their primitive indices; XCD x's list starts at its share of
+  // the queries) and walk again. border_n holds the counts (kBorderCounters words,
+  // zero before the core pass).
   int* brec_i;
   int* brec_nb;
-  int* brec_n;
   int brec_cap;
   int* qborder;
-  int* qborder_n;
+  int* border_n;
   const int* cid;
   int* border;
-  // DenseBox core pass over lists of point primitives, one per XCD segment
-  // (core_list[x * segment + 0 .. core_qn[x]), kNumXcd of them), or over every
-  // primitive when core_list is null
-  const int* core_list;
-  const int* core_qn;
-  const int* lone_on;  // device flag: core_list is in use (null = whenever core_list is set)
   // DenseBox primitives (null for FDbscan). Primitive r covers sorted points
   // [prim_start[r], prim_start[r] + |prim_cnt[r]|); prim_cnt > 0: a single
   // point, < 0: a dense cell. prim_lo[r] is the leaf record a walk loads: a
@@ -251,6 +267,7 @@ struct TravArgs {
   const float4* prim_hi;
   const int* dense_list;  // dense-cell primitive indices
   const int* d_ndense;    // their number (device)
+  CellIndex ix;           // DenseBox: the grid's cells; ix.plan->grid_on says whether the walks go through it
   // batches (null pkeys = one cloud): cloud of sorted point i = pkeys[i] >> key_shift;
   // per cloud: first node and last primitive of its subtree, eps^2, minPts
   const uint64_t* pkeys;
@@ -269,15 +286,6 @@ void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s);
 // a.t.cut must be set) for a.t.cut_sum.
 void launch_fdb_local(const TravArgs& a, int dim, bool all_core, hipStream_t s);
 void launch_cut_summary(const TravArgs& a, bool all_core, int* sum, hipStream_t s);
-// Isolated points before the DenseBox core pass (one cloud, 32-bit grid keys): an
-// occupancy map of the grid cells (words: plan->lone_words 64-bit words, one per
-// brick of 64 cells, written only for occupied bricks; table: one bit per brick,
-// cleared here) settles every point primitive with no occupied cell within reach
-// but its own, which it shares with no other primitive: core 0, lone, border -1.
-// The others are listed (list, list_n[kNumXcd]) for the core pass. Runs only where
-// plan->lone_on; bounds are the scene bounds of launch_bounds.
-void launch_lone_filter(const TravArgs& a, int dim, const uint64_t* prim_key, const GridPlan* plan, uint32_t* table,
-                        uint64_t* words, const uint32_t* bounds, int* list, int* list_n, hipStream_t s);
 void launch_main(const TravArgs& a, int dim, bool densebox, bool all_core, bool first_border, int part,
                  hipStream_t s);
 void launch_border(const TravArgs& a, int dim, bool densebox, hipStream_t s);
@@ -285,8 +293,9 @@ void launch_debug_walk(const TreeView& t, int m, int mask, int* out_leaves, int*
                        uint32_t* info, hipStream_t s);
 
 // k_label.hip
-// labels[i] = i; with ends / minorig, also those starting values (see densebox_cells).
-void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends = nullptr, int* minorig = nullptr);
+// labels[i] = i; with ends / minorig / border_n, also those starting values (see densebox_cells).
+void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends = nullptr, int* minorig = nullptr,
+                        int* border_n = nullptr);
 // With minorig (core flags final): also the smallest input index (perm) of each
 // root's core points, in minorig[root] (INT_MAX beforehand, unless minorig_init:
 // then filled here first), and the leader words `bits` (ceil(n/32)) cleared.
@@ -307,12 +316,13 @@ void canonical_ids(const int* labels, const uint8_t* core, const uint32_t* perm,
 // k_batch.hip
 void batch_prep(const float* pts, const int64_t* off, int num_clouds, int64_t n, int dim, const float* eps,
                 const int32_t* min_pts, int bpd, bool densebox, uint32_t* cl_ord, float4* cl_lo, float4* cl_scale,
-                float* cl_eps2, int* cl_minpts, int* cl_flags, uint32_t* info, hipStream_t s);
+                float* cl_eps2, int* cl_minpts, int* cl_flags, uint32_t* info, GridPlan* plan, int64_t super_cap,
+                hipStream_t s);
 void batch_keys(const float* pts, const int64_t* off, int num_clouds, int64_t n, int dim, const float4* cl_lo,
                 const float4* cl_scale, int bpd, int shift, uint64_t* keys, uint32_t* vals, int sort_bits,
-                uint32_t* hist, hipStream_t s);
+                uint32_t* hist, uint4* supers, const GridPlan* plan, hipStream_t s);
 void batch_roots(const int64_t* off, int num_clouds, int64_t n, const int* pidx, const int* d_m, const int* other,
-                 int* root, int* end, uint32_t* info, hipStream_t s);
+                 int* root, int* end, uint32_t* info, const int* d_skip, hipStream_t s);
 void batch_cluster_ids(const int* labels, const uint8_t* core, const int* minorig, const uint32_t* bits,
                        const int* wpre, const uint64_t* pkeys, int shift, const int64_t* off, int num_clouds,
                        int64_t n, const int* total, const int* cl_flags, int* cid, int32_t* num_clusters,

@@ -5,6 +5,7 @@
 // one cloud - all keys sharing that prefix - form exactly one subtree: the node
 // whose range is the cloud's range, which is internal node first or last of
 // that range (a Karras node's index is one end of its range), or a leaf.
+#include "fdb_cells.hpp"
 #include "fdb_device.hpp"
 #include "fdb_internal.hpp"
 #include "fdbscan.h"
@@ -152,14 +153,19 @@ __global__ __launch_bounds__(kBlock) void k_cloud_bounds(const float* __restrict
 
 // Per-cloud validity, eps^2, minPts and key scale (points normalised to the
 // cloud's box, or DenseBox cells of side eps/sqrt(d), slightly shrunk; the
-// exactness guard covers any rounding). One thread per cloud.
+// exactness guard covers any rounding). For DenseBox also the cloud's grid for the
+// neighbour search: its reach (as k_grid_plan has it), cells per axis and share of
+// the super table, in whatever order the clouds come; a cloud whose grid is too wide,
+// or a table too small for all of them, sends the whole batch through the hierarchy.
+// A cloud with undefined labels gets no grid. One thread per cloud.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restrict__ off, int num_clouds, int64_t n,
                                                          const float* __restrict__ eps, const int32_t* __restrict__ mp,
-                                                         int bpd, int densebox, const uint32_t* __restrict__ cl_ord,
+                                                         int bpd, int densebox, const uint32_t* cl_ord,
                                                          float4* __restrict__ cl_lo, float4* __restrict__ cl_scale,
                                                          float* __restrict__ cl_eps2, int* __restrict__ cl_minpts,
-                                                         int* __restrict__ cl_flags, uint32_t* __restrict__ info) {
+                                                         int* __restrict__ cl_flags, uint32_t* __restrict__ info,
+                                                         int4* cl_grid, GridPlan* plan, int64_t super_cap) {
   const int c = blockIdx.x * kBlock + threadIdx.x;
   if (c >= num_clouds) return;
   int64_t b, e;
@@ -188,8 +194,38 @@ __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restri
       sc[k] = ext > 0.0f ? static_cast<float>(maxq) / ext : 0.0f;
     }
   }
+  float reach = 0.0f;
+  if (densebox) {
+    int nc[3] = {1, 1, 1};
+    double cmax = 1.0, supers = 1.0;
+    for (int k = 0; k < D; ++k) {
+      const double cells = floor((static_cast<double>(hi[k]) - static_cast<double>(lo[k])) * sc[k]) + 2.0;
+      cmax = cells > cmax ? cells : cmax;
+      supers *= ceil(cells / kSuperSide<D>);
+      nc[k] = cells < 1.0e9 ? static_cast<int>(cells) : 0;
+    }
+    const double r = static_cast<double>(ec) * static_cast<double>(sc[0]) * (1.0 + 1.0 / 65536.0) +
+                     4.0 * (cmax / 4194304.0 + 1.0 / 1048576.0) + 1.0 / 65536.0;
+    reach = static_cast<float>(r);
+    uint64_t at = 0;
+    if (flags || e <= b) {
+      nc[0] = 0;
+    } else if (!(r < kMaxReach) || !(supers <= static_cast<double>(super_cap)) ||
+               !(cmax < static_cast<double>(maxq))) {
+      atomicAnd(&plan->grid_on, 0);
+      nc[0] = 0;
+    } else {
+      const uint64_t add = static_cast<uint64_t>(supers);
+      at = atomicAdd(reinterpret_cast<unsigned long long*>(&plan->supers), static_cast<unsigned long long>(add));
+      if (at + add > static_cast<uint64_t>(super_cap)) {
+        atomicAnd(&plan->grid_on, 0);
+        nc[0] = 0;
+      }
+    }
+    cl_grid[2 * c] = make_int4(nc[0], nc[1], nc[2], static_cast<int>(at));  // over the cloud's bounds, read above
+  }
   cl_lo[c] = make_float4(lo[0], lo[1], lo[2], 0.0f);
-  cl_scale[c] = make_float4(sc[0], sc[1], sc[2], 0.0f);
+  cl_scale[c] = make_float4(sc[0], sc[1], sc[2], reach);
 }
 
 // Lower-bound words of every cloud start at the largest order-preserving value.
@@ -207,10 +243,12 @@ __global__ __launch_bounds__(kBlock) void k_batch_keys(const float* __restrict__
                                                        int num_clouds, int64_t n, const float4* __restrict__ cl_lo,
                                                        const float4* __restrict__ cl_scale, int bpd, int shift,
                                                        uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                       int passes, uint32_t* __restrict__ hist) {
+                                                       int passes, uint32_t* __restrict__ hist,
+                                                       uint4* __restrict__ supers, const GridPlan* __restrict__ plan) {
   __shared__ uint32_t s_h[8 * 256];
   __shared__ int s_c[2];
   hist_clear(s_h, passes);
+  if (supers && plan->grid_on) clear_supers(supers, plan->supers);
   const int64_t base = blockIdx.x * int64_t(kChunk);
   chunk_clouds(off, num_clouds, base, n, s_c);
   const int c0 = s_c[0], c1 = s_c[1];
@@ -248,7 +286,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_keys(const float* __restrict__
 __global__ __launch_bounds__(kBlock) void k_cloud_roots(const int64_t* __restrict__ off, int num_clouds, int64_t n,
                                                         const int* __restrict__ pidx, const int* __restrict__ d_m,
                                                         const int* __restrict__ other, int* __restrict__ root,
-                                                        int* __restrict__ end, uint32_t* __restrict__ info) {
+                                                        int* __restrict__ end, uint32_t* __restrict__ info,
+                                                        const int* __restrict__ d_skip) {
+  if (d_skip && *d_skip) return;  // no hierarchy was built
   const int c = blockIdx.x * kBlock + threadIdx.x;
   if (c >= num_clouds) return;
   int64_t b, e;
@@ -329,7 +369,8 @@ inline int grid_for(int64_t n) {
 
 void batch_prep(const float* pts, const int64_t* off, int num_clouds, int64_t n, int dim, const float* eps,
                 const int32_t* min_pts, int bpd, bool densebox, uint32_t* cl_ord, float4* cl_lo, float4* cl_scale,
-                float* cl_eps2, int* cl_minpts, int* cl_flags, uint32_t* info, hipStream_t s) {
+                float* cl_eps2, int* cl_minpts, int* cl_flags, uint32_t* info, GridPlan* plan, int64_t super_cap,
+                hipStream_t s) {
   fill_u32(cl_ord, 0u, 8 * int64_t(num_clouds), s);  // hi words 0; k_ord_init sets the lo words
   hipLaunchKernelGGL(k_ord_init, dim3(static_cast<unsigned>(ceil_div(num_clouds, kBlock))), dim3(kBlock), 0, s,
                      cl_ord, num_clouds);
@@ -340,34 +381,36 @@ void batch_prep(const float* pts, const int64_t* off, int num_clouds, int64_t n,
     if (chunks) hipLaunchKernelGGL(k_cloud_bounds<3>, dim3(chunks), dim3(kBlock), 0, s, pts, off, num_clouds, n, cl_ord,
                                    cl_flags);
     hipLaunchKernelGGL(k_cloud_params<3>, dim3(pg), dim3(kBlock), 0, s, off, num_clouds, n, eps, min_pts, bpd,
-                       densebox ? 1 : 0, cl_ord, cl_lo, cl_scale, cl_eps2, cl_minpts, cl_flags, info);
+                       densebox ? 1 : 0, cl_ord, cl_lo, cl_scale, cl_eps2, cl_minpts, cl_flags, info,
+                       reinterpret_cast<int4*>(cl_ord), plan, super_cap);
   } else {
     if (chunks) hipLaunchKernelGGL(k_cloud_bounds<2>, dim3(chunks), dim3(kBlock), 0, s, pts, off, num_clouds, n, cl_ord,
                                    cl_flags);
     hipLaunchKernelGGL(k_cloud_params<2>, dim3(pg), dim3(kBlock), 0, s, off, num_clouds, n, eps, min_pts, bpd,
-                       densebox ? 1 : 0, cl_ord, cl_lo, cl_scale, cl_eps2, cl_minpts, cl_flags, info);
+                       densebox ? 1 : 0, cl_ord, cl_lo, cl_scale, cl_eps2, cl_minpts, cl_flags, info,
+                       reinterpret_cast<int4*>(cl_ord), plan, super_cap);
   }
 }
 
 void batch_keys(const float* pts, const int64_t* off, int num_clouds, int64_t n, int dim, const float4* cl_lo,
                 const float4* cl_scale, int bpd, int shift, uint64_t* keys, uint32_t* vals, int sort_bits,
-                uint32_t* hist, hipStream_t s) {
+                uint32_t* hist, uint4* supers, const GridPlan* plan, hipStream_t s) {
   const int passes = (sort_bits + 7) / 8;
   fill_u32(hist, 0, passes * 256, s);
   const unsigned chunks = static_cast<unsigned>(ceil_div(n, kChunk));
   if (!chunks) return;
   if (dim == 3)
     hipLaunchKernelGGL(k_batch_keys<3>, dim3(chunks), dim3(kBlock), 0, s, pts, off, num_clouds, n, cl_lo, cl_scale,
-                       bpd, shift, keys, vals, passes, hist);
+                       bpd, shift, keys, vals, passes, hist, supers, plan);
   else
     hipLaunchKernelGGL(k_batch_keys<2>, dim3(chunks), dim3(kBlock), 0, s, pts, off, num_clouds, n, cl_lo, cl_scale,
-                       bpd, shift, keys, vals, passes, hist);
+                       bpd, shift, keys, vals, passes, hist, supers, plan);
 }
 
 void batch_roots(const int64_t* off, int num_clouds, int64_t n, const int* pidx, const int* d_m, const int* other,
-                 int* root, int* end, uint32_t* info, hipStream_t s) {
+                 int* root, int* end, uint32_t* info, const int* d_skip, hipStream_t s) {
   hipLaunchKernelGGL(k_cloud_roots, dim3(static_cast<unsigned>(ceil_div(num_clouds, kBlock))), dim3(kBlock), 0, s,
-                     off, num_clouds, n, pidx, d_m, other, root, end, info);
+                     off, num_clouds, n, pidx, d_m, other, root, end, info, d_skip);
 }
 
 void batch_cluster_ids(const int* labels, const uint8_t* core, const int* minorig, const uint32_t* bits,

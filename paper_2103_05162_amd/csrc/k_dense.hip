@@ -12,6 +12,7 @@
 // cell index computation suffered.
 #include <algorithm>
 
+#include "fdb_cells.hpp"
 #include "fdb_device.hpp"
 #include "fdb_internal.hpp"
 
@@ -50,13 +51,19 @@ __device__ __forceinline__ float cell_eps2(const CloudParams& cp, int head, floa
 
 constexpr int kSmallCell = 64;
 
-__device__ __forceinline__ bool is_head(const KeyIn& k, bool wide, int64_t i) {
-  return i == 0 || key_at(k, wide, i) != key_at(k, wide, i - 1);
+// Opening flags of sorted point i: bit 0 a cell, bit 16 a brick of 64 cells (its
+// lowest 6 key bits dropped). code: its key's lowest 6 bits.
+__device__ __forceinline__ int head_flags(const KeyIn& k, bool wide, int64_t i, uint32_t* code) {
+  const uint64_t key = key_at(k, wide, i);
+  const uint64_t d = i == 0 ? ~0ull : key ^ key_at(k, wide, i - 1);
+  *code = static_cast<uint32_t>(key) & 63u;
+  return (d ? 1 : 0) | (d >> 6 ? 1 << 16 : 0);
 }
 
 // The stage runs as two scans over tiles of kScanTile sorted points (256 threads x
 // kScanItems): first over cell heads (a point whose key differs from the one
-// before it), giving every point its cell and every cell its start; then, once the
+// before it) and brick heads, giving every point its cell, every cell its start and
+// every brick of the grid's index its first cell; then, once the
 // cells are decided, over primitive openings (a point outside dense cells, or a
 // dense cell's first point) and dense-cell openings, giving every primitive its
 // index and every dense cell its place in the dense list. Each scan is a reduce
@@ -111,49 +118,67 @@ __device__ __forceinline__ void tile_exclusive_scan(int* s_v, int* s_w) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kBlock) void k_heads_reduce(KeyIn keys, int64_t n, int* __restrict__ bsums) {
+__global__ __launch_bounds__(kBlock) void k_heads_reduce(KeyIn keys, int64_t n, int* __restrict__ bsums,
+                                                         int* __restrict__ bsums_b, int* __restrict__ border_n) {
   __shared__ int s_w[kBlock / 64];
+  if (border_n && blockIdx.x == 0)  // (the digit histograms' place: the sort is done with them)
+    for (int k = threadIdx.x; k < kBorderCounters; k += kBlock) border_n[k] = 0;
   const bool wide = keys.wide();
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   int x = 0;
   for (int k = 0; k < kScanItems; ++k) {
     const int64_t i = base + k * kBlock + threadIdx.x;
-    if (i < n && is_head(keys, wide, i)) ++x;
+    uint32_t code;
+    if (i < n) x += head_flags(keys, wide, i, &code);
   }
   const int t = tile_reduce(x, s_w);
-  if (threadIdx.x == 0) bsums[blockIdx.x] = t;
+  if (threadIdx.x == 0) {
+    bsums[blockIdx.x] = t & 0xffff;
+    bsums_b[blockIdx.x] = t >> 16;
+  }
 }
 
-// cell_id[i] for every point; cell_start[c] for every cell and cell_start[#cells] = n.
+// cell_id[i] for every point; cell_start[c] for every cell and cell_start[#cells] = n;
+// the code of every cell in its brick, and every brick's first cell.
 __global__ __launch_bounds__(kBlock) void k_heads_apply(KeyIn keys, int64_t n, const int* __restrict__ bsums,
-                                                        int* __restrict__ cell_id, int* __restrict__ cell_start) {
+                                                        const int* __restrict__ bsums_b, int* __restrict__ cell_id,
+                                                        int* __restrict__ cell_start, uint8_t* __restrict__ cell_code,
+                                                        int* __restrict__ brick_base) {
   static_assert(kScanItems == 16, "the LDS layout assumes 16 items per thread");
   __shared__ int s_v[kScanTile + kScanTile / 16];
   __shared__ int s_w[kBlock / 64];
   const bool wide = keys.wide();
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   const int tid = threadIdx.x;
-  uint32_t hmask = 0;  // bit k: striped item k is a head
+  uint32_t hmask = 0, bmask = 0;  // bit k: striped item k is a cell head, a brick head
+  uint32_t code[kScanItems];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
     const int64_t i = base + p;
-    const bool h = i < n && is_head(keys, wide, i);
-    hmask |= h ? 1u << k : 0u;
-    s_v[tile_lds(p)] = h ? 1 : 0;
+    code[k] = 0;
+    const int f = i < n ? head_flags(keys, wide, i, &code[k]) : 0;
+    hmask |= (f & 1) ? 1u << k : 0u;
+    bmask |= (f >> 16) ? 1u << k : 0u;
+    s_v[tile_lds(p)] = f;
   }
   __syncthreads();
   tile_exclusive_scan(s_v, s_w);
-  const int carry = bsums[blockIdx.x];
+  const int carry = bsums[blockIdx.x], carry_b = bsums_b[blockIdx.x];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
     const int64_t i = base + p;
     if (i < n) {
       const bool h = (hmask >> k) & 1u;
-      const int c = carry + s_v[tile_lds(p)] + (h ? 1 : 0) - 1;
+      const int ex = s_v[tile_lds(p)];
+      const int c = carry + (ex & 0xffff) + (h ? 1 : 0) - 1;
       cell_id[i] = c;
-      if (h) cell_start[c] = static_cast<int>(i);
+      if (h) {
+        cell_start[c] = static_cast<int>(i);
+        cell_code[c] = static_cast<uint8_t>(code[k]);
+      }
+      if ((bmask >> k) & 1u) brick_base[carry_b + (ex >> 16)] = c;
       if (i == n - 1) cell_start[c + 1] = static_cast<int>(n);
     }
   }
@@ -235,12 +260,14 @@ __global__ __launch_bounds__(kBlock) void k_cells_small(const float* __restrict_
 // Opening flags of point i: bit 0 a primitive (outside dense cells, or a dense
 // cell's first point), bit 16 a dense cell (its first point).
 __device__ __forceinline__ int open_flags(const int* __restrict__ cell_id, const int* __restrict__ cell_start,
-                                          const uint8_t* __restrict__ dense, int64_t i, int* c_out, bool* d_out) {
+                                          const uint8_t* __restrict__ dense, int64_t i, int* c_out, bool* d_out,
+                                          bool* first_out) {
   const int c = cell_id[i];
   const bool d = dense[c] != 0;
   const bool first = cell_start[c] == i;
   *c_out = c;
   *d_out = d;
+  *first_out = first;
   return (!d || first ? 1 : 0) | (d && first ? 1 << 16 : 0);
 }
 
@@ -255,8 +282,8 @@ __global__ __launch_bounds__(kBlock) void k_prims_reduce(const int* __restrict__
     const int64_t i = base + k * kBlock + threadIdx.x;
     if (i < n) {
       int c;
-      bool d;
-      x += open_flags(cell_id, cell_start, dense, i, &c, &d);
+      bool d, first;
+      x += open_flags(cell_id, cell_start, dense, i, &c, &d, &first);
     }
   }
   const int t = tile_reduce(x, s_w);
@@ -284,14 +311,14 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
                                                         uint64_t* __restrict__ prim_key, int* __restrict__ dense_list,
                                                         int* __restrict__ labels, uint8_t* __restrict__ core,
                                                         int* __restrict__ pidx, int* __restrict__ ends,
-                                                        int* __restrict__ minorig) {
+                                                        int* __restrict__ minorig, int* __restrict__ cell_prim) {
   __shared__ int s_v[kScanTile + kScanTile / 16];
   __shared__ int s_w[kBlock / 64];
   const bool wide = keys.wide();
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   const int tid = threadIdx.x;
   int cl[kScanItems];
-  uint32_t dmask = 0;  // bit k: striped item k lies in a dense cell
+  uint32_t dmask = 0, cmask = 0;  // bit k: striped item k lies in a dense cell, is its cell's first point
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
@@ -299,9 +326,10 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
     int f = 0;
     cl[k] = 0;
     if (i < n) {
-      bool d;
-      f = open_flags(cell_id, cell_start, dense, i, &cl[k], &d);
+      bool d, first;
+      f = open_flags(cell_id, cell_start, dense, i, &cl[k], &d, &first);
       dmask |= d ? 1u << k : 0u;
+      cmask |= first ? 1u << k : 0u;
     }
     s_v[tile_lds(p)] = f;
   }
@@ -327,6 +355,8 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
     if (minorig) minorig[i] = 0x7fffffff;
     if (ends && (fl[k] & 1)) ends[pi] = -1;
     const bool d = (dmask >> k) & 1u;
+    if ((cmask >> k) & 1u) cell_prim[cl[k]] = d ? ~pi : pi;
+    if (i64 == n - 1) cell_prim[cl[k] + 1] = pi + (fl[k] & 1);
     if (d) {
       const int c = cl[k];
       const int st = cell_start[c];
@@ -349,6 +379,97 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
       prim_cnt[pi] = 1;
       prim_lo[pi] = make_float4(xs[i], xs[n + i], D == 3 ? xs[2 * n + i] : 0.0f, __int_as_float(i));
       prim_key[pi] = key_at(keys, wide, i);
+    }
+  }
+}
+
+__device__ __forceinline__ uint32_t gather_bits(uint64_t x, int d) {  // every d-th bit, from bit 0
+  if (d == 3) {
+    x &= 0x1249249249249249ull;
+    x = (x | x >> 2) & 0x10c30c30c30c30c3ull;
+    x = (x | x >> 4) & 0x100f00f00f00f00full;
+    x = (x | x >> 8) & 0x001f0000ff0000ffull;
+    x = (x | x >> 16) & 0x001f00000000ffffull;
+    x = (x | x >> 32) & 0x1fffffull;
+  } else {
+    x &= 0x5555555555555555ull;
+    x = (x | x >> 1) & 0x3333333333333333ull;
+    x = (x | x >> 2) & 0x0f0f0f0f0f0f0f0full;
+    x = (x | x >> 4) & 0x00ff00ff00ff00ffull;
+    x = (x | x >> 8) & 0x0000ffff0000ffffull;
+    x = (x | x >> 16) & 0xffffffffull;
+  }
+  return static_cast<uint32_t>(x);
+}
+
+__device__ __forceinline__ uint64_t shfl_up64(uint64_t v, int off) {
+  const uint32_t lo = static_cast<uint32_t>(__shfl_up(static_cast<int>(v), off));
+  const uint32_t hi = static_cast<uint32_t>(__shfl_up(static_cast<int>(v >> 32), off));
+  return uint64_t(hi) << 32 | lo;
+}
+
+// The grid's index: a lane per brick gathers its word from its cells' codes (at most
+// 64, next to each other) and marks itself in its super, one atomic per run of lanes
+// with the same super; a super's first brick stores its index. A brick beyond its
+// grid (a batch's cloud with undefined labels) is left out.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_bricks(KeyIn keys, CloudParams cp, const int* __restrict__ cell_start,
+                                                   const int* __restrict__ d_cells, const int* __restrict__ d_bricks,
+                                                   CellIndex ix, int num_clouds) {
+  if (!ix.plan->grid_on) return;
+  const bool wide = keys.wide();
+  const int nb = *d_bricks, ncells = *d_cells;
+  const int lane = lane_id();
+  for (int64_t b0 = blockIdx.x * int64_t(kBlock) + (threadIdx.x & ~63); b0 < nb; b0 += int64_t(gridDim.x) * kBlock) {
+    const int64_t b = b0 + lane;
+    const bool valid = b < nb;
+    int c0 = 0, sid = -1;
+    uint64_t bit = 0;
+    bool head = false;
+    if (valid) {
+      c0 = ix.brick_base[b];
+      const int c1 = b + 1 < nb ? ix.brick_base[b + 1] : ncells;
+      const int first = cell_start[c0];
+      const uint64_t key = key_at(keys, wide, first);
+      const uint64_t prev = first > 0 ? key_at(keys, wide, first - 1) : ~key;
+      head = (key ^ prev) >> 12 != 0;
+      uint64_t word = 0;
+      for (int c = c0; c < c1; ++c) word |= 1ull << (ix.cell_code[c] & 63);
+      ix.bricks[b] = make_uint4(static_cast<uint32_t>(word), static_cast<uint32_t>(word >> 32),
+                                static_cast<uint32_t>(c0), 0u);
+      int cloud = 0;
+      uint64_t code = key;
+      if (cp.minpts) {
+        cloud = min(static_cast<int>(key >> cp.shift), num_clouds - 1);
+        code = key & ((uint64_t(1) << cp.shift) - 1);
+      }
+      const CellGrid g = cp.minpts ? query_grid<D, true>(ix, cloud) : query_grid<D, false>(ix, 0);
+      int br[3] = {0, 0, 0};
+      bool in = true;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        br[a] = static_cast<int>(gather_bits((code >> 6) >> (D - 1 - a), D));
+        in = in && br[a] <= ((g.ncell[a] - 1) >> kLevelShift<D>);
+      }
+      if (in) {
+        sid = super_index<D>(g, br);
+        bit = 1ull << child_code<D>(br);
+        if (head) ix.supers[sid].z = static_cast<uint32_t>(b);
+      }
+    }
+    // OR over the run of lanes with this super; its last lane adds it to the table
+    uint64_t v = bit;
+    int s = sid;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t u = shfl_up64(v, off);
+      const int su = __shfl_up(s, off);
+      if (lane >= off && su == sid) v |= u;
+    }
+    const int snext = __shfl_down(sid, 1);
+    if (sid >= 0 && (lane == 63 || snext != sid)) {
+      unsigned long long* w = reinterpret_cast<unsigned long long*>(ix.supers + sid);
+      atomicOr(w, static_cast<unsigned long long>(v));
     }
   }
 }
@@ -409,7 +530,7 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
              int* cell_start, int* cand, uint8_t* dense, float4* cell_lo, float4* cell_hi, int* pflag,
              int* prim_start, int* prim_cnt, float4* prim_lo, float4* prim_hi, uint64_t* prim_key, int* dense_list,
              int* labels, uint8_t* core, int* misc, int* bsums, int64_t scan_blocks, const CloudParams& cp,
-             hipStream_t s, int* ends, int* minorig) {
+             hipStream_t s, int* ends, int* minorig, int* border_n, const CellIndex& ix, int num_clouds) {
   (void)scan_blocks;
   int* d_cells = misc + kMiscNumCells;
   int* d_big = misc + kMiscNumCand;  // candidate cells of more than kSmallCell points
@@ -417,9 +538,12 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
   int* d_dense = misc + kMiscNumDense;
   const int64_t tiles = ceil_div(n, kScanTile);
   const dim3 gt(static_cast<unsigned>(tiles));
-  hipLaunchKernelGGL(k_heads_reduce, gt, dim3(kBlock), 0, s, keys, n, bsums);
-  scan_block_sums(bsums, tiles, d_cells, s);
-  hipLaunchKernelGGL(k_heads_apply, gt, dim3(kBlock), 0, s, keys, n, bsums, cell_id, cell_start);
+  int* bsums2 = pflag;  // the second count of each tile: bricks, then dense cells
+  int* d_bricks = misc + kMiscNumBricks;
+  hipLaunchKernelGGL(k_heads_reduce, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2, border_n);
+  scan_block_sums(bsums, tiles, d_cells, s, bsums2, d_bricks);
+  hipLaunchKernelGGL(k_heads_apply, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2, cell_id, cell_start, ix.cell_code,
+                     ix.brick_base);
   // d_big (a misc slot) is zero: the caller cleared misc before this stage
   int* big = cand;
   const int gs = static_cast<int>(std::min<int64_t>(std::max<int64_t>(ceil_div(n, kBlock / 8), 1), 8192));
@@ -435,20 +559,27 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
     hipLaunchKernelGGL((k_cell_boxes<2, 64>), dim3(gb), dim3(kBlock), 0, s, xs, n, cell_start, big, d_big, eps2, cp,
                        dense, cell_lo, cell_hi);
   }
-  int* bsums_d = pflag;  // the dense-cell counts of each tile
   // a batch reads every point's primitive index afterwards (in cand, which the
   // large-cell list no longer needs by then)
   int* pidx = cp.minpts ? cand : nullptr;
-  hipLaunchKernelGGL(k_prims_reduce, gt, dim3(kBlock), 0, s, cell_id, cell_start, dense, n, bsums, bsums_d);
-  scan_block_sums(bsums, tiles, d_prims, s, bsums_d, d_dense);
+  hipLaunchKernelGGL(k_prims_reduce, gt, dim3(kBlock), 0, s, cell_id, cell_start, dense, n, bsums, bsums2);
+  scan_block_sums(bsums, tiles, d_prims, s, bsums2, d_dense);
   if (dim == 3)
     hipLaunchKernelGGL(k_prims_apply<3>, gt, dim3(kBlock), 0, s, keys, xs, n, cell_id, cell_start, dense, cell_lo,
-                       cell_hi, bsums, bsums_d, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
-                       core, pidx, ends, minorig);
+                       cell_hi, bsums, bsums2, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
+                       core, pidx, ends, minorig, ix.cell_prim);
   else
     hipLaunchKernelGGL(k_prims_apply<2>, gt, dim3(kBlock), 0, s, keys, xs, n, cell_id, cell_start, dense, cell_lo,
-                       cell_hi, bsums, bsums_d, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
-                       core, pidx, ends, minorig);
+                       cell_hi, bsums, bsums2, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
+                       core, pidx, ends, minorig, ix.cell_prim);
+  // the bricks' buffer is the cell boxes', dead once the primitives are written
+  const unsigned gk = static_cast<unsigned>(std::min<int64_t>(ceil_div(n, kBlock), 4096));
+  if (dim == 3)
+    hipLaunchKernelGGL(k_bricks<3>, dim3(gk), dim3(kBlock), 0, s, keys, cp, cell_start, d_cells, d_bricks, ix,
+                       num_clouds);
+  else
+    hipLaunchKernelGGL(k_bricks<2>, dim3(gk), dim3(kBlock), 0, s, keys, cp, cell_start, d_cells, d_bricks, ix,
+                       num_clouds);
 }
 
 }  // namespace
@@ -457,14 +588,14 @@ void densebox_cells(const void* sorted_keys, bool key64, const int* d_key64, int
                     float eps2, int min_pts, int* cell_id, int* cell_start, int* cand, uint8_t* cell_dense,
                     float4* cell_lo, float4* cell_hi, int* pflag, int* prim_start, int* prim_cnt, float4* prim_lo,
                     float4* prim_hi, uint64_t* prim_key, int* dense_list, int* labels, uint8_t* core, int* misc,
-                    int* bsums, int64_t scan_blocks, hipStream_t s, int key_shift, const int* cl_minpts,
-                    const float* cl_eps2, int* ends, int* minorig) {
+                    int* bsums, int64_t scan_blocks, hipStream_t s, const CellIndex& ix, int key_shift,
+                    const int* cl_minpts, const float* cl_eps2, int num_clouds, int* ends, int* minorig, int* border_n) {
   // per-cloud parameters come with batches, whose keys are always 64-bit
   CloudParams cp{static_cast<const uint64_t*>(sorted_keys), key_shift, cl_minpts, cl_eps2};
   const KeyIn keys{sorted_keys, d_key64, key64 ? 1 : 0};
   cells_t(keys, n, dim, xs, eps2, min_pts, cell_id, cell_start, cand, cell_dense, cell_lo, cell_hi, pflag, prim_start,
           prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels, core, misc, bsums, scan_blocks, cp, s, ends,
-          minorig);
+          minorig, border_n, ix, num_clouds);
 }
 
 }  // namespace fdb

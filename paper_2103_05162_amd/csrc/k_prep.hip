@@ -1,6 +1,7 @@
 // Preparation kernels: scene bounds and finite check, space-filling-curve keys
 // (Section 4.1 orders queries and primitives along a Morton curve), grid-cell
 // keys for DenseBox (Section 4.2), and the gather of points into sorted SoA.
+#include "fdb_cells.hpp"
 #include "fdb_device.hpp"
 #include "fdb_internal.hpp"
 #include "fdbscan.h"
@@ -211,11 +212,10 @@ __global__ __launch_bounds__(kBlock) void k_morton(const float* __restrict__ pts
 // side is shrunk by 2^-20 so that rounding in the cell index rarely pushes a
 // cell's extent past h (the exactness guard catches the rest). A grid wider than
 // a 64-bit key holds gets wider cells (every pair in a dense cell still passes the
-// guard). The isolated-point test runs for 32-bit keys when its occupancy map (one
-// bit per cell, a 64-bit word per brick of 64 cells) fits in map_bytes and its
-// brick table (a bit per brick) in n 32-bit words.
+// guard). Neighbours are searched through the grid (grid_on) when its super table
+// fits in super_cap entries and a reach stays within two cells per axis.
 template <int D>
-__global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int64_t n, int64_t map_bytes,
+__global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int64_t super_cap,
                             GridPlan* __restrict__ plan, uint32_t* __restrict__ info) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   constexpr int maxbits = D == 3 ? 21 : 31;
@@ -254,19 +254,22 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
   g.passes = (D * bits + 7) / 8;
   g.start = (g.passes & 1) ? 0 : 1;
   g.coarse = coarse;
-  // isolated-point test: a word per brick of 64 grid cells (in map_bytes) and a
-  // table bit per brick (in an n-int buffer); reach = eps / side in cell units plus
-  // a slack for the rounding of the cell coordinates t = (x - lo) * inv_h: each is
-  // within 2^-23 t of exact, so a difference within cmax 2^-22 (times 4 here), and
-  // the fp32 test passes pairs up to eps (1 + 2^-22) apart (2^-16 here)
+  // reach = eps / side in cell units plus a slack for the rounding of the cell
+  // coordinates t = (x - lo) * inv_h: each is within 2^-23 t of exact, so a difference
+  // within cmax 2^-22 (times 4 here), and the fp32 test passes pairs up to
+  // eps (1 + 2^-22) apart (2^-16 here)
   double cmax = 1.0;
   for (int k = 0; k < D; ++k) cmax = g.ncell[k] > cmax ? g.ncell[k] : cmax;
   const double reach = static_cast<double>(eps) * static_cast<double>(ih) * (1.0 + 1.0 / 65536.0) +
                        4.0 * (cmax / 4194304.0 + 1.0 / 1048576.0) + 1.0 / 65536.0;
-  g.lone_words = D * bits >= 6 ? int64_t(1) << (D * bits - 6) : 1;
   g.reach = static_cast<float>(reach);
-  g.lone_on = (!g.key64 && bits >= 1 && reach < 1.999 && g.lone_words * 8 <= map_bytes &&
-               (g.lone_words + 63) / 64 * 2 <= n) ? 1 : 0;
+  double supers = 1.0;
+  for (int k = 0; k < 3; ++k) {
+    g.lo[k] = k < D ? ord2f(bounds[k]) : 0.0f;
+    if (k < D) supers *= static_cast<double>((static_cast<uint64_t>(g.ncell[k]) + kSuperSide<D> - 1) / kSuperSide<D>);
+  }
+  g.grid_on = reach < kMaxReach && supers <= static_cast<double>(super_cap) ? 1 : 0;
+  g.supers = g.grid_on ? static_cast<uint64_t>(supers) : 0;
   *plan = g;
   if (coarse) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
 }
@@ -282,9 +285,11 @@ __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ p
                                                      const uint32_t* __restrict__ bounds,
                                                      const GridPlan* __restrict__ plan, void* __restrict__ keys0,
                                                      void* __restrict__ keys1, uint32_t* __restrict__ vals0,
-                                                     uint32_t* __restrict__ vals1, uint32_t* __restrict__ hist) {
+                                                     uint32_t* __restrict__ vals1, uint32_t* __restrict__ hist,
+                                                     uint4* __restrict__ supers) {
   __shared__ uint32_t s_h[8 * 256];
   const GridPlan g = *plan;
+  clear_supers(supers, g.supers);
   const int passes = g.passes;
   hist_clear(s_h, passes);
   uint32_t* vals = g.start ? vals1 : vals0;
@@ -426,27 +431,27 @@ void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds,
     hipLaunchKernelGGL(k_morton<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, keys, vals, passes, hist);
 }
 
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t n, int64_t map_bytes, GridPlan* plan,
-                      uint32_t* info, hipStream_t s) {
+void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,
+                      hipStream_t s) {
   if (dim == 3)
-    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, bounds, eps, n, map_bytes, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, plan, info);
   else
-    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, bounds, eps, n, map_bytes, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, plan, info);
 }
 
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
-                     void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, hipStream_t s,
-                     bool hist_clear) {
+                     void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
+                     hipStream_t s, bool hist_clear) {
   if (hist_clear) fill_u32(hist, 0, 8 * 256, s);
   // A workgroup histogram per 4096+ keys, at most 1024 of them: each flushes up to 2048 bins into the
   // one global histogram, and fewer flushes contend less at L2 than more workgroups gain.
   int g = grid_for(n, kBlock * 16, 1024);
   if (dim == 3)
     hipLaunchKernelGGL(k_gridkeys<3>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0, vals1,
-                       hist);
+                       hist, supers);
   else
     hipLaunchKernelGGL(k_gridkeys<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0, vals1,
-                       hist);
+                       hist, supers);
 }
 
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,

@@ -15,7 +15,9 @@
 // a batch the keys carry the cloud id above the Morton bits, so each cloud is
 // one subtree, and a query's scope is its cloud's (with its own eps, minPts).
 #include <algorithm>
+#include <type_traits>
 
+#include "fdb_cells.hpp"
 #include "fdb_device.hpp"
 #include "fdb_internal.hpp"
 
@@ -426,11 +428,21 @@ __device__ __forceinline__ int cell_ref(int s) { return -2 - s; }
 __device__ __forceinline__ bool is_cell_ref(int v) { return v < -1; }
 __device__ __forceinline__ int ref_point(int v) { return v < -1 ? -2 - v : v; }
 
+// Where the border pass finds its work: a count of records and of listed walks per
+// XCD, and the queries per XCD of the core pass, each on a memory line of its own (a
+// counter that every workgroup of the chip adds to passes them one at a time: with
+// one for all, the core pass of the uniform 2M-point set took 0.69 ms in workgroups
+// of 64, 0.39 of 128 and 0.29 of 256).
+__device__ __forceinline__ constexpr int kRecCount(int xcd) { return 32 * xcd; }
+__device__ __forceinline__ constexpr int kWalkCount(int xcd) { return 32 * (kNumXcd + xcd); }
+constexpr int kWalkShare = 32 * 2 * kNumXcd;
+
 // End of a core pass for query point i (primitive p): core and lone flags, and
 // what the border pass will need: nothing (core, or lone: border -1 now), a
 // neighbour record, or a walk. Called by every thread of the workgroup.
+// first: the first query of this XCD's share (which its walk list starts at).
 __device__ __forceinline__ void core_epilogue(const TravArgs& a, bool mine, int i, int p, int cnt, int min_pts,
-                                              const NbRec& rec, int* s_w) {
+                                              const NbRec& rec, int* s_w, int64_t first) {
   const bool core = mine && cnt >= min_pts;
   const bool lone = mine && cnt <= 1 && !core;
   if (mine) {
@@ -450,16 +462,19 @@ __device__ __forceinline__ void core_epilogue(const TravArgs& a, bool mine, int 
   }
   const bool want = mine && !core && !lone;
   const bool fits = want && rec.nn <= kRecNb;
-  const int slot = block_reserve(a.brec_n, fits, s_w);
+  const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
+  const int slot = block_reserve(a.border_n + kRecCount(xcd), fits, s_w);
   const bool stored = fits && slot < a.brec_cap;
   if (stored) {
-    a.brec_i[slot] = i;
+    const int64_t k = int64_t(xcd) * a.brec_cap + slot;
+    a.brec_i[k] = i;
 #pragma unroll
-    for (int t = 0; t < kRecNb; ++t)
-      a.brec_nb[int64_t(slot) * kRecNb + t] = t < rec.nn ? ref_point(rec_get(rec, t)) : -1;
+    for (int t = 0; t < kRecNb; ++t) a.brec_nb[k * kRecNb + t] = t < rec.nn ? ref_point(rec_get(rec, t)) : -1;
   }
-  const int wslot = block_reserve(a.qborder_n, want && !stored, s_w);
-  if (wslot >= 0) a.qborder[wslot] = p;
+  if (__syncthreads_or(want && !stored)) {
+    const int wslot = block_reserve(a.border_n + kWalkCount(xcd), want && !stored, s_w);
+    if (wslot >= 0) a.qborder[first + wslot] = p;
+  }
 }
 
 // A non-core point with no neighbour but itself (known once the core pass has
@@ -511,7 +526,9 @@ __global__ void k_core_fdb(TravArgs a) {
       if (j != i) rec_add(rec, j);
       return ++cnt >= sc.min_pts;
     });
-  core_epilogue(a, mine, i, i, cnt, sc.min_pts, rec, s_w);
+  const int64_t share = xcd_share(a.n, blockDim.x);
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(share);
+  core_epilogue(a, mine, i, i, cnt, sc.min_pts, rec, s_w, (blockIdx.x % kNumXcd) * share);
 }
 
 // First-claim main phase (the paper's border rule): per-lane walks, or a packet
@@ -886,9 +903,10 @@ __global__ __launch_bounds__(256) void k_main_fdb_q(TravArgs a) {
 // Border pass from the core pass's neighbour records (no walk): the smallest
 // cluster id among the recorded core neighbours.
 __global__ void k_border_rec(TravArgs a) {
-  const int nr = min(*a.brec_n, a.brec_cap);
-  const int64_t k = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, nr);
-  if (k < 0 || k >= nr) return;
+  const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
+  const int64_t slot = int64_t(blockIdx.x / kNumXcd) * blockDim.x + threadIdx.x;
+  if (slot >= min(a.border_n[kRecCount(xcd)], a.brec_cap)) return;
+  const int64_t k = int64_t(xcd) * a.brec_cap + slot;
   const int i = a.brec_i[k];
   int best = 0x7fffffff;
 #pragma unroll
@@ -907,10 +925,10 @@ __global__ void k_border_rec(TravArgs a) {
 // cover the rest).
 template <int D, bool B>
 __global__ void k_border_fdb(TravArgs a) {
-  const int nq = *a.qborder_n;
-  const int64_t k = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, nq);
-  if (k < 0 || k >= nq) return;
-  const int i = a.qborder[k];
+  const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
+  const int64_t slot = int64_t(blockIdx.x / kNumXcd) * blockDim.x + threadIdx.x;
+  if (slot >= a.border_n[kWalkCount(xcd)]) return;
+  const int i = a.qborder[int64_t(xcd) * a.border_n[kWalkShare] + slot];
   const int m = tree_m(a.t);
   const Scope sc = scope_of<B>(a, m, static_cast<int>(i));
   const Query q = load_point<D>(a.xs, a.n, i);
@@ -1148,445 +1166,244 @@ __device__ __forceinline__ int walk_step(Walk& w, const TreeView& t, int m, cons
   return -1;
 }
 
-// ---- isolated points (one cloud, DenseBox, 32-bit grid keys) --------------------
-// Before the core walks, a point primitive that has no neighbour but itself is
-// settled by an occupancy map of the grid cells (side eps/sqrt(d)): one bit per
-// cell, in 64-bit words per brick of 4x4x4 cells (3D) or 8x8 (2D). Bricks follow
-// the Morton order, so a brick is the grid key without its lowest 6 bits; inside
-// a brick, local cell (x, y, z) is bit x*16 + y*4 + z (3D) or x*8 + y (2D). A word
-// is written only for an occupied brick, which a table of one bit per brick marks
-// (the table is cleared each call, the words never are).
-template <int D>
-constexpr int kBrickShift = D == 3 ? 2 : 3;  // local coordinate bits per axis
+// ---- grid or hierarchy ------------------------------------------------------------
+// The DenseBox kernels are built twice: G walks the grid's cells (fdb_cells.hpp),
+// !G the hierarchy. Both are launched and the plan on the device says which one
+// runs; the other leaves at once. A walker yields one primitive per step, so that a
+// wavefront can pause its lanes between steps and scan a large dense cell together.
+template <bool G>
+__device__ __forceinline__ bool other_walk(const TravArgs& a) {
+  return (a.ix.plan->grid_on != 0) != G;
+}
 
-template <int D>
-__device__ __forceinline__ int brick_bit(uint32_t code) {  // from the code's lowest 6 bits
-  if constexpr (D == 3) {
-    const uint32_t z = (code & 1u) | ((code >> 2) & 2u);
-    const uint32_t y = ((code >> 1) & 1u) | ((code >> 3) & 2u);
-    const uint32_t x = ((code >> 2) & 1u) | ((code >> 4) & 2u);
-    return static_cast<int>(x * 16 + y * 4 + z);
-  } else {
-    const uint32_t y = (code & 1u) | ((code >> 1) & 2u) | ((code >> 2) & 4u);
-    const uint32_t x = ((code >> 1) & 1u) | ((code >> 2) & 2u) | ((code >> 3) & 4u);
-    return static_cast<int>(x * 8 + y);
+// LDS of a wavefront's search through the grid: a packet's cell list or the columns
+// of its lanes' walks (dynamic shared memory).
+template <int D, bool G>
+constexpr int kSearchLds = G ? kWalkWaveBytes<D> : 0;
+static_assert(kWalkWaveBytes<2> >= kBoxList * 4 && kWalkWaveBytes<3> >= kBoxList * 4, "a packet's list fits too");
+template <int D, bool G>
+__device__ __forceinline__ char* search_lds(char* base) {
+  return base + (threadIdx.x >> 6) * kSearchLds<D, G>;
+}
+
+template <int D, bool B, bool MASKED, bool G, bool NEAR = false>
+struct Walker {
+  using State = std::conditional_t<G, CellWalk<D>, Walk>;
+  State w;
+  char* lds;
+
+  // wave_lds: search_lds of the wavefront. The query is the box [lo, hi] (a point
+  // when they are equal) at sorted point i.
+  __device__ __forceinline__ void init(const TravArgs& a, int m, const Scope& sc, int i, const float* lo,
+                                       const float* hi, int mask, bool on, char* wave_lds) {
+    lds = wave_lds;
+    if constexpr (G) {
+      const CellGrid g = query_grid<D, B>(a.ix, B ? cloud_of(a, i) : 0);
+      CellRange<D> cr;
+      cell_range<D>(cr, g, lo, hi);
+      cell_walk_init<D, MASKED, NEAR>(w, a.ix, g, cr, on && g.ncell[0] > 0, lds);
+    } else {
+      walk_init<MASKED>(w, m, sc, mask, on);
+    }
   }
+  __device__ __forceinline__ bool done() const {
+    if constexpr (G) return cell_walk_done(w);
+    else return walk_done(w);
+  }
+  template <typename QT>
+  __device__ __forceinline__ int step(const TravArgs& a, int m, const QT& q, float eps2, int mask) {
+    if constexpr (G) return cell_walk_step<D, MASKED>(w, a.ix, mask, lds);
+    else return walk_step<D, MASKED>(w, a.t, m, q, eps2, mask, a.info);
+  }
+};
+
+// Neighbours that a lane has to join to its query's set, put off until some lane has
+// kHits of them: a union is a chain of several round trips for which the whole
+// wavefront waits, so lanes do theirs together (a column per lane in the wavefront's
+// LDS). Uniform 2M-point set: point main phase 0.72 -> 0.66 ms. (The dense-cell main
+// phase keeps joining at once: its pair tests are what costs, and the set they skip
+// by has to be up to date; put off, the batch's 5.0 ms became 9.5.)
+constexpr int kHits = 8;
+constexpr int kHitBytes = kHits * 64 * 4;
+
+struct Hits {
+  int* col;
+  int n;
+};
+
+__device__ __forceinline__ void hits_init(Hits& h, char* lds) {
+  h.col = reinterpret_cast<int*>(lds) + lane_id();
+  h.n = 0;
 }
 
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int off) {
-  const uint32_t lo = static_cast<uint32_t>(__shfl_up(static_cast<int>(v), off));
-  const uint32_t hi = static_cast<uint32_t>(__shfl_up(static_cast<int>(v >> 32), off));
-  return (uint64_t(hi) << 32) | lo;
+__device__ __forceinline__ void hits_add(Hits& h, int j) { h.col[64 * h.n++] = j; }
+
+__device__ __forceinline__ bool hits_full(const Hits& h) { return ballot(h.n >= kHits) != 0; }
+
+__device__ __forceinline__ void hits_join(Hits& h, int* labels, int& root, uint32_t* info) {
+  for (int t = 0; ballot(t < h.n); ++t) {
+    if (t < h.n) {
+      const int j = h.col[64 * t];
+      if (!known_same_set(labels, j, root)) root = uf_union(labels, root, j, info);
+    }
+  }
+  h.n = 0;
 }
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int off) {
-  const uint32_t lo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), off));
-  const uint32_t hi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(v >> 32), off));
-  return (uint64_t(hi) << 32) | lo;
-}
+// The queries of a DenseBox kernel, whose number `total` only the device knows: a
+// workgroup takes chunks of kLanes queries a wavefront, blockIdx.x, + gridDim.x, ...
+// (gridDim.x a multiple of kNumXcd), laid out over the XCDs as xcd_spread has them.
+// The grid is capped (query_grid_blocks): with a workgroup for each of the n points
+// the queries could be, 65,536 workgroups without work took 15 us a launch (8M set).
+// Few queries take fewer lanes a wavefront, down to 8, so that kWaves wavefronts or
+// more share them: a wavefront's time is its lanes' loads, scans and unions one after the
+// other, and 44k queries (370k-point mixture) fill only 700 wavefronts of 64.
+constexpr int kWaves = 4096;
 
-// A brick word is written once, by the wavefront holding the brick's first
-// primitive: a segmented OR over the wavefront's 64 primitives, and for its last
-// brick the following primitives of the same brick, read 64 at a time.
-// It also clears the list counters of k_lone_filter, which runs after it.
-// Primitive keys are 64-bit words; the isolated-point test runs on grids keyed in
-// 32 bits, so only the low word carries the key.
-__device__ __forceinline__ uint32_t key32(const uint64_t* __restrict__ pkey, int64_t p) {
-  return static_cast<uint32_t>(pkey[p]);
-}
+struct Chunks {
+  int64_t chunk, off;  // queries per XCD; this workgroup's first within its XCD's
+  int lanes, step, slot, xcd;
 
-// Clears the occupancy words (as many as the plan asks for; none when the test
-// does not run).
-__global__ __launch_bounds__(256) void k_lone_clear(const GridPlan* __restrict__ plan, uint64_t* __restrict__ bits) {
-  if (!plan->lone_on) return;
-  const int64_t words = (plan->lone_words + 63) / 64;  // the brick table, 64 brick bits per word
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < words; i += int64_t(gridDim.x) * blockDim.x)
-    bits[i] = 0ull;
-}
+  __device__ __forceinline__ Chunks(int64_t total, bool spread) {
+    lanes = 64;
+    while (spread && lanes > 8 && total < int64_t(kWaves) * (lanes / 2)) lanes >>= 1;
+    const int per = lanes * static_cast<int>(blockDim.x >> 6);  // queries a workgroup and chunk
+    chunk = xcd_share(total, per);
+    xcd = static_cast<int>(blockIdx.x % kNumXcd);
+    off = int64_t(blockIdx.x / kNumXcd) * per;
+    step = static_cast<int>(gridDim.x / kNumXcd) * per;
+    slot = lane_id() < lanes ? static_cast<int>(threadIdx.x >> 6) * lanes + lane_id() : -1;
+  }
+  __device__ __forceinline__ bool in() const { return off < chunk; }
+  __device__ __forceinline__ void next() { off += step; }
+  // this lane's query (at or above the total where the chunk runs past it), -1: none
+  __device__ __forceinline__ int query() const { return slot < 0 ? -1 : static_cast<int>(xcd * chunk + off + slot); }
+};
 
+// Cells and pairs this small are tested by the lane that reached them (all lanes at
+// once) instead of by the wavefront one lane after another.
+constexpr int kLaneScan = 16;    // points of a dense cell against one point
+constexpr int kLanePairs = 128;  // pairs of two dense cells
+
+// Number of points of the cell [s, s+c) within eps of q (this lane alone).
 template <int D>
-__global__ __launch_bounds__(256) void k_lone_bits(const uint64_t* __restrict__ pkey, const int* __restrict__ d_m,
-                                                   const GridPlan* __restrict__ plan, uint64_t* __restrict__ bits,
-                                                   uint32_t* __restrict__ table, int* __restrict__ list_n) {
-  if (!plan->lone_on) return;
-  if (blockIdx.x == 0 && threadIdx.x < kNumXcd) list_n[threadIdx.x] = 0;
-  const int m = *d_m;
+__device__ __forceinline__ int lane_count_near(const float* __restrict__ xs, int64_t n, int s, int c, const Query& q,
+                                               float eps2) {
+  int found = 0;
+  for (int j = 0; j < c; j += 4) {
+    float v[4][3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t k = s + min(j + u, c - 1);
+      v[u][0] = xs[k];
+      v[u][1] = xs[n + k];
+      v[u][2] = D == 3 ? xs[2 * n + k] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (j + u < c && dist2v<D>(v[u][0], v[u][1], v[u][2], q.x, q.y, q.z) <= eps2) ++found;
+  }
+  settle(found);
+  return found;
+}
+
+// Is some pair of a point of cell [sa, sa+na) and one of [sb, sb+nb), whose tight box
+// is [blo, bhi], within eps? (this lane alone)
+template <int D>
+__device__ __forceinline__ bool lane_cells_touch(const float* __restrict__ xs, int64_t n, int sa, int na, int sb,
+                                                 int nb, float4 blo, float4 bhi, float eps2) {
+  int hits = 0;
+  for (int j = 0; j < na && hits == 0; ++j) {
+    const Query q = load_point<D>(xs, n, sa + j);
+    if (box_dist2<D>(q.x, q.y, q.z, blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z) <= eps2)
+      hits = cell_within<D>(blo, bhi, q, eps2) ? 1 : lane_count_near<D>(xs, n, sb, nb, q, eps2);
+  }
+  settle(hits);
+  return hits != 0;
+}
+
+// Core pass for points outside dense cells, one lane per point primitive p (called by
+// every thread of the workgroup).
+template <int D, bool B, bool G>
+__device__ __forceinline__ void core_query(const TravArgs& a, int m, int p, int64_t first, char* s_dyn, int* s_w) {
   const int lane = lane_id();
-  // a wavefront per 64 primitives, over a grid-stride loop (uniform per wavefront)
-  const int64_t waves = int64_t(gridDim.x) * (blockDim.x >> 6);
-  for (int64_t p0 = (blockIdx.x * int64_t(blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; p0 < m; p0 += waves * 64) {
-    const int64_t p = p0 + lane;
-    const bool valid = p < m;
-    const uint32_t code = valid ? key32(pkey, p) : 0xffffffffu;
-    const uint32_t word = code >> 6;  // invalid lanes: above every valid brick
-    const uint32_t prevw = static_cast<uint32_t>(__shfl_up(static_cast<int>(word), 1));
-    const uint32_t nextw = static_cast<uint32_t>(__shfl_down(static_cast<int>(word), 1));
-    const bool head = lane == 0 || word != prevw;
-    // segmented inclusive OR: the last lane of a run of equal bricks holds the run's bits
-    uint64_t v = valid ? (1ull << brick_bit<D>(code)) : 0ull;
-    bool f = head;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint64_t u = shfl_up_u64(v, off);
-      const bool g = __shfl_up(static_cast<int>(f), off) != 0;
-      if (lane >= off && !f) {
-        v |= u;
-        f = g;
-      }
-    }
-    const uint32_t w0 = static_cast<uint32_t>(__shfl(static_cast<int>(word), 0));
-    // the wavefront's first run may continue a brick begun by the previous
-    // wavefront, which then writes it
-    const bool continued = p0 > 0 && (key32(pkey, p0 - 1) >> 6) == w0;
-    const bool in_first_run = __popcll(ballot(head) & (lanemask_lt() | (1ull << lane))) == 1;
-    const uint32_t w63 = static_cast<uint32_t>(__shfl(static_cast<int>(word), 63));
-    uint64_t extra = 0;
-    // lane 63 is valid and its run may go on past this wavefront; only the
-    // wavefront that writes that brick reads ahead
-    if (p0 + 64 < m && !(continued && w63 == w0)) {
-      for (int64_t b = p0 + 64; b < m; b += 64) {
-        const int64_t q = b + lane;
-        const uint32_t c2 = q < m ? key32(pkey, q) : 0xffffffffu;
-        const bool in = q < m && (c2 >> 6) == w63;
-        uint64_t x = in ? (1ull << brick_bit<D>(c2)) : 0ull;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x |= shfl_xor_u64(x, off);
-        extra |= x;
-        if (!((ballot(in) >> 63) & 1)) break;  // codes are sorted: the run ended in this chunk
-      }
-    }
-    const bool tail = valid && (lane == 63 || nextw != word);
-    const bool writes = tail && !(continued && in_first_run);
-    if (writes) bits[word] = v | (lane == 63 ? extra : 0ull);
-    // mark the written bricks in the table: the writers' bricks rise with the lanes,
-    // so those sharing a table word are consecutive; one atomic per table word
-    const uint32_t tw = word >> 5;
-    for (uint64_t wm = ballot(writes); wm;) {
-      const int L = __ffsll(static_cast<unsigned long long>(wm)) - 1;
-      const uint32_t t0 = static_cast<uint32_t>(__shfl(static_cast<int>(tw), L));
-      const uint64_t grp = ballot(writes && tw == t0);
-      uint32_t mbits = (writes && tw == t0) ? 1u << (word & 31) : 0u;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) mbits |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(mbits), off));
-      if (lane == L) atomicOr(table + t0, mbits);
-      wm &= ~grp;
-    }
-  }
-}
-
-__device__ __forceinline__ uint32_t compact_every(uint32_t x, int d) {  // inverse of the Morton spread
-  if (d == 3) {
-    x &= 0x09249249u;
-    x = (x | (x >> 2)) & 0x030c30c3u;
-    x = (x | (x >> 4)) & 0x0300f00fu;
-    x = (x | (x >> 8)) & 0xff0000ffu;
-    x = (x | (x >> 16)) & 0x000003ffu;
-  } else {
-    x &= 0x55555555u;
-    x = (x | (x >> 1)) & 0x33333333u;
-    x = (x | (x >> 2)) & 0x0f0f0f0fu;
-    x = (x | (x >> 4)) & 0x00ff00ffu;
-    x = (x | (x >> 8)) & 0x0000ffffu;
-  }
-  return x;
-}
-
-__device__ __forceinline__ uint32_t spread_every(uint32_t x, int d) {  // Morton spread of one coordinate
-  if (d == 3) {
-    x &= 0x000003ffu;
-    x = (x | (x << 16)) & 0xff0000ffu;
-    x = (x | (x << 8)) & 0x0300f00fu;
-    x = (x | (x << 4)) & 0x030c30c3u;
-    x = (x | (x << 2)) & 0x09249249u;
-  } else {
-    x &= 0x0000ffffu;
-    x = (x | (x << 8)) & 0x00ff00ffu;
-    x = (x | (x << 4)) & 0x0f0f0f0fu;
-    x = (x | (x << 2)) & 0x33333333u;
-    x = (x | (x << 1)) & 0x55555555u;
-  }
-  return x;
-}
-
-// A point primitive is isolated when no other primitive shares its cell (they
-// would be next to it in key order) and no occupied cell lies within reach of it:
-// in cell units, the per-axis gaps between the point's coordinate t = (x - lo) /
-// side and a cell's interval, summed in squares, exceed plan->reach^2, where reach
-// is eps / side plus a slack covering the rounding of t (computed as the key
-// kernel computes it) for both points. A neighbour j of the point (the fp32 test
-// true) is within eps (1 + 2^-22) per axis; its cell's gap vector is bounded by
-// |t_j - t| per axis, whose norm the slack covers, so its cell is within reach.
-// Conservative: a false answer only means "walk it". Reach is below 2, so the
-// reachable cells lie within 2 per axis: at most 2^d brick words per query, each
-// current only when its bit in the table is set.
-
-// Bits of a brick whose coordinate on axis a lies in [l, h] (local, l <= h).
-template <int D>
-__device__ __forceinline__ uint64_t axis_bits(int a, int l, int h) {
-  if constexpr (D == 3) {
-    if (a == 0) return (~0ull >> (48 - 16 * h)) & (~0ull << (16 * l));
-    if (a == 1) return uint64_t((0xffffu >> (12 - 4 * h)) & (0xffffu << (4 * l)) & 0xffffu) * 0x0001000100010001ull;
-    return uint64_t((0xfu >> (3 - h)) & (0xfu << l) & 0xfu) * 0x1111111111111111ull;
-  } else {
-    if (a == 0) return (~0ull >> (56 - 8 * h)) & (~0ull << (8 * l));
-    return uint64_t((0xffu >> (7 - h)) & (0xffu << l) & 0xffu) * 0x0101010101010101ull;
-  }
-}
-
-// Gap of coordinate t (its own cell c) to the interval of cell `cell`, in cell units.
-__device__ __forceinline__ float cell_gap(float t, int c, int cell) {
-  return cell == c ? 0.0f : (cell > c ? static_cast<float>(cell) - t : t - static_cast<float>(cell + 1));
-}
-
-template <int D>
-__device__ __forceinline__ bool isolated(const uint64_t* __restrict__ pkey, int m, int p, float4 pt,
-                                         const GridPlan& g, const float* lo_b, const uint64_t* __restrict__ words,
-                                         const uint32_t* __restrict__ table) {
-  // Straight-line on purpose: the three keys are loaded together, then every
-  // brick's table bit and word together (a word of an unmarked brick is stale
-  // and discarded), so a query waits for two memory round trips, not one per
-  // brick. Bricks outside the grid load brick 0 and are masked out.
-  const uint32_t key = key32(pkey, p);
-  const uint32_t kprev = key32(pkey, p > 0 ? p - 1 : p);
-  const uint32_t knext = key32(pkey, p + 1 < m ? p + 1 : p);
-  const bool shared = (p > 0 && kprev == key) || (p + 1 < m && knext == key);
-  constexpr int S = kBrickShift<D>, W = 1 << S;
-  constexpr int NB = D == 3 ? 8 : 4;  // bricks that can hold cells within 2 per axis
-  const float xv[3] = {pt.x, pt.y, pt.z};
-  float t[3] = {0.0f, 0.0f, 0.0f};
-  int c[3] = {0, 0, 0}, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    t[a] = fmaxf((xv[a] - lo_b[a]) * g.inv_h[a], 0.0f);  // as the key kernel computes it
-    c[a] = static_cast<int>(compact_every(key >> (D - 1 - a), D));
-    lo[a] = c[a] >= 2 ? c[a] - 2 : 0;
-    hi[a] = min(c[a] + 2, static_cast<int>(g.ncell[a]) - 1);
-  }
-  uint32_t bidx[NB];
-  uint64_t bbox[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    const int br[3] = {(lo[0] >> S) + (n >> (D - 1)), (lo[1] >> S) + ((n >> (D - 2)) & 1), (lo[2] >> S) + (n & 1)};
-    bool use = br[0] <= (hi[0] >> S) && br[1] <= (hi[1] >> S);
-    if (D == 3) use = use && br[2] <= (hi[2] >> S);
-    uint32_t b = 0;
-    uint64_t box = ~0ull;  // the brick's cells within 2 per axis
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-      const int base = br[a] << S;
-      box &= axis_bits<D>(a, max(lo[a], base) - base, min(hi[a], base + W - 1) - base);
-      b |= spread_every(static_cast<uint32_t>(br[a]), D) << (D - 1 - a);
-    }
-    bidx[n] = use ? b : 0u;
-    bbox[n] = use ? box : 0ull;
-  }
-  uint32_t tw[NB];
-  uint64_t ww[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    tw[n] = table[bidx[n] >> 5];
-    ww[n] = words[bidx[n]];
-  }
-  const uint32_t own_brick = key >> 6;
-  const int own_bit = brick_bit<D>(key);
-  const float r2 = g.reach * g.reach;
-  bool near = shared;
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    uint64_t occ = (tw[n] >> (bidx[n] & 31)) & 1u ? ww[n] & bbox[n] : 0ull;
-    if (bidx[n] == own_brick) occ &= ~(1ull << own_bit);
-    // the occupied cells among them (usually none, or a few): exact reach test
-    const int bx = static_cast<int>(compact_every(bidx[n] >> (D - 1), D)) << S;
-    const int by = static_cast<int>(compact_every(bidx[n] >> (D - 2), D)) << S;
-    const int bz = D == 3 ? static_cast<int>(compact_every(bidx[n], D)) << S : 0;
-    for (; occ && !near; occ &= occ - 1) {
-      const int bit = __ffsll(static_cast<unsigned long long>(occ)) - 1;
-      const int lx = D == 3 ? bit >> 4 : bit >> 3;
-      const int ly = D == 3 ? (bit >> 2) & 3 : bit & 7;
-      const int lz = D == 3 ? bit & 3 : 0;
-      const float gx = cell_gap(t[0], c[0], bx + lx);
-      const float gy = cell_gap(t[1], c[1], by + ly);
-      const float gz = D == 3 ? cell_gap(t[2], c[2], bz + lz) : 0.0f;
-      near = gx * gx + gy * gy + gz * gz <= r2;
-    }
-  }
-  return !near;
-}
-
-// A workgroup tests kLoneRounds x 256 consecutive primitives and lists the ones
-// left for the core pass with one atomic (a counter taken by many workgroups is
-// the cost to keep low), in primitive order within the workgroup. The primitives
-// are cut into kNumXcd segments of lone_segment(m) (a multiple of a workgroup's
-// share); segment s has its own counter and lists into list[s * segment ...], which
-// never passes its own primitive range, so the list needs m entries. The core pass
-// gives segment s to the workgroups of XCD s: each XCD walks one contiguous range
-// of the curve, as it does without the test.
-constexpr int kLoneRounds = 4;
-
-__device__ __forceinline__ int64_t lone_segment(int m) {
-  const int64_t share = kLoneRounds * 256;
-  return ((m + kNumXcd - 1) / kNumXcd + share - 1) / share * share;
-}
-
-template <int D>
-__global__ __launch_bounds__(256) void k_lone_filter(TravArgs a, const uint64_t* __restrict__ pkey,
-                                                     const GridPlan* __restrict__ plan,
-                                                     const uint64_t* __restrict__ words,
-                                                     const uint32_t* __restrict__ table,
-                                                     const uint32_t* __restrict__ bounds, int* __restrict__ list,
-                                                     int* __restrict__ list_n) {
-  __shared__ int s_cnt[kLoneRounds * 4 + 1];
-  if (!plan->lone_on) return;
-  const GridPlan gp = *plan;
-  float lo_b[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int k = 0; k < D; ++k) lo_b[k] = ord2f(bounds[k]);
-  const int m = tree_m(a.t);
-  const int64_t base = blockIdx.x * int64_t(kLoneRounds * 256);
-  if (base >= m) return;  // whole workgroup
-  const int64_t segment = lone_segment(m);
-  const int seg = static_cast<int>(base / segment);  // a workgroup lies in one segment
-  const int w = threadIdx.x >> 6;
-  uint32_t keep = 0;  // bit r: primitive of round r is listed
-  for (int r = 0; r < kLoneRounds; ++r) {
-    const int64_t p = base + r * 256 + threadIdx.x;
-    bool query = false, lone = false;
-    int i = 0;
-    if (p < m) {
-      // the test's loads do not wait for the record (a dense cell's answer is discarded)
-      const float4 lr = a.prim_lo[p];
-      const bool iso = isolated<D>(pkey, m, static_cast<int>(p), lr, gp, lo_b, words, table);
-      i = rec_index(lr);
-      query = i >= 0;
-      lone = query && iso;
-    }
-    if (lone) {
-      a.core[i] = 0;
-      a.lone[i] = 1;
-      a.border[i] = -1;
-    }
-    const bool listed = query && !lone;
-    keep |= listed ? 1u << r : 0u;
-    const uint64_t bal = ballot(listed);
-    if (lane_id() == 0) s_cnt[r * 4 + w] = __popcll(bal);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int tot = 0;
-    for (int k = 0; k < kLoneRounds * 4; ++k) {
-      const int c = s_cnt[k];
-      s_cnt[k] = tot;
-      tot += c;
-    }
-    s_cnt[kLoneRounds * 4] = tot ? atomicAdd(list_n + seg, tot) : 0;
-  }
-  __syncthreads();
-  const int64_t start = s_cnt[kLoneRounds * 4] + seg * segment;
-  for (int r = 0; r < kLoneRounds; ++r) {
-    const bool listed = (keep >> r) & 1u;
-    const uint64_t bal = ballot(listed);
-    if (listed)
-      list[start + s_cnt[r * 4 + w] + __popcll(bal & lanemask_lt())] = static_cast<int>(base + r * 256 + threadIdx.x);
-  }
-}
-
-// Core pass for points outside dense cells. Each lane walks for kCoreQ
-// neighbouring point primitives (kCoreQ k + t for lane k of the index space).
-// Two walks per lane keep more node loads in flight, but a wavefront then waits
-// for the longest of 128 walks and the 8M-point set fills fewer wavefronts than
-// the chip has slots: measured slower (0.55 vs 0.47 ms), so one.
-constexpr int kCoreQ = 1;
-
-template <int D, bool B>
-__global__ void k_core_dbx(TravArgs a) {
-  __shared__ int s_w[17];
-  extern __shared__ int s_rec[];  // kCoreQ tables of kRecNb * blockDim.x
-  const int m = tree_m(a.t);
-  const int lane = lane_id();
-  // the grid is sized for n queries; a workgroup past the m primitives leaves
-  // at once (uniformly, before any barrier)
-  static_assert(kCoreQ == 1, "a listed query is one primitive");
-  // listed queries: XCD x (workgroup index mod kNumXcd) takes segment x of the list
-  const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
-  const bool listed = a.core_list && (!a.lone_on || *a.lone_on);
-  const int* qlist = listed ? a.core_list + xcd * lone_segment(m) : nullptr;
-  const int64_t total = listed ? a.core_qn[xcd] : (m + kCoreQ - 1) / kCoreQ;
-  const int64_t k0 = listed ? int64_t(blockIdx.x / kNumXcd) * blockDim.x
-                            : xcd_spread(blockIdx.x, blockDim.x, 0, total);
-  if (k0 < 0 || k0 >= total) return;
-  const int64_t k = listed ? k0 + threadIdx.x : xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, total);
-  int p[kCoreQ], i[kCoreQ], cnt[kCoreQ];
-  bool mine[kCoreQ], active[kCoreQ];
-  Scope sc[kCoreQ];
-  Query q[kCoreQ];
-  NbRec rec[kCoreQ];
-  Walk w[kCoreQ];
-#pragma unroll
-  for (int t = 0; t < kCoreQ; ++t) {
-    p[t] = k < 0 || k >= total ? -1 : (qlist ? qlist[k] : static_cast<int>(k * kCoreQ + t));
-    own_record(a, p[t], m, mine[t], i[t], q[t]);  // dense cells are core by construction
-    sc[t] = scope_of<B>(a, m, i[t]);
-    cnt[t] = 0;
-    rec_init(rec[t], s_rec + t * kRecNb * blockDim.x);
-  }
-#pragma unroll
-  for (int t = 0; t < kCoreQ; ++t) {
-    walk_init<false>(w[t], m, sc[t], 0, mine[t]);
-    active[t] = mine[t] && !walk_done(w[t]);
-  }
-  for (;;) {
-    bool any = false;
-#pragma unroll
-    for (int t = 0; t < kCoreQ; ++t) any |= active[t];
-    if (!ballot(any)) break;
-    int pend[kCoreQ], pcnt[kCoreQ];  // a dense cell to scan: its first point and its size
-#pragma unroll
-    for (int t = 0; t < kCoreQ; ++t) {
-      pend[t] = -1;
-      pcnt[t] = 0;
-      if (active[t]) {
-        const int r = walk_step<D, false>(w[t], a.t, m, q[t], sc[t].eps2, 0, a.info);
-        if (r >= 0) {
-          const float4 lr = a.prim_lo[r];
-          const int s = rec_index(lr);
-          if (s >= 0) {
-            if (rec_point_near<D>(lr, q[t], sc[t].eps2)) {
-              ++cnt[t];
-              if (s != i[t]) rec_add(rec[t], s);
-            }
-          } else {
-            const float4 hr = a.prim_hi[r];
-            if (box_dist2<D>(q[t].x, q[t].y, q[t].z, lr.x, lr.y, lr.z, hr.x, hr.y, hr.z) <= sc[t].eps2) {
-              if (cell_within<D>(lr, hr, q[t], sc[t].eps2)) {  // counted whole, no scan
-                cnt[t] += __float_as_int(hr.w);
-                rec_add(rec[t], s);  // s == cell_ref(first point)
-              } else {  // both from the records already loaded: the scan starts with the points
-                pend[t] = ref_point(s);
-                pcnt[t] = __float_as_int(hr.w);
-              }
+  bool mine;
+  int i;
+  Query q;
+  own_record(a, p, m, mine, i, q);  // dense cells are core by construction
+  const Scope sc = scope_of<B>(a, m, i);
+  int cnt = 0;
+  NbRec rec;
+  rec_init(rec, reinterpret_cast<int*>(s_dyn + size_t(kSearchLds<D, G>) * (blockDim.x >> 6)));
+  const float qv[3] = {q.x, q.y, q.z};
+  Walker<D, B, false, G, true> w;
+  w.init(a, m, sc, i, qv, qv, 0, mine, search_lds<D, G>(s_dyn));
+  bool active = mine && !w.done();
+  while (ballot(active)) {
+    int pend = -1, pcnt = 0;  // a dense cell to scan: its first point and its size
+    if (active) {
+      const int r = w.step(a, m, q, sc.eps2, 0);
+      if (r >= 0) {
+        const float4 lr = a.prim_lo[r];
+        const int s = rec_index(lr);
+        if (s >= 0) {
+          if (rec_point_near<D>(lr, q, sc.eps2)) {
+            ++cnt;
+            if (s != i) rec_add(rec, s);
+          }
+        } else {
+          const float4 hr = a.prim_hi[r];
+          if (box_dist2<D>(q.x, q.y, q.z, lr.x, lr.y, lr.z, hr.x, hr.y, hr.z) <= sc.eps2) {
+            const int np = __float_as_int(hr.w);
+            if (cell_within<D>(lr, hr, q, sc.eps2)) {  // counted whole, no scan
+              cnt += np;
+              rec_add(rec, s);  // s == cell_ref(first point)
+            } else if (G && np <= kLaneScan) {
+              const int found = lane_count_near<D>(a.xs, a.n, ref_point(s), np, q, sc.eps2);
+              cnt += found;
+              if (found) rec_add(rec, s);
+            } else {  // both from the records already loaded: the scan starts with the points
+              pend = ref_point(s);
+              pcnt = np;
             }
           }
         }
       }
     }
-#pragma unroll
-    for (int t = 0; t < kCoreQ; ++t) {
-      for (uint64_t pm = ballot(pend[t] >= 0); pm; pm &= pm - 1) {
-        const int L = __ffsll(static_cast<unsigned long long>(pm)) - 1;
-        const int s = __shfl(pend[t], L);
-        const int want = __shfl(sc[t].min_pts - cnt[t], L);
-        const int found = cell_count_near<D>(a.xs, a.n, s, __shfl(pcnt[t], L), __shfl(q[t].x, L), __shfl(q[t].y, L),
-                                             __shfl(q[t].z, L), readlane_f(sc[t].eps2, L), want);
-        if (lane == L && found > 0) {
-          cnt[t] += found;
-          rec_add(rec[t], cell_ref(s));  // a dense cell: all core, one cluster; its first point stands for it
-        }
+    for (uint64_t pm = ballot(pend >= 0); pm; pm &= pm - 1) {
+      const int L = __ffsll(static_cast<unsigned long long>(pm)) - 1;
+      const int s = __shfl(pend, L);
+      const int want = __shfl(sc.min_pts - cnt, L);
+      const int found = cell_count_near<D>(a.xs, a.n, s, __shfl(pcnt, L), __shfl(q.x, L), __shfl(q.y, L),
+                                           __shfl(q.z, L), readlane_f(sc.eps2, L), want);
+      if (lane == L && found > 0) {
+        cnt += found;
+        rec_add(rec, cell_ref(s));  // a dense cell: all core, one cluster; its first point stands for it
       }
-      if (active[t] && (cnt[t] >= sc[t].min_pts || walk_done(w[t]))) active[t] = false;
     }
+    if (active && (cnt >= sc.min_pts || w.done())) active = false;
   }
-#pragma unroll
-  for (int t = 0; t < kCoreQ; ++t) core_epilogue(a, mine[t], i[t], p[t], cnt[t], sc[t].min_pts, rec[t], s_w);
+  core_epilogue(a, mine, i, p, cnt, sc.min_pts, rec, s_w, first);
+}
+
+template <int D, bool B, bool G>
+__global__ __launch_bounds__(G ? 256 : 1024) void k_core_dbx(TravArgs a) {
+  __shared__ int s_w[17];
+  extern __shared__ __align__(16) char s_dyn[];  // the walk's columns, then neighbour records
+  if (other_walk<G>(a)) return;
+  const int m = tree_m(a.t);
+  Chunks c(m, G);
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(c.chunk);
+  for (; c.in(); c.next()) core_query<D, B, G>(a, m, c.query(), c.xcd * c.chunk, s_dyn, s_w);
+}
+
+// Do the dense cells hold kLargeCell points or more on average (m primitives, nd dense
+// cells)? Then packets and brick summaries pay in the point main phase: a query's
+// candidates are mostly large cells of few sets, met by its neighbours too.
+constexpr int kLargeCell = 16;
+__device__ __forceinline__ bool large_cells(const TravArgs& a, int m) {
+  const int64_t nd = *a.d_ndense;
+  return nd > 0 && a.n - (m - nd) >= kLargeCell * nd;
 }
 
 // Main phase, points outside dense cells: pairs with primitives above their own.
@@ -1604,14 +1421,13 @@ constexpr float kPointsPacketExt = 8.0f;
 constexpr int kPointsFewQueries = 32;   // at most this many queries ...
 constexpr float kPointsFewExt = 32.0f;  // ... form a packet up to this many eps wide
 
-template <int D, bool ALL_CORE, bool FIRST, bool B>
-__global__ void k_main_dbx_points(TravArgs a) {
-  extern __shared__ uint32_t s_pstack[];  // kWideStack entries per wavefront
-  const int m = tree_m(a.t);
+template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
+__device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, char* s_dyn) {
+  // G: the walk's columns; else packet walks, kWideStack entries per wavefront
+  uint32_t* s_pstack = reinterpret_cast<uint32_t*>(s_dyn);
+  constexpr int kWaveLds = kSearchLds<D, G> + (G ? kHitBytes : 0);
+  char* lds = s_dyn + (threadIdx.x >> 6) * kWaveLds;
   const int lane = lane_id();
-  const int64_t p0 = xcd_spread(blockIdx.x, blockDim.x, 0, m);
-  if (p0 < 0 || p0 >= m) return;  // the grid is sized for n; past the primitives
-  const int p = static_cast<int>(xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, m));
   bool pt;
   int i;
   Query q;
@@ -1622,7 +1438,147 @@ __global__ void k_main_dbx_points(TravArgs a) {
   int* labels = a.labels;
   // the core pass may already have joined i to dense cells it reaches
   int root = mine && ci ? uf_find(labels, i, a.info) : i;
-  if (!FIRST) {
+  // A packet of queries (lanes mm, in the box [lo, hi]): their own pairs, then the
+  // candidates that walk() brings, above the first of them. Point primitives up to
+  // plast are the packet's own.
+  auto packet = [&](uint64_t mm, const float* lo, const float* hi, float eps2, int plast, auto&& walk) {
+    const bool on = (mm >> lane) & 1;
+    const int fl = __ffsll(static_cast<unsigned long long>(mm)) - 1;
+    // Phase A: pairs of this wavefront's own queries (every core point primitive
+    // in its range is a query), each joined from its lower primitive.
+    for (uint64_t km = mm; km; km &= km - 1) {
+      const int kl = __ffsll(static_cast<unsigned long long>(km)) - 1;
+      const int jk = __shfl(i, kl);
+      const float px = readlane_f(q.x, kl), py = readlane_f(q.y, kl), pz = readlane_f(q.z, kl);
+      if (on && lane < kl && dist2v<D>(px, py, pz, q.x, q.y, q.z) <= eps2 && !known_same_set(labels, jk, root))
+        root = uf_union(labels, root, jk, a.info);
+    }
+    if (on) root = uf_find(labels, root, a.info);
+    int r = __shfl(root, fl);
+    bool common = !ballot(on && root != r);
+    walk([&](int rr) {
+      float4 lr = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hr = lr;
+      bool hit = false;
+      int anc = -1;
+      if (rr >= 0) {
+        lr = a.prim_lo[rr];
+        const int v = rec_index(lr);
+        if (v >= 0) {
+          hit = rr > plast && (ALL_CORE || a.core[v]) &&
+                box_dist2<D>(lr.x, lr.y, lr.z, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2]) <= eps2;
+        } else {
+          hr = a.prim_hi[rr];
+          hit = boxbox_dist2<D>(lo, hi, lr.x, lr.y, lr.z, hr.x, hr.y, hr.z) <= eps2;
+        }
+        if (hit) anc = ancestor_compress(labels, ref_point(v));
+      }
+      const bool is_pt = rec_index(lr) >= 0;
+      if (common) {
+        // Points, all at once: every lane tests its own candidate against all
+        // queries (register broadcasts), then the lanes that reach one join
+        // the packet's set in parallel.
+        const bool cand = hit && is_pt && anc != r;
+        if (ballot(cand)) {
+          bool reach = false;
+          for (uint64_t qm = mm; qm; qm &= qm - 1) {
+            const int kl = __ffsll(static_cast<unsigned long long>(qm)) - 1;
+            reach |= cand && dist2v<D>(lr.x, lr.y, lr.z, readlane_f(q.x, kl), readlane_f(q.y, kl),
+                                       readlane_f(q.z, kl)) <= eps2;
+          }
+          if (ballot(reach)) {
+            if (reach && !known_same_set(labels, rec_index(lr), r)) uf_union(labels, r, rec_index(lr), a.info);
+            int nr = 0;
+            if (lane == fl) nr = uf_find(labels, r, a.info);
+            r = __shfl(nr, fl);
+            if (on) root = r;
+          }
+        }
+      }
+      // cells, and points when the queries are in several sets: one at a time
+      for (uint64_t vm = ballot(hit && !(common && (is_pt || anc == r))); vm; vm &= vm - 1) {
+        const int k = __ffsll(static_cast<unsigned long long>(vm)) - 1;
+        const int rk = __builtin_amdgcn_readlane(rr, k);
+        const int v = __builtin_amdgcn_readlane(rec_index(lr), k);
+        const int j = ref_point(v);
+        const int ak = __builtin_amdgcn_readlane(anc, k);
+        const float px = readlane_f(lr.x, k), py = readlane_f(lr.y, k), pz = readlane_f(lr.z, k);
+        if (common && ak == r) continue;  // joined by an earlier candidate of this walk
+        if (v >= 0) {  // a core point above every query of the wavefront (queries in several sets)
+          if (on && ak != root && dist2v<D>(px, py, pz, q.x, q.y, q.z) <= eps2 && !known_same_set(labels, j, root))
+            root = uf_union(labels, root, j, a.info);
+          continue;
+        }
+        // a dense cell: one of its points within eps of a query suffices
+        const float ux = readlane_f(hr.x, k), uy = readlane_f(hr.y, k), uz = readlane_f(hr.z, k);
+        const int nk = __builtin_amdgcn_readlane(__float_as_int(hr.w), k);  // the cell's size
+        const bool nb = on && rk > p && (common || ak != root) &&
+                        box_dist2<D>(q.x, q.y, q.z, px, py, pz, ux, uy, uz) <= eps2 &&
+                        (common || !known_same_set(labels, j, root));
+        if (common && ballot(nb) && known_same_set(labels, j, r)) continue;
+        // a query whose eps-ball holds the whole cell reaches it without a scan
+        const bool full = nb && cell_within<D>(make_float4(px, py, pz, 0.0f), make_float4(ux, uy, uz, 0.0f), q, eps2);
+        if (common) {
+          const uint64_t fm = ballot(full);
+          if (fm) {
+            const int L = __ffsll(static_cast<unsigned long long>(fm)) - 1;
+            int nr = 0;
+            if (lane == L) nr = uf_union(labels, r, j, a.info);
+            r = __shfl(nr, L);
+            if (on) root = r;
+            continue;  // the whole packet is in one set with the cell now
+          }
+        } else if (full) {
+          root = uf_union(labels, root, j, a.info);
+        }
+        if (G && nk <= kLaneScan) {
+          const bool reach = nb && !full && lane_count_near<D>(a.xs, a.n, j, nk, q, eps2) > 0;
+          const uint64_t rm = ballot(reach);
+          if (common && rm) {
+            const int L = __ffsll(static_cast<unsigned long long>(rm)) - 1;
+            int nr = 0;
+            if (lane == L) nr = uf_union(labels, r, j, a.info);
+            r = __shfl(nr, L);
+            if (on) root = r;
+          } else if (reach) {
+            root = uf_union(labels, root, j, a.info);
+          }
+          continue;
+        }
+        for (uint64_t lm = ballot(nb && !full); lm; lm &= lm - 1) {
+          const int L = __ffsll(static_cast<unsigned long long>(lm)) - 1;
+          const bool reach = cell_reaches_point<D>(a.xs, a.n, j, nk, readlane_f(q.x, L),
+                                                   readlane_f(q.y, L), readlane_f(q.z, L), eps2);
+          if (common) {
+            if (!reach) continue;
+            int nr = 0;
+            if (lane == L) nr = uf_union(labels, r, j, a.info);
+            r = __shfl(nr, L);
+            if (on) root = r;
+            break;  // the whole packet is in one set with the cell now
+          }
+          if (lane == L && reach) root = uf_union(labels, root, j, a.info);
+        }
+      }
+      return false;
+    });
+  };
+  const uint64_t mm = ballot(mine);
+  if (!mm) return;
+  const float qv[3] = {q.x, q.y, q.z};
+  bool single = mine;
+  if (!FIRST && G && large_cells(a, m)) {
+    single = (for_packets<D, B>(a.ix, B ? cloud_of(a, i) : 0, qv, qv, mm,
+                                [&](uint64_t lanes, const CellGrid& g, const CellBox<D>& box, const float* lo,
+                                    const float* hi) {
+                                  const int fl = __ffsll(static_cast<unsigned long long>(lanes)) - 1;
+                                  const int ll = 63 - __clzll(static_cast<unsigned long long>(lanes));
+                                  const int pmin = __builtin_amdgcn_readlane(p, fl);
+                                  packet(lanes, lo, hi, readlane_f(sc.eps2, fl), __builtin_amdgcn_readlane(p, ll),
+                                         [&](auto&& visit) {
+                                           box_candidates<D>(a.ix, g, box, pmin, reinterpret_cast<int*>(lds), visit);
+                                         });
+                                }) >> lane) & 1;
+  } else if constexpr (!FIRST && !G) {
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     if (mine) {
       lo[0] = hi[0] = q.x;
@@ -1635,8 +1591,6 @@ __global__ void k_main_dbx_points(TravArgs a) {
         lo[d] = fminf(lo[d], __shfl_xor(lo[d], off));
         hi[d] = fmaxf(hi[d], __shfl_xor(hi[d], off));
       }
-    const uint64_t mm = ballot(mine);
-    if (!mm) return;
     const int fl = __ffsll(static_cast<unsigned long long>(mm)) - 1;
     const int i0 = __shfl(i, fl), pmin = __shfl(p, fl);  // primitives rise with the lanes
     const Scope ps = scope_of<B>(a, m, i0);
@@ -1647,122 +1601,22 @@ __global__ void k_main_dbx_points(TravArgs a) {
     // would each cross the clumps in between on their own
     const float ext_max = __popcll(mm) <= kPointsFewQueries ? kPointsFewExt : kPointsPacketExt;
     if (!ballot(other_cloud) && ext * ext <= ext_max * ext_max * ps.eps2) {
-      const float eps2 = ps.eps2;
-      // Phase A: pairs of this wavefront's own queries (every core point primitive
-      // in its range is a query), each joined from its lower primitive.
-      for (uint64_t km = mm; km; km &= km - 1) {
-        const int kl = __ffsll(static_cast<unsigned long long>(km)) - 1;
-        const int jk = __shfl(i, kl);
-        const float px = readlane_f(q.x, kl), py = readlane_f(q.y, kl), pz = readlane_f(q.z, kl);
-        if (mine && lane < kl && dist2v<D>(px, py, pz, q.x, q.y, q.z) <= eps2 && !known_same_set(labels, jk, root))
-          root = uf_union(labels, root, jk, a.info);
-      }
-      if (mine) root = uf_find(labels, root, a.info);
-      int r = __shfl(root, fl);
-      bool common = !ballot(mine && root != r);
-      const int plast = __shfl(p, 63);  // point primitives up to here are this wavefront's (phase A)
       uint32_t* stack = s_pstack + (threadIdx.x >> 6) * kWideStack;
-      traverse_box_wide_lanes<D>(a.t, m, ps, lo, hi, pmin, a.t.leaf_size, a.info, stack, [&](int rr) {
-        float4 lr = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hr = lr;
-        bool hit = false;
-        int anc = -1;
-        if (rr >= 0) {
-          lr = a.prim_lo[rr];
-          const int v = rec_index(lr);
-          if (v >= 0) {
-            hit = rr > plast && (ALL_CORE || a.core[v]) &&
-                  box_dist2<D>(lr.x, lr.y, lr.z, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2]) <= eps2;
-          } else {
-            hr = a.prim_hi[rr];
-            hit = boxbox_dist2<D>(lo, hi, lr.x, lr.y, lr.z, hr.x, hr.y, hr.z) <= eps2;
-          }
-          if (hit) anc = ancestor_compress(labels, ref_point(v));
-        }
-        const bool is_pt = rec_index(lr) >= 0;
-        if (common) {
-          // Points, all at once: every lane tests its own candidate against all
-          // queries (register broadcasts), then the lanes that reach one join
-          // the packet's set in parallel.
-          const bool cand = hit && is_pt && anc != r;
-          if (ballot(cand)) {
-            bool reach = false;
-            for (uint64_t qm = mm; qm; qm &= qm - 1) {
-              const int kl = __ffsll(static_cast<unsigned long long>(qm)) - 1;
-              reach |= cand && dist2v<D>(lr.x, lr.y, lr.z, readlane_f(q.x, kl), readlane_f(q.y, kl),
-                                         readlane_f(q.z, kl)) <= eps2;
-            }
-            if (ballot(reach)) {
-              if (reach && !known_same_set(labels, rec_index(lr), r)) uf_union(labels, r, rec_index(lr), a.info);
-              int nr = 0;
-              if (lane == fl) nr = uf_find(labels, r, a.info);
-              r = __shfl(nr, fl);
-              root = r;
-            }
-          }
-        }
-        // cells, and points when the queries are in several sets: one at a time
-        for (uint64_t vm = ballot(hit && !(common && (is_pt || anc == r))); vm; vm &= vm - 1) {
-          const int k = __ffsll(static_cast<unsigned long long>(vm)) - 1;
-          const int rk = __builtin_amdgcn_readlane(rr, k);
-          const int v = __builtin_amdgcn_readlane(rec_index(lr), k);
-          const int j = ref_point(v);
-          const int ak = __builtin_amdgcn_readlane(anc, k);
-          const float px = readlane_f(lr.x, k), py = readlane_f(lr.y, k), pz = readlane_f(lr.z, k);
-          if (common && ak == r) continue;  // joined by an earlier candidate of this walk
-          if (v >= 0) {  // a core point above every query of the wavefront (queries in several sets)
-            if (mine && ak != root && dist2v<D>(px, py, pz, q.x, q.y, q.z) <= eps2 && !known_same_set(labels, j, root))
-              root = uf_union(labels, root, j, a.info);
-            continue;
-          }
-          // a dense cell: one of its points within eps of a query suffices
-          const float ux = readlane_f(hr.x, k), uy = readlane_f(hr.y, k), uz = readlane_f(hr.z, k);
-          const int nk = __builtin_amdgcn_readlane(__float_as_int(hr.w), k);  // the cell's size
-          const bool nb = mine && rk > p && (common || ak != root) &&
-                          box_dist2<D>(q.x, q.y, q.z, px, py, pz, ux, uy, uz) <= eps2 &&
-                          (common || !known_same_set(labels, j, root));
-          if (common && ballot(nb) && known_same_set(labels, j, r)) continue;
-          // a query whose eps-ball holds the whole cell reaches it without a scan
-          const bool full = nb && cell_within<D>(make_float4(px, py, pz, 0.0f), make_float4(ux, uy, uz, 0.0f), q, eps2);
-          if (common) {
-            const uint64_t fm = ballot(full);
-            if (fm) {
-              const int L = __ffsll(static_cast<unsigned long long>(fm)) - 1;
-              int nr = 0;
-              if (lane == L) nr = uf_union(labels, r, j, a.info);
-              r = __shfl(nr, L);
-              root = r;
-              continue;  // the whole packet is in one set with the cell now
-            }
-          } else if (full) {
-            root = uf_union(labels, root, j, a.info);
-          }
-          for (uint64_t lm = ballot(nb && !full); lm; lm &= lm - 1) {
-            const int L = __ffsll(static_cast<unsigned long long>(lm)) - 1;
-            const bool reach = cell_reaches_point<D>(a.xs, a.n, j, nk, readlane_f(q.x, L),
-                                                     readlane_f(q.y, L), readlane_f(q.z, L), eps2);
-            if (common) {
-              if (!reach) continue;
-              int nr = 0;
-              if (lane == L) nr = uf_union(labels, r, j, a.info);
-              r = __shfl(nr, L);
-              root = r;
-              break;  // the whole packet is in one set with the cell now
-            }
-            if (lane == L && reach) root = uf_union(labels, root, j, a.info);
-          }
-        }
-        return false;
+      packet(mm, lo, hi, ps.eps2, __shfl(p, 63), [&](auto&& visit) {
+        traverse_box_wide_lanes<D>(a.t, m, ps, lo, hi, pmin, a.t.leaf_size, a.info, stack, visit);
       });
       return;
     }
   }
-  Walk w;
-  walk_init<true>(w, m, sc, p, mine);
-  bool active = mine && !walk_done(w);
+  Walker<D, B, true, G> w;
+  w.init(a, m, sc, i, qv, qv, p, single, lds);
+  Hits hits;
+  hits_init(hits, lds + kSearchLds<D, G>);
+  bool active = single && !w.done();
   while (ballot(active)) {
-    int pend = -1;
+    int pend = -1, pcnt = 0;  // a dense cell to scan: its first point and its size
     if (active) {
-      const int r = walk_step<D, true>(w, a.t, m, q, sc.eps2, p, a.info);
+      const int r = w.step(a, m, q, sc.eps2, p);
       if (r >= 0) {
         const float4 lr = a.prim_lo[r];
         const int s = rec_index(lr);
@@ -1770,7 +1624,11 @@ __global__ void k_main_dbx_points(TravArgs a) {
           if (rec_point_near<D>(lr, q, sc.eps2)) {
             const bool cj = ALL_CORE || a.core[s];
             if (ci && cj) {
-              if (!known_same_set(labels, s, root)) root = uf_union(labels, root, s, a.info);
+              if (G) {
+                if (labels[s] != root) hits_add(hits, s);
+              } else if (!known_same_set(labels, s, root)) {
+                root = uf_union(labels, root, s, a.info);
+              }
             } else if (FIRST && ci) {
               uf_claim(labels, s, i);
             } else if (FIRST && cj) {
@@ -1778,17 +1636,33 @@ __global__ void k_main_dbx_points(TravArgs a) {
               active = false;  // i is a member now (by this or an earlier claim)
             }
           }
-        } else if (cell_box_near<D>(a, r, lr, q, sc.eps2) && !(ci && known_same_set(labels, ref_point(s), root))) {
-          pend = r;
+        } else {
+          const float4 hr = a.prim_hi[r];
+          if (box_dist2<D>(q.x, q.y, q.z, lr.x, lr.y, lr.z, hr.x, hr.y, hr.z) <= sc.eps2 &&
+              !(ci && known_same_set(labels, ref_point(s), root))) {
+            pend = ref_point(s);
+            pcnt = __float_as_int(hr.w);
+            if (G && (pcnt <= kLaneScan || cell_within<D>(lr, hr, q, sc.eps2))) {
+              if (cell_within<D>(lr, hr, q, sc.eps2) ||
+                  lane_count_near<D>(a.xs, a.n, pend, pcnt, q, sc.eps2) > 0) {
+                if (ci) {
+                  hits_add(hits, pend);
+                } else if (FIRST) {
+                  uf_claim(labels, i, pend);
+                  active = false;
+                }
+              }
+              pend = -1;
+            }
+          }
         }
       }
     }
     // a dense cell: one of its points within eps suffices
     for (uint64_t pm = ballot(pend >= 0); pm; pm &= pm - 1) {
       const int L = __ffsll(static_cast<unsigned long long>(pm)) - 1;
-      const int r = __shfl(pend, L);
-      const int s = a.prim_start[r];
-      const bool hit = cell_reaches_point<D>(a.xs, a.n, s, -a.prim_cnt[r], __shfl(q.x, L), __shfl(q.y, L),
+      const int s = __shfl(pend, L);
+      const bool hit = cell_reaches_point<D>(a.xs, a.n, s, __shfl(pcnt, L), __shfl(q.x, L), __shfl(q.y, L),
                                              __shfl(q.z, L), readlane_f(sc.eps2, L));
       if (lane == L && hit) {
         if (ci) {
@@ -1799,8 +1673,18 @@ __global__ void k_main_dbx_points(TravArgs a) {
         }
       }
     }
-    if (active && walk_done(w)) active = false;
+    if (G && hits_full(hits)) hits_join(hits, labels, root, a.info);
+    if (active && w.done()) active = false;
   }
+  if (G) hits_join(hits, labels, root, a.info);
+}
+
+template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
+__global__ __launch_bounds__(G ? 256 : 1024) void k_main_dbx_points(TravArgs a) {
+  extern __shared__ __align__(16) char s_dyn[];
+  if (other_walk<G>(a)) return;
+  const int m = tree_m(a.t);
+  for (Chunks c(m, G); c.in(); c.next()) points_query<D, ALL_CORE, FIRST, B, G>(a, m, c.query(), s_dyn);
 }
 
 // Main phase, dense cells, when they are few (see cells_lane_mode):
@@ -1820,12 +1704,67 @@ constexpr int kCellsPerWaveMax = 65536;
 // the count.
 __device__ __forceinline__ bool cells_lane_mode(const TravArgs& a) { return *a.d_ndense > kCellsPerWaveMax; }
 
-template <int D, bool ALL_CORE, bool FIRST, bool B>
+// The whole wavefront hands the primitives above A in the cells within reach of A's
+// box to visit_lanes, a primitive per lane (-1: none). The lanes first look up a
+// brick each, then take the cells of a brick by its bits, lane = code, and list those
+// within reach in LDS (at most 5^D).
+constexpr int kCellList = 128;
+
+template <int D, typename F>
+__device__ __forceinline__ void cells_near_box_lanes(const CellIndex& ix, const CellGrid& g, const float* lo,
+                                                     const float* hi, int A, int* list, F&& visit_lanes) {
+  if (g.ncell[0] <= 0) return;
+  const int lane = lane_id();
+  CellRange<D> cr;
+  cell_range<D>(cr, g, lo, hi);
+  int br[3] = {0, 0, 0};
+  bool use = range_brick<D>(cr, lane, br) && lane < kMaxBricks<D>;
+  const uint32_t code = child_code<D>(br);
+  uint4 e = make_uint4(0, 0, 0, 0);
+  if (use) e = ix.supers[super_index<D>(g, br)];
+  const uint64_t sw = word_of(e);
+  use = use && ((sw >> code) & 1);
+  const int b = static_cast<int>(e.z) + __popcll(sw & ((1ull << code) - 1));
+  bool own = use;
+#pragma unroll
+  for (int a = 0; a < D; ++a) own = own && br[a] == (cr.own[a] >> kLevelShift<D>);
+  const uint64_t om = ballot(own);
+  const int b_own = om ? __shfl(b, __ffsll(static_cast<unsigned long long>(om)) - 1) : -1;
+  e = make_uint4(0, 0, 0, 0);
+  if (use && b >= b_own) e = ix.bricks[b];
+  const uint64_t mask = word_of(e) & range_codes<D, true>(cr, br);
+  int cnt = 0;
+  for (uint64_t bm = ballot(mask != 0); bm; bm &= bm - 1) {
+    const int n = __ffsll(static_cast<unsigned long long>(bm)) - 1;
+    const uint64_t wn = uint64_t(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(e.y), n))) << 32 |
+                        static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(e.x), n));
+    const uint64_t mn = uint64_t(static_cast<uint32_t>(
+                            __builtin_amdgcn_readlane(static_cast<int>(mask >> 32), n))) << 32 |
+                        static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mask), n));
+    const int base = __builtin_amdgcn_readlane(static_cast<int>(e.z), n);
+    int bn[3];
+    range_brick<D>(cr, n, bn);
+    const bool in = ((mn >> lane) & 1) && cell_in_reach<D>(cr, bn, static_cast<uint32_t>(lane));
+    const uint64_t im = ballot(in);
+    if (in) list[cnt + __popcll(im & lanemask_lt())] = base + __popcll(wn & lanemask_lt());
+    cnt += __popcll(im);
+  }
+  for (int q = 0; q < cnt; q += 64) {
+    int cur = 0, end = 0;
+    bool dense;
+    if (q + lane < cnt) cell_prims(ix, list[q + lane], cur, end, dense);
+    cur = max(cur, A + 1);
+    while (ballot(cur < end)) visit_lanes(cur < end ? cur++ : -1);
+  }
+}
+
+template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
 __global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
-  __shared__ uint32_t s_stack[4 * kWideStack];  // 256-thread workgroups
-  uint32_t* stack = s_stack + (threadIdx.x >> 6) * kWideStack;
+  constexpr int kPerWave = G ? kCellList : kWideStack;
+  __shared__ uint32_t s_stack[4 * kPerWave];  // 256-thread workgroups
+  uint32_t* stack = s_stack + (threadIdx.x >> 6) * kPerWave;
   const int nd = *a.d_ndense;
-  if (cells_lane_mode(a)) return;
+  if (cells_lane_mode(a) || other_walk<G>(a)) return;
   const int m = tree_m(a.t);
   const int lane = lane_id();
   const int wave = (xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6;
@@ -1844,7 +1783,7 @@ __global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
     const float alo[3] = {alo4.x, alo4.y, alo4.z}, ahi[3] = {ahi4.x, ahi4.y, ahi4.z};
     // the core pass may already have joined A to other sets
     int root = uf_find(labels, sa, a.info);
-    traverse_box_wide_lanes<D>(a.t, m, sc, alo, ahi, A, a.t.leaf_size, a.info, stack, [&](int r) {
+    auto visit = [&](int r) {
       // every lane loads its primitive's record and what decides a skip (core
       // flag, an ancestor near the root); candidates then go one after another
       float4 lr = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hr = lr;
@@ -1895,7 +1834,12 @@ __global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
         }
       }
       return false;
-    });
+    };
+    if constexpr (G)
+      cells_near_box_lanes<D>(a.ix, query_grid<D, B>(a.ix, B ? cloud_of(a, sa) : 0), alo, ahi, A,
+                              reinterpret_cast<int*>(stack), visit);
+    else
+      traverse_box_wide_lanes<D>(a.t, m, sc, alo, ahi, A, a.t.leaf_size, a.info, stack, visit);
   }
 }
 
@@ -1904,37 +1848,32 @@ __global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
 // lock-step with the other lanes of its wavefront) with A's box over the
 // primitives above A, with the same rules as above; each pair test runs on the
 // whole wavefront (64 points per ballot), one pending lane after another.
-template <int D, bool ALL_CORE, bool FIRST, bool B>
-__global__ void k_main_dbx_cells_lane(TravArgs a) {
-  const int nd = *a.d_ndense;
-  if (!cells_lane_mode(a)) return;
-  const int m = tree_m(a.t);
+template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
+__device__ __forceinline__ void cells_query(const TravArgs& a, int m, int nd, int k, char* s_dyn) {
   const int lane = lane_id();
-  const int64_t k = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, nd);
   const bool mine = k >= 0 && k < nd;
   const int A = mine ? a.dense_list[k] : 0;
-  const int sa = mine ? a.prim_start[A] : 0;
-  const int na = mine ? -a.prim_cnt[A] : 0;
+  const float4 alo = mine ? a.prim_lo[A] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const float4 ahi = mine ? a.prim_hi[A] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const int sa = mine ? ref_point(rec_index(alo)) : 0;
+  const int na = mine ? __float_as_int(ahi.w) : 0;
   const Scope sc = scope_of<B>(a, m, sa);
   BoxQ qa;
-  {
-    const float4 lo = mine ? a.prim_lo[A] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    const float4 hi = mine ? a.prim_hi[A] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    qa.lo[0] = lo.x; qa.lo[1] = lo.y; qa.lo[2] = lo.z;
-    qa.hi[0] = hi.x; qa.hi[1] = hi.y; qa.hi[2] = hi.z;
-  }
+  qa.lo[0] = alo.x; qa.lo[1] = alo.y; qa.lo[2] = alo.z;
+  qa.hi[0] = ahi.x; qa.hi[1] = ahi.y; qa.hi[2] = ahi.z;
   int* labels = a.labels;
   int root = sa;
-  Walk w;
-  walk_init<true>(w, m, sc, A, mine);
-  bool active = mine && !walk_done(w);
+  Walker<D, B, true, G> w;
+  w.init(a, m, sc, sa, qa.lo, qa.hi, A, mine, search_lds<D, G>(s_dyn));
+  bool active = mine && !w.done();
   while (ballot(active)) {
     int pend = -1;
     if (active) {
-      const int r = walk_step<D, true>(w, a.t, m, qa, sc.eps2, A, a.info);
+      const int r = w.step(a, m, qa, sc.eps2, A);
       if (r >= 0) {
         const float4 lr = a.prim_lo[r];
         const int s = ref_point(rec_index(lr));
+        bool hit = false;  // settled by this lane alone
         if (rec_index(lr) >= 0) {
           const float px = lr.x, py = lr.y, pz = lr.z;
           if (box_dist2<D>(px, py, pz, qa.lo[0], qa.lo[1], qa.lo[2], qa.hi[0], qa.hi[1], qa.hi[2]) <= sc.eps2) {
@@ -1944,12 +1883,26 @@ __global__ void k_main_dbx_cells_lane(TravArgs a) {
               pend = r;
             }
           }
+          if (G && pend >= 0 && na <= kLaneScan) {
+            hit = lane_count_near<D>(a.xs, a.n, sa, na, Query{px, py, pz}, sc.eps2) > 0;
+            pend = -1;
+          }
+          if (hit && !(ALL_CORE || a.core[s])) {
+            uf_claim(labels, s, sa);  // first-claim mode: a non-core neighbour joins A's cluster
+            hit = false;
+          }
         } else {
           const float4 blo = lr, bhi = a.prim_hi[r];
           if (boxbox_dist2<D>(qa.lo, qa.hi, blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z) <= sc.eps2 &&
               !known_same_set(labels, s, root))
             pend = r;
+          const int nb = __float_as_int(bhi.w);
+          if (G && pend >= 0 && int64_t(na) * nb <= kLanePairs) {
+            hit = lane_cells_touch<D>(a.xs, a.n, sa, na, s, nb, blo, bhi, sc.eps2);
+            pend = -1;
+          }
         }
+        if (hit) root = uf_union(labels, root, s, a.info);
       }
     }
     for (uint64_t pm = ballot(pend >= 0); pm; pm &= pm - 1) {
@@ -1972,33 +1925,38 @@ __global__ void k_main_dbx_cells_lane(TravArgs a) {
           root = uf_union(labels, root, s, a.info);
       }
     }
-    if (active && walk_done(w)) active = false;
+    if (active && w.done()) active = false;
   }
+}
+
+template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
+__global__ __launch_bounds__(G ? 256 : 1024) void k_main_dbx_cells_lane(TravArgs a) {
+  extern __shared__ __align__(16) char s_dyn[];  // the walk's columns
+  const int nd = *a.d_ndense;
+  if (!cells_lane_mode(a) || other_walk<G>(a)) return;
+  const int m = tree_m(a.t);
+  for (Chunks c(nd, G); c.in(); c.next()) cells_query<D, ALL_CORE, FIRST, B, G>(a, m, nd, c.query(), s_dyn);
 }
 
 // Canonical border pass for non-core points (all outside dense cells).
 // Queries: the listed non-core points whose neighbours were not all recorded
 // by the core pass (which wrote -1 for lone points; the records cover the rest).
-template <int D, bool B>
-__global__ void k_border_dbx(TravArgs a) {
-  const int m = tree_m(a.t);
+template <int D, bool B, bool G>
+__device__ __forceinline__ void border_query(const TravArgs& a, int m, bool mine, int p, char* s_dyn) {
   const int lane = lane_id();
-  const int nq = *a.qborder_n;
-  const int64_t k = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, nq);
-  const bool mine = k >= 0 && k < nq;
-  const int p = mine ? a.qborder[k] : 0;
   const float4 own = mine ? a.prim_lo[p] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   const int i = mine ? rec_index(own) : 0;
   const Scope sc = scope_of<B>(a, m, i);
   const Query q{own.x, own.y, own.z};
   int best = 0x7fffffff;
-  Walk w;
-  walk_init<false>(w, m, sc, 0, mine);
-  bool active = mine && !walk_done(w);
+  const float qv[3] = {q.x, q.y, q.z};
+  Walker<D, B, false, G> w;
+  w.init(a, m, sc, i, qv, qv, 0, mine, search_lds<D, G>(s_dyn));
+  bool active = mine && !w.done();
   while (ballot(active)) {
     int pend = -1;
     if (active) {
-      const int r = walk_step<D, false>(w, a.t, m, q, sc.eps2, 0, a.info);
+      const int r = w.step(a, m, q, sc.eps2, 0);
       if (r >= 0) {
         const float4 lr = a.prim_lo[r];
         const int s = rec_index(lr);
@@ -2023,9 +1981,24 @@ __global__ void k_border_dbx(TravArgs a) {
         best = id < best ? id : best;
       }
     }
-    if (active && (best == 0 || walk_done(w))) active = false;
+    if (active && (best == 0 || w.done())) active = false;
   }
   if (mine) a.border[i] = best == 0x7fffffff ? -1 : best;
+}
+
+template <int D, bool B, bool G>
+__global__ __launch_bounds__(G ? 256 : 1024) void k_border_dbx(TravArgs a) {
+  extern __shared__ __align__(16) char s_dyn[];  // the walk's columns
+  if (other_walk<G>(a)) return;
+  const int m = tree_m(a.t);
+  const int xcd = static_cast<int>(blockIdx.x % kNumXcd), nq = a.border_n[kWalkCount(xcd)];
+  const int* list = a.qborder + int64_t(xcd) * a.border_n[kWalkShare];
+  for (int64_t k0 = int64_t(blockIdx.x / kNumXcd) * blockDim.x; k0 < nq;
+       k0 += int64_t(gridDim.x / kNumXcd) * blockDim.x) {
+    const int64_t k = k0 + threadIdx.x;
+    const bool mine = k < nq;
+    if (ballot(mine)) border_query<D, B, G>(a, m, mine, mine ? list[k] : 0, s_dyn);
+  }
 }
 
 // Test hook: one lane walks the tree with an always-true box test and records,
@@ -2050,36 +2023,31 @@ inline dim3 grid_of(int64_t n, int block) {
   return dim3(static_cast<unsigned>(kNumXcd * ceil_div(ceil_div(n, kNumXcd), block)));
 }
 
+// Threads per workgroup of the grid walks: the caller's block_size up to the 256
+// that their LDS columns are sized for.
+inline int grid_block(const TravArgs& a) { return a.block < 256 ? a.block : 256; }
+// Workgroups of a DenseBox kernel of up to n queries (see Chunks), in a multiple of
+// kNumXcd; fewer lanes a wavefront make more of them.
+inline dim3 query_grid_blocks(int64_t n, int block) {
+  constexpr int64_t kMost = 16384;
+  const int64_t need = std::max<int64_t>(grid_of(n, block).x, grid_of(std::min<int64_t>(n, kWaves * 64), block / 8).x);
+  return dim3(static_cast<unsigned>(std::min<int64_t>(need, kMost)));
+}
 template <int D>
-void lone_t(const TravArgs& a, const uint64_t* pkey, const GridPlan* plan, uint32_t* table, uint64_t* words,
-            const uint32_t* bounds, int* list, int* list_n, hipStream_t s) {
-  // the plan allows a table of at most n / 2 64-bit words (it lives in an n-int buffer)
-  const int64_t gc = std::min<int64_t>(std::max<int64_t>(ceil_div(a.n / 2, 256 * 4), 1), 2048);
-  hipLaunchKernelGGL(k_lone_clear, dim3(static_cast<unsigned>(gc)), dim3(256), 0, s, plan,
-                     reinterpret_cast<uint64_t*>(table));
-  const int64_t gb = std::min<int64_t>(ceil_div(a.t.m_cap, 256), 4096);  // 4 wavefronts of 64 primitives
-  hipLaunchKernelGGL(k_lone_bits<D>, dim3(static_cast<unsigned>(gb > 0 ? gb : 1)), dim3(256), 0, s, pkey, a.t.d_m,
-                     plan, words, table, list_n);
-  const int64_t gf = ceil_div(a.t.m_cap, kLoneRounds * 256);
-  hipLaunchKernelGGL(k_lone_filter<D>, dim3(static_cast<unsigned>(gf > 0 ? gf : 1)), dim3(256), 0, s, a, pkey, plan,
-                     words, table, bounds, list, list_n);
+size_t walk_lds(int block, int more = 0) {  // LDS of a workgroup's searches, and `more` bytes a wavefront
+  return size_t(kSearchLds<D, true> + more) * (block / 64);
 }
 
 template <int D, bool B>
 void core_t(const TravArgs& a, bool densebox, hipStream_t s) {
+  const size_t rec = sizeof(int) * kRecNb;  // neighbour records, per thread
   const dim3 g = grid_of(a.n, a.block), b(a.block);
-  const size_t lds = sizeof(int) * kRecNb * a.block;  // neighbour records
-  if (densebox && a.core_list) {
-    // kNumXcd segments of at most lone_segment(m) <= this many listed queries, or
-    // (when the plan turns the list off) every primitive
-    const int64_t share = kLoneRounds * 256;
-    const int64_t seg = ceil_div(ceil_div(a.t.m_cap, kNumXcd), share) * share;
-    const int64_t gl = std::max<int64_t>(kNumXcd * ceil_div(seg, a.block), grid_of(ceil_div(a.n, kCoreQ), a.block).x);
-    hipLaunchKernelGGL((k_core_dbx<D, B>), dim3(static_cast<unsigned>(gl)), b, kCoreQ * lds, s, a);
-  } else if (densebox) {
-    hipLaunchKernelGGL((k_core_dbx<D, B>), grid_of(ceil_div(a.n, kCoreQ), a.block), b, kCoreQ * lds, s, a);
+  if (densebox) {
+    const int gb = grid_block(a);
+    hipLaunchKernelGGL((k_core_dbx<D, B, true>), query_grid_blocks(a.n, gb), dim3(gb), walk_lds<D>(gb) + rec * gb, s, a);
+    hipLaunchKernelGGL((k_core_dbx<D, B, false>), query_grid_blocks(a.n, a.block), b, rec * a.block, s, a);
   } else {
-    hipLaunchKernelGGL((k_core_fdb<D, B>), g, b, lds, s, a);
+    hipLaunchKernelGGL((k_core_fdb<D, B>), g, b, rec * a.block, s, a);
   }
 }
 
@@ -2087,18 +2055,27 @@ void core_t(const TravArgs& a, bool densebox, hipStream_t s) {
 template <int D, bool ALL, bool FIRST, bool B>
 void main_t(const TravArgs& a, bool densebox, int part, hipStream_t s) {
   const dim3 g = grid_of(a.n, a.block), b(a.block);
+  const int gb = grid_block(a);
   if (densebox) {
     if (part != 2) {
       // a batch's many cells usually go to the lane kernel, where this one exits at once
-      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B>), dim3(B ? 2048 : 4096), dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, true>), dim3(B ? 2048 : 4096), dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, false>), dim3(B ? 2048 : 4096), dim3(256), 0, s, a);
       // dense cells hold >= minPts points each, so there are at most n / minPts
       const int64_t max_cells = a.min_pts > 1 ? a.n / a.min_pts + 1 : a.n;
-      if (max_cells > kCellsPerWaveMax)
-        hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B>), grid_of(max_cells, a.block), b, 0, s, a);
+      if (max_cells > kCellsPerWaveMax) {
+        hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, true>), query_grid_blocks(max_cells, gb), dim3(gb),
+                           walk_lds<D>(gb), s, a);
+        hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, false>), query_grid_blocks(max_cells, a.block), b, 0,
+                           s, a);
+      }
     }
-    if (part != 1)
-      hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B>), g, b, sizeof(uint32_t) * kWideStack * (a.block / 64), s,
-                         a);
+    if (part != 1) {
+      hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, true>), query_grid_blocks(a.n, gb), dim3(gb),
+                         walk_lds<D>(gb, kHitBytes), s, a);
+      hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, false>), query_grid_blocks(a.n, a.block), b,
+                         sizeof(uint32_t) * kWideStack * (a.block / 64), s, a);
+    }
   } else if (FIRST) {
     hipLaunchKernelGGL((k_main_fdb_first<D, B>), g, b, 0, s, a);
   } else {
@@ -2111,9 +2088,12 @@ void main_t(const TravArgs& a, bool densebox, int part, hipStream_t s) {
 template <int D, bool B>
 void border_t(const TravArgs& a, bool densebox, hipStream_t s) {
   const dim3 g = grid_of(a.n, a.block), b(a.block);
-  hipLaunchKernelGGL(k_border_rec, grid_of(a.brec_cap, 256), dim3(256), 0, s, a);
-  if (densebox) hipLaunchKernelGGL((k_border_dbx<D, B>), g, b, 0, s, a);
-  else hipLaunchKernelGGL((k_border_fdb<D, B>), g, b, 0, s, a);
+  hipLaunchKernelGGL(k_border_rec, dim3(static_cast<unsigned>(kNumXcd * ceil_div(a.brec_cap, 256))), dim3(256), 0, s, a);
+  if (densebox) {
+    const int gb = grid_block(a);
+    hipLaunchKernelGGL((k_border_dbx<D, B, true>), query_grid_blocks(a.n, gb), dim3(gb), walk_lds<D>(gb), s, a);
+    hipLaunchKernelGGL((k_border_dbx<D, B, false>), query_grid_blocks(a.n, a.block), b, 0, s, a);
+  } else hipLaunchKernelGGL((k_border_fdb<D, B>), g, b, 0, s, a);
 }
 
 template <int D>
@@ -2131,13 +2111,6 @@ void main_dispatch(const TravArgs& a, bool densebox, bool all_core, bool first_b
 }
 
 }  // namespace
-
-void launch_lone_filter(const TravArgs& a, int dim, const uint64_t* prim_key, const GridPlan* plan, uint32_t* table,
-                        uint64_t* words, const uint32_t* bounds, int* list, int* list_n, hipStream_t s) {
-  if (a.n <= 0) return;
-  if (dim == 3) lone_t<3>(a, prim_key, plan, table, words, bounds, list, list_n, s);
-  else lone_t<2>(a, prim_key, plan, table, words, bounds, list, list_n, s);
-}
 
 void launch_fdb_local(const TravArgs& a, int dim, bool all_core, hipStream_t s) {
   if (a.n <= 1) return;

@@ -39,7 +39,9 @@ __device__ __forceinline__ int successor(const int* __restrict__ other, int m, i
 }
 
 __global__ __launch_bounds__(kBlock) void k_ropes(const int* __restrict__ other, int m_cap, const int* __restrict__ d_m,
-                                                  int* __restrict__ rope, int* __restrict__ leaf_rope) {
+                                                  int* __restrict__ rope, int* __restrict__ leaf_rope,
+                                                  const int* __restrict__ d_skip) {
+  if (d_skip && *d_skip) return;
   const int m = d_m ? *d_m : m_cap;
   int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < m - 1) {
@@ -181,7 +183,9 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ 
                                                      int64_t n, LeafSrc ls, int* __restrict__ other,
                                                      int* __restrict__ gamma, int* __restrict__ ends, float4* node_a,
                                                      float4* node_b, uint32_t* __restrict__ info,
-                                                     float4* __restrict__ cut, int* __restrict__ cut_n, int cut_div) {
+                                                     float4* __restrict__ cut, int* __restrict__ cut_n, int cut_div,
+                                                     const int* __restrict__ d_skip) {
+  if (d_skip && *d_skip) return;
   constexpr int E = kRefitBlock + 1;  // edges L0-1 .. L0+255
   __shared__ int s_far[kRefitBlock];
   __shared__ float s_side[2][6][kRefitBlock];  // [child side][lo.xyz, hi.xyz][split - L0]
@@ -321,7 +325,8 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ 
 template <typename K>
 void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs, int64_t n_pts,
              const LeafSrc& ls, float4* node_a, float4* node_b, int* rope, int* leaf_rope, int* ends, int* other,
-             int* gamma, uint32_t* info, hipStream_t s, float4* cut, int* cut_n, bool ends_ready, int cut_div) {
+             int* gamma, uint32_t* info, hipStream_t s, float4* cut, int* cut_n, bool ends_ready, int cut_div,
+             const int* d_skip) {
   if (m_cap <= 0) return;
   int g = static_cast<int>(ceil_div(m_cap, kBlock));
   if (m_cap >= 2) {
@@ -330,18 +335,18 @@ void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs,
     const dim3 rg(static_cast<unsigned>(ceil_div(m_cap, kRefitBlock))), rb(kRefitBlock);
     if (dim == 3 && buf)
       hipLaunchKernelGGL((k_build_up<K, 3, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div);
+                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else if (dim == 3)
       hipLaunchKernelGGL((k_build_up<K, 3, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div);
+                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else if (buf)
       hipLaunchKernelGGL((k_build_up<K, 2, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div);
+                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else
       hipLaunchKernelGGL((k_build_up<K, 2, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div);
+                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
   }
-  hipLaunchKernelGGL(k_ropes, dim3(g), dim3(kBlock), 0, s, other, m_cap, d_m, rope, leaf_rope);
+  hipLaunchKernelGGL(k_ropes, dim3(g), dim3(kBlock), 0, s, other, m_cap, d_m, rope, leaf_rope, d_skip);
 }
 
 }  // namespace
@@ -349,14 +354,14 @@ void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs,
 void build_lbvh(const void* keys, bool key64, int m, int dim, const float* xs, int64_t n_pts, const float4* prim_lo,
                 const float4* prim_hi, float4* node_a, float4* node_b, int* rope, int* leaf_rope, int* ends,
                 int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s, float4* cut, int* cut_n,
-                bool ends_ready, int cut_div) {
+                bool ends_ready, int cut_div, const int* d_skip) {
   const LeafSrc ls{prim_lo, prim_hi};
   if (key64)
     build_t(static_cast<const uint64_t*>(keys), m, d_m, dim, xs, n_pts, ls, node_a, node_b, rope, leaf_rope, ends,
-            other, gamma, info, s, cut, cut_n, ends_ready, cut_div);
+            other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
   else
     build_t(static_cast<const uint32_t*>(keys), m, d_m, dim, xs, n_pts, ls, node_a, node_b, rope, leaf_rope, ends,
-            other, gamma, info, s, cut, cut_n, ends_ready, cut_div);
+            other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
 }
 
 }  // namespace fdb
