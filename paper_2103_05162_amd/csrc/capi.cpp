@@ -902,7 +902,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   ta.border_n = at<int>(ws, plan.hist);
   ta.brec_i = at<int>(ws, plan.brec_i);
   ta.brec_nb = at<int>(ws, plan.brec_nb);
-  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per XCD
+  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per shard
   if (!all_core) {
     st.mark("core");
     launch_core(ta, dim, densebox, s);
@@ -1161,7 +1161,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   ta.border_n = at<int>(ws, plan.hist);
   ta.brec_i = at<int>(ws, plan.brec_i);
   ta.brec_nb = at<int>(ws, plan.brec_nb);
-  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per XCD
+  ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per shard
   launch_core(ta, dim, densebox, s);
   if (densebox) {
     st.mark("main_cells");

@@ -239,15 +239,14 @@ struct TravArgs {
   uint8_t* lone;  // set by the core pass (or the isolated-point test before it): 1 = not core and no
                   // neighbour but itself (noise); NULL if no core pass
   // Border work left by the core pass for non-core points with some neighbour
-  // other than themselves, kept per XCD that found it (kNumXcd of each list). Up to
-  // kRecNb neighbouring primitives of such a point (the point itself, or a dense
-  // cell's first point) are recorded, so the border pass needs no walk: record k of
-  // XCD x, at r = x * brec_cap + k, is point brec_i[r] with neighbours
-  // brec_nb[r * kRecNb + t] (-1 = none); the first brec_cap asked for are stored.
-  // Points with more neighbouring primitives, or past the capacity, are listed in
-  // qborder (DenseBox: their primitive indices; XCD x's list starts at its share of
-  // the queries) and walk again. border_n holds the counts (kBorderCounters words,
-  // zero before the core pass).
+  // other than themselves. Up to kRecNb neighbouring primitives of such a point (the
+  // point itself, or a dense cell's first point) are recorded, so the border pass
+  // needs no walk: record k of shard x (of kNumXcd), at r = x * brec_cap + k, is point
+  // brec_i[r] with neighbours brec_nb[r * kRecNb + t] (-1 = none); the first brec_cap
+  // asked for in a shard are stored. Points with more neighbouring primitives, or past
+  // the capacity, are listed in qborder per XCD (DenseBox: their primitive indices;
+  // XCD x's list starts at its share of the queries) and walk again. border_n holds
+  // the counts (kBorderCounters words, zero before the core pass).
   int* brec_i;
   int* brec_nb;
   int brec_cap;

@@ -428,12 +428,14 @@ __device__ __forceinline__ int cell_ref(int s) { return -2 - s; }
 __device__ __forceinline__ bool is_cell_ref(int v) { return v < -1; }
 __device__ __forceinline__ int ref_point(int v) { return v < -1 ? -2 - v : v; }
 
-// Where the border pass finds its work: a count of records and of listed walks per
-// XCD, and the queries per XCD of the core pass, each on a memory line of its own (a
+// Where the border pass finds its work: counts of records (in kNumXcd shards, which
+// the workgroups of each XCD take in turn, so that a region of many non-core points
+// fills all of them alike) and of listed walks per XCD, and the queries per XCD of the
+// core pass, each on a memory line of its own (a
 // counter that every workgroup of the chip adds to passes them one at a time: with
 // one for all, the core pass of the uniform 2M-point set took 0.69 ms in workgroups
 // of 64, 0.39 of 128 and 0.29 of 256).
-__device__ __forceinline__ constexpr int kRecCount(int xcd) { return 32 * xcd; }
+__device__ __forceinline__ constexpr int kRecCount(int shard) { return 32 * shard; }
 __device__ __forceinline__ constexpr int kWalkCount(int xcd) { return 32 * (kNumXcd + xcd); }
 constexpr int kWalkShare = 32 * 2 * kNumXcd;
 
@@ -463,10 +465,11 @@ __device__ __forceinline__ void core_epilogue(const TravArgs& a, bool mine, int 
   const bool want = mine && !core && !lone;
   const bool fits = want && rec.nn <= kRecNb;
   const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
-  const int slot = block_reserve(a.border_n + kRecCount(xcd), fits, s_w);
+  const int shard = static_cast<int>(blockIdx.x / kNumXcd % kNumXcd);
+  const int slot = block_reserve(a.border_n + kRecCount(shard), fits, s_w);
   const bool stored = fits && slot < a.brec_cap;
   if (stored) {
-    const int64_t k = int64_t(xcd) * a.brec_cap + slot;
+    const int64_t k = int64_t(shard) * a.brec_cap + slot;
     a.brec_i[k] = i;
 #pragma unroll
     for (int t = 0; t < kRecNb; ++t) a.brec_nb[k * kRecNb + t] = t < rec.nn ? ref_point(rec_get(rec, t)) : -1;
@@ -903,10 +906,10 @@ __global__ __launch_bounds__(256) void k_main_fdb_q(TravArgs a) {
 // Border pass from the core pass's neighbour records (no walk): the smallest
 // cluster id among the recorded core neighbours.
 __global__ void k_border_rec(TravArgs a) {
-  const int xcd = static_cast<int>(blockIdx.x % kNumXcd);
+  const int shard = static_cast<int>(blockIdx.x % kNumXcd);
   const int64_t slot = int64_t(blockIdx.x / kNumXcd) * blockDim.x + threadIdx.x;
-  if (slot >= min(a.border_n[kRecCount(xcd)], a.brec_cap)) return;
-  const int64_t k = int64_t(xcd) * a.brec_cap + slot;
+  if (slot >= min(a.border_n[kRecCount(shard)], a.brec_cap)) return;
+  const int64_t k = int64_t(shard) * a.brec_cap + slot;
   const int i = a.brec_i[k];
   int best = 0x7fffffff;
 #pragma unroll
