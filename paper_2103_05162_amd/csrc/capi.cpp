@@ -35,7 +35,6 @@ Plan make_plan(int64_t n, int dim, int algo, int num_clouds) {
   p.algo = algo;
   p.num_clouds = num_clouds;
   const size_t N = static_cast<size_t>(n > 0 ? n : 1);
-  p.sort_tiles = ceil_div(static_cast<int64_t>(N), kSortTileMin);
   p.scan_blocks = ceil_div(static_cast<int64_t>(N), kScanTile);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -51,10 +50,11 @@ Plan make_plan(int64_t n, int dim, int algo, int num_clouds) {
   p.vals0 = take(N * 4);
   p.vals1 = take(N * 4);
   p.hist = take(8 * 256 * 4);
-  p.digoff = take((8 * 256 + 8) * 4);  // digit offsets of 8 passes, then a "digit constant" flag per pass
+  p.pass_plan = take(8 * 4);
   p.tilectr = take(64);
-  p.status = take(static_cast<size_t>(p.sort_tiles) * 256 * 8);
-  p.xs = take(static_cast<size_t>(dim) * N * 4);
+  // the sort's look-back words: done with before the sorted coordinates are written
+  p.xs = take(std::max(static_cast<size_t>(dim) * N * 4, static_cast<size_t>(sort_status_words(N, false)) * 4));
+  p.status = p.xs;
   p.node_a = take(N * 32);  // interleaved node records (kNodeStride float4 per node)
   p.node_b = p.node_a + 16;
   p.rope = take(N * 4);
@@ -791,18 +791,16 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   h->last_n = n;
   {
     // the call's counters and flags in one launch: info bits and the forest check's
-    // count, the bounds' identities, the misc counters, and for DenseBox the digit
-    // histograms, tile counters and look-back words of the planned sort
+    // count, the bounds' identities, the misc counters, and the digit histograms,
+    // tile counters and look-back words of the sort
     FillList init;
     init.add(h->d_info, 0u, 2);
     init.add(bounds, 0xffffffffu, 4);
     init.add(bounds + 4, 0u, 4);
     init.add(misc, 0u, kMiscCount);
-    if (densebox) {
-      init.add(at<uint32_t>(ws, plan.hist), 0u, 8 * 256);
-      init.add(at<uint32_t>(ws, plan.tilectr), 0u, 8);
-      init.add(at<uint32_t>(ws, plan.status), 0u, planned_status_words(n));
-    }
+    init.add(at<uint32_t>(ws, plan.hist), 0u, 8 * 256);
+    init.add(at<uint32_t>(ws, plan.tilectr), 0u, 16);
+    init.add(at<uint32_t>(ws, plan.status), 0u, densebox ? planned_status_words(n) : sort_status_words(n, true));
     fill_multi(init, s);
   }
   launch_bounds(points, n, dim, bounds, h->d_info, s);
@@ -837,11 +835,10 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     ta.ix = ix;
     st.mark("cell_keys");
     launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist),
-                    ix.supers, s, false);
+                    ix.supers, s);
     st.mark("sort");
     radix_sort_planned(keys[0], keys[1], vals[0], vals[1], n, gplan, at<uint32_t>(ws, plan.hist),
-                       at<uint32_t>(ws, plan.digoff), at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status),
-                       h->d_info, s, false);
+                       at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);
     cur = 1;  // the planned sort ends in buffer 1
     perm = vals[cur];
     st.mark("permute");
@@ -880,7 +877,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
                   at<uint32_t>(ws, plan.hist), s);
     st.mark("sort");
     cur = radix_sort(keys[0], keys[1], vals[0], vals[1], n, true, mbits, at<uint32_t>(ws, plan.hist), true,
-                     at<uint32_t>(ws, plan.digoff), at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);
+                     at<uint32_t>(ws, plan.pass_plan), at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s, false);
     perm = vals[cur];
     st.mark("permute");
     launch_permute(points, n, dim, perm, xs, h->d_info, s);
@@ -1085,7 +1082,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
              vals[0], shift + cb, at<uint32_t>(ws, plan.hist), ix.supers, gplan, s);
   st.mark("sort");
   const int cur = radix_sort(keys[0], keys[1], vals[0], vals[1], n, true, shift + cb, at<uint32_t>(ws, plan.hist), true,
-                             at<uint32_t>(ws, plan.digoff), at<uint32_t>(ws, plan.tilectr),
+                             at<uint32_t>(ws, plan.pass_plan), at<uint32_t>(ws, plan.tilectr),
                              at<uint64_t>(ws, plan.status), h->d_info, s);
   const uint32_t* perm = vals[cur];
   const uint64_t* pkeys = static_cast<const uint64_t*>(keys[cur]);

@@ -12,10 +12,9 @@ namespace fdb {
 
 // Keys per thread in a radix pass, by key width (measured: 64-bit keys fit two
 // 6144-key tiles per CU in LDS; 32-bit keys do best at 5120). The workspace
-// sizes the look-back status for the smaller tile.
+// sizes the look-back status for the tile taken (sort_status_words).
 template <typename K>
 constexpr int sort_items() { return sizeof(K) == 8 ? 24 : 22; }
-constexpr int kSortTileMin = 256 * 20;  // smallest keys-per-workgroup tile
 constexpr int kScanItems = 16;                 // items per thread in the device scan
 constexpr int kScanTile = 256 * kScanItems;
 constexpr int64_t kMaxPoints = (int64_t(1) << 30) - 1;
@@ -33,7 +32,7 @@ struct Plan {
   int algo = 0;
   size_t bytes = 0;
   // common
-  size_t bounds, misc, gplan, keys0, keys1, vals0, vals1, hist, digoff, tilectr, status;
+  size_t bounds, misc, gplan, keys0, keys1, vals0, vals1, hist, pass_plan, tilectr, status;
   size_t xs;                       // dim * n floats, sorted SoA
   size_t node_a, node_b, rope, leaf_rope, ends, other, gamma, cut;
   size_t labels, core, lone, qborder, brec_i, brec_nb;
@@ -45,7 +44,7 @@ struct Plan {
   // batches
   int num_clouds = 0;
   size_t cl_lo, cl_scale, cl_eps2, cl_minpts, cl_root, cl_end, cl_flags, cl_ord;
-  int64_t sort_tiles = 0, scan_blocks = 0;
+  int64_t scan_blocks = 0;
   int64_t super_cap = 0;  // DenseBox: supers that the node records' buffer holds
 };
 
@@ -161,40 +160,39 @@ void fill_multi(const FillList& L, hipStream_t s);
 // k_prep.hip
 void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint32_t* info, hipStream_t s);
 // The key kernels also count the digits of the `sort_bits`-bit keys for the
-// radix sort into hist (ceil(sort_bits / 8) x 256 words, cleared here).
+// radix sort into hist (ceil(sort_bits / 8) x 256 words, cleared by the caller).
 void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds, uint64_t* keys, uint32_t* vals,
                    int sort_bits, uint32_t* hist, hipStream_t s);
 // DenseBox of one cloud: k_grid_plan writes *plan from the bounds (after
 // launch_bounds; eps is the caller's), then the cell keys go to key buffer
 // plan->start as 32- or 64-bit words with the identity permutation, and their
-// digits are counted for the sort (hist: 8 x 256 words, cleared here unless the
-// caller has, hist_clear = false). The key kernel also clears the super table that
+// digits are counted for the sort (hist: 8 x 256 words, cleared by the caller). The key kernel also clears the super table that
 // the grid's index is built into (plan->supers entries, when plan->grid_on).
 void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,
                       hipStream_t s);
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
                      void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
-                     hipStream_t s, bool hist_clear = true);
+                     hipStream_t s);
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
                     hipStream_t s);
 
 // k_sort.hip: LSD radix sort of (key, index) pairs over the low `bits` bits.
 // hist_ready: hist already holds the digit counts of every pass (from the key
-// kernel). digoff: 8 * 256 + 8 words (digit offsets, and per pass a flag set when
-// every key has the same digit, whose pass then copies instead of sorting).
-// Returns which of the two buffers holds the result (0 or 1).
+// kernel). pass_plan: 8 words (which passes run: one over a constant digit need not).
+// The tile counters (16 words)
+// and look-back words (sort_status_words) are cleared here unless the caller has
+// (clear = false). Returns which of the two buffers holds the result (0 or 1).
 int radix_sort(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, bool key64, int bits,
-               uint32_t* hist, bool hist_ready, uint32_t* digoff, uint32_t* tilectr, uint64_t* status,
-               uint32_t* info, hipStream_t s);
+               uint32_t* hist, bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status,
+               uint32_t* info, hipStream_t s, bool clear = true);
+int64_t sort_status_words(int64_t n, bool key64);
 // The same with key width and pass count taken from a GridPlan on the device:
 // passes for both widths are launched and those the plan does not call for exit
 // at once. The keys start in buffer plan->start and end in buffer 1; hist holds
-// every pass's digit counts (from the key kernel). The tile counters (8 words)
-// and look-back words (planned_status_words(n)) are cleared here unless the
-// caller has (clear = false).
+// every pass's digit counts (from the key kernel). The caller has cleared the tile
+// counters (16 words) and the look-back words (planned_status_words(n)).
 void radix_sort_planned(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, const GridPlan* plan,
-                        const uint32_t* hist, uint32_t* digoff, uint32_t* tilectr, uint64_t* status,
-                        uint32_t* info, hipStream_t s, bool clear = true);
+                        const uint32_t* hist, uint32_t* tilectr, uint64_t* status, uint32_t* info, hipStream_t s);
 int64_t planned_status_words(int64_t n);
 
 // k_tree.hip

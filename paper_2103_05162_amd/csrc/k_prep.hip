@@ -423,7 +423,6 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
 void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds, uint64_t* keys, uint32_t* vals,
                    int sort_bits, uint32_t* hist, hipStream_t s) {
   const int passes = (sort_bits + 7) / 8;
-  fill_u32(hist, 0, passes * 256, s);
   int g = grid_for(n, kBlock * 16, 1024);  // a workgroup histogram per 4096+ keys, flushes kept few
   if (dim == 3)
     hipLaunchKernelGGL(k_morton<3>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, keys, vals, passes, hist);
@@ -441,8 +440,7 @@ void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_
 
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
                      void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
-                     hipStream_t s, bool hist_clear) {
-  if (hist_clear) fill_u32(hist, 0, 8 * 256, s);
+                     hipStream_t s) {
   // A workgroup histogram per 4096+ keys, at most 1024 of them: each flushes up to 2048 bins into the
   // one global histogram, and fewer flushes contend less at L2 than more workgroups gain.
   int g = grid_for(n, kBlock * 16, 1024);

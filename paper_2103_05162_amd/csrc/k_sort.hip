@@ -15,6 +15,7 @@
 // nothing. With ~770 tiles in flight at once on 256 CUs, the look-back's walks over
 // earlier tiles' uncached status words cost more than the count kernel's extra
 // read of the keys (per-tile clocks: ~10 of a tile's ~24 us went to the look-back).
+// Small inputs, where launches cost the most, run all passes in one (k_sort_all).
 #include "fdb_device.hpp"
 #include "fdb_internal.hpp"
 
@@ -56,47 +57,30 @@ __global__ __launch_bounds__(kBlock) void k_hist(const K* __restrict__ keys, int
   hist_flush(s_h, passes, hist);
 }
 
-// Exclusive scan of each pass's 256 digit counts -> global digit offsets, and in
-// digoff[8 * 256 + p] a flag (1) for a pass whose digit is the same for every key.
-__global__ __launch_bounds__(kRadix) void k_digit_offsets(const uint32_t* __restrict__ hist,
-                                                          uint32_t* __restrict__ digoff) {
-  __shared__ uint32_t s[kRadix];
-  __shared__ uint32_t s_one;
-  const int p = blockIdx.x, d = threadIdx.x;
-  s[d] = hist[p * kRadix + d];
-  if (d == 0) s_one = 0;
-  __syncthreads();
-  uint32_t tot = 0;
-  for (int k = 0; k < kRadix; ++k) tot += s[k];  // every thread, from LDS
-  if (tot > 0 && s[d] == tot) s_one = 1;
-  __syncthreads();
-  if (d == 0) digoff[8 * kRadix + p] = s_one;
-  for (int off = 1; off < kRadix; off <<= 1) {
-    uint32_t v = d >= off ? s[d - off] : 0;
-    __syncthreads();
-    s[d] += v;
-    __syncthreads();
-  }
-  digoff[p * kRadix + d] = s[d] - hist[p * kRadix + d];
+// Passes of a host-sequenced sort that need not run, as a bit mask: a pass whose digit
+// is the same for every key is the identity permutation. Left out two at a time, so the
+// number of passes run keeps its parity and the result ends where the host expects it.
+// Called by a whole workgroup (kBlock threads).
+__device__ __forceinline__ uint32_t skipped_passes(const uint32_t* hist, int64_t n, int passes) {
+  uint32_t constant = 0, skip = 0;
+  for (int p = 0; p < passes; ++p)
+    constant |= __syncthreads_or(hist[p * kRadix + threadIdx.x] == static_cast<uint32_t>(n)) ? 1u << p : 0u;
+  for (int p = 0; p + 1 < passes; ++p)
+    if ((constant >> p & 3u) == 3u) skip |= 3u << p++;
+  return skip;
 }
 
-// Pass plan of a host-sequenced sort (one thread): constant-digit passes are
-// skipped two at a time, so the number of passes run keeps its parity; each pass
-// run gets the buffer it reads. digoff[8 * 256 + p] becomes bit 1 = skip, bit 0 =
+// Pass plan of a host-sequenced sort (one workgroup), passes[p]: bit 1 = skip, bit 0 =
 // source buffer.
-__global__ void k_pass_plan(uint32_t* __restrict__ digoff, int passes) {
-  uint32_t* f = digoff + 8 * kRadix;
-  bool skip[8];
-  for (int p = 0; p < 8; ++p) skip[p] = false;
-  for (int p = 0; p + 1 < passes; ++p)
-    if (f[p] && f[p + 1]) {
-      skip[p] = skip[p + 1] = true;
-      ++p;
-    }
-  int cur = 0;
+__global__ __launch_bounds__(kBlock) void k_pass_plan(const uint32_t* __restrict__ hist, int64_t n, int passes,
+                                                      uint32_t* __restrict__ pass_plan) {
+  const uint32_t skip = skipped_passes(hist, n, passes);
+  if (threadIdx.x) return;
+  uint32_t cur = 0;
   for (int p = 0; p < passes; ++p) {
-    f[p] = (skip[p] ? 2u : 0u) | static_cast<uint32_t>(cur);
-    if (!skip[p]) cur ^= 1;
+    const uint32_t left_out = skip >> p & 1u;
+    pass_plan[p] = left_out << 1 | cur;
+    if (!left_out) cur ^= 1u;
   }
 }
 
@@ -124,13 +108,13 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // whose digit is the same for every key is the identity permutation and is
 // skipped (in pairs, so the result still ends in the buffer the host expects).
 template <typename K>
-__device__ __forceinline__ bool pass_source(int p, const GridPlan* plan, const uint32_t* digoff_all, int& from) {
+__device__ __forceinline__ bool pass_source(int p, const GridPlan* plan, const uint32_t* pass_plan, int& from) {
   if (plan) {
     if (plan->key64 != (sizeof(K) == 8 ? 1 : 0) || p >= plan->passes) return false;
     from = (plan->start ^ p) & 1;
     return true;
   }
-  const uint32_t f = digoff_all[8 * kRadix + p];
+  const uint32_t f = pass_plan[p];
   if (f & 2u) return false;
   from = static_cast<int>(f & 1u);
   return true;
@@ -141,10 +125,9 @@ __device__ __forceinline__ bool pass_source(int p, const GridPlan* plan, const u
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_tile_counts(const K* __restrict__ k0, const K* __restrict__ k1,
                                                         int64_t n, int p, const GridPlan* __restrict__ plan,
-                                                        const uint32_t* __restrict__ digoff_all,
                                                         uint32_t* __restrict__ counts, int64_t tiles) {
   int from = 0;
-  if (!pass_source<K>(p, plan, digoff_all, from)) return;  // the whole grid leaves
+  if (!pass_source<K>(p, plan, nullptr, from)) return;  // the whole grid leaves
   const K* __restrict__ kin = from ? k1 : k0;
   constexpr int kItems = sort_items<K>();
   constexpr int kTile = 256 * kItems;
@@ -170,21 +153,26 @@ __global__ __launch_bounds__(kBlock) void k_tile_counts(const K* __restrict__ k0
   counts[int64_t(tid) * tiles + tile] = s_h[tid];
 }
 
-// Scan step: for digit d (workgroup d), the digit's global offset plus the
-// running sum of its counts in earlier tiles, in place: where each tile's keys of
+// Scan step: for digit d (workgroup d), the digit's global offset (from the pass'
+// digit counts) plus the running sum of its counts in earlier tiles, in place: where each tile's keys of
 // digit d start in the output.
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_tile_scan(uint32_t* __restrict__ counts, int64_t tiles, int p,
                                                       const GridPlan* __restrict__ plan,
-                                                      const uint32_t* __restrict__ digoff_all) {
+                                                      const uint32_t* __restrict__ hist) {
   int from = 0;
-  if (!pass_source<K>(p, plan, digoff_all, from)) return;
+  if (!pass_source<K>(p, plan, nullptr, from)) return;
   constexpr int kPer = 8;
   __shared__ uint32_t s_wsum[kWaves];
   __shared__ uint32_t s_tot;
   const int d = blockIdx.x, tid = threadIdx.x;
   uint32_t* __restrict__ c = counts + int64_t(d) * tiles;
-  uint32_t run = digoff_all[p * kRadix + d];
+  // where digit d starts: the keys of smaller digits
+  const uint32_t ex = block_exclusive_scan(hist[p * kRadix + tid], s_wsum);
+  if (tid == d) s_tot = ex;
+  __syncthreads();
+  uint32_t run = s_tot;
+  __syncthreads();
   for (int64_t c0 = 0; c0 < tiles; c0 += kBlock * kPer) {
     uint32_t v[kPer];
     uint32_t sum = 0;
@@ -209,62 +197,49 @@ __global__ __launch_bounds__(kBlock) void k_tile_scan(uint32_t* __restrict__ cou
   }
 }
 
-// One pass: reads buffer `from` (pass_source) and writes the other. OFFS: the
-// tile follows from the workgroup's index and its offsets come from k_tile_scan
-// (offs); otherwise from the look-back.
-template <typename K, bool OFFS>
-__global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __restrict__ k1,
-                                                     uint32_t* __restrict__ v0, uint32_t* __restrict__ v1, int64_t n,
-                                                     int p, const GridPlan* __restrict__ plan,
-                                                     const uint32_t* __restrict__ digoff_all,
-                                                     uint32_t* __restrict__ tilectr_all, uint64_t* __restrict__ status,
-                                                     const uint32_t* __restrict__ offs, int64_t otiles,
-                                                     uint32_t* __restrict__ info) {
-  int from = 0;
-  if (!pass_source<K>(p, plan, digoff_all, from)) return;  // the whole grid leaves
-  const K* __restrict__ kin = from ? k1 : k0;
-  K* __restrict__ kout = from ? k0 : k1;
-  const uint32_t* __restrict__ vin = from ? v1 : v0;
-  uint32_t* __restrict__ vout = from ? v0 : v1;
+template <typename K, int ITEMS>
+struct SortLds {
+  uint32_t tile;
+  uint32_t wcnt[kWaves][kRadix];  // per-wave digit counts, then per-wave prefixes
+  uint32_t dstart[kRadix];        // tile-local start of each digit
+  uint32_t gbase[kRadix];         // global start of this tile's run of each digit
+  uint32_t wsum[kWaves];
+  K keys[256 * ITEMS];
+  uint32_t vals[256 * ITEMS];
+};
+
+// The tiles of one pass that this workgroup takes, from (kin, vin) to (kout, vout).
+// OFFS: one tile, which follows from the workgroup's index, its offsets coming from
+// k_tile_scan (offs). Otherwise tiles by ticket until none is left, so the grid is what
+// is resident at once rather than a workgroup per tile, with the look-back; digit0 is
+// where digit threadIdx.x starts. iota: the values are the identity permutation (the
+// planned sort's first pass: the key kernel writes none). Returns the tiles taken.
+template <typename K, int ITEMS, bool OFFS>
+__device__ __forceinline__ int sort_pass(SortLds<K, ITEMS>& s, const K* kin, const uint32_t* vin, K* kout,
+                                         uint32_t* vout, int64_t n, int p, bool iota, uint32_t digit0,
+                                         uint32_t* tilectr, uint64_t* status, const uint32_t* offs, int64_t otiles,
+                                         uint32_t* info) {
   const int shift = 8 * p;
-
   const uint32_t epoch = static_cast<uint32_t>(p + 1);
-  const uint32_t* __restrict__ digoff = digoff_all + p * kRadix;
-  uint32_t* __restrict__ tilectr = tilectr_all + p;
-  constexpr int kItems = sort_items<K>();
+  constexpr int kItems = ITEMS;
   constexpr int kTile = 256 * kItems;
-  static_assert(kTile >= kSortTileMin, "the workspace sizes the status words for kSortTileMin");
   constexpr int kWaveTile = 64 * kItems;
-  __shared__ uint32_t s_tile;
-  __shared__ uint32_t s_wcnt[kWaves][kRadix];  // per-wave digit counts, then per-wave prefixes
-  __shared__ uint32_t s_dstart[kRadix];        // tile-local start of each digit
-  __shared__ uint32_t s_gbase[kRadix];         // global start of this tile's run of each digit
-  __shared__ uint32_t s_wsum[kWaves];
-  __shared__ K s_keys[kTile];
-  __shared__ uint32_t s_vals[kTile];
-
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int64_t ntiles = (n + kTile - 1) / kTile;
-  // Look-back: a workgroup takes tiles by ticket until none is left, so the grid
-  // is what is resident at once rather than a workgroup per tile. OFFS: one tile
-  // per workgroup.
-  for (;;) {
-    if (!OFFS && tid == 0) s_tile = atomicAdd(tilectr, 1u);
-    for (int i = tid; i < kWaves * kRadix; i += kBlock) (&s_wcnt[0][0])[i] = 0;
+  for (int taken = 0;; ++taken) {
+    if (!OFFS && tid == 0) s.tile = atomicAdd(tilectr, 1u);
+    for (int i = tid; i < kWaves * kRadix; i += kBlock) (&s.wcnt[0][0])[i] = 0;
     __syncthreads();
     // OFFS: tiles laid contiguously per XCD (as in k_tile_counts), so the partial
     // output lines where one tile's run of a digit meets the next tile's are
     // completed in one L2 instead of being written to memory from two
-    const int64_t tile = OFFS ? int64_t(xcd_block(blockIdx.x, gridDim.x)) : int64_t(s_tile);
-    if (tile >= ntiles) break;  // uniform: s_tile is shared
+    const int64_t tile = OFFS ? int64_t(xcd_block(blockIdx.x, gridDim.x)) : int64_t(s.tile);
+    if (tile >= ntiles) return taken;  // uniform: s.tile is shared
     const int64_t wbase = tile * kTile + int64_t(w) * kWaveTile;
 
     K key[kItems];
     uint32_t val[kItems];
     uint32_t rank[kItems];
-    // the planned sort's first pass starts from the identity permutation (the key
-    // kernel writes no values then)
-    const bool iota = plan && p == 0;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
       int64_t pos = wbase + k * 64 + lane;
@@ -273,17 +248,20 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __re
       val[k] = valid ? (iota ? static_cast<uint32_t>(pos) : vin[pos]) : 0u;
     }
     // Rank within the wavefront: positions run wave-major, then item, then lane,
-    // so processing items in order keeps the sort stable.
+    // so processing items in order keeps the sort stable. Items past the end (small
+    // inputs) are left out, for the whole wavefront alike.
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
+      rank[k] = 0;
+      if (wbase + k * 64 >= n) continue;
       bool valid = wbase + k * 64 + lane < n;
       uint32_t d = digit_of(key[k], shift);
       uint64_t m = match_digit(d, valid);
       int leader = __ffsll(static_cast<unsigned long long>(m)) - 1;
       uint32_t before = 0;
       if (valid && lane == leader) {  // leaders of distinct digits touch distinct words
-        before = s_wcnt[w][d];
-        s_wcnt[w][d] = before + static_cast<uint32_t>(__popcll(m));
+        before = s.wcnt[w][d];
+        s.wcnt[w][d] = before + static_cast<uint32_t>(__popcll(m));
       }
       before = __shfl(before, leader < 0 ? 0 : leader);
       rank[k] = before + static_cast<uint32_t>(__popcll(m & lanemask_lt()));
@@ -295,13 +273,13 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __re
     uint32_t total = 0;
 #pragma unroll
     for (int j = 0; j < kWaves; ++j) {
-      uint32_t c = s_wcnt[j][d];
-      s_wcnt[j][d] = total;
+      uint32_t c = s.wcnt[j][d];
+      s.wcnt[j][d] = total;
       total += c;
     }
     // Thread d: its tile's global start for digit d.
     if constexpr (OFFS) {
-      s_gbase[d] = offs[int64_t(d) * otiles + tile];
+      s.gbase[d] = offs[int64_t(d) * otiles + tile];
     } else {
       uint64_t* st = status + tile * kRadix + d;
       uint32_t excl = 0;
@@ -311,7 +289,7 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __re
         st_agent64(st, pack_status(epoch, kFlagAgg, total));
         int spins = 0;
         for (int64_t j = tile - 1; j >= 0;) {
-          // four predecessors per round trip
+          // four predecessors per round trip (16: slower, every word read comes from memory)
           uint64_t v[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) v[u] = j - u >= 0 ? ld_agent64(status + (j - u) * kRadix + d) : 0;
@@ -338,10 +316,10 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __re
         }
         st_agent64(st, pack_status(epoch, kFlagIncl, excl + total));
       }
-      s_gbase[d] = digoff[d] + excl;
+      s.gbase[d] = digit0 + excl;
     }
-    uint32_t ds = block_exclusive_scan(total, s_wsum);
-    s_dstart[d] = ds;
+    uint32_t ds = block_exclusive_scan(total, s.wsum);
+    s.dstart[d] = ds;
     __syncthreads();
 
     // Local scatter into LDS in sorted order.
@@ -349,27 +327,121 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __re
     for (int k = 0; k < kItems; ++k) {
       if (wbase + k * 64 + lane < n) {
         uint32_t dk = digit_of(key[k], shift);
-        uint32_t pos = s_dstart[dk] + s_wcnt[w][dk] + rank[k];
-        s_keys[pos] = key[k];
-        s_vals[pos] = val[k];
+        uint32_t pos = s.dstart[dk] + s.wcnt[w][dk] + rank[k];
+        s.keys[pos] = key[k];
+        s.vals[pos] = val[k];
       }
     }
     __syncthreads();
     const int64_t tile_n = n - tile * kTile < kTile ? n - tile * kTile : kTile;
     for (int i = tid; i < tile_n; i += kBlock) {
-      K kk = s_keys[i];
+      K kk = s.keys[i];
       uint32_t dk = digit_of(kk, shift);
-      uint32_t dest = s_gbase[dk] + (i - s_dstart[dk]);
+      uint32_t dest = s.gbase[dk] + (i - s.dstart[dk]);
       if (dest >= n) {  // only after a failed look-back
         atomicOr(info, kInternalBit);
         continue;
       }
       kout[dest] = kk;
-      vout[dest] = s_vals[i];
+      vout[dest] = s.vals[i];
     }
-    if (OFFS) break;
+    if (OFFS) return 1;
     __syncthreads();  // the next tile reuses the LDS
   }
+}
+
+// One pass per launch (see sort_pass): the passes whose tile offsets are scanned
+// beforehand, and the look-back passes of large inputs. Digit offsets come from the
+// histograms.
+template <typename K, bool OFFS>
+__global__ __launch_bounds__(kBlock) void k_onesweep(K* __restrict__ k0, K* __restrict__ k1,
+                                                     uint32_t* __restrict__ v0, uint32_t* __restrict__ v1, int64_t n,
+                                                     int p, const GridPlan* __restrict__ plan,
+                                                     const uint32_t* __restrict__ pass_plan,
+                                                     const uint32_t* __restrict__ hist,
+                                                     uint32_t* __restrict__ tilectr_all, uint64_t* __restrict__ status,
+                                                     const uint32_t* __restrict__ offs, int64_t otiles,
+                                                     uint32_t* __restrict__ info) {
+  __shared__ SortLds<K, sort_items<K>()> s;
+  int from = 0;
+  if (!pass_source<K>(p, plan, pass_plan, from)) return;  // the whole grid leaves
+  const uint32_t digit0 = OFFS ? 0u : block_exclusive_scan(hist[p * kRadix + threadIdx.x], s.wsum);
+  sort_pass<K, sort_items<K>(), OFFS>(s, from ? k1 : k0, from ? v1 : v0, from ? k0 : k1, from ? v0 : v1, n, p,
+                                      plan && p == 0, digit0, tilectr_all + p, status, offs, otiles, info);
+}
+
+// Every look-back pass in one launch. A workgroup that finds no tile left of a pass
+// publishes what it wrote, counts its tiles as done, waits until all of the pass' are,
+// and takes tiles of the next. It only ever waits for tiles that workgroups already
+// running have taken, so no workgroup need be resident for another's sake. Digit
+// offsets come straight from the histograms, passes over constant digits are skipped
+// in pairs (as k_pass_plan has it). With a plan: nothing for the other key width.
+// done: a counter per pass, zero beforehand.
+template <typename K, int ITEMS>
+__device__ __forceinline__ void sort_all(SortLds<K, ITEMS>& s, K* k0, K* k1, uint32_t* v0, uint32_t* v1, int64_t n,
+                                         int passes, const GridPlan* plan, const uint32_t* hist, uint32_t* tilectr,
+                                         uint32_t* done, uint64_t* status, uint32_t* info) {
+  int cur = 0;
+  if (plan) {
+    passes = plan->passes;
+    cur = plan->start;
+  }
+  const int64_t ntiles = (n + 256 * ITEMS - 1) / (256 * ITEMS);
+  const uint32_t skip = plan ? 0u : skipped_passes(hist, n, passes);
+  int last = -1;  // the pass before, which has to be complete
+  for (int p = 0; p < passes; ++p) {
+    if (skip >> p & 1u) continue;
+    if (last >= 0) {
+      if (threadIdx.x == 0) {
+        int spins = 0;
+        while (__hip_atomic_load(done + last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+               static_cast<uint32_t>(ntiles)) {
+          if (++spins > (1 << 24)) {
+            atomicOr(info, kInternalBit);
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    const uint32_t digit0 = block_exclusive_scan(hist[p * kRadix + threadIdx.x], s.wsum);
+    const int taken = sort_pass<K, ITEMS, false>(s, cur ? k1 : k0, cur ? v1 : v0, cur ? k0 : k1, cur ? v0 : v1, n, p,
+                                          plan && p == 0, digit0, tilectr + p, status, nullptr, 0, info);
+    if (taken) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __syncthreads();
+      if (threadIdx.x == 0) atomicAdd(done + p, static_cast<uint32_t>(taken));
+    }
+    cur ^= 1;
+    last = p;
+  }
+}
+
+template <typename K, int ITEMS>
+__global__ __launch_bounds__(kBlock) void k_sort_all(K* k0, K* k1, uint32_t* v0, uint32_t* v1, int64_t n, int passes,
+                                                     const GridPlan* __restrict__ plan, const uint32_t* hist,
+                                                     uint32_t* tilectr, uint32_t* done, uint64_t* status,
+                                                     uint32_t* info) {
+  __shared__ SortLds<K, ITEMS> s;
+  if (plan && plan->key64 != (sizeof(K) == 8 ? 1 : 0)) return;  // the whole grid leaves
+  sort_all<K, ITEMS>(s, k0, k1, v0, v1, n, passes, plan, hist, tilectr, done, status, info);
+}
+
+// Both key widths of a planned sort in one launch.
+template <int ITEMS>
+__global__ __launch_bounds__(kBlock) void k_sort_all_planned(void* k0, void* k1, uint32_t* v0, uint32_t* v1, int64_t n,
+                                                             const GridPlan* __restrict__ plan, const uint32_t* hist,
+                                                             uint32_t* tilectr, uint32_t* done, uint64_t* status,
+                                                             uint32_t* info) {
+  __shared__ alignas(16) unsigned char lds[sizeof(SortLds<uint64_t, ITEMS>)];
+  if (plan->key64)
+    sort_all<uint64_t, ITEMS>(*reinterpret_cast<SortLds<uint64_t, ITEMS>*>(lds), static_cast<uint64_t*>(k0),
+                              static_cast<uint64_t*>(k1), v0, v1, n, 8, plan, hist, tilectr, done, status, info);
+  else
+    sort_all<uint32_t, ITEMS>(*reinterpret_cast<SortLds<uint32_t, ITEMS>*>(lds), static_cast<uint32_t*>(k0),
+                              static_cast<uint32_t*>(k1), v0, v1, n, 4, plan, hist, tilectr, done, status, info);
 }
 
 // Workgroups of a look-back pass: at most what is resident at once on 256 CUs
@@ -381,30 +453,76 @@ unsigned lookback_grid(int64_t tiles) {
   return static_cast<unsigned>(tiles < cap ? tiles : cap);
 }
 
+// Which sort a number of keys takes: all passes in one launch, or passes of their own.
+// One launch saves what a launch costs (4 to 5 us, three launches a pass with 32-bit
+// keys, and as many again of the other width), but its passes are separated by
+// release and acquire fences of every workgroup, which empty the XCD's L2 under those
+// still running. From the end of the key kernel to the permute, one launch / passes of
+// their own, us: planned, 32-bit keys, 131,072: 54 / 206; 524,288: 100 / 231; 1M: 161
+// (kernel) / 144; planned, 64-bit keys, 524,288: 127 / 264; 1M: 393 / 290; 4M: 876 /
+// 350. Eight 64-bit passes (Morton) 131,072: 172 / 178; 262,144: 195 / 200; 524,288:
+// 285 / 226.
+constexpr int64_t kSortAllMax = int64_t(1) << 19, kSortAllUnplanned = int64_t(1) << 18;
+// Keys per thread of a tile: fewer while they put more CUs to work, until the look-back
+// over more tiles costs more (one launch, 32-bit / 64-bit keys, us, with 4, 8 and 22 keys
+// per thread: 16,384 keys 18/78, 22/90, 33/137; 32,768: 23/100, 23/98, 34/143; 65,536:
+// 29/154, 27/115, 37/152; 131,072: 81/259, 56/170, 59/167).
+constexpr int64_t kSort4Max = int64_t(1) << 15, kSort8Max = int64_t(1) << 17;
+template <typename K>
+int64_t sort_tile(int64_t n) {
+  return 256 * (n <= kSort4Max ? 4 : n <= kSort8Max ? 8 : sort_items<K>());
+}
+
+template <typename K, int ITEMS>
+void launch_sort_all(K* keys0, K* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, int passes, const GridPlan* plan,
+                     const uint32_t* hist, uint32_t* tilectr, uint64_t* status, uint32_t* info, hipStream_t s) {
+  hipLaunchKernelGGL((k_sort_all<K, ITEMS>), dim3(lookback_grid<K>(ceil_div(n, 256 * ITEMS))), dim3(kBlock), 0, s,
+                     keys0, keys1, vals0, vals1, n, passes, plan, hist, tilectr, tilectr + 8, status, info);
+}
+
+template <int ITEMS>
+void launch_sort_all_planned(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n,
+                             const GridPlan* plan, const uint32_t* hist, uint32_t* tilectr, uint64_t* status,
+                             uint32_t* info, hipStream_t s) {
+  hipLaunchKernelGGL(k_sort_all_planned<ITEMS>, dim3(lookback_grid<uint64_t>(ceil_div(n, 256 * ITEMS))), dim3(kBlock),
+                     0, s, keys0, keys1, vals0, vals1, n, plan, hist, tilectr, tilectr + 8, status, info);
+}
+
 template <typename K>
 int radix_sort_t(K* keys0, K* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, int bits, uint32_t* hist,
-                 bool hist_ready, uint32_t* digoff, uint32_t* tilectr, uint64_t* status, uint32_t* info,
-                 hipStream_t s) {
+                 bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status, uint32_t* info,
+                 hipStream_t s, bool clear) {
   const int passes = (bits + 7) / 8;
   if (n <= 1 || passes == 0) return 0;
   const int64_t tiles = ceil_div(n, 256 * sort_items<K>());
-  fill_u32(tilectr, 0, passes, s);
-  fill_u32(reinterpret_cast<uint32_t*>(status), 0, tiles * kRadix * 2, s);
+  if (clear) {
+    fill_u32(tilectr, 0, 16, s);
+    fill_u32(reinterpret_cast<uint32_t*>(status), 0, sort_status_words(n, sizeof(K) == 8), s);
+  }
   if (!hist_ready) {
     fill_u32(hist, 0, passes * kRadix, s);
     int hg = static_cast<int>(ceil_div(n, kBlock * 16));
     if (hg > 2048) hg = 2048;
     hipLaunchKernelGGL(k_hist<K>, dim3(hg), dim3(kBlock), 0, s, keys0, n, passes, hist);
   }
-  hipLaunchKernelGGL(k_digit_offsets, dim3(passes), dim3(kRadix), 0, s, hist, digoff);
-  hipLaunchKernelGGL(k_pass_plan, dim3(1), dim3(1), 0, s, digoff, passes);
+  if (n <= kSortAllUnplanned) {
+    if (n <= kSort4Max)
+      launch_sort_all<K, 4>(keys0, keys1, vals0, vals1, n, passes, nullptr, hist, tilectr, status, info, s);
+    else if (n <= kSort8Max)
+      launch_sort_all<K, 8>(keys0, keys1, vals0, vals1, n, passes, nullptr, hist, tilectr, status, info, s);
+    else
+      launch_sort_all<K, sort_items<K>()>(keys0, keys1, vals0, vals1, n, passes, nullptr, hist, tilectr, status, info,
+                                          s);
+    return passes & 1;
+  }
+  hipLaunchKernelGGL(k_pass_plan, dim3(1), dim3(kBlock), 0, s, hist, n, passes, pass_plan);
   // (look-back passes: for 64-bit keys, a count kernel's second read of the keys
   // and its extra launches cost more than the look-back; measured on the Morton
   // and batch sorts)
   int cur = 0;
   for (int p = 0; p < passes; ++p) {
     hipLaunchKernelGGL((k_onesweep<K, false>), dim3(lookback_grid<K>(tiles)), dim3(kBlock), 0, s, keys0, keys1,
-                       vals0, vals1, n, p, static_cast<const GridPlan*>(nullptr), digoff, tilectr, status,
+                       vals0, vals1, n, p, static_cast<const GridPlan*>(nullptr), pass_plan, hist, tilectr, status,
                        static_cast<const uint32_t*>(nullptr), int64_t(0), info);
     cur ^= 1;
   }
@@ -413,47 +531,60 @@ int radix_sort_t(K* keys0, K* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n
 
 }  // namespace
 
-// Look-back words of the planned sort's 64-bit passes (the 32-bit passes keep
-// their tile counts in the same buffer; a call runs one width only).
-int64_t planned_status_words(int64_t n) { return ceil_div(n, 256 * sort_items<uint64_t>()) * kRadix * 2; }
+int64_t sort_status_words(int64_t n, bool key64) {
+  return ceil_div(n, key64 ? sort_tile<uint64_t>(n) : sort_tile<uint32_t>(n)) * kRadix * 2;
+}
+// Either width's (the separate 32-bit passes keep their tile counts in the same buffer;
+// a call runs one width only).
+int64_t planned_status_words(int64_t n) { return sort_status_words(n, false); }
 
 void radix_sort_planned(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, const GridPlan* plan,
-                        const uint32_t* hist, uint32_t* digoff, uint32_t* tilectr, uint64_t* status,
-                        uint32_t* info, hipStream_t s, bool clear) {
+                        const uint32_t* hist, uint32_t* tilectr, uint64_t* status, uint32_t* info, hipStream_t s) {
   if (n <= 1) return;  // the key kernel's start buffer already is buffer 1 when there is nothing to sort
-  const int64_t tiles32 = ceil_div(n, 256 * sort_items<uint32_t>());
-  const int64_t tiles64 = ceil_div(n, 256 * sort_items<uint64_t>());
-  if (clear) {
-    fill_u32(tilectr, 0, 8, s);
-    fill_u32(reinterpret_cast<uint32_t*>(status), 0, planned_status_words(n), s);
+  if (n <= kSort4Max) {
+    launch_sort_all_planned<4>(keys0, keys1, vals0, vals1, n, plan, hist, tilectr, status, info, s);
+    return;
   }
-  hipLaunchKernelGGL(k_digit_offsets, dim3(8), dim3(kRadix), 0, s, hist, digoff);
-  // 32-bit keys (at most 4 passes): reduce, scan, then the pass, the tile counts
-  // in the look-back buffer (tiles32 * 256 words of its tiles32 * 512)
-  uint32_t* counts = reinterpret_cast<uint32_t*>(status);
+  if (n <= kSort8Max) {
+    launch_sort_all_planned<8>(keys0, keys1, vals0, vals1, n, plan, hist, tilectr, status, info, s);
+    return;
+  }
   uint32_t* k32[2] = {static_cast<uint32_t*>(keys0), static_cast<uint32_t*>(keys1)};
-  for (int p = 0; p < 4; ++p) {
-    hipLaunchKernelGGL(k_tile_counts<uint32_t>, dim3(static_cast<unsigned>(tiles32)), dim3(kBlock), 0, s, k32[0],
-                       k32[1], n, p, plan, digoff, counts, tiles32);
-    hipLaunchKernelGGL(k_tile_scan<uint32_t>, dim3(kRadix), dim3(kBlock), 0, s, counts, tiles32, p, plan, digoff);
-    hipLaunchKernelGGL((k_onesweep<uint32_t, true>), dim3(static_cast<unsigned>(tiles32)), dim3(kBlock), 0, s, k32[0],
-                       k32[1], vals0, vals1, n, p, plan, digoff, tilectr, status,
-                       static_cast<const uint32_t*>(counts), tiles32, info);
+  uint64_t* k64[2] = {static_cast<uint64_t*>(keys0), static_cast<uint64_t*>(keys1)};
+  if (n <= kSortAllMax) {
+    launch_sort_all<uint32_t, sort_items<uint32_t>()>(k32[0], k32[1], vals0, vals1, n, 4, plan, hist, tilectr, status,
+                                                      info, s);
+    launch_sort_all<uint64_t, sort_items<uint64_t>()>(k64[0], k64[1], vals0, vals1, n, 8, plan, hist, tilectr, status,
+                                                      info, s);
+  } else {
+    const int64_t tiles64 = ceil_div(n, 256 * sort_items<uint64_t>());
+    // 32-bit keys (at most 4 passes): reduce, scan, then the pass, the tile counts
+    // in the look-back buffer (tiles * 256 words of its tiles * 512)
+    const int64_t tiles = ceil_div(n, 256 * sort_items<uint32_t>());
+    uint32_t* counts = reinterpret_cast<uint32_t*>(status);
+    for (int p = 0; p < 4; ++p) {
+      hipLaunchKernelGGL(k_tile_counts<uint32_t>, dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, s, k32[0],
+                         k32[1], n, p, plan, counts, tiles);
+      hipLaunchKernelGGL(k_tile_scan<uint32_t>, dim3(kRadix), dim3(kBlock), 0, s, counts, tiles, p, plan, hist);
+      hipLaunchKernelGGL((k_onesweep<uint32_t, true>), dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, s, k32[0],
+                         k32[1], vals0, vals1, n, p, plan, static_cast<const uint32_t*>(nullptr), hist, tilectr,
+                         status, static_cast<const uint32_t*>(counts), tiles, info);
+    }
+    for (int p = 0; p < 8; ++p)
+      hipLaunchKernelGGL((k_onesweep<uint64_t, false>), dim3(lookback_grid<uint64_t>(tiles64)), dim3(kBlock), 0, s,
+                         k64[0], k64[1], vals0, vals1, n, p, plan, static_cast<const uint32_t*>(nullptr), hist, tilectr,
+                         status, static_cast<const uint32_t*>(nullptr), int64_t(0), info);
   }
-  for (int p = 0; p < 8; ++p)  // 64-bit keys
-    hipLaunchKernelGGL((k_onesweep<uint64_t, false>), dim3(lookback_grid<uint64_t>(tiles64)), dim3(kBlock), 0, s,
-                       static_cast<uint64_t*>(keys0), static_cast<uint64_t*>(keys1), vals0, vals1, n, p, plan,
-                       digoff, tilectr, status, static_cast<const uint32_t*>(nullptr), int64_t(0), info);
 }
 
 int radix_sort(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, bool key64, int bits,
-               uint32_t* hist, bool hist_ready, uint32_t* digoff, uint32_t* tilectr, uint64_t* status,
-               uint32_t* info, hipStream_t s) {
+               uint32_t* hist, bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status,
+               uint32_t* info, hipStream_t s, bool clear) {
   if (key64)
     return radix_sort_t(static_cast<uint64_t*>(keys0), static_cast<uint64_t*>(keys1), vals0, vals1, n, bits, hist,
-                        hist_ready, digoff, tilectr, status, info, s);
+                        hist_ready, pass_plan, tilectr, status, info, s, clear);
   return radix_sort_t(static_cast<uint32_t*>(keys0), static_cast<uint32_t*>(keys1), vals0, vals1, n, bits, hist,
-                      hist_ready, digoff, tilectr, status, info, s);
+                      hist_ready, pass_plan, tilectr, status, info, s, clear);
 }
 
 }  // namespace fdb
