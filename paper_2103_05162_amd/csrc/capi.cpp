@@ -60,7 +60,7 @@ Plan make_plan(int64_t n, int dim, int algo, int num_clouds) {
   p.rope = take(N * 4);
   p.leaf_rope = take(N * 4);
   p.ends = take(N * 4);
-  p.cut = take(static_cast<size_t>(kCutMax) * 36);  // kCutMax box pairs, then a summary word each
+  p.cut = take(static_cast<size_t>(kCutMax) * 32);  // kCutMax box pairs
   p.other = take(N * 4);
   p.gamma = take(N * 4);
   p.labels = take(N * 4);
@@ -881,16 +881,17 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     perm = vals[cur];
     st.mark("permute");
     launch_permute(points, n, dim, perm, xs, h->d_info, s);
-    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
+    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist), core);
     st.mark("lbvh");
     build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
                at<int>(ws, plan.ends), at<int>(ws, plan.other), at<int>(ws, plan.gamma),
-               nullptr, h->d_info, s, at<float4>(ws, plan.cut), misc + kMiscCut, true, kCutDivFine);
+               nullptr, h->d_info, s, nullptr, nullptr, true);
     ta.t.m_cap = static_cast<int>(n);
     ta.t.d_m = nullptr;
-    ta.t.cut = at<float4>(ws, plan.cut);
-    ta.t.cut_n = misc + kMiscCut;
+    ta.cliques = at<int>(ws, plan.other);  // the build is done with it
+    ta.num_cliques = misc + kMiscNumCliques;
+    launch_cliques(ta, dim, s);
   }
 
   const bool all_core = min_pts <= 2;
@@ -911,19 +912,9 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     launch_main(ta, dim, true, all_core, first_border && !all_core, 2, s);
   } else {
     st.mark("main");
-    if (all_core || !first_border) {
-      // the packet main phase: core pairs of curve neighbours first, then per cut
-      // subtree the set its core points are in, so packets pass over subtrees
-      // already in their own set
-      int* csum = reinterpret_cast<int*>(at<float4>(ws, plan.cut) + 2 * kCutMax);
-      launch_fdb_local(ta, dim, all_core, s);
-      launch_cut_summary(ta, all_core, csum, s);
-      ta.t.cut_sum = csum;
-      launch_main(ta, dim, false, all_core, false, 0, s);
-    } else {
-      launch_main(ta, dim, false, all_core, first_border && !all_core, 0, s);
-    }
-    ta.t.cut_sum = nullptr;
+    const bool first = first_border && !all_core;  // (its one pass covers the cliques too)
+    if (!first) launch_main_cliques(ta, dim, all_core, s);
+    launch_main(ta, dim, false, all_core, first, 0, s);
   }
   if (o.flags & FDB_FLAG_VALIDATE) launch_check_forest(lab, all_core ? nullptr : core, n, h->d_info + 1, h->d_info, s);
   st.mark("finalize");
@@ -1142,7 +1133,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
     ta.dense_list = at<int>(ws, plan.dense_list);
     ta.d_ndense = misc + kMiscNumDense;
   } else {
-    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
+    launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist), core);
     st.mark("lbvh");
     build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
@@ -1151,6 +1142,9 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
     batch_roots(offsets, num_clouds, n, nullptr, nullptr, at<int>(ws, plan.other), cl_root, cl_end, h->d_info,
                 nullptr, s);
     ta.t.d_m = nullptr;
+    ta.cliques = at<int>(ws, plan.other);  // the build is done with it
+    ta.num_cliques = misc + kMiscNumCliques;
+    launch_cliques(ta, dim, s);
   }
   st.mark("core");
   ta.lone = at<uint8_t>(ws, plan.lone);
@@ -1167,6 +1161,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
     launch_main(ta, dim, true, false, first_border, 2, s);
   } else {
     st.mark("main");
+    if (!first_border) launch_main_cliques(ta, dim, false, s);
     launch_main(ta, dim, false, false, first_border, 0, s);
   }
   if (o.flags & FDB_FLAG_VALIDATE) launch_check_forest(lab, core, n, h->d_info + 1, h->d_info, s);

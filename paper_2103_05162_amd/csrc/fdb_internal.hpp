@@ -18,6 +18,7 @@ constexpr int sort_items() { return sizeof(K) == 8 ? 24 : 22; }
 constexpr int kScanItems = 16;                 // items per thread in the device scan
 constexpr int kScanTile = 256 * kScanItems;
 constexpr int64_t kMaxPoints = (int64_t(1) << 30) - 1;
+constexpr uint8_t kCliqueCore = 2, kInClique = 3;  // core flag of a point in one of FDbscan's cliques (TravArgs::core)
 constexpr int kRecNb = 8;  // neighbouring primitives recorded per non-core point
 constexpr int kBorderCounters = 32 * 17;  // words of TravArgs::border_n (they fit the digit histograms)
 
@@ -59,6 +60,7 @@ enum MiscSlot : int {
   kMiscNumDense = 4,     // DenseBox: dense cells
   kMiscCut = 7,          // entries of the hierarchy's cut (TreeView::cut)
   kMiscNumBricks = 8,    // DenseBox: occupied bricks
+  kMiscNumCliques = 9,   // FDbscan: cliques that take a wavefront, then (10) those that take a lane
   kMiscCount = 16
 };
 
@@ -124,17 +126,11 @@ struct TreeView {
   // instead of descending from the root. Null, or a count above kCutMax: no cut.
   const float4* cut = nullptr;
   const int* cut_n = nullptr;
-  // Optional, per cut subtree (FDbscan's main phase): the root that every core point
-  // under it had when the summary was taken, kCutNoCore when it holds none, or
-  // kCutMixed. A subtree already in a packet's set adds no union and is not walked.
-  const int* cut_sum = nullptr;
 };
 
 constexpr int kCutMax = 8192;
 constexpr int kCutDiv = 256;      // the cut holds about kCutDiv to 2 kCutDiv subtrees
-constexpr int kCutDivFine = 4096;  // FDbscan: subtrees of ~m/4096 primitives, smaller than a clump
 constexpr int kCutUnroll = 4;     // cut entries a lane loads at once
-constexpr int kCutMixed = -1, kCutNoCore = -2;
 __host__ __device__ inline int cut_span(int m, int div = kCutDiv) {
   return (m + div - 1) / div > 64 ? (m + div - 1) / div : 64;
 }
@@ -233,7 +229,11 @@ struct TravArgs {
   int packet_leaf;    // bucket size of packet walks (<= 64: a bucket is loaded one point per lane)
   int min_pts;
   int* labels;
-  uint8_t* core;
+  uint8_t* core;     // 1 = core; FDbscan: kInClique for a point of a clique, 0 elsewhere before the core pass
+  // FDbscan: the nodes that are cliques and in no larger one, num_cliques[0] large ones
+  // from the front of the list (n words) and num_cliques[1] small ones from its end
+  int* cliques;
+  int* num_cliques;
   uint8_t* lone;  // set by the core pass (or the isolated-point test before it): 1 = not core and no
                   // neighbour but itself (noise); NULL if no core pass
   // Border work left by the core pass for non-core points with some neighbour
@@ -278,11 +278,10 @@ struct TravArgs {
   int block;
 };
 void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s);
-// FDbscan, one cloud, before the packet main phase: core pairs among curve
-// neighbours joined early, then a summary per cut subtree (kCutMax words at sum;
-// a.t.cut must be set) for a.t.cut_sum.
-void launch_fdb_local(const TravArgs& a, int dim, bool all_core, hipStream_t s);
-void launch_cut_summary(const TravArgs& a, bool all_core, int* sum, hipStream_t s);
+// FDbscan's cliques (subtrees whose points are pairwise within eps): found, marked in
+// labels and core, listed in cliques; then joined to what is within reach of them.
+void launch_cliques(const TravArgs& a, int dim, hipStream_t s);
+void launch_main_cliques(const TravArgs& a, int dim, bool all_core, hipStream_t s);
 void launch_main(const TravArgs& a, int dim, bool densebox, bool all_core, bool first_border, int part,
                  hipStream_t s);
 void launch_border(const TravArgs& a, int dim, bool densebox, hipStream_t s);
@@ -290,9 +289,10 @@ void launch_debug_walk(const TreeView& t, int m, int mask, int* out_leaves, int*
                        uint32_t* info, hipStream_t s);
 
 // k_label.hip
-// labels[i] = i; with ends / minorig / border_n, also those starting values (see densebox_cells).
+// labels[i] = i; with ends / minorig / border_n, also those starting values (see densebox_cells);
+// with core, no point is core yet.
 void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends = nullptr, int* minorig = nullptr,
-                        int* border_n = nullptr);
+                        int* border_n = nullptr, uint8_t* core = nullptr);
 // With minorig (core flags final): also the smallest input index (perm) of each
 // root's core points, in minorig[root] (INT_MAX beforehand, unless minorig_init:
 // then filled here first), and the leader words `bits` (ceil(n/32)) cleared.

@@ -20,13 +20,15 @@ inline int grid_for(int64_t n) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_iota(int* __restrict__ labels, int64_t n, int* __restrict__ ends,
-                                                 int* __restrict__ minorig, int* __restrict__ border_n) {
+                                                 int* __restrict__ minorig, int* __restrict__ border_n,
+                                                 uint8_t* __restrict__ core) {
   if (border_n && blockIdx.x == 0)
     for (int k = threadIdx.x; k < kBorderCounters; k += kBlock) border_n[k] = 0;
   for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
     labels[i] = static_cast<int>(i);
     if (ends) ends[i] = -1;
     if (minorig) minorig[i] = 0x7fffffff;
+    if (core) core[i] = 0;
   }
 }
 
@@ -438,8 +440,9 @@ void scan_block_sums(int* bsums, int64_t blocks, int* d_total, hipStream_t s, in
                      d_total2);
 }
 
-void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends, int* minorig, int* border_n) {
-  hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(kBlock), 0, s, labels, n, ends, minorig, border_n);
+void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends, int* minorig, int* border_n,
+                        uint8_t* core) {
+  hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(kBlock), 0, s, labels, n, ends, minorig, border_n, core);
 }
 
 void launch_finalize(int* labels, int64_t n, uint32_t* info, hipStream_t s, const uint8_t* core, const uint32_t* perm,

@@ -76,23 +76,41 @@ __device__ __forceinline__ Scope scope_of(const TravArgs& a, int m, int i) {
   return s;
 }
 
-// Walk the subtree of sc, calling visit(prim) for every primitive whose leaf
-// (or bucket) the walk reaches; visit returns true to stop. With MASKED,
-// subtrees whose primitives all have index <= mask are never entered: at a node
-// whose left child ends at or below the mask, the walk goes straight to the
-// right child, and buckets start above the mask. Every node the walk reaches
-// then holds a primitive above the mask. The walk ends where an escape link
-// would leave the subtree (past primitive sc.end).
+// A box query (every point of [lo, hi]); the walks take it or a point.
+struct BoxQ {
+  float lo[3], hi[3];
+};
+
+template <int D>
+__device__ __forceinline__ float node_gap2(const Query& q, float4 a, float4 b) {
+  return box_dist2<D>(q.x, q.y, q.z, a.x, a.y, a.z, b.x, b.y, b.z);
+}
+template <int D>
+__device__ __forceinline__ float node_gap2(const BoxQ& q, float4 a, float4 b) {
+  return boxbox_dist2<D>(q.lo, q.hi, a.x, a.y, a.z, b.x, b.y, b.z);
+}
+
+// Walk the subtree of sc, calling visit(first, last) for every bucket (at most
+// leaf_size primitives) and single leaf the walk reaches; visit returns true to stop.
+// With MASKED, only the primitives above the mask (>= 0) are walked: the escape links
+// from leaf `mask` on lead to the subtrees right of it, so no node above them is looked
+// at. The walk ends where an escape link would leave the subtree (past primitive sc.end).
+// subtree(first, last, lo, hi), called for a node within reach, says what to do with
+// it: 0 walk it, 1 pass over it, 2 stop.
 //
 // A pre-order walk reaches each node at most once, so more than 2m steps, or a
 // reference outside the tree, means the tree is broken: the walk then stops and
 // raises the internal-error bit instead of looping or reading out of bounds.
-template <int D, bool MASKED, typename F>
-__device__ __forceinline__ void traverse(const TreeView& t, int m, const Scope& sc, const Query& q, int mask,
-                                         uint32_t* info, F&& visit) {
+struct EverySubtree {
+  __device__ __forceinline__ int operator()(int, int, const float4&, const float4&) const { return 0; }
+};
+
+template <int D, bool MASKED, typename QT, typename F, typename S = EverySubtree>
+__device__ __forceinline__ void traverse(const TreeView& t, int m, const Scope& sc, const QT& q, int mask,
+                                         uint32_t* info, F&& visit, S&& subtree = S{}) {
   if (m <= 0) return;
   if (MASKED && mask >= sc.end) return;
-  uint32_t node = sc.start;
+  uint32_t node = MASKED ? static_cast<uint32_t>(t.leaf_rope[mask]) : sc.start;
   int64_t steps = 0;
   const int64_t max_steps = 2 * int64_t(m) + 2;
   while (node != kEnd) {
@@ -106,7 +124,7 @@ __device__ __forceinline__ void traverse(const TreeView& t, int m, const Scope& 
         atomicOr(info, kInternalBit);
         return;
       }
-      if (visit(l) || l >= sc.end) return;
+      if (visit(l, l) || l >= sc.end) return;
       node = static_cast<uint32_t>(t.leaf_rope[l]);
       continue;
     }
@@ -121,7 +139,7 @@ __device__ __forceinline__ void traverse(const TreeView& t, int m, const Scope& 
     const int k = static_cast<int>(node);
     const int o = __float_as_int(a.w), g = __float_as_int(b.w);
     const int first = o < k ? o : k, last = o > k ? o : k;
-    if (box_dist2<D>(q.x, q.y, q.z, a.x, a.y, a.z, b.x, b.y, b.z) > sc.eps2) {
+    if (node_gap2<D>(q, a, b) > sc.eps2) {
       if (last >= sc.end) return;
       node = esc;
       continue;
@@ -130,20 +148,60 @@ __device__ __forceinline__ void traverse(const TreeView& t, int m, const Scope& 
       atomicOr(info, kInternalBit);
       return;
     }
-    if (last - first < t.leaf_size) {
-      int s = first;
-      if (MASKED && s <= mask) s = mask + 1;
-      for (int l = s; l <= last; ++l)
-        if (visit(l)) return;
+    const int whole = subtree(first, last, a, b);
+    if (whole == 2) return;
+    if (whole == 1) {
       if (last >= sc.end) return;
       node = esc;
       continue;
     }
-    if (MASKED && g <= mask)
-      node = last == g + 1 ? (kLeaf | static_cast<uint32_t>(g + 1)) : static_cast<uint32_t>(g + 1);
-    else
-      node = first == g ? (kLeaf | static_cast<uint32_t>(g)) : static_cast<uint32_t>(g);
+    if (last - first < t.leaf_size) {
+      if (visit(first, last) || last >= sc.end) return;
+      node = esc;
+      continue;
+    }
+    node = first == g ? (kLeaf | static_cast<uint32_t>(g)) : static_cast<uint32_t>(g);
   }
+}
+
+// Which of the points s .. min(s + 3, e) are within eps of q, as bits: a lane's loads of
+// all four are in flight together.
+template <int D>
+__device__ __forceinline__ unsigned near_bits(const float* __restrict__ xs, int64_t n, int s, int e, const Query& q,
+                                              float eps2) {
+  float v[4][3];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t k = min(s + u, e);
+    v[u][0] = xs[k];
+    v[u][1] = xs[n + k];
+    v[u][2] = D == 3 ? xs[2 * n + k] : 0.0f;
+  }
+  unsigned bits = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    bits |= s + u <= e && dist2v<D>(v[u][0], v[u][1], v[u][2], q.x, q.y, q.z) <= eps2 ? 1u << u : 0u;
+  return bits;
+}
+
+// FDbscan: is the node [first, last] a clique, at least kCliqueMin (and minPts) points
+// in a box of diagonal at most eps? Its points are then pairwise within eps, as the
+// point-by-point test would decide: rounded subtraction, squaring and addition are
+// monotone, so the test of the box's corners bounds every pair's. All of them are core
+// and in one set (k_cliques says so beforehand), whatever part of the tree a walk
+// meets them in.
+constexpr int kCliqueMin = 4;
+// Cliques of this many points search for themselves, a wavefront each; the points of
+// smaller ones search each for itself, as points outside cliques do (but are in one set
+// and known to be core). Main phase with 8 / 12 / 16, us: 2M-point friends-of-friends
+// set 1812 / 1825 / 1829, 8M-point set 853 / 670 / 743, 16,384 points in 2D 169 / 174 /
+// 175. kCliqueMin 2, 4: alike; 16: 160 us more on the friends-of-friends set.
+constexpr int kCliqueWave = 12;
+template <int D>
+__device__ __forceinline__ bool is_clique(int first, int last, const float4& lo, const float4& hi, const Scope& sc) {
+  const int size = last - first + 1;
+  return size >= kCliqueMin && size >= sc.min_pts &&
+         dist2v<D>(hi.x, hi.y, hi.z, lo.x, lo.y, lo.z) <= sc.eps2;
 }
 
 // Wave-uniform walk for a box query (every point of box [lo,hi]), masked like
@@ -208,6 +266,26 @@ __device__ __forceinline__ bool traverse_box(const TreeView& t, int m, const Sco
   return false;
 }
 
+// An ancestor of x close to its root: labels followed for up to 16 hops, all
+// lanes of a bucket at once. Equal to a query's root means the two are already
+// in one set (sets only grow); anything else only means "unknown". When the chain
+// had more than one link, x is re-pointed straight at the ancestor found (an
+// ancestor stays an ancestor, so the store is safe however it races): points are
+// visited by many walks, and the next visit takes one load (FDbscan main phase on
+// the 8M set 37.4 -> 35.2 ms).
+__device__ __forceinline__ int ancestor_compress(int* labels, int x) {
+  const int x0 = x;
+  int p = labels[x];
+  int h = 0;
+#pragma unroll 1
+  for (; h < 16 && p != x; ++h) {
+    x = p;
+    p = labels[x];
+  }
+  if (h > 1) labels[x0] = p;
+  return p;
+}
+
 // Wavefront-cooperative form of traverse_box: the wavefront expands up to 64
 // tree nodes per step (one per lane) from its own stack in LDS, newest first,
 // so a walk takes about as many steps as the tree is deep instead of one step
@@ -216,16 +294,17 @@ __device__ __forceinline__ bool traverse_box(const TreeView& t, int m, const Sco
 // each lane's own primitive (-1 for none), so the visitor loads all of them at
 // once. It visits the same buckets and leaves as traverse_box (in another order:
 // callers only union, which does not depend on it). Children that do not fit on
-// the stack have their subtrees walked with traverse_box instead. SKIP: cut
-// subtrees that t.cut_sum marks as holding no core point, or as already in the
-// set of root skip_root (labels skip_labels), are not walked.
+// the stack have their subtrees walked with traverse_box instead. SKIP (FDbscan's
+// unions): the walk starts from the escape links above the mask (>= 0), and cliques
+// already in the set of root skip_root (labels skip_labels; the visitor may advance it)
+// are not walked.
 constexpr int kWideStack = 512;  // entries per wavefront
 
-template <int D, bool SKIP = false, typename F>
+template <int D, bool SKIP, typename F>
 __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m, const Scope& sc, const float* lo,
                                                         const float* hi, int mask, int leaf_size, uint32_t* info,
                                                         uint32_t* stack, F&& visit_lanes,
-                                                        const int* skip_labels = nullptr, int skip_root = -1) {
+                                                        int* skip_labels, const int& skip_root) {
   if (m <= 0 || mask >= sc.end) return;
   const int lane = lane_id();
   // a range [s, e] of one lane (wave-uniform arguments), 64 primitives per call
@@ -235,29 +314,42 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
     return false;
   };
   int top = 0;
+  if (SKIP) {
+    // the subtrees above the mask, as the escape links have them, left to right
+    uint32_t x = static_cast<uint32_t>(t.leaf_rope[mask]);
+    for (int last = mask; last < sc.end && x != kEnd;) {
+      if (top == kWideStack || (x & ~kLeaf) >= static_cast<uint32_t>(m)) {
+        if (lane == 0) atomicOr(info, kInternalBit);
+        return;
+      }
+      if (lane == 0) stack[top] = x;
+      ++top;
+      const int k = static_cast<int>(x & ~kLeaf);
+      if (x & kLeaf) {
+        last = k;
+        x = static_cast<uint32_t>(t.leaf_rope[k]);
+      } else {
+        last = max(k, __float_as_int(t.node_a[kNodeStride * size_t(k)].w));
+        x = static_cast<uint32_t>(t.rope[k]);
+      }
+    }
+  }
   // a walk over the whole tree starts from the cut: its boxes are tested 64 at a
   // time and the ones within reach pushed, instead of descending from the root
-  const int nc = t.cut && sc.start == 0 && sc.end == m - 1 ? *t.cut_n : 0;
+  const int nc = !SKIP && t.cut && sc.start == 0 && sc.end == m - 1 ? *t.cut_n : 0;
   if (nc > 0 && nc <= kCutMax) {
     for (int b = 0; b < nc && top >= 0; b += 64 * kCutUnroll) {
       float4 ca[kCutUnroll], cb[kCutUnroll];
-      int cs[kCutUnroll];
 #pragma unroll
       for (int u = 0; u < kCutUnroll; ++u) {  // the loads of kCutUnroll chunks in flight together
         const int c = min(b + u * 64 + lane, nc - 1);
         ca[u] = t.cut[2 * c];
         cb[u] = t.cut[2 * c + 1];
-        cs[u] = SKIP && t.cut_sum ? t.cut_sum[c] : kCutMixed;
       }
 #pragma unroll
       for (int u = 0; u < kCutUnroll; ++u) {
-        bool hit = b + u * 64 + lane < nc && __float_as_int(cb[u].w) > mask &&
+        const bool hit = b + u * 64 + lane < nc && __float_as_int(cb[u].w) > mask &&
                    boxbox_dist2<D>(lo, hi, ca[u].x, ca[u].y, ca[u].z, cb[u].x, cb[u].y, cb[u].z) <= sc.eps2;
-        // a subtree without core points, or one whose core points were all in the
-        // walker's set (skip_root) when summarised, adds no union: sets only merge
-        if (SKIP && hit && cs[u] != kCutMixed)
-          hit = !(cs[u] == kCutNoCore ||
-                  (skip_root >= 0 && (cs[u] == skip_root || skip_labels[cs[u]] == skip_root)));
         const uint64_t hm = ballot(hit);
         if (top < 0 || top + __popcll(hm) > kWideStack) {
           top = -1;  // more than the stack holds: start from the root instead
@@ -268,7 +360,7 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
       }
     }
   }
-  if (nc <= 0 || nc > kCutMax || top < 0) {
+  if (!SKIP && (nc <= 0 || nc > kCutMax || top < 0)) {
     if (lane == 0) stack[0] = sc.start;
     top = 1;
   }
@@ -300,6 +392,9 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
         if (last > mask && boxbox_dist2<D>(lo, hi, na.x, na.y, na.z, nb.x, nb.y, nb.z) <= sc.eps2) {
           if (first < 0 || last >= m || g < first || g >= last) {
             atomicOr(info, kInternalBit);
+          } else if (SKIP && skip_root >= 0 && is_clique<D>(first, last, na, nb, sc) &&
+                     ancestor_compress(skip_labels, first) == skip_root) {
+            // nothing to join
           } else if (last - first < leaf_size) {
             bs = first <= mask ? mask + 1 : first;
             be = last;
@@ -359,6 +454,14 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
       }
     }
   }
+}
+
+template <int D, typename F>
+__device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m, const Scope& sc, const float* lo,
+                                                        const float* hi, int mask, int leaf_size, uint32_t* info,
+                                                        uint32_t* stack, F&& visit_lanes) {
+  const int none = -1;
+  traverse_box_wide_lanes<D, false>(t, m, sc, lo, hi, mask, leaf_size, info, stack, visit_lanes, nullptr, none);
 }
 
 // True only if `root` is an ancestor of x within a few plain-load hops (then x
@@ -484,28 +587,21 @@ __device__ __forceinline__ void core_epilogue(const TravArgs& a, bool mine, int 
 // run) is noise: nothing to claim, no cluster to join.
 __device__ __forceinline__ bool is_lone(const TravArgs& a, int i) { return a.lone && a.lone[i]; }
 
-// An ancestor of x close to its root: labels followed for up to 16 hops, all
-// lanes of a bucket at once. Equal to a query's root means the two are already
-// in one set (sets only grow); anything else only means "unknown". When the chain
-// had more than one link, x is re-pointed straight at the ancestor found (an
-// ancestor stays an ancestor, so the store is safe however it races): points are
-// visited by many walks, and the next visit takes one load (FDbscan main phase on
-// the 8M set 37.4 -> 35.2 ms).
-__device__ __forceinline__ int ancestor_compress(int* labels, int x) {
-  const int x0 = x;
-  int p = labels[x];
-  int h = 0;
-#pragma unroll 1
-  for (; h < 16 && p != x; ++h) {
-    x = p;
-    p = labels[x];
-  }
-  if (h > 1) labels[x0] = p;
-  return p;
-}
-
 __device__ __forceinline__ float readlane_f(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+
+// Is every point in the box [lo, hi] within eps of q, as the
+// point-by-point test would decide? Per axis the corner farther from q (by the
+// rounded difference) bounds every point's rounded difference, since rounded
+// subtraction, squaring and addition are monotone; so the test at that corner,
+// made with the same operations in the same order, holds for all of them.
+template <int D>
+__device__ __forceinline__ bool cell_within(float4 lo, float4 hi, const Query& q, float eps2) {
+  const float cx = fabsf(lo.x - q.x) > fabsf(hi.x - q.x) ? lo.x : hi.x;
+  const float cy = fabsf(lo.y - q.y) > fabsf(hi.y - q.y) ? lo.y : hi.y;
+  const float cz = fabsf(lo.z - q.z) > fabsf(hi.z - q.z) ? lo.z : hi.z;
+  return dist2v<D>(cx, cy, cz, q.x, q.y, q.z) <= eps2;
 }
 
 // ---------------------------------------------------------------- FDbscan ----
@@ -515,7 +611,7 @@ __global__ void k_core_fdb(TravArgs a) {
   __shared__ int s_w[17];
   extern __shared__ int s_rec[];  // kRecNb * blockDim.x
   const int64_t i64 = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, a.n);
-  const bool mine = i64 >= 0 && i64 < a.n;
+  const bool mine = i64 >= 0 && i64 < a.n && a.core[i64] < kCliqueCore;
   const int i = mine ? static_cast<int>(i64) : 0;
   const int m = tree_m(a.t);
   const Scope sc = scope_of<B>(a, m, i);
@@ -524,14 +620,118 @@ __global__ void k_core_fdb(TravArgs a) {
   NbRec rec;
   rec_init(rec, s_rec);
   if (mine)
-    traverse<D, false>(a.t, m, sc, q, 0, a.info, [&](int j) {
-      if (!near<D>(a.xs, a.n, j, q, sc.eps2)) return false;
-      if (j != i) rec_add(rec, j);
-      return ++cnt >= sc.min_pts;
+    traverse<D, false>(a.t, m, sc, q, 0, a.info, [&](int s, int e) {
+      for (int j = s; j <= e && cnt < sc.min_pts; j += 4)
+        for (unsigned nb = near_bits<D>(a.xs, a.n, j, e, q, sc.eps2); nb; nb &= nb - 1) {
+          const int k = j + __ffs(nb) - 1;
+          if (k != i) rec_add(rec, k);
+          ++cnt;
+        }
+      return cnt >= sc.min_pts;
+    }, [&](int first, int last, const float4& lo, const float4& hi) {
+      // enough points in a box all within eps: core, whichever they are
+      if (cnt + (last - first + 1) < sc.min_pts || !cell_within<D>(lo, hi, q, sc.eps2)) return 0;
+      cnt = sc.min_pts;
+      return 2;
     });
   const int64_t share = xcd_share(a.n, blockDim.x);
   if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(share);
   core_epilogue(a, mine, i, i, cnt, sc.min_pts, rec, s_w, (blockIdx.x % kNumXcd) * share);
+}
+
+// The queries of a kernel whose number `total` only the device knows: a
+// workgroup takes chunks of kLanes queries a wavefront, blockIdx.x, + gridDim.x, ...
+// (gridDim.x a multiple of kNumXcd), laid out over the XCDs as xcd_spread has them.
+// The grid is capped (query_grid_blocks): with a workgroup for each of the n points
+// the queries could be, 65,536 workgroups without work took 15 us a launch (8M set).
+// Few queries take fewer lanes a wavefront, down to 8, so that kWaves wavefronts or
+// more share them: a wavefront's time is its lanes' loads, scans and unions one after the
+// other, and 44k queries (370k-point mixture) fill only 700 wavefronts of 64.
+constexpr int kWaves = 4096;
+
+struct Chunks {
+  int64_t chunk, off;  // queries per XCD; this workgroup's first within its XCD's
+  int lanes, step, slot, xcd;
+
+  __device__ __forceinline__ Chunks(int64_t total, bool spread) {
+    lanes = 64;
+    while (spread && lanes > 8 && total < int64_t(kWaves) * (lanes / 2)) lanes >>= 1;
+    const int per = lanes * static_cast<int>(blockDim.x >> 6);  // queries a workgroup and chunk
+    chunk = xcd_share(total, per);
+    xcd = static_cast<int>(blockIdx.x % kNumXcd);
+    off = int64_t(blockIdx.x / kNumXcd) * per;
+    step = static_cast<int>(gridDim.x / kNumXcd) * per;
+    slot = lane_id() < lanes ? static_cast<int>(threadIdx.x >> 6) * lanes + lane_id() : -1;
+  }
+  __device__ __forceinline__ bool in() const { return off < chunk; }
+  __device__ __forceinline__ void next() { off += step; }
+  // this lane's query (at or above the total where the chunk runs past it), -1: none
+  __device__ __forceinline__ int query() const { return slot < 0 ? -1 : static_cast<int>(xcd * chunk + off + slot); }
+};
+
+// Cliques (is_clique) that are in no larger one: a thread takes kCliqueItems nodes in
+// turn and looks at the two children of each that is no clique itself (their records
+// lie side by side). Their points become core and one set; those of kCliqueWave points
+// or more (kInClique, the rest kCliqueCore) are listed for k_main_cliques. A workgroup
+// lists through LDS and reserves once. Bound by the node records: 8M points (80% of them
+// in cliques) 120 us for 268 MB of nodes read up to three times.
+constexpr int kCliqueItems = 8;
+
+template <int D, bool B>
+__global__ __launch_bounds__(256) void k_cliques(TravArgs a) {
+  __shared__ int s_list[2 * 256 * kCliqueItems];
+  __shared__ int s_n, s_at;
+  const int m = tree_m(a.t);
+  const int lane = lane_id();
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  // node k's range, or first > last where it is no clique
+  auto clique = [&](int k, int& first, int& last, int& g) {
+    const float4 lo = a.t.node_a[kNodeStride * size_t(k)], hi = a.t.node_b[kNodeStride * size_t(k)];
+    const int o = __float_as_int(lo.w);
+    first = o < k ? o : k;
+    last = o > k ? o : k;
+    g = __float_as_int(hi.w);
+    if (first < 0 || last >= m || g < first || g >= last) {  // not a node: the walks report it
+      g = -1;
+      return false;
+    }
+    if (B && cloud_of(a, first) != cloud_of(a, last)) return false;
+    return is_clique<D>(first, last, lo, hi, scope_of<B>(a, m, first));
+  };
+  const int64_t base = blockIdx.x * int64_t(256 * kCliqueItems) + threadIdx.x;
+  for (int t = 0; t < kCliqueItems; ++t) {
+    const int64_t k64 = base + t * 256;
+    int found[2] = {-1, -1}, lo[2] = {0, 0}, hi[2] = {-1, -1};
+    if (k64 < m - 1) {
+      const int k = static_cast<int>(k64);
+      int first, last, g, gc;
+      if (!clique(k, first, last, g)) {
+        if (g >= 0 && first < g && clique(g, lo[0], hi[0], gc)) found[0] = g;
+        if (g >= 0 && last > g + 1 && clique(g + 1, lo[1], hi[1], gc)) found[1] = g + 1;
+      } else if (k == 0) {
+        found[0] = 0;
+        lo[0] = first;
+        hi[0] = last;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      if (found[c] >= 0 && hi[c] - lo[c] + 1 >= kCliqueWave) s_list[atomicAdd(&s_n, 1)] = found[c];
+      for (uint64_t fm = ballot(found[c] >= 0); fm; fm &= fm - 1) {
+        const int L = __ffsll(static_cast<unsigned long long>(fm)) - 1;
+        const int first = __builtin_amdgcn_readlane(lo[c], L), last = __builtin_amdgcn_readlane(hi[c], L);
+        for (int i = first + lane; i <= last; i += 64) {
+          a.labels[i] = first;
+          a.core[i] = last - first + 1 >= kCliqueWave ? kInClique : kCliqueCore;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) s_at = s_n ? atomicAdd(a.num_cliques, s_n) : 0;
+  __syncthreads();
+  for (int k = threadIdx.x; k < s_n; k += 256) a.cliques[s_at + k] = s_list[k];
 }
 
 // First-claim main phase (the paper's border rule): per-lane walks, or a packet
@@ -607,300 +807,112 @@ __global__ void k_main_fdb_first(TravArgs a) {
     return;
   }
   if (!mine) return;
-  traverse<D, true>(a.t, m, sc, q, i, a.info, [&](int j) {
-    if (!near<D>(a.xs, a.n, j, q, sc.eps2)) return false;
-    main_pair_first(a, i, ci, j, a.core[j] != 0, root, done);
+  traverse<D, true>(a.t, m, sc, q, i, a.info, [&](int s, int e) {
+    for (int j = s; j <= e && !done; j += 4)
+      for (unsigned nb = near_bits<D>(a.xs, a.n, j, e, q, sc.eps2); nb && !done; nb &= nb - 1) {
+        const int k = j + __ffs(nb) - 1;
+        main_pair_first(a, i, ci, k, a.core[k] != 0, root, done);
+      }
     return done;
   });
 }
 
-// Before FDbscan's packet main phase: each core point joins the core points among
-// the next kLocalWindow along the curve that are within eps (pairs of the main
-// phase, taken early: in a dense clump consecutive points are close, so a clump
-// ends up in one or a few sets), so that the cut summaries below find whole
-// subtrees already in one set.
-constexpr int kLocalWindow = 8;
-
-template <int D, bool ALL_CORE>
-__global__ __launch_bounds__(256) void k_fdb_local(TravArgs a) {
-  const int64_t i64 = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (i64 >= a.n) return;
+// Canonical (and minPts <= 2) main phase of the points outside the cliques of
+// k_main_cliques: a lane each, walking over the points above its own and passing over
+// cliques that already are in its set, so a dense clump costs a look at each of its
+// cliques. Bound by each lane's chain of dependent loads and, in sparse sets, by unions.
+// Before there were cliques, wavefronts of 64 near queries walked as packets, to share
+// the clumps' candidates; with them walks of their own are faster everywhere (main phase
+// with the packets / without: 8M-point set 1124 / 256 us, 16,384 points 430 / 123,
+// friends-of-friends set 1629 / 1673), and a packet of spread-out queries, which took
+// them one by one, no longer exists (1.5M uniform points, minPts 5: 18.0 -> 2.4 ms a call).
+template <int D, bool ALL_CORE, bool B>
+__global__ void k_main_fdb(TravArgs a) {
+  const int64_t i64 = xcd_spread(blockIdx.x, blockDim.x, threadIdx.x, a.n);
+  if (i64 < 0 || i64 >= a.n) return;
   const int i = static_cast<int>(i64);
-  if (!(ALL_CORE || a.core[i])) return;
-  const Query q = load_point<D>(a.xs, a.n, i);
-  int root = i;
-  for (int u = 1; u <= kLocalWindow; ++u) {
-    const int j = i + u;
-    if (j >= a.n) break;
-    if (!(ALL_CORE || a.core[j]) || !near<D>(a.xs, a.n, j, q, a.eps2)) continue;
-    if (!known_same_set(a.labels, j, root)) root = uf_union(a.labels, root, j, a.info);
-  }
-}
-
-// Summary of cut subtree c (a workgroup each): the root of every core point under
-// it (kCutNoCore: none; kCutMixed: more than one, or a chain too long to follow).
-template <bool ALL_CORE>
-__global__ __launch_bounds__(256) void k_cut_summary(TreeView t, int m, const int* __restrict__ labels,
-                                                     const uint8_t* __restrict__ core, int* __restrict__ sum) {
-  __shared__ int s_lo[4], s_hi[4];
-  const int nc = *t.cut_n;
-  const int c = blockIdx.x;
-  if (nc > kCutMax || c >= nc) return;  // whole workgroup
-  const float4 ca = t.cut[2 * c], cb = t.cut[2 * c + 1];
-  const uint32_t ref = __float_as_uint(ca.w);
-  const int last = __float_as_int(cb.w);
-  int first = last;
-  if (!(ref & kLeaf) && ref < static_cast<uint32_t>(m - 1)) {
-    const int k = static_cast<int>(ref);
-    const int o = __float_as_int(t.node_a[kNodeStride * size_t(k)].w);
-    first = o < k ? o : k;
-  }
-  int lo = 0x7fffffff, hi = -1;  // smallest and largest root among the core points
-  if (first < 0 || last >= m || first > last) lo = -3;  // not a range: never skipped
-  for (int i = first + static_cast<int>(threadIdx.x); lo != -3 && i <= last; i += 256) {
-    if (!(ALL_CORE || core[i])) continue;
-    int x = i, p = labels[x];
-    for (int h = 0; p != x && h < 64; ++h) {
-      x = p;
-      p = labels[x];
-    }
-    if (p != x) {
-      lo = -3;  // mixed
-      break;
-    }
-    lo = x < lo ? x : lo;
-    hi = x > hi ? x : hi;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, __shfl_xor(lo, off));
-    hi = max(hi, __shfl_xor(hi, off));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s_lo[threadIdx.x >> 6] = lo;
-    s_hi[threadIdx.x >> 6] = hi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      lo = min(lo, s_lo[w]);
-      hi = max(hi, s_hi[w]);
-    }
-    sum[c] = lo == -3 ? kCutMixed : (hi < 0 ? kCutNoCore : (lo == hi ? lo : kCutMixed));
-  }
-}
-
-// Canonical (and minPts <= 2) main phase, Q queries per lane: a wavefront owns
-// 64*Q consecutive queries. When they lie in a small box (and, in a batch, in
-// one cloud) they walk as one packet: the lanes load a bucket of candidates
-// once and broadcast it. Phase A unions the packet's own pairs; if then every
-// query shares one root r, a candidate whose label is r is skipped untested and
-// a candidate within eps of any query costs one union for the whole packet.
-template <int D, bool ALL_CORE, bool B, int Q>
-__global__ __launch_bounds__(256) void k_main_fdb_q(TravArgs a) {
-  __shared__ uint32_t s_stack[4 * kWideStack];  // packet walks (256-thread workgroups)
-  const int lane = lane_id();
-  const int64_t bbase = xcd_spread(blockIdx.x, 256 * Q, 0, a.n);
-  if (bbase < 0) return;
-  const int64_t base = bbase + int64_t(threadIdx.x >> 6) * 64 * Q;  // this wavefront's first query
-  if (base >= a.n) return;
+  const int f = a.core[i];
+  if (f == kInClique || !(ALL_CORE || f)) return;
   const int m = tree_m(a.t);
+  const Scope sc = scope_of<B>(a, m, i);
+  const Query q = load_point<D>(a.xs, a.n, i);
   int* labels = a.labels;
-  int idx[Q], root[Q];
-  bool mine[Q];
-  Query q[Q];
-  uint64_t mm[Q];
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-#pragma unroll
-  for (int s = 0; s < Q; ++s) {
-    const int64_t i64 = base + s * 64 + lane;
-    const bool valid = i64 < a.n;
-    idx[s] = valid ? static_cast<int>(i64) : 0;
-    mine[s] = valid && (ALL_CORE || a.core[idx[s]]);
-    q[s] = load_point<D>(a.xs, a.n, idx[s]);
-    root[s] = idx[s];
-    if (mine[s]) {
-      lo[0] = fminf(lo[0], q[s].x); hi[0] = fmaxf(hi[0], q[s].x);
-      lo[1] = fminf(lo[1], q[s].y); hi[1] = fmaxf(hi[1], q[s].y);
-      lo[2] = fminf(lo[2], q[s].z); hi[2] = fmaxf(hi[2], q[s].z);
-    }
-    mm[s] = ballot(mine[s]);
-  }
-  uint64_t any = 0;
-#pragma unroll
-  for (int s = 0; s < Q; ++s) any |= mm[s];
-  if (!any) return;
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    for (int off = 32; off > 0; off >>= 1) {
-      lo[k] = fminf(lo[k], __shfl_xor(lo[k], off));
-      hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off));
-    }
-  float ext = fmaxf(hi[0] - lo[0], hi[1] - lo[1]);
-  if (D == 3) ext = fmaxf(ext, hi[2] - lo[2]);
-  int first_slot = 0;
-#pragma unroll
-  for (int s = Q - 1; s >= 0; --s)
-    if (mm[s]) first_slot = s;
-  const int fl = __ffsll(static_cast<unsigned long long>(mm[first_slot])) - 1;
-  const int i0 = static_cast<int>(base) + first_slot * 64 + fl;
-  const Scope ps = scope_of<B>(a, m, i0);
-  bool other_cloud = false;
-  if (B) {
-#pragma unroll
-    for (int s = 0; s < Q; ++s) other_cloud |= mine[s] && cloud_of(a, idx[s]) != cloud_of(a, i0);
-  }
-  const bool packet = !ballot(other_cloud) && ext * ext <= a.packet_ext_eps2 * ps.eps2;
-
-  if (!ALL_CORE && !packet && a.t.cut_sum && !B) {
-    // spread out, with cut summaries and minPts > 2 (so every query is a core
-    // point, in a dense neighbourhood): each query walks as a packet of one (the
-    // lane-wide walk, passing over cut subtrees already in its set). Per-lane
-    // rope walks of a wavefront of such queries at a clump's edge took 13-15 ms,
-    // each lane visiting the clump's candidates one by one. With minPts <= 2
-    // every point is a query and sparse ones walk cheaply on their own lanes
-    // (a 2M-point friends-of-friends set: 5.0 ms that way, 11.1 ms as packets of one).
-    uint32_t* qstack = s_stack + (threadIdx.x >> 6) * kWideStack;
-#pragma unroll
-    for (int s = 0; s < Q; ++s)
-      for (uint64_t qm = mm[s]; qm; qm &= qm - 1) {
-        const int kl = __ffsll(static_cast<unsigned long long>(qm)) - 1;
-        const int i = __builtin_amdgcn_readlane(idx[s], kl);
-        const float qx = readlane_f(q[s].x, kl), qy = readlane_f(q[s].y, kl), qz = readlane_f(q[s].z, kl);
-        const float qb[3] = {qx, qy, qz};
-        const Scope sc = scope_of<B>(a, m, i);
-        int r = 0;
-        if (lane == 0) r = uf_find(labels, i, a.info);
-        r = __shfl(r, 0);
-        traverse_box_wide_lanes<D, true>(a.t, m, sc, qb, qb, i, a.packet_leaf, a.info, qstack, [&](int jl) {
-          bool hit = false;
-          if (jl > i && (ALL_CORE || a.core[jl]))
-            hit = dist2v<D>(a.xs[jl], a.xs[a.n + jl], D == 3 ? a.xs[2 * a.n + jl] : 0.0f, qx, qy, qz) <= sc.eps2;
-          if (ballot(hit)) {
-            if (hit && !known_same_set(labels, jl, r)) uf_union(labels, r, jl, a.info);
-            int nr = 0;
-            if (lane == 0) nr = uf_find(labels, r, a.info);
-            r = __shfl(nr, 0);
-          }
-          return false;
-        }, labels, r);
+  int root = i;
+  traverse<D, true>(a.t, m, sc, q, i, a.info, [&](int s, int e) {
+    for (int j = s; j <= e; j += 4)
+      for (unsigned nb = near_bits<D>(a.xs, a.n, j, e, q, sc.eps2); nb; nb &= nb - 1) {
+        const int k = j + __ffs(nb) - 1;
+        if ((ALL_CORE || a.core[k]) && !known_same_set(labels, k, root)) root = uf_union(labels, root, k, a.info);
       }
-    return;
-  }
-  if (!packet) {  // spread out: every query walks on its own
-#pragma unroll
-    for (int s = 0; s < Q; ++s) {
-      if (!mine[s]) continue;
-      const int i = idx[s];
-      const Query qs = q[s];
-      const Scope sc = scope_of<B>(a, m, i);
-      int rs = root[s];
-      traverse<D, true>(a.t, m, sc, qs, i, a.info, [&](int j) {
-        if (!near<D>(a.xs, a.n, j, qs, sc.eps2)) return false;
-        if (!(ALL_CORE || a.core[j])) return false;
-        if (!known_same_set(labels, j, rs)) rs = uf_union(labels, rs, j, a.info);
-        return false;
-      });
-    }
-    return;
-  }
-  const float eps2 = ps.eps2;
+    return false;
+  }, [&](int first, int last, const float4& lo, const float4& hi) {
+    return is_clique<D>(first, last, lo, hi, sc) && known_same_set(labels, first, root) ? 1 : 0;
+  });
+}
 
-  // Phase A: pairs inside the packet. Skipped when every query is already in one
-  // set (the curve-neighbour unions usually see to that): its pairs would then
-  // only join a set to itself.
-  bool split = false;
-#pragma unroll
-  for (int s = 0; s < Q; ++s)
-    if (mine[s]) root[s] = uf_find(labels, root[s], a.info);
-  {
-    int r0 = 0;
-#pragma unroll
-    for (int s = 0; s < Q; ++s)
-      if (s == first_slot) r0 = root[s];
-    r0 = __shfl(r0, fl);
-#pragma unroll
-    for (int s = 0; s < Q; ++s) split |= mine[s] && root[s] != r0;
-  }
-  const bool phase_a = ballot(split) != 0;
-#pragma unroll
-  for (int ks = 0; ks < Q && phase_a; ++ks) {
-    for (int kl = 0; kl < 64; ++kl) {
-      if (!((mm[ks] >> kl) & 1)) continue;
-      const int jk = static_cast<int>(base) + ks * 64 + kl;
-      const float px = readlane_f(q[ks].x, kl), py = readlane_f(q[ks].y, kl), pz = readlane_f(q[ks].z, kl);
-#pragma unroll
-      for (int s = 0; s < Q; ++s)
-        if (mine[s] && jk > idx[s] && dist2v<D>(px, py, pz, q[s].x, q[s].y, q[s].z) <= eps2 &&
-            !known_same_set(labels, jk, root[s]))
-          root[s] = uf_union(labels, root[s], jk, a.info);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < Q; ++s)
-    if (mine[s]) root[s] = uf_find(labels, root[s], a.info);
-  int rl = 0;
-#pragma unroll
-  for (int s = 0; s < Q; ++s)
-    if (s == first_slot) rl = root[s];
-  int r = __shfl(rl, fl);
-  bool differ = false;
-#pragma unroll
-  for (int s = 0; s < Q; ++s) differ |= mine[s] && root[s] != r;
-  const bool common = !ballot(differ);
-  const int p1 = static_cast<int>(base) + 64 * Q - 1;
-
+// Main phase of the cliques of kCliqueWave points or more: one wavefront per clique A walks the tree once with A's
+// box over the points above A. A candidate is a core point within eps of A's box that is
+// not known to be in A's set, one per lane; it joins the set if some point of A is
+// within eps (the points below A look for A themselves: other points in k_main_fdb,
+// points of cliques here). A wavefront's time is its rounds, each a chain of
+// dependent loads; starting from the cut's 8192 boxes instead of the escape links cost
+// 128 rounds of box tests a clique (friends-of-friends set, cliques of 4 and more: 1426
+// us, 896 us from the links). One lane per clique was slower (1222 us, and on 16,384
+// points 190 us instead of 40).
+template <int D, bool ALL_CORE, bool B>
+__global__ __launch_bounds__(256) void k_main_cliques(TravArgs a) {
+  __shared__ uint32_t s_stack[4 * kWideStack];
   uint32_t* stack = s_stack + (threadIdx.x >> 6) * kWideStack;
-  // the buckets a step reaches are laid end to end over the lanes (one candidate
-  // per lane), so a step costs a round per 64 candidates, not one per bucket
-  traverse_box_wide_lanes<D, true>(a.t, m, ps, lo, hi, i0, a.packet_leaf, a.info, stack, [&](int jl) {
-    float cx = 0.0f, cy = 0.0f, cz = 0.0f;
-    int cc = 0, cl = 0;
-    if (jl >= 0) {
-      cx = a.xs[jl];
-      cy = a.xs[a.n + jl];
-      cz = D == 3 ? a.xs[2 * a.n + jl] : 0.0f;
-      cc = (ALL_CORE || a.core[jl]) ? 1 : 0;
-      cl = ancestor_compress(labels, jl);
-    }
-    // candidates that need a test, decided by each candidate's own lane: outside the
-    // packet (its pairs are phase A's; j > i0 by the mask), core, and not already in
-    // the packet's set (r may grow during the round; a candidate skipped for the
-    // old r is in the new r's set too, sets only merge)
-    const bool need = jl > p1 && cc && !(common && cl == r);
-    if (!ballot(need)) return false;
-    if (common) {
-      // every lane tests its own candidate against the queries (register
-      // broadcasts, until every candidate has one within eps), and the lanes
-      // that reach one join the packet's set together rather than one by one
+  const int m = tree_m(a.t), nq = *a.num_cliques;
+  const int lane = lane_id();
+  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  int* labels = a.labels;
+  for (int w = (xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6; w < nq; w += nwaves) {
+    const int k = a.cliques[w];
+    const float4 na = a.t.node_a[kNodeStride * size_t(k)], nb = a.t.node_b[kNodeStride * size_t(k)];
+    const int o = __float_as_int(na.w);
+    const int sa = o < k ? o : k, ea = o > k ? o : k;
+    const float alo[3] = {na.x, na.y, na.z}, ahi[3] = {nb.x, nb.y, nb.z};
+    const Scope sc = scope_of<B>(a, m, sa);
+    const float eps2 = sc.eps2;
+    int r = uf_find(labels, sa, a.info);
+    traverse_box_wide_lanes<D, true>(a.t, m, sc, alo, ahi, ea, a.packet_leaf, a.info, stack, [&](int jl) {
+      float cx = 0.0f, cy = 0.0f, cz = 0.0f;
+      int cl = -1;
+      bool need = false;
+      if (jl >= 0 && (ALL_CORE || a.core[jl])) {
+        cx = a.xs[jl];
+        cy = a.xs[a.n + jl];
+        cz = D == 3 ? a.xs[2 * a.n + jl] : 0.0f;
+        need = box_dist2<D>(cx, cy, cz, alo[0], alo[1], alo[2], ahi[0], ahi[1], ahi[2]) <= eps2;
+        if (need) cl = ancestor_compress(labels, jl);
+        need = need && cl != r;
+      }
       bool reach = false;
-#pragma unroll
-      for (int s = 0; s < Q; ++s)
-        for (uint64_t qm = mm[s]; qm && ballot(need && !reach); qm &= qm - 1) {
-          const int kl = __ffsll(static_cast<unsigned long long>(qm)) - 1;
-          reach |= need && dist2v<D>(cx, cy, cz, readlane_f(q[s].x, kl), readlane_f(q[s].y, kl),
-                                     readlane_f(q[s].z, kl)) <= eps2;
-        }
+      for (int base = sa; base <= ea && ballot(need && !reach); base += 64) {
+        const int at = min(base + lane, ea);
+        const float px = a.xs[at], py = a.xs[a.n + at], pz = D == 3 ? a.xs[2 * a.n + at] : 0.0f;
+        const int cnt = min(64, ea - base + 1);
+        for (int u = 0; u < cnt; ++u)
+          reach |= need && dist2v<D>(cx, cy, cz, readlane_f(px, u), readlane_f(py, u), readlane_f(pz, u)) <= eps2;
+      }
       if (ballot(reach)) {
-        if (reach && !known_same_set(labels, jl, r)) uf_union(labels, r, jl, a.info);
+        // one union for all candidates of a set
+        bool joins = false;
+        for (uint64_t rm = ballot(reach); rm;) {
+          const int L = __ffsll(static_cast<unsigned long long>(rm)) - 1;
+          const int c = __builtin_amdgcn_readlane(cl, L);
+          if (lane == L) joins = true;
+          rm &= ~ballot(reach && cl == c);
+        }
+        if (joins) uf_union(labels, r, jl, a.info);
         int nr = 0;
-        if (lane == fl) nr = uf_find(labels, r, a.info);
-        r = __shfl(nr, fl);
+        if (lane == 0) nr = uf_find(labels, r, a.info);
+        r = __builtin_amdgcn_readfirstlane(nr);
       }
       return false;
-    }
-    for (uint64_t km = ballot(need); km; km &= km - 1) {
-      const int k = __ffsll(static_cast<unsigned long long>(km)) - 1;
-      const int j = __builtin_amdgcn_readlane(jl, k);
-      const int lj = __builtin_amdgcn_readlane(cl, k);
-      const float px = readlane_f(cx, k), py = readlane_f(cy, k), pz = readlane_f(cz, k);
-#pragma unroll
-      for (int s = 0; s < Q; ++s)
-        if (mine[s] && lj != root[s] && dist2v<D>(px, py, pz, q[s].x, q[s].y, q[s].z) <= eps2 &&
-            !known_same_set(labels, j, root[s]))
-          root[s] = uf_union(labels, root[s], j, a.info);
-    }
-    return false;
-  }, labels, common ? r : -1);
+    }, labels, r);
+  }
 }
 
 // Border pass from the core pass's neighbour records (no walk): the smallest
@@ -936,10 +948,14 @@ __global__ void k_border_fdb(TravArgs a) {
   const Scope sc = scope_of<B>(a, m, static_cast<int>(i));
   const Query q = load_point<D>(a.xs, a.n, i);
   int best = 0x7fffffff;
-  traverse<D, false>(a.t, m, sc, q, 0, a.info, [&](int j) {
-    if (!a.core[j] || !near<D>(a.xs, a.n, j, q, sc.eps2)) return false;
-    int c = a.cid[a.labels[j]];
-    best = c < best ? c : best;
+  traverse<D, false>(a.t, m, sc, q, 0, a.info, [&](int s, int e) {
+    for (int j = s; j <= e && best > 0; j += 4)
+      for (unsigned nb = near_bits<D>(a.xs, a.n, j, e, q, sc.eps2); nb; nb &= nb - 1) {
+        const int k = j + __ffs(nb) - 1;
+        if (!a.core[k]) continue;
+        const int c = a.cid[a.labels[k]];
+        best = c < best ? c : best;
+      }
     return best == 0;
   });
   a.border[i] = best == 0x7fffffff ? -1 : best;
@@ -966,19 +982,6 @@ template <int D>
 __device__ __forceinline__ bool cell_box_near(const TravArgs& a, int r, float4 lo, const Query& q, float eps2) {
   const float4 hi = a.prim_hi[r];
   return box_dist2<D>(q.x, q.y, q.z, lo.x, lo.y, lo.z, hi.x, hi.y, hi.z) <= eps2;
-}
-
-// Is every point of the dense cell with tight box [lo, hi] within eps of q, as the
-// point-by-point test would decide? Per axis the corner farther from q (by the
-// rounded difference) bounds every point's rounded difference, since rounded
-// subtraction, squaring and addition are monotone; so the test at that corner,
-// made with the same operations in the same order, holds for all of them.
-template <int D>
-__device__ __forceinline__ bool cell_within(float4 lo, float4 hi, const Query& q, float eps2) {
-  const float cx = fabsf(lo.x - q.x) > fabsf(hi.x - q.x) ? lo.x : hi.x;
-  const float cy = fabsf(lo.y - q.y) > fabsf(hi.y - q.y) ? lo.y : hi.y;
-  const float cz = fabsf(lo.z - q.z) > fabsf(hi.z - q.z) ? lo.z : hi.z;
-  return dist2v<D>(cx, cy, cz, q.x, q.y, q.z) <= eps2;
 }
 
 // The query of point primitive p (its record), or an idle lane's (mine false).
@@ -1100,20 +1103,6 @@ __device__ __forceinline__ void walk_init(Walk& w, int m, const Scope& sc, int m
 }
 
 __device__ __forceinline__ bool walk_done(const Walk& w) { return w.node == kEnd && w.cur > w.end; }
-
-// A box query (every point of [lo, hi]); walk_step takes it or a point.
-struct BoxQ {
-  float lo[3], hi[3];
-};
-
-template <int D>
-__device__ __forceinline__ float node_gap2(const Query& q, float4 a, float4 b) {
-  return box_dist2<D>(q.x, q.y, q.z, a.x, a.y, a.z, b.x, b.y, b.z);
-}
-template <int D>
-__device__ __forceinline__ float node_gap2(const BoxQ& q, float4 a, float4 b) {
-  return boxbox_dist2<D>(q.lo, q.hi, a.x, a.y, a.z, b.x, b.y, b.z);
-}
 
 template <int D, bool MASKED, typename QT>
 __device__ __forceinline__ int walk_step(Walk& w, const TreeView& t, int m, const QT& q, float eps2, int mask,
@@ -1252,36 +1241,6 @@ __device__ __forceinline__ void hits_join(Hits& h, int* labels, int& root, uint3
   }
   h.n = 0;
 }
-
-// The queries of a DenseBox kernel, whose number `total` only the device knows: a
-// workgroup takes chunks of kLanes queries a wavefront, blockIdx.x, + gridDim.x, ...
-// (gridDim.x a multiple of kNumXcd), laid out over the XCDs as xcd_spread has them.
-// The grid is capped (query_grid_blocks): with a workgroup for each of the n points
-// the queries could be, 65,536 workgroups without work took 15 us a launch (8M set).
-// Few queries take fewer lanes a wavefront, down to 8, so that kWaves wavefronts or
-// more share them: a wavefront's time is its lanes' loads, scans and unions one after the
-// other, and 44k queries (370k-point mixture) fill only 700 wavefronts of 64.
-constexpr int kWaves = 4096;
-
-struct Chunks {
-  int64_t chunk, off;  // queries per XCD; this workgroup's first within its XCD's
-  int lanes, step, slot, xcd;
-
-  __device__ __forceinline__ Chunks(int64_t total, bool spread) {
-    lanes = 64;
-    while (spread && lanes > 8 && total < int64_t(kWaves) * (lanes / 2)) lanes >>= 1;
-    const int per = lanes * static_cast<int>(blockDim.x >> 6);  // queries a workgroup and chunk
-    chunk = xcd_share(total, per);
-    xcd = static_cast<int>(blockIdx.x % kNumXcd);
-    off = int64_t(blockIdx.x / kNumXcd) * per;
-    step = static_cast<int>(gridDim.x / kNumXcd) * per;
-    slot = lane_id() < lanes ? static_cast<int>(threadIdx.x >> 6) * lanes + lane_id() : -1;
-  }
-  __device__ __forceinline__ bool in() const { return off < chunk; }
-  __device__ __forceinline__ void next() { off += step; }
-  // this lane's query (at or above the total where the chunk runs past it), -1: none
-  __device__ __forceinline__ int query() const { return slot < 0 ? -1 : static_cast<int>(xcd * chunk + off + slot); }
-};
 
 // Cells and pairs this small are tested by the lane that reached them (all lanes at
 // once) instead of by the wavefront one lane after another.
@@ -2012,11 +1971,13 @@ __global__ void k_debug_walk(TreeView t, int m, int mask, int* out_leaves, int* 
   const Query q{0.0f, 0.0f, 0.0f};
   const Scope sc{m == 1 ? kLeaf : 0u, m - 1, INFINITY, 0};
   int cnt = 0;
-  traverse<3, true>(t, m, sc, q, mask, info, [&](int l) {
-    if (cnt < cap) out_leaves[cnt] = l;
-    ++cnt;
+  auto visit = [&](int s, int e) {
+    for (int l = s; l <= e; ++l, ++cnt)
+      if (cnt < cap) out_leaves[cnt] = l;
     return false;
-  });
+  };
+  if (mask < 0) traverse<3, false>(t, m, sc, q, 0, info, visit);
+  else traverse<3, true>(t, m, sc, q, mask, info, visit);
   *out_count = cnt;
 }
 
@@ -2082,9 +2043,7 @@ void main_t(const TravArgs& a, bool densebox, int part, hipStream_t s) {
   } else if (FIRST) {
     hipLaunchKernelGGL((k_main_fdb_first<D, B>), g, b, 0, s, a);
   } else {
-    constexpr int kQ = 1;
-    const dim3 gq(static_cast<unsigned>(kNumXcd * ceil_div(ceil_div(a.n, kNumXcd), 256 * kQ)));
-    hipLaunchKernelGGL((k_main_fdb_q<D, ALL, B, kQ>), gq, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_main_fdb<D, ALL, B>), g, b, 0, s, a);
   }
 }
 
@@ -2115,25 +2074,6 @@ void main_dispatch(const TravArgs& a, bool densebox, bool all_core, bool first_b
 
 }  // namespace
 
-void launch_fdb_local(const TravArgs& a, int dim, bool all_core, hipStream_t s) {
-  if (a.n <= 1) return;
-  const dim3 g(static_cast<unsigned>(ceil_div(a.n, 256))), b(256);
-  if (dim == 3) {
-    if (all_core) hipLaunchKernelGGL((k_fdb_local<3, true>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_fdb_local<3, false>), g, b, 0, s, a);
-  } else {
-    if (all_core) hipLaunchKernelGGL((k_fdb_local<2, true>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_fdb_local<2, false>), g, b, 0, s, a);
-  }
-}
-
-void launch_cut_summary(const TravArgs& a, bool all_core, int* sum, hipStream_t s) {
-  if (a.n <= 1 || !a.t.cut || !a.t.cut_n) return;
-  const int m = static_cast<int>(a.n);
-  if (all_core) hipLaunchKernelGGL(k_cut_summary<true>, dim3(kCutMax), dim3(256), 0, s, a.t, m, a.labels, a.core, sum);
-  else hipLaunchKernelGGL(k_cut_summary<false>, dim3(kCutMax), dim3(256), 0, s, a.t, m, a.labels, a.core, sum);
-}
-
 void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s) {
   if (a.n <= 0) return;
   const bool B = a.pkeys != nullptr;
@@ -2151,6 +2091,33 @@ void launch_main(const TravArgs& a, int dim, bool densebox, bool all_core, bool 
   if (a.n <= 0) return;
   if (dim == 3) main_dispatch<3>(a, densebox, all_core, first_border, part, s);
   else main_dispatch<2>(a, densebox, all_core, first_border, part, s);
+}
+
+void launch_cliques(const TravArgs& a, int dim, hipStream_t s) {
+  if (a.n <= 1) return;
+  const dim3 g(static_cast<unsigned>(ceil_div(a.n - 1, 256 * kCliqueItems))), b(256);
+  if (dim == 3) {
+    if (a.pkeys) hipLaunchKernelGGL((k_cliques<3, true>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_cliques<3, false>), g, b, 0, s, a);
+  } else {
+    if (a.pkeys) hipLaunchKernelGGL((k_cliques<2, true>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_cliques<2, false>), g, b, 0, s, a);
+  }
+}
+
+template <int D>
+static void main_cliques_t(const TravArgs& a, bool all_core, hipStream_t s) {
+  // a wavefront per clique of kCliqueWave points or more, up to what is resident at once
+  const dim3 g(static_cast<unsigned>(std::min<int64_t>(2048, kNumXcd * ceil_div(a.n, kNumXcd * 4 * kCliqueWave)))), b(256);
+  if (a.pkeys) hipLaunchKernelGGL((k_main_cliques<D, false, true>), g, b, 0, s, a);
+  else if (all_core) hipLaunchKernelGGL((k_main_cliques<D, true, false>), g, b, 0, s, a);
+  else hipLaunchKernelGGL((k_main_cliques<D, false, false>), g, b, 0, s, a);
+}
+
+void launch_main_cliques(const TravArgs& a, int dim, bool all_core, hipStream_t s) {
+  if (a.n < kCliqueMin) return;
+  if (dim == 3) main_cliques_t<3>(a, all_core, s);
+  else main_cliques_t<2>(a, all_core, s);
 }
 
 void launch_debug_walk(const TreeView& t, int m, int mask, int* out_leaves, int* out_count, int cap,
