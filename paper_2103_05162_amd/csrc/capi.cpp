@@ -273,6 +273,14 @@ bool valid_options(const fdb_options& o) {
 
 constexpr int kDefaultLeaf = 8;     // measured against 2, 4, 6 and 16 (8M set and the 4096-cloud batch)
 constexpr int kDefaultBlock = 128;  // measured against 64, 256 and 512
+// FDbscan's curve: cells of kCurveEps eps / sqrt(dim), so a radix pass for every 8 bits
+// that the domain is eps wide instead of eight passes (8M-point set: 5 passes of 64-bit
+// keys, 420 us for 675; friends-of-friends set: 4 or 5). Within a cell the order is that of
+// the input, so finer cells make better boxes: core pass of the 8M set with 1, 0.5,
+// 0.25, 0.125: 1057, 897, 656, 615 us; the whole call 3656, 3582, 3358, 3289 (63-bit keys:
+// 3310), 2M friends-of-friends 2514, 2552, 2600, 2580 (2574), 16,384 points 498, 486, 504,
+// 502 (518).
+constexpr float kCurveEps = 0.125f;
 constexpr int kDefaultTile = 64;    // packet bucket: a candidate per lane (measured against 32)
 constexpr size_t kMaxGraphs = 16;
 
@@ -626,7 +634,7 @@ fdb_status fdb_debug_lbvh(fdb_handle* h, const uint64_t* h_keys, int32_t m, int3
   if (st == FDB_OK) {
     fill_u32(reinterpret_cast<uint32_t*>(xs), 0, 3 * M, s);
     fill_u32(h->d_info, 0, 1, s);
-    build_lbvh(keys, true, m, 3, xs, m, nullptr, nullptr, na, nb, rope, lrope, ends, other, gamma, nullptr,
+    build_lbvh(keys, nullptr, m, 3, xs, m, nullptr, nullptr, na, nb, rope, lrope, ends, other, gamma, nullptr,
                h->d_info, s);
     TreeView t{na, nb, rope, lrope, m, nullptr, leaf_size};
     launch_debug_walk(t, m, mask, leaves, count, m, h->d_info, s);
@@ -800,14 +808,16 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     init.add(misc, 0u, kMiscCount);
     init.add(at<uint32_t>(ws, plan.hist), 0u, 8 * 256);
     init.add(at<uint32_t>(ws, plan.tilectr), 0u, 16);
-    init.add(at<uint32_t>(ws, plan.status), 0u, densebox ? planned_status_words(n) : sort_status_words(n, true));
+    init.add(at<uint32_t>(ws, plan.status), 0u, planned_status_words(n));
     fill_multi(init, s);
   }
   launch_bounds(points, n, dim, bounds, h->d_info, s);
 
-  // DenseBox sizes its grid on the device (k_grid_plan): nothing waits for the GPU
+  // The grid is sized on the device (k_grid_plan): nothing waits for the GPU. FDbscan
+  // only orders its points by it, and has no index over its cells.
   GridPlan* gplan = at<GridPlan>(ws, plan.gplan);
-  if (densebox) launch_grid_plan(bounds, dim, eps, plan.super_cap, gplan, h->d_info, s);
+  launch_grid_plan(bounds, dim, densebox ? eps : eps * kCurveEps, densebox ? plan.super_cap : 0, gplan,
+                   densebox ? h->d_info : nullptr, s);
 
   int cur = 0;
   const uint32_t* perm = nullptr;
@@ -855,7 +865,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   h->last_densebox = densebox;
   if (densebox) {
     st.mark("lbvh");
-    build_lbvh(at<void>(ws, plan.prim_key), true, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
+    build_lbvh(at<void>(ws, plan.prim_key), nullptr, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s,
@@ -872,18 +882,18 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     ta.d_ndense = misc + kMiscNumDense;
   } else {
     st.mark("morton");
-    const int mbits = dim == 3 ? 63 : 62;
-    launch_morton(points, n, dim, bounds, static_cast<uint64_t*>(keys[0]), vals[0], mbits,
-                  at<uint32_t>(ws, plan.hist), s);
+    launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist),
+                    nullptr, s);
     st.mark("sort");
-    cur = radix_sort(keys[0], keys[1], vals[0], vals[1], n, true, mbits, at<uint32_t>(ws, plan.hist), true,
-                     at<uint32_t>(ws, plan.pass_plan), at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s, false);
+    radix_sort_planned(keys[0], keys[1], vals[0], vals[1], n, gplan, at<uint32_t>(ws, plan.hist),
+                       at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);
+    cur = 1;
     perm = vals[cur];
     st.mark("permute");
     launch_permute(points, n, dim, perm, xs, h->d_info, s);
     launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist), core);
     st.mark("lbvh");
-    build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
+    build_lbvh(keys[cur], &gplan->key64, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
                at<int>(ws, plan.ends), at<int>(ws, plan.other), at<int>(ws, plan.gamma),
                nullptr, h->d_info, s, nullptr, nullptr, true);
@@ -1117,7 +1127,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
                    core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, ix, shift, cl_minpts,
                    cl_eps2, num_clouds, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
     st.mark("lbvh");
-    build_lbvh(at<void>(ws, plan.prim_key), true, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
+    build_lbvh(at<void>(ws, plan.prim_key), nullptr, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s, nullptr,
@@ -1135,7 +1145,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   } else {
     launch_init_labels(lab, n, s, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist), core);
     st.mark("lbvh");
-    build_lbvh(keys[cur], true, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
+    build_lbvh(keys[cur], nullptr, static_cast<int>(n), dim, xs, n, nullptr, nullptr, at<float4>(ws, plan.node_a),
                at<float4>(ws, plan.node_b), at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope),
                at<int>(ws, plan.ends), at<int>(ws, plan.other), at<int>(ws, plan.gamma),
                nullptr, h->d_info, s, nullptr, nullptr, true);

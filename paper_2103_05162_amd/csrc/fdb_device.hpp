@@ -280,4 +280,16 @@ __device__ __forceinline__ void hist_flush(const uint32_t* s_h, int passes, uint
   }
 }
 
+// Sorted keys as 32- or 64-bit words: the width is fixed by the caller (key64) or,
+// for a grid sized on the device, read from the plan's flag (d_key64).
+struct KeyIn {
+  const void* p;
+  const int* d_key64;
+  int key64;
+  __device__ __forceinline__ bool wide() const { return d_key64 ? *d_key64 != 0 : key64 != 0; }
+};
+__device__ __forceinline__ uint64_t key_at(const KeyIn& k, bool wide, int64_t i) {
+  return wide ? static_cast<const uint64_t*>(k.p)[i] : static_cast<const uint32_t*>(k.p)[i];
+}
+
 }  // namespace fdb

@@ -155,10 +155,6 @@ void fill_multi(const FillList& L, hipStream_t s);
 
 // k_prep.hip
 void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint32_t* info, hipStream_t s);
-// The key kernels also count the digits of the `sort_bits`-bit keys for the
-// radix sort into hist (ceil(sort_bits / 8) x 256 words, cleared by the caller).
-void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds, uint64_t* keys, uint32_t* vals,
-                   int sort_bits, uint32_t* hist, hipStream_t s);
 // DenseBox of one cloud: k_grid_plan writes *plan from the bounds (after
 // launch_bounds; eps is the caller's), then the cell keys go to key buffer
 // plan->start as 32- or 64-bit words with the identity permutation, and their
@@ -196,8 +192,9 @@ int64_t planned_status_words(int64_t n);
 // the sorted points); see TravArgs. ends: m words of scratch; other / gamma:
 // each internal node's other range end and split (m - 1 words each). cut / cut_n:
 // the cut of TreeView (kCutMax pairs, and a counter the caller zeroed), or null.
+// keys: 64-bit words, or where d_key64 is given and *d_key64 on the device is 0, 32-bit.
 // d_skip (device, optional): nonzero = no hierarchy is needed, the kernels leave.
-void build_lbvh(const void* keys, bool key64, int m, int dim, const float* xs, int64_t n_pts,
+void build_lbvh(const void* keys, const int* d_key64, int m, int dim, const float* xs, int64_t n_pts,
                 const float4* prim_lo, const float4* prim_hi, float4* node_a, float4* node_b, int* rope,
                 int* leaf_rope, int* ends, int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s,
                 float4* cut = nullptr, int* cut_n = nullptr, bool ends_ready = false, int cut_div = kCutDiv,

@@ -22,18 +22,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Sorted keys as 32- or 64-bit words: the width is fixed by the caller (key64) or,
-// for a DenseBox grid sized on the device, read from the plan's flag (d_key64).
-struct KeyIn {
-  const void* p;
-  const int* d_key64;
-  int key64;
-  __device__ __forceinline__ bool wide() const { return d_key64 ? *d_key64 != 0 : key64 != 0; }
-};
-__device__ __forceinline__ uint64_t key_at(const KeyIn& k, bool wide, int64_t i) {
-  return wide ? static_cast<const uint64_t*>(k.p)[i] : static_cast<const uint32_t*>(k.p)[i];
-}
-
 // Per-cloud parameters of a batch (null cl_minpts: one cloud with the scalars).
 struct CloudParams {
   const uint64_t* keys;  // sorted point keys; cloud = key >> shift

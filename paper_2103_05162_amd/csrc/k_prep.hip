@@ -173,40 +173,6 @@ __device__ __forceinline__ uint32_t quantize(float v, float lo, float scale, uin
   return t >= fmax ? maxq : static_cast<uint32_t>(t);
 }
 
-// 63-bit (3D, 21 bits per axis) or 62-bit (2D, 31 bits per axis) Morton codes
-// of the points normalised to the scene bounds, and the identity permutation.
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_morton(const float* __restrict__ pts, int64_t n,
-                                                   const uint32_t* __restrict__ bounds, uint64_t* __restrict__ keys,
-                                                   uint32_t* __restrict__ vals, int passes,
-                                                   uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s_h[8 * 256];
-  hist_clear(s_h, passes);
-  constexpr uint32_t maxq = D == 3 ? 0x1fffffu : 0x7fffffffu;
-  float lo[D], scale[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    lo[k] = ord2f(bounds[k]);
-    float ext = ord2f(bounds[4 + k]) - lo[k];
-    scale[k] = ext > 0.0f ? static_cast<float>(maxq) / ext : 0.0f;
-  }
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x) {
-    uint64_t code;
-    if constexpr (D == 3) {
-      code = (spread3(quantize(pts[i * 3 + 0], lo[0], scale[0], maxq)) << 2) |
-             (spread3(quantize(pts[i * 3 + 1], lo[1], scale[1], maxq)) << 1) |
-             spread3(quantize(pts[i * 3 + 2], lo[2], scale[2], maxq));
-    } else {
-      code = (spread2(quantize(pts[i * 2 + 0], lo[0], scale[0], maxq)) << 1) |
-             spread2(quantize(pts[i * 2 + 1], lo[1], scale[1], maxq));
-    }
-    keys[i] = code;
-    vals[i] = static_cast<uint32_t>(i);
-    hist_add(code, true, passes, s_h);
-  }
-  hist_flush(s_h, passes, hist);
-}
-
 // The DenseBox grid of one cloud (Section 4.2: cells of side h = eps/sqrt(d)),
 // sized here from the bounds so that nothing returns to the host mid-call. The
 // side is shrunk by 2^-20 so that rounding in the cell index rarely pushes a
@@ -271,7 +237,7 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
   g.grid_on = reach < kMaxReach && supers <= static_cast<double>(super_cap) ? 1 : 0;
   g.supers = g.grid_on ? static_cast<uint64_t>(supers) : 0;
   *plan = g;
-  if (coarse) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
+  if (coarse && info) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
 }
 
 constexpr int kGridKeyItems = 4;
@@ -418,16 +384,6 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
     hipLaunchKernelGGL(k_bounds<3>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, info);
   else
     hipLaunchKernelGGL(k_bounds<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, info);
-}
-
-void launch_morton(const float* pts, int64_t n, int dim, const uint32_t* bounds, uint64_t* keys, uint32_t* vals,
-                   int sort_bits, uint32_t* hist, hipStream_t s) {
-  const int passes = (sort_bits + 7) / 8;
-  int g = grid_for(n, kBlock * 16, 1024);  // a workgroup histogram per 4096+ keys, flushes kept few
-  if (dim == 3)
-    hipLaunchKernelGGL(k_morton<3>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, keys, vals, passes, hist);
-  else
-    hipLaunchKernelGGL(k_morton<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, keys, vals, passes, hist);
 }
 
 void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,

@@ -17,15 +17,11 @@ constexpr int kBlock = 256;
 
 // Common-prefix length of keys i and j; -1 outside [0, m). Equal keys are told
 // apart by their positions, so every prefix is strictly ordered.
-template <typename K>
-__device__ __forceinline__ int prefix_len(const K* __restrict__ keys, int m, int i, int64_t j) {
+__device__ __forceinline__ int prefix_len(const KeyIn& keys, bool wide, int m, int i, int64_t j) {
   if (j < 0 || j >= m) return -1;
-  K a = keys[i], b = keys[j];
-  if (a == b) return int(8 * sizeof(K)) + __clz(static_cast<uint32_t>(i) ^ static_cast<uint32_t>(j));
-  if constexpr (sizeof(K) == 8)
-    return __clzll(static_cast<unsigned long long>(a ^ b));
-  else
-    return __clz(static_cast<uint32_t>(a ^ b));
+  const uint64_t a = key_at(keys, wide, i), b = key_at(keys, wide, j);
+  if (a == b) return 64 + __clz(static_cast<uint32_t>(i) ^ static_cast<uint32_t>(j));
+  return __clzll(static_cast<unsigned long long>(a ^ b));
 }
 
 // Pre-order successor of a subtree whose last leaf is l: the right child of the
@@ -165,9 +161,8 @@ constexpr int kRefitBlock = 256;  // leaves per workgroup of the build
 
 // Common-prefix length of edge k (keys k and k+1); -1 for the edges before the
 // first and after the last key, which are less similar than every inner edge.
-template <typename K>
-__device__ __forceinline__ int edge_len(const K* __restrict__ keys, int m, int64_t k) {
-  return k < 0 || k >= m - 1 ? -1 : prefix_len(keys, m, static_cast<int>(k), k + 1);
+__device__ __forceinline__ int edge_len(const KeyIn& keys, bool wide, int m, int64_t k) {
+  return k < 0 || k >= m - 1 ? -1 : prefix_len(keys, wide, m, static_cast<int>(k), k + 1);
 }
 
 __device__ __forceinline__ void cut_add(float4* cut, int* cut_n, uint32_t ref, int last, const Box& b) {
@@ -177,8 +172,8 @@ __device__ __forceinline__ void cut_add(float4* cut, int* cut_n, uint32_t ref, i
   cut[2 * k + 1] = make_float4(b.hi[0], b.hi[1], b.hi[2], __int_as_float(last));
 }
 
-template <typename K, int D, bool BUF>
-__global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ keys, int m_cap,
+template <int D, bool BUF>
+__global__ __launch_bounds__(kRefitBlock) void k_build_up(KeyIn keys, int m_cap,
                                                      const int* __restrict__ d_m, const float* __restrict__ xs,
                                                      int64_t n, LeafSrc ls, int* __restrict__ other,
                                                      int* __restrict__ gamma, int* __restrict__ ends, float4* node_a,
@@ -193,11 +188,12 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ 
   const int m = d_m ? *d_m : m_cap;
   const int L0 = blockIdx.x * kRefitBlock;
   if (m < 2 || L0 >= m) return;  // whole workgroup
+  const bool wide = keys.wide();
   const int L1 = min(L0 + kRefitBlock, m) - 1;  // this workgroup's leaves are [L0, L1]
   const int t = threadIdx.x;
   const int ne = L1 - L0 + 2;  // edges L0-1 .. L1, entry e is edge L0-1+e
   s_far[t] = -1;
-  for (int e = t; e < ne; e += kRefitBlock) s_len[e] = s_pmin[e] = s_smin[e] = edge_len(keys, m, int64_t(L0) - 1 + e);
+  for (int e = t; e < ne; e += kRefitBlock) s_len[e] = s_pmin[e] = s_smin[e] = edge_len(keys, wide, m, int64_t(L0) - 1 + e);
   __syncthreads();
   for (int off = 1; off < ne; off <<= 1) {  // prefix and suffix minima of the edge lengths
     int a[2], b[2];
@@ -223,7 +219,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ 
   const __amdgpu_buffer_rsrc_t rb =
       __builtin_amdgcn_make_buffer_rsrc(node_a, 0, BUF ? m_cap * (16 * kNodeStride) : 0, kBufferWord3);
   auto len = [&](int64_t k) -> int {
-    return k >= L0 - 1 && k <= L1 ? s_len[k - (L0 - 1)] : edge_len(keys, m, k);
+    return k >= L0 - 1 && k <= L1 ? s_len[k - (L0 - 1)] : edge_len(keys, wide, m, k);
   };
   Box box = leaf_box<D>(l, xs, n, ls);
   int i = l, j = l;
@@ -322,8 +318,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(const K* __restrict__ 
 
 // m_cap: number of primitives, or an upper bound when d_m (device) holds it.
 // ends: m_cap words, the far-end exchange of meetings across workgroups.
-template <typename K>
-void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs, int64_t n_pts,
+void build_t(const KeyIn& keys, int m_cap, const int* d_m, int dim, const float* xs, int64_t n_pts,
              const LeafSrc& ls, float4* node_a, float4* node_b, int* rope, int* leaf_rope, int* ends, int* other,
              int* gamma, uint32_t* info, hipStream_t s, float4* cut, int* cut_n, bool ends_ready, int cut_div,
              const int* d_skip) {
@@ -334,16 +329,16 @@ void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs,
     const bool buf = m_cap <= kRefitBufMaxNodes;
     const dim3 rg(static_cast<unsigned>(ceil_div(m_cap, kRefitBlock))), rb(kRefitBlock);
     if (dim == 3 && buf)
-      hipLaunchKernelGGL((k_build_up<K, 3, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
+      hipLaunchKernelGGL((k_build_up<3, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
                          node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else if (dim == 3)
-      hipLaunchKernelGGL((k_build_up<K, 3, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
+      hipLaunchKernelGGL((k_build_up<3, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
                          node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else if (buf)
-      hipLaunchKernelGGL((k_build_up<K, 2, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
+      hipLaunchKernelGGL((k_build_up<2, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
                          node_a, node_b, info, cut, cut_n, cut_div, d_skip);
     else
-      hipLaunchKernelGGL((k_build_up<K, 2, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
+      hipLaunchKernelGGL((k_build_up<2, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
                          node_a, node_b, info, cut, cut_n, cut_div, d_skip);
   }
   hipLaunchKernelGGL(k_ropes, dim3(g), dim3(kBlock), 0, s, other, m_cap, d_m, rope, leaf_rope, d_skip);
@@ -351,17 +346,12 @@ void build_t(const K* keys, int m_cap, const int* d_m, int dim, const float* xs,
 
 }  // namespace
 
-void build_lbvh(const void* keys, bool key64, int m, int dim, const float* xs, int64_t n_pts, const float4* prim_lo,
-                const float4* prim_hi, float4* node_a, float4* node_b, int* rope, int* leaf_rope, int* ends,
-                int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s, float4* cut, int* cut_n,
-                bool ends_ready, int cut_div, const int* d_skip) {
-  const LeafSrc ls{prim_lo, prim_hi};
-  if (key64)
-    build_t(static_cast<const uint64_t*>(keys), m, d_m, dim, xs, n_pts, ls, node_a, node_b, rope, leaf_rope, ends,
-            other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
-  else
-    build_t(static_cast<const uint32_t*>(keys), m, d_m, dim, xs, n_pts, ls, node_a, node_b, rope, leaf_rope, ends,
-            other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
+void build_lbvh(const void* keys, const int* d_key64, int m, int dim, const float* xs, int64_t n_pts,
+                const float4* prim_lo, const float4* prim_hi, float4* node_a, float4* node_b, int* rope,
+                int* leaf_rope, int* ends, int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s,
+                float4* cut, int* cut_n, bool ends_ready, int cut_div, const int* d_skip) {
+  build_t(KeyIn{keys, d_key64, 1}, m, d_m, dim, xs, n_pts, LeafSrc{prim_lo, prim_hi}, node_a, node_b, rope, leaf_rope,
+          ends, other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
 }
 
 }  // namespace fdb
