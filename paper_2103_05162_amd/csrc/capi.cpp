@@ -934,7 +934,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   if (all_core) launch_core_from_sets(lab, core, n, min_pts, s);
   st.mark("cluster_ids");
   canonical_ids(lab, core, perm, n, at<int>(ws, plan.minorig), at<uint32_t>(ws, plan.lflag), at<int>(ws, plan.rank),
-                at<int>(ws, plan.bsums), plan.scan_blocks, at<int>(ws, plan.cid), misc + kMiscNumClusters, s, true,
+                at<int>(ws, plan.bsums), at<int>(ws, plan.cid), misc + kMiscNumClusters, s, true,
                 !all_core);
   const bool have_border = !all_core && o.border == FDB_BORDER_CANONICAL;  // DBSCAN*: non-core stays noise
   if (have_border) {
@@ -1182,7 +1182,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   int* rank = at<int>(ws, plan.rank);
   uint32_t* lbits = at<uint32_t>(ws, plan.lflag);
   canonical_ids(lab, core, perm, n, at<int>(ws, plan.minorig), lbits, rank, at<int>(ws, plan.bsums),
-                plan.scan_blocks, at<int>(ws, plan.cid), misc + kMiscNumClusters, s, false, true);
+                at<int>(ws, plan.cid), misc + kMiscNumClusters, s, false, true);
   batch_cluster_ids(lab, core, at<int>(ws, plan.minorig), lbits, rank, pkeys, shift, offsets, num_clouds, n,
                     misc + kMiscNumClusters, cl_flags, at<int>(ws, plan.cid), num_clusters, s);
   if (o.border == FDB_BORDER_CANONICAL) {

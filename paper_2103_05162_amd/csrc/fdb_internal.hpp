@@ -304,7 +304,7 @@ void launch_check_forest(const int* labels, const uint8_t* core, int64_t n, uint
 // ints of scratch (fits the n-int lflag array); wpre: ceil(n/32) ints.
 // minorig_ready: launch_finalize already filled minorig and cleared the leader words.
 void canonical_ids(const int* labels, const uint8_t* core, const uint32_t* perm, int64_t n, int* minorig,
-                   uint32_t* bits, int* wpre, int* bsums, int64_t scan_blocks, int* cid, int* d_k, hipStream_t s,
+                   uint32_t* bits, int* wpre, int* bsums, int* cid, int* d_k, hipStream_t s,
                    bool ids = true, bool minorig_ready = false);
 
 // k_batch.hip
@@ -328,13 +328,8 @@ void launch_scatter(const int* labels, const uint8_t* core, const uint32_t* perm
 // ordered on a stream; the server reads its batches' bits this way).
 const uint32_t* handle_info(const fdb_handle* h);
 
-// Exclusive scan of blocks int32 counts in place (one workgroup); the total goes to *d_total.
-// With bsums2, a second array of as many counts is scanned by a second workgroup of
-// the same launch (its total to *d_total2).
-void scan_block_sums(int* bsums, int64_t blocks, int* d_total, hipStream_t s, int* bsums2 = nullptr,
-                     int* d_total2 = nullptr);
-void device_scan(const int* in, int* out, int64_t n, const int* d_n, int* bsums, int64_t blocks, int* d_total,
-                 hipStream_t s);
+// Exclusive scan of two arrays of int32 counts in place.
+void scan_block_sums(int* a, int* b, int64_t blocks, hipStream_t s);
 
 // k_serve.hip: one job of a served batch - its own buffers and its place in the
 // batch (first point off; first workgroup gblk of the gather and sblk of the

@@ -106,11 +106,32 @@ __device__ __forceinline__ void tile_exclusive_scan(int* s_v, int* s_w) {
   __syncthreads();
 }
 
+// Counts of the tiles before this one, in both arrays: read where they have been scanned,
+// else added up here by the whole workgroup. Up to kCarryTiles tiles the adding (two
+// loads a thread at most) takes less than the launch of a scan does (4 to 5 us); a single
+// tile has no counts before it and needs no counting launch either.
+constexpr int64_t kCarryTiles = 512;
+struct Carry {
+  int a, b;
+};
+__device__ __forceinline__ Carry tile_carry(const int* __restrict__ a, const int* __restrict__ b, bool scanned,
+                                            int* s_w) {
+  const int tile = static_cast<int>(blockIdx.x);
+  if (scanned) return Carry{a[tile], b[tile]};
+  if (tile == 0) return Carry{0, 0};
+  int x = 0, y = 0;
+  for (int j = threadIdx.x; j < tile; j += kBlock) {
+    x += a[j];
+    y += b[j];
+  }
+  x = tile_reduce(x, s_w);
+  y = tile_reduce(y, s_w);
+  return Carry{x, y};
+}
+
 __global__ __launch_bounds__(kBlock) void k_heads_reduce(KeyIn keys, int64_t n, int* __restrict__ bsums,
-                                                         int* __restrict__ bsums_b, int* __restrict__ border_n) {
+                                                         int* __restrict__ bsums_b) {
   __shared__ int s_w[kBlock / 64];
-  if (border_n && blockIdx.x == 0)  // (the digit histograms' place: the sort is done with them)
-    for (int k = threadIdx.x; k < kBorderCounters; k += kBlock) border_n[k] = 0;
   const bool wide = keys.wide();
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   int x = 0;
@@ -127,14 +148,19 @@ __global__ __launch_bounds__(kBlock) void k_heads_reduce(KeyIn keys, int64_t n, 
 }
 
 // cell_id[i] for every point; cell_start[c] for every cell and cell_start[#cells] = n;
-// the code of every cell in its brick, and every brick's first cell.
+// the code of every cell in its brick, and every brick's first cell; the numbers of cells
+// and bricks.
 __global__ __launch_bounds__(kBlock) void k_heads_apply(KeyIn keys, int64_t n, const int* __restrict__ bsums,
-                                                        const int* __restrict__ bsums_b, int* __restrict__ cell_id,
-                                                        int* __restrict__ cell_start, uint8_t* __restrict__ cell_code,
-                                                        int* __restrict__ brick_base) {
+                                                        const int* __restrict__ bsums_b, bool scanned,
+                                                        int* __restrict__ cell_id, int* __restrict__ cell_start,
+                                                        uint8_t* __restrict__ cell_code, int* __restrict__ brick_base,
+                                                        int* __restrict__ d_cells, int* __restrict__ d_bricks,
+                                                        int* __restrict__ border_n) {
   static_assert(kScanItems == 16, "the LDS layout assumes 16 items per thread");
   __shared__ int s_v[kScanTile + kScanTile / 16];
   __shared__ int s_w[kBlock / 64];
+  if (border_n && blockIdx.x == 0)  // (the digit histograms' place: the sort is done with them)
+    for (int k = threadIdx.x; k < kBorderCounters; k += kBlock) border_n[k] = 0;
   const bool wide = keys.wide();
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   const int tid = threadIdx.x;
@@ -152,7 +178,7 @@ __global__ __launch_bounds__(kBlock) void k_heads_apply(KeyIn keys, int64_t n, c
   }
   __syncthreads();
   tile_exclusive_scan(s_v, s_w);
-  const int carry = bsums[blockIdx.x], carry_b = bsums_b[blockIdx.x];
+  const Carry carry = tile_carry(bsums, bsums_b, scanned, s_w);
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
@@ -160,14 +186,19 @@ __global__ __launch_bounds__(kBlock) void k_heads_apply(KeyIn keys, int64_t n, c
     if (i < n) {
       const bool h = (hmask >> k) & 1u;
       const int ex = s_v[tile_lds(p)];
-      const int c = carry + (ex & 0xffff) + (h ? 1 : 0) - 1;
+      const int c = carry.a + (ex & 0xffff) + (h ? 1 : 0) - 1;
       cell_id[i] = c;
       if (h) {
         cell_start[c] = static_cast<int>(i);
         cell_code[c] = static_cast<uint8_t>(code[k]);
       }
-      if ((bmask >> k) & 1u) brick_base[carry_b + (ex >> 16)] = c;
-      if (i == n - 1) cell_start[c + 1] = static_cast<int>(n);
+      const bool bh = (bmask >> k) & 1u;
+      if (bh) brick_base[carry.b + (ex >> 16)] = c;
+      if (i == n - 1) {
+        cell_start[c + 1] = static_cast<int>(n);
+        *d_cells = c + 1;
+        *d_bricks = carry.b + (ex >> 16) + (bh ? 1 : 0);
+      }
     }
   }
 }
@@ -284,7 +315,7 @@ __global__ __launch_bounds__(kBlock) void k_prims_reduce(const int* __restrict__
 // Primitive records in key order (DenseBox leaf records: a point's coordinates
 // and index, or a dense cell's low corner and -2 - its first point, beside its
 // high corner), the dense list (dense cells' primitive indices, in key order),
-// and the union-find start: a dense cell's points hang under its first point and
+// the numbers of primitives and dense cells, and the union-find start: a dense cell's points hang under its first point and
 // are core by construction; every other point starts alone.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float* __restrict__ xs, int64_t n,
@@ -294,7 +325,8 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
                                                         const float4* __restrict__ cell_lo,
                                                         const float4* __restrict__ cell_hi,
                                                         const int* __restrict__ bsums_p, const int* __restrict__ bsums_d,
-                                                        int* __restrict__ prim_start, int* __restrict__ prim_cnt,
+                                                        bool scanned, int* __restrict__ d_prims,
+                                                        int* __restrict__ d_dense, int* __restrict__ prim_start, int* __restrict__ prim_cnt,
                                                         float4* __restrict__ prim_lo, float4* __restrict__ prim_hi,
                                                         uint64_t* __restrict__ prim_key, int* __restrict__ dense_list,
                                                         int* __restrict__ labels, uint8_t* __restrict__ core,
@@ -328,7 +360,8 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
   for (int k = 0; k < kScanItems; ++k) fl[k] = s_v[tile_lds(k * kBlock + tid)];
   __syncthreads();
   tile_exclusive_scan(s_v, s_w);
-  const int carry_p = bsums_p[blockIdx.x], carry_d = bsums_d[blockIdx.x];
+  const Carry carry = tile_carry(bsums_p, bsums_d, scanned, s_w);
+  const int carry_p = carry.a, carry_d = carry.b;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
@@ -344,7 +377,11 @@ __global__ __launch_bounds__(kBlock) void k_prims_apply(KeyIn keys, const float*
     if (ends && (fl[k] & 1)) ends[pi] = -1;
     const bool d = (dmask >> k) & 1u;
     if ((cmask >> k) & 1u) cell_prim[cl[k]] = d ? ~pi : pi;
-    if (i64 == n - 1) cell_prim[cl[k] + 1] = pi + (fl[k] & 1);
+    if (i64 == n - 1) {
+      cell_prim[cl[k] + 1] = pi + (fl[k] & 1);
+      *d_prims = pi + (fl[k] & 1);
+      *d_dense = carry_d + (ex >> 16) + (fl[k] >> 16);
+    }
     if (d) {
       const int c = cl[k];
       const int st = cell_start[c];
@@ -528,14 +565,16 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
   const dim3 gt(static_cast<unsigned>(tiles));
   int* bsums2 = pflag;  // the second count of each tile: bricks, then dense cells
   int* d_bricks = misc + kMiscNumBricks;
-  hipLaunchKernelGGL(k_heads_reduce, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2, border_n);
-  scan_block_sums(bsums, tiles, d_cells, s, bsums2, d_bricks);
-  hipLaunchKernelGGL(k_heads_apply, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2, cell_id, cell_start, ix.cell_code,
-                     ix.brick_base);
+  const bool scanned = tiles > kCarryTiles;
+  if (tiles > 1) hipLaunchKernelGGL(k_heads_reduce, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2);
+  if (scanned) scan_block_sums(bsums, bsums2, tiles, s);
+  hipLaunchKernelGGL(k_heads_apply, gt, dim3(kBlock), 0, s, keys, n, bsums, bsums2, scanned, cell_id, cell_start,
+                     ix.cell_code, ix.brick_base, d_cells, d_bricks, border_n);
   // d_big (a misc slot) is zero: the caller cleared misc before this stage
   int* big = cand;
   const int gs = static_cast<int>(std::min<int64_t>(std::max<int64_t>(ceil_div(n, kBlock / 8), 1), 8192));
-  const int gb = 2048;  // 8192 wavefronts, grid-stride over the listed cells
+  // a wavefront per listed cell (more than kSmallCell points), up to 8192 of them
+  const int gb = static_cast<int>(std::min<int64_t>(ceil_div(n, (kSmallCell + 1) * (kBlock / 64)), 2048));
   if (dim == 3) {
     hipLaunchKernelGGL(k_cells_small<3>, dim3(gs), dim3(kBlock), 0, s, xs, n, cell_start, d_cells, min_pts, eps2, cp,
                        dense, cell_lo, cell_hi, big, d_big);
@@ -550,16 +589,16 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
   // a batch reads every point's primitive index afterwards (in cand, which the
   // large-cell list no longer needs by then)
   int* pidx = cp.minpts ? cand : nullptr;
-  hipLaunchKernelGGL(k_prims_reduce, gt, dim3(kBlock), 0, s, cell_id, cell_start, dense, n, bsums, bsums2);
-  scan_block_sums(bsums, tiles, d_prims, s, bsums2, d_dense);
+  if (tiles > 1) hipLaunchKernelGGL(k_prims_reduce, gt, dim3(kBlock), 0, s, cell_id, cell_start, dense, n, bsums, bsums2);
+  if (scanned) scan_block_sums(bsums, bsums2, tiles, s);
   if (dim == 3)
     hipLaunchKernelGGL(k_prims_apply<3>, gt, dim3(kBlock), 0, s, keys, xs, n, cell_id, cell_start, dense, cell_lo,
-                       cell_hi, bsums, bsums2, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
-                       core, pidx, ends, minorig, ix.cell_prim);
+                       cell_hi, bsums, bsums2, scanned, d_prims, d_dense, prim_start, prim_cnt, prim_lo, prim_hi, prim_key,
+                       dense_list, labels, core, pidx, ends, minorig, ix.cell_prim);
   else
     hipLaunchKernelGGL(k_prims_apply<2>, gt, dim3(kBlock), 0, s, keys, xs, n, cell_id, cell_start, dense, cell_lo,
-                       cell_hi, bsums, bsums2, prim_start, prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels,
-                       core, pidx, ends, minorig, ix.cell_prim);
+                       cell_hi, bsums, bsums2, scanned, d_prims, d_dense, prim_start, prim_cnt, prim_lo, prim_hi, prim_key,
+                       dense_list, labels, core, pidx, ends, minorig, ix.cell_prim);
   // the bricks' buffer is the cell boxes', dead once the primitives are written
   const unsigned gk = static_cast<unsigned>(std::min<int64_t>(ceil_div(n, kBlock), 4096));
   if (dim == 3)

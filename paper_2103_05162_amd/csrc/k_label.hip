@@ -230,12 +230,6 @@ __global__ __launch_bounds__(kBlock) void k_leader_bits(const int* __restrict__ 
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_word_popc(const uint32_t* __restrict__ bits, int64_t words,
-                                                      int* __restrict__ cnt) {
-  for (int64_t w = blockIdx.x * int64_t(kBlock) + threadIdx.x; w < words; w += int64_t(gridDim.x) * kBlock)
-    cnt[w] = __popc(bits[w]);
-}
-
 __global__ __launch_bounds__(kBlock) void k_cluster_ids(const int* __restrict__ labels,
                                                         const uint8_t* __restrict__ core,
                                                         const int* __restrict__ minorig,
@@ -304,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void k_split_core(int32_t* __restrict__ out
   }
 }
 
-// ---- device-wide exclusive scan of int32 (reduce, scan block sums, apply) ----
+// ---- device-wide exclusive scans (reduce, scan block sums, apply) ----
 
 __device__ __forceinline__ int wave_inclusive(int x) {
   const int lane = threadIdx.x & 63;
@@ -326,34 +320,29 @@ __device__ __forceinline__ int block_reduce(int x, int* s_w) {
   return t;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_reduce(const int* __restrict__ in, int64_t n_cap,
-                                                        const int* __restrict__ d_n, int* __restrict__ bsums) {
+__global__ __launch_bounds__(kBlock) void k_leader_reduce(const uint32_t* __restrict__ bits, int64_t n,
+                                                          int* __restrict__ bsums) {
   __shared__ int s_w[kBlock / 64];
-  const int64_t n = d_n ? *d_n : n_cap;
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   int x = 0;
   for (int k = 0; k < kScanItems; ++k) {
     int64_t i = base + k * kBlock + threadIdx.x;
-    if (i < n) x += in[i];
+    if (i < n) x += __popc(bits[i]);
   }
   int t = block_reduce(x, s_w);
   if (threadIdx.x == 0) bsums[blockIdx.x] = t;
 }
 
-// Exclusive scan of the block sums in place, by one workgroup of kBsumsBlock
-// threads: thread t sums its own run of consecutive entries, the run totals are
+// Exclusive scan of two arrays of block sums in place, a workgroup of kBsumsBlock
+// threads each: thread t sums its own run of consecutive entries, the run totals are
 // scanned across the workgroup, and each thread rescans its run (a few entries
 // per thread for the sizes here, so the kernel is two short passes).
 constexpr int kBsumsBlock = 1024;
 
-__global__ __launch_bounds__(kBsumsBlock) void k_scan_bsums(int* __restrict__ bsums, int64_t blocks,
-                                                            int* __restrict__ d_total, int* __restrict__ bsums2,
-                                                            int* __restrict__ d_total2) {
+__global__ __launch_bounds__(kBsumsBlock) void k_scan_bsums(int* __restrict__ a, int* __restrict__ b,
+                                                            int64_t blocks) {
   __shared__ int s_w[kBsumsBlock / 64];
-  if (blockIdx.x == 1) {  // a second array, scanned by the second workgroup
-    bsums = bsums2;
-    d_total = d_total2;
-  }
+  int* __restrict__ bsums = blockIdx.x ? b : a;
   const int64_t per = (blocks + kBsumsBlock - 1) / kBsumsBlock;
   const int64_t b0 = threadIdx.x * per, b1 = b0 + per < blocks ? b0 + per : blocks;
   int sum = 0;
@@ -370,7 +359,6 @@ __global__ __launch_bounds__(kBsumsBlock) void k_scan_bsums(int* __restrict__ bs
     bsums[i] = run;
     run += v;
   }
-  if (threadIdx.x == kBsumsBlock - 1 && d_total) *d_total = run;
 }
 
 // Tile position p lives at LDS word p + p/16: thread t's blocked items
@@ -378,21 +366,24 @@ __global__ __launch_bounds__(kBsumsBlock) void k_scan_bsums(int* __restrict__ bs
 // and global memory is read and written striped (coalesced).
 __device__ __forceinline__ int scan_lds(int p) { return p + (p >> 4); }
 
-__global__ __launch_bounds__(kBlock) void k_scan_apply(const int* __restrict__ in, int* __restrict__ out, int64_t n_cap,
-                                                       const int* __restrict__ d_n, const int* __restrict__ bsums) {
+// Leaders in the words before each word, and their number. A workgroup adds up the tile
+// counts before its own (131,072 points a tile).
+__global__ __launch_bounds__(kBlock) void k_leader_apply(const uint32_t* __restrict__ bits, int* __restrict__ out,
+                                                         int64_t n, const int* __restrict__ bsums,
+                                                         int* __restrict__ d_total) {
   static_assert(kScanItems == 16, "the LDS padding assumes 16 items per thread");
   __shared__ int s_v[kScanTile + kScanTile / 16];
   __shared__ int s_w[kBlock / 64];
-  __shared__ int s_carry;
-  const int64_t n = d_n ? *d_n : n_cap;
   const int64_t base = blockIdx.x * int64_t(kScanTile);
   const int tid = threadIdx.x;
+  int before = 0;
+  for (int j = tid; j < static_cast<int>(blockIdx.x); j += kBlock) before += bsums[j];
+  const int carry = block_reduce(before, s_w);
   for (int k = 0; k < kScanItems; ++k) {
     const int p = k * kBlock + tid;
     const int64_t i = base + p;
-    s_v[scan_lds(p)] = i < n ? in[i] : 0;
+    s_v[scan_lds(p)] = i < n ? __popc(bits[i]) : 0;
   }
-  if (tid == 0) s_carry = bsums[blockIdx.x];
   __syncthreads();
   int v[kScanItems];
   int sum = 0;
@@ -405,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const int* __restrict__ i
   const int w = tid >> 6;
   if ((tid & 63) == 63) s_w[w] = inc;
   __syncthreads();
-  int run = s_carry + inc - sum;
+  int run = carry + inc - sum;
   for (int j = 0; j < w; ++j) run += s_w[j];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
@@ -417,27 +408,14 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const int* __restrict__ i
     const int p = k * kBlock + tid;
     const int64_t i = base + p;
     if (i < n) out[i] = s_v[scan_lds(p)];
+    if (i == n - 1) *d_total = s_v[scan_lds(p)] + __popc(bits[i]);
   }
 }
 
 }  // namespace
 
-void device_scan(const int* in, int* out, int64_t n, const int* d_n, int* bsums, int64_t blocks, int* d_total,
-                 hipStream_t s) {
-  if (n <= 0) {
-    if (d_total) fill_u32(reinterpret_cast<uint32_t*>(d_total), 0, 1, s);
-    return;
-  }
-  const int64_t nb = ceil_div(n, kScanTile);
-  (void)blocks;
-  hipLaunchKernelGGL(k_scan_reduce, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, in, n, d_n, bsums);
-  hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(kBsumsBlock), 0, s, bsums, nb, d_total, nullptr, nullptr);
-  hipLaunchKernelGGL(k_scan_apply, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, in, out, n, d_n, bsums);
-}
-
-void scan_block_sums(int* bsums, int64_t blocks, int* d_total, hipStream_t s, int* bsums2, int* d_total2) {
-  hipLaunchKernelGGL(k_scan_bsums, dim3(bsums2 ? 2 : 1), dim3(kBsumsBlock), 0, s, bsums, blocks, d_total, bsums2,
-                     d_total2);
+void scan_block_sums(int* a, int* b, int64_t blocks, hipStream_t s) {
+  hipLaunchKernelGGL(k_scan_bsums, dim3(2), dim3(kBsumsBlock), 0, s, a, b, blocks);
 }
 
 void launch_init_labels(int* labels, int64_t n, hipStream_t s, int* ends, int* minorig, int* border_n,
@@ -472,19 +450,19 @@ void launch_core_from_sets(const int* labels, uint8_t* core, int64_t n, int min_
 }
 
 void canonical_ids(const int* labels, const uint8_t* core, const uint32_t* perm, int64_t n, int* minorig,
-                   uint32_t* bits, int* wpre, int* bsums, int64_t scan_blocks, int* cid, int* d_k, hipStream_t s,
+                   uint32_t* bits, int* wpre, int* bsums, int* cid, int* d_k, hipStream_t s,
                    bool ids, bool minorig_ready) {
   const int g = grid_for(n);
   const int64_t words = ceil_div(n, 32);
-  int* cnt = reinterpret_cast<int*>(bits + words);
   if (!minorig_ready) {
     fill_u32(bits, 0, words, s);
     fill_u32(reinterpret_cast<uint32_t*>(minorig), 0x7fffffffu, n, s);
     hipLaunchKernelGGL(k_minorig, dim3(g), dim3(kBlock), 0, s, labels, core, perm, n, minorig);
   }
   hipLaunchKernelGGL(k_leader_bits, dim3(g), dim3(kBlock), 0, s, labels, core, minorig, n, bits);
-  hipLaunchKernelGGL(k_word_popc, dim3(grid_for(words)), dim3(kBlock), 0, s, bits, words, cnt);
-  device_scan(cnt, wpre, words, nullptr, bsums, scan_blocks, d_k, s);
+  const dim3 tiles(static_cast<unsigned>(ceil_div(words, kScanTile)));
+  if (tiles.x > 1) hipLaunchKernelGGL(k_leader_reduce, tiles, dim3(kBlock), 0, s, bits, words, bsums);
+  hipLaunchKernelGGL(k_leader_apply, tiles, dim3(kBlock), 0, s, bits, wpre, words, bsums, d_k);
   if (ids)
     hipLaunchKernelGGL(k_cluster_ids, dim3(g), dim3(kBlock), 0, s, labels, core, minorig, bits, wpre, n, d_k, cid);
 }

@@ -2022,11 +2022,12 @@ void main_t(const TravArgs& a, bool densebox, int part, hipStream_t s) {
   const int gb = grid_block(a);
   if (densebox) {
     if (part != 2) {
-      // a batch's many cells usually go to the lane kernel, where this one exits at once
-      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, true>), dim3(B ? 2048 : 4096), dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, false>), dim3(B ? 2048 : 4096), dim3(256), 0, s, a);
       // dense cells hold >= minPts points each, so there are at most n / minPts
       const int64_t max_cells = a.min_pts > 1 ? a.n / a.min_pts + 1 : a.n;
+      // a batch's many cells usually go to the lane kernel, where this one exits at once
+      const dim3 gw(static_cast<unsigned>(std::min<int64_t>(kNumXcd * ceil_div(max_cells, kNumXcd * 4), B ? 2048 : 4096)));
+      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, true>), gw, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, false>), gw, dim3(256), 0, s, a);
       if (max_cells > kCellsPerWaveMax) {
         hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, true>), query_grid_blocks(max_cells, gb), dim3(gb),
                            walk_lds<D>(gb), s, a);
