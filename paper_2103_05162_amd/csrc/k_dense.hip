@@ -125,6 +125,7 @@ __device__ __forceinline__ Carry tile_carry(const int* __restrict__ a, const int
     y += b[j];
   }
   x = tile_reduce(x, s_w);
+  __syncthreads();  // every wavefront has read s_w
   y = tile_reduce(y, s_w);
   return Carry{x, y};
 }
