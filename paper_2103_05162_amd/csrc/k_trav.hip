@@ -1159,13 +1159,23 @@ __device__ __forceinline__ int walk_step(Walk& w, const TreeView& t, int m, cons
 }
 
 // ---- grid or hierarchy ------------------------------------------------------------
-// The DenseBox kernels are built twice: G walks the grid's cells (fdb_cells.hpp),
-// !G the hierarchy. Both are launched and the plan on the device says which one
-// runs; the other leaves at once. A walker yields one primitive per step, so that a
-// wavefront can pause its lanes between steps and scan a large dense cell together.
-template <bool G>
-__device__ __forceinline__ bool other_walk(const TravArgs& a) {
-  return (a.ix.plan->grid_on != 0) != G;
+// The DenseBox kernels walk the grid's cells (G, fdb_cells.hpp) or the hierarchy (!G), as
+// the plan on the device says. Each is built for either walk alone, and both are
+// launched, the other leaving at once: the hierarchy's walks then keep the occupancy
+// that the grid's LDS would take. Up to kEitherMax points a call's time is its launches
+// (3 to 4.5 us each), and one kernel holds both (1,000 points 192 -> 180 us, 370k 636 ->
+// 616 us; a 300k set through the hierarchy, one far outlier, 9.5 -> 9.6 ms). A walker yields one primitive per step, so
+// that a wavefront can pause its lanes between steps and scan a large dense cell together.
+enum Walks { kHierarchy, kGrid, kEither };
+constexpr int64_t kEitherMax = int64_t(1) << 19;
+
+template <int W, typename F>
+__device__ __forceinline__ void with_walk(const TravArgs& a, F&& f) {
+  const bool grid = a.ix.plan->grid_on != 0;
+  if constexpr (W != kHierarchy)
+    if (grid) f(std::true_type{});
+  if constexpr (W != kGrid)
+    if (!grid) f(std::false_type{});
 }
 
 // LDS of a wavefront's search through the grid: a packet's cell list or the columns
@@ -1348,15 +1358,17 @@ __device__ __forceinline__ void core_query(const TravArgs& a, int m, int p, int6
   core_epilogue(a, mine, i, p, cnt, sc.min_pts, rec, s_w, first);
 }
 
-template <int D, bool B, bool G>
-__global__ __launch_bounds__(G ? 256 : 1024) void k_core_dbx(TravArgs a) {
+template <int D, bool B, int W>
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_core_dbx(TravArgs a) {
   __shared__ int s_w[17];
   extern __shared__ __align__(16) char s_dyn[];  // the walk's columns, then neighbour records
-  if (other_walk<G>(a)) return;
-  const int m = tree_m(a.t);
-  Chunks c(m, G);
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(c.chunk);
-  for (; c.in(); c.next()) core_query<D, B, G>(a, m, c.query(), c.xcd * c.chunk, s_dyn, s_w);
+  with_walk<W>(a, [&](auto grid) {
+    constexpr bool G = decltype(grid)::value;
+    const int m = tree_m(a.t);
+    Chunks c(m, G);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(c.chunk);
+    for (; c.in(); c.next()) core_query<D, B, G>(a, m, c.query(), c.xcd * c.chunk, s_dyn, s_w);
+  });
 }
 
 // Do the dense cells hold kLargeCell points or more on average (m primitives, nd dense
@@ -1641,12 +1653,14 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
   if (G) hits_join(hits, labels, root, a.info);
 }
 
-template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
-__global__ __launch_bounds__(G ? 256 : 1024) void k_main_dbx_points(TravArgs a) {
+template <int D, bool ALL_CORE, bool FIRST, bool B, int W>
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_main_dbx_points(TravArgs a) {
   extern __shared__ __align__(16) char s_dyn[];
-  if (other_walk<G>(a)) return;
-  const int m = tree_m(a.t);
-  for (Chunks c(m, G); c.in(); c.next()) points_query<D, ALL_CORE, FIRST, B, G>(a, m, c.query(), s_dyn);
+  with_walk<W>(a, [&](auto grid) {
+    constexpr bool G = decltype(grid)::value;
+    const int m = tree_m(a.t);
+    for (Chunks c(m, G); c.in(); c.next()) points_query<D, ALL_CORE, FIRST, B, G>(a, m, c.query(), s_dyn);
+  });
 }
 
 // Main phase, dense cells, when they are few (see cells_lane_mode):
@@ -1721,12 +1735,7 @@ __device__ __forceinline__ void cells_near_box_lanes(const CellIndex& ix, const 
 }
 
 template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
-__global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
-  constexpr int kPerWave = G ? kCellList : kWideStack;
-  __shared__ uint32_t s_stack[4 * kPerWave];  // 256-thread workgroups
-  uint32_t* stack = s_stack + (threadIdx.x >> 6) * kPerWave;
-  const int nd = *a.d_ndense;
-  if (cells_lane_mode(a) || other_walk<G>(a)) return;
+__device__ __forceinline__ void cells_wave(const TravArgs& a, int nd, uint32_t* stack) {
   const int m = tree_m(a.t);
   const int lane = lane_id();
   const int wave = (xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6;
@@ -1803,6 +1812,17 @@ __global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
     else
       traverse_box_wide_lanes<D>(a.t, m, sc, alo, ahi, A, a.t.leaf_size, a.info, stack, visit);
   }
+}
+
+template <int D, bool ALL_CORE, bool FIRST, bool B, int W>
+__global__ __launch_bounds__(256) void k_main_dbx_cells_wave(TravArgs a) {
+  constexpr int kPerWave = W == kGrid ? kCellList : kWideStack;
+  static_assert(kPerWave >= kCellList, "a list of cells fits");
+  __shared__ uint32_t s_stack[4 * kPerWave];  // 256-thread workgroups
+  if (cells_lane_mode(a)) return;
+  with_walk<W>(a, [&](auto grid) {
+    cells_wave<D, ALL_CORE, FIRST, B, decltype(grid)::value>(a, *a.d_ndense, s_stack + (threadIdx.x >> 6) * kPerWave);
+  });
 }
 
 // Main phase, dense cells, when they are many (e.g. a batch of many clouds;
@@ -1891,13 +1911,16 @@ __device__ __forceinline__ void cells_query(const TravArgs& a, int m, int nd, in
   }
 }
 
-template <int D, bool ALL_CORE, bool FIRST, bool B, bool G>
-__global__ __launch_bounds__(G ? 256 : 1024) void k_main_dbx_cells_lane(TravArgs a) {
+template <int D, bool ALL_CORE, bool FIRST, bool B, int W>
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_main_dbx_cells_lane(TravArgs a) {
   extern __shared__ __align__(16) char s_dyn[];  // the walk's columns
   const int nd = *a.d_ndense;
-  if (!cells_lane_mode(a) || other_walk<G>(a)) return;
-  const int m = tree_m(a.t);
-  for (Chunks c(nd, G); c.in(); c.next()) cells_query<D, ALL_CORE, FIRST, B, G>(a, m, nd, c.query(), s_dyn);
+  if (!cells_lane_mode(a)) return;
+  with_walk<W>(a, [&](auto grid) {
+    constexpr bool G = decltype(grid)::value;
+    const int m = tree_m(a.t);
+    for (Chunks c(nd, G); c.in(); c.next()) cells_query<D, ALL_CORE, FIRST, B, G>(a, m, nd, c.query(), s_dyn);
+  });
 }
 
 // Canonical border pass for non-core points (all outside dense cells).
@@ -1948,19 +1971,20 @@ __device__ __forceinline__ void border_query(const TravArgs& a, int m, bool mine
   if (mine) a.border[i] = best == 0x7fffffff ? -1 : best;
 }
 
-template <int D, bool B, bool G>
-__global__ __launch_bounds__(G ? 256 : 1024) void k_border_dbx(TravArgs a) {
+template <int D, bool B, int W>
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_border_dbx(TravArgs a) {
   extern __shared__ __align__(16) char s_dyn[];  // the walk's columns
-  if (other_walk<G>(a)) return;
-  const int m = tree_m(a.t);
-  const int xcd = static_cast<int>(blockIdx.x % kNumXcd), nq = a.border_n[kWalkCount(xcd)];
-  const int* list = a.qborder + int64_t(xcd) * a.border_n[kWalkShare];
-  for (int64_t k0 = int64_t(blockIdx.x / kNumXcd) * blockDim.x; k0 < nq;
-       k0 += int64_t(gridDim.x / kNumXcd) * blockDim.x) {
-    const int64_t k = k0 + threadIdx.x;
-    const bool mine = k < nq;
-    if (ballot(mine)) border_query<D, B, G>(a, m, mine, mine ? list[k] : 0, s_dyn);
-  }
+  with_walk<W>(a, [&](auto grid) {
+    const int m = tree_m(a.t);
+    const int xcd = static_cast<int>(blockIdx.x % kNumXcd), nq = a.border_n[kWalkCount(xcd)];
+    const int* list = a.qborder + int64_t(xcd) * a.border_n[kWalkShare];
+    for (int64_t k0 = int64_t(blockIdx.x / kNumXcd) * blockDim.x; k0 < nq;
+         k0 += int64_t(gridDim.x / kNumXcd) * blockDim.x) {
+      const int64_t k = k0 + threadIdx.x;
+      const bool mine = k < nq;
+      if (ballot(mine)) border_query<D, B, decltype(grid)::value>(a, m, mine, mine ? list[k] : 0, s_dyn);
+    }
+  });
 }
 
 // Test hook: one lane walks the tree with an always-true box test and records,
@@ -1997,6 +2021,9 @@ inline dim3 query_grid_blocks(int64_t n, int block) {
   const int64_t need = std::max<int64_t>(grid_of(n, block).x, grid_of(std::min<int64_t>(n, kWaves * 64), block / 8).x);
   return dim3(static_cast<unsigned>(std::min<int64_t>(need, kMost)));
 }
+// Do the DenseBox kernels of this call hold both walks (see Walks)?
+template <bool B>
+constexpr bool one_kernel(const TravArgs& a) { return !B && a.n <= kEitherMax; }
 template <int D>
 size_t walk_lds(int block, int more = 0) {  // LDS of a workgroup's searches, and `more` bytes a wavefront
   return size_t(kSearchLds<D, true> + more) * (block / 64);
@@ -2008,8 +2035,14 @@ void core_t(const TravArgs& a, bool densebox, hipStream_t s) {
   const dim3 g = grid_of(a.n, a.block), b(a.block);
   if (densebox) {
     const int gb = grid_block(a);
-    hipLaunchKernelGGL((k_core_dbx<D, B, true>), query_grid_blocks(a.n, gb), dim3(gb), walk_lds<D>(gb) + rec * gb, s, a);
-    hipLaunchKernelGGL((k_core_dbx<D, B, false>), query_grid_blocks(a.n, a.block), b, rec * a.block, s, a);
+    const dim3 gg = query_grid_blocks(a.n, gb);
+    const size_t lds = walk_lds<D>(gb) + rec * gb;
+    if (one_kernel<B>(a)) {
+      hipLaunchKernelGGL((k_core_dbx<D, B, kEither>), gg, dim3(gb), lds, s, a);
+    } else {
+      hipLaunchKernelGGL((k_core_dbx<D, B, kGrid>), gg, dim3(gb), lds, s, a);
+      hipLaunchKernelGGL((k_core_dbx<D, B, kHierarchy>), query_grid_blocks(a.n, a.block), b, rec * a.block, s, a);
+    }
   } else {
     hipLaunchKernelGGL((k_core_fdb<D, B>), g, b, rec * a.block, s, a);
   }
@@ -2026,20 +2059,34 @@ void main_t(const TravArgs& a, bool densebox, int part, hipStream_t s) {
       const int64_t max_cells = a.min_pts > 1 ? a.n / a.min_pts + 1 : a.n;
       // a batch's many cells usually go to the lane kernel, where this one exits at once
       const dim3 gw(static_cast<unsigned>(std::min<int64_t>(kNumXcd * ceil_div(max_cells, kNumXcd * 4), B ? 2048 : 4096)));
-      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, true>), gw, dim3(256), 0, s, a);
-      hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, false>), gw, dim3(256), 0, s, a);
+      if (one_kernel<B>(a)) {
+        hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, kEither>), gw, dim3(256), 0, s, a);
+      } else {
+        hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, kGrid>), gw, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_main_dbx_cells_wave<D, ALL, FIRST, B, kHierarchy>), gw, dim3(256), 0, s, a);
+      }
       if (max_cells > kCellsPerWaveMax) {
-        hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, true>), query_grid_blocks(max_cells, gb), dim3(gb),
-                           walk_lds<D>(gb), s, a);
-        hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, false>), query_grid_blocks(max_cells, a.block), b, 0,
-                           s, a);
+        const dim3 gg = query_grid_blocks(max_cells, gb);
+        if (one_kernel<B>(a)) {
+          hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, kEither>), gg, dim3(gb), walk_lds<D>(gb), s, a);
+        } else {
+          hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, kGrid>), gg, dim3(gb), walk_lds<D>(gb), s, a);
+          hipLaunchKernelGGL((k_main_dbx_cells_lane<D, ALL, FIRST, B, kHierarchy>), query_grid_blocks(max_cells, a.block),
+                             b, 0, s, a);
+        }
       }
     }
     if (part != 1) {
-      hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, true>), query_grid_blocks(a.n, gb), dim3(gb),
-                         walk_lds<D>(gb, kHitBytes), s, a);
-      hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, false>), query_grid_blocks(a.n, a.block), b,
-                         sizeof(uint32_t) * kWideStack * (a.block / 64), s, a);
+      const dim3 gg = query_grid_blocks(a.n, gb);
+      const size_t lds = walk_lds<D>(gb, kHitBytes), wide = sizeof(uint32_t) * kWideStack;
+      if (one_kernel<B>(a)) {
+        hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, kEither>), gg, dim3(gb), std::max(lds, wide * (gb / 64)),
+                           s, a);
+      } else {
+        hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, kGrid>), gg, dim3(gb), lds, s, a);
+        hipLaunchKernelGGL((k_main_dbx_points<D, ALL, FIRST, B, kHierarchy>), query_grid_blocks(a.n, a.block), b,
+                           wide * (a.block / 64), s, a);
+      }
     }
   } else if (FIRST) {
     hipLaunchKernelGGL((k_main_fdb_first<D, B>), g, b, 0, s, a);
@@ -2054,8 +2101,13 @@ void border_t(const TravArgs& a, bool densebox, hipStream_t s) {
   hipLaunchKernelGGL(k_border_rec, dim3(static_cast<unsigned>(kNumXcd * ceil_div(a.brec_cap, 256))), dim3(256), 0, s, a);
   if (densebox) {
     const int gb = grid_block(a);
-    hipLaunchKernelGGL((k_border_dbx<D, B, true>), query_grid_blocks(a.n, gb), dim3(gb), walk_lds<D>(gb), s, a);
-    hipLaunchKernelGGL((k_border_dbx<D, B, false>), query_grid_blocks(a.n, a.block), b, 0, s, a);
+    const dim3 gg = query_grid_blocks(a.n, gb);
+    if (one_kernel<B>(a)) {
+      hipLaunchKernelGGL((k_border_dbx<D, B, kEither>), gg, dim3(gb), walk_lds<D>(gb), s, a);
+    } else {
+      hipLaunchKernelGGL((k_border_dbx<D, B, kGrid>), gg, dim3(gb), walk_lds<D>(gb), s, a);
+      hipLaunchKernelGGL((k_border_dbx<D, B, kHierarchy>), query_grid_blocks(a.n, a.block), b, 0, s, a);
+    }
   } else hipLaunchKernelGGL((k_border_fdb<D, B>), g, b, 0, s, a);
 }
 
