@@ -18,7 +18,7 @@ constexpr int sort_items() { return sizeof(K) == 8 ? 24 : 22; }
 constexpr int kScanItems = 16;                 // items per thread in the device scan
 constexpr int kScanTile = 256 * kScanItems;
 constexpr int64_t kMaxPoints = (int64_t(1) << 30) - 1;
-constexpr uint8_t kCliqueCore = 2, kInClique = 3;  // core flag of a point in one of FDbscan's cliques (TravArgs::core)
+constexpr uint8_t kCliqueCore = 2, kInClique = 3;  // core flags of points in FDbscan's cliques (TravArgs::core)
 constexpr int kRecNb = 8;  // neighbouring primitives recorded per non-core point
 constexpr int kBorderCounters = 32 * 17;  // words of TravArgs::border_n (they fit the digit histograms)
 
@@ -60,7 +60,7 @@ enum MiscSlot : int {
   kMiscNumDense = 4,     // DenseBox: dense cells
   kMiscCut = 7,          // entries of the hierarchy's cut (TreeView::cut)
   kMiscNumBricks = 8,    // DenseBox: occupied bricks
-  kMiscNumCliques = 9,   // FDbscan: cliques that take a wavefront, then (10) those that take a lane
+  kMiscNumCliques = 9,   // FDbscan: listed cliques
   kMiscCount = 16
 };
 
@@ -82,6 +82,8 @@ struct GridPlan {
   int32_t grid_on;     // neighbours are searched through the grid (CellIndex), else through the hierarchy
   float reach;         // eps / side plus rounding slack, in cell units
   float lo[3];         // the scene's low corner
+  int32_t axis_bits[3];  // key bits of each axis (FDbscan's curve: its own for each)
+  double curve_inv[3];   // FDbscan's curve: 1 / cell side of each axis
   uint64_t supers;     // supers of the grid (a batch: of all its grids)
 };
 
@@ -160,11 +162,11 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
 // plan->start as 32- or 64-bit words with the identity permutation, and their
 // digits are counted for the sort (hist: 8 x 256 words, cleared by the caller). The key kernel also clears the super table that
 // the grid's index is built into (plan->supers entries, when plan->grid_on).
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,
-                      hipStream_t s);
+void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
+                      uint32_t* info, hipStream_t s);
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
                      void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
-                     hipStream_t s);
+                     bool curve, hipStream_t s);
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
                     hipStream_t s);
 
@@ -226,12 +228,12 @@ struct TravArgs {
   int packet_leaf;    // bucket size of packet walks (<= 64: a bucket is loaded one point per lane)
   int min_pts;
   int* labels;
-  uint8_t* core;     // 1 = core; FDbscan: kInClique for a point of a clique, 0 elsewhere before the core pass
-  // FDbscan: the nodes that are cliques and in no larger one, num_cliques[0] large ones
-  // from the front of the list (n words) and num_cliques[1] small ones from its end
-  int* cliques;
+  // nonzero = core; FDbscan: kInClique for a point of a listed clique, kCliqueCore for one
+  // of a smaller clique, 0 elsewhere before the core pass
+  uint8_t* core;
+  int* cliques;      // FDbscan: the nodes that are listed cliques, *num_cliques of them
   int* num_cliques;
-  uint8_t* lone;  // set by the core pass (or the isolated-point test before it): 1 = not core and no
+  uint8_t* lone;  // set by the core pass: 1 = not core and no
                   // neighbour but itself (noise); NULL if no core pass
   // Border work left by the core pass for non-core points with some neighbour
   // other than themselves. Up to kRecNb neighbouring primitives of such a point (the

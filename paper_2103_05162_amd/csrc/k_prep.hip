@@ -180,8 +180,9 @@ __device__ __forceinline__ uint32_t quantize(float v, float lo, float scale, uin
 // a 64-bit key holds gets wider cells (every pair in a dense cell still passes the
 // guard). Neighbours are searched through the grid (grid_on) when its super table
 // fits in super_cap entries and a reach stays within two cells per axis.
+// curve: only an order is wanted (FDbscan), and each axis has its own cells and bits.
 template <int D>
-__global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int64_t super_cap,
+__global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int64_t super_cap, bool curve,
                             GridPlan* __restrict__ plan, uint32_t* __restrict__ info) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   constexpr int maxbits = D == 3 ? 21 : 31;
@@ -216,8 +217,37 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
     bits = b > bits ? b : bits;
   }
   g.bits = bits;
-  g.key64 = D * bits > 32 ? 1 : 0;
-  g.passes = (D * bits + 7) / 8;
+  int total = D * bits;
+  for (int k = 0; k < 3; ++k) g.axis_bits[k] = k < D ? bits : 0;
+  if (curve) {
+    // As many bits for each axis as its own extent asks for, up to 31; if they are more
+    // than a key has, the cells of the axis with the most are widened, one bit at a time.
+    double h[3];
+    auto count = [&](int k) {
+      const double cells = floor(ext[k] / h[k]) + 1.0;
+      g.ncell[k] = cells < 2147483646.0 ? static_cast<uint32_t>(cells) : 2147483646u;
+      int b = 0;
+      while ((uint64_t(1) << b) < g.ncell[k]) ++b;
+      return b;
+    };
+    total = 0;
+    for (int k = 0; k < D; ++k) {
+      h[k] = ext[k] / 2147483646.0;
+      h[k] = h[k] > side0 ? h[k] : side0;
+      h[k] = h[k] > 0.0 ? h[k] : 1.0;
+      total += g.axis_bits[k] = count(k);
+    }
+    while (total > 63) {
+      int w = 0;
+      for (int k = 1; k < D; ++k) w = g.axis_bits[k] > g.axis_bits[w] ? k : w;
+      h[w] *= 2.0;
+      total -= g.axis_bits[w];
+      total += g.axis_bits[w] = count(w);
+    }
+    for (int k = 0; k < D; ++k) g.curve_inv[k] = 1.0 / h[k];
+  }
+  g.key64 = total > 32 ? 1 : 0;
+  g.passes = (total + 7) / 8;
   g.start = (g.passes & 1) ? 0 : 1;
   g.coarse = coarse;
   // reach = eps / side in cell units plus a slack for the rounding of the cell
@@ -242,11 +272,41 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
 
 constexpr int kGridKeyItems = 4;
 
+// The curve's key of cell c: the Morton interleave of coordinates of axis_bits each,
+// without the zero bits that the shorter ones would have on the higher levels. Three
+// axes share the lowest levels, then the two longest, then the longest is alone.
+template <int D>
+__device__ __forceinline__ uint64_t curve_key(const uint32_t* c, const int32_t* bits) {
+  auto mask = [](int b) { return b >= 32 ? 0xffffffffu : (1u << b) - 1u; };
+  uint32_t a = c[0], b = c[1], e = D == 3 ? c[2] : 0u;  // to be ordered by bits, most first
+  int na = bits[0], nb = bits[1], ne = D == 3 ? bits[2] : 0;
+  auto order = [](uint32_t& x, int& nx, uint32_t& y, int& ny) {
+    const bool swap = nx < ny;
+    const uint32_t t = x;
+    const int nt = nx;
+    x = swap ? y : x;
+    nx = swap ? ny : nx;
+    y = swap ? t : y;
+    ny = swap ? nt : ny;
+  };
+  if constexpr (D == 3) order(b, nb, e, ne);
+  order(a, na, b, nb);
+  if constexpr (D == 3) order(b, nb, e, ne);
+  uint64_t code = 0;
+  if constexpr (D == 3)
+    code = (spread3(a & mask(ne)) << 2) | (spread3(b & mask(ne)) << 1) | spread3(e);
+  const uint64_t two = (spread2((a >> ne) & mask(nb - ne)) << 1) | spread2((b >> ne) & mask(nb - ne));
+  if (nb > ne) code |= two << (3 * ne);
+  if (na > nb) code |= static_cast<uint64_t>(a >> nb) << (3 * ne + 2 * (nb - ne));
+  return code;
+}
+
 // DenseBox cell keys: cell c_k = floor((x_k - lo_k) / h), clamped to the grid; the
 // key is the Morton interleave of the cell coordinates, so equal keys are one cell
 // and cells follow the curve. Written as 32- or 64-bit words as the plan says, into
 // the buffer the plan names, with the identity permutation beside them.
-template <int D>
+// CURVE: FDbscan's keys (curve_key), the cells taken in double precision.
+template <int D, bool CURVE>
 __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ pts, int64_t n,
                                                      const uint32_t* __restrict__ bounds,
                                                      const GridPlan* __restrict__ plan, void* __restrict__ keys0,
@@ -279,9 +339,18 @@ __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ p
       const bool valid = i < n;
       uint32_t c[D];
 #pragma unroll
-      for (int k = 0; k < D; ++k) c[k] = quantize(x[t][k], lo[k], g.inv_h[k], g.ncell[k] - 1);
+      for (int k = 0; k < D; ++k) {
+        if constexpr (CURVE) {
+          const double u = fmax((static_cast<double>(x[t][k]) - static_cast<double>(lo[k])) * g.curve_inv[k], 0.0);
+          c[k] = u >= static_cast<double>(g.ncell[k] - 1) ? g.ncell[k] - 1 : static_cast<uint32_t>(u);
+        } else {
+          c[k] = quantize(x[t][k], lo[k], g.inv_h[k], g.ncell[k] - 1);
+        }
+      }
       uint64_t code;
-      if constexpr (D == 3)
+      if constexpr (CURVE)
+        code = curve_key<D>(c, g.axis_bits);
+      else if constexpr (D == 3)
         code = (spread3(c[0]) << 2) | (spread3(c[1]) << 1) | spread3(c[2]);
       else
         code = (spread2(c[0]) << 1) | spread2(c[1]);
@@ -386,26 +455,34 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
     hipLaunchKernelGGL(k_bounds<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, info);
 }
 
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, GridPlan* plan, uint32_t* info,
-                      hipStream_t s) {
+void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
+                      uint32_t* info, hipStream_t s) {
   if (dim == 3)
-    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, curve, plan, info);
   else
-    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, curve, plan, info);
 }
 
-void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
-                     void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
+template <int D>
+static void gridkeys_t(int g, const float* pts, int64_t n, const uint32_t* bounds, const GridPlan* plan, void* keys0,
+                       void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers, bool curve,
+                       hipStream_t s) {
+  if (curve)
+    hipLaunchKernelGGL((k_gridkeys<D, true>), dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0,
+                       vals1, hist, supers);
+  else
+    hipLaunchKernelGGL((k_gridkeys<D, false>), dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0,
+                       vals1, hist, supers);
+}
+
+void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan, void* keys0,
+                     void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers, bool curve,
                      hipStream_t s) {
   // A workgroup histogram per 4096+ keys, at most 1024 of them: each flushes up to 2048 bins into the
   // one global histogram, and fewer flushes contend less at L2 than more workgroups gain.
-  int g = grid_for(n, kBlock * 16, 1024);
-  if (dim == 3)
-    hipLaunchKernelGGL(k_gridkeys<3>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0, vals1,
-                       hist, supers);
-  else
-    hipLaunchKernelGGL(k_gridkeys<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0, vals1,
-                       hist, supers);
+  const int g = grid_for(n, kBlock * 16, 1024);
+  if (dim == 3) gridkeys_t<3>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, curve, s);
+  else gridkeys_t<2>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, curve, s);
 }
 
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,

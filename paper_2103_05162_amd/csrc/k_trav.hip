@@ -7,8 +7,9 @@
 //            Figure 1).
 //   border - canonical labels: a non-core point takes the smallest cluster id
 //            among its core neighbours.
-// DenseBox variants (Section 4.2) walk a tree over dense-cell boxes plus the
-// points outside dense cells; a box hit scans the cell's points.
+// FDbscan takes subtrees of points pairwise within eps (cliques) as one set at once.
+// DenseBox variants (Section 4.2) search the grid's cells, or a tree over dense-cell
+// boxes plus the points outside dense cells; a box hit scans the cell's points.
 //
 // Every walk has a scope: the subtree it starts from, the last primitive of
 // that subtree, eps^2 and minPts. A single cloud's scope is the whole tree; in
