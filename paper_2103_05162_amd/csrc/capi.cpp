@@ -816,8 +816,8 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   // The grid is sized on the device (k_grid_plan): nothing waits for the GPU. FDbscan
   // only orders its points by it, and has no index over its cells.
   GridPlan* gplan = at<GridPlan>(ws, plan.gplan);
-  launch_grid_plan(bounds, dim, densebox ? eps : eps * kCurveEps, densebox ? plan.super_cap : 0, !densebox, gplan,
-                   densebox ? h->d_info : nullptr, s);
+  launch_grid_plan(points, n, bounds, dim, densebox ? eps : eps * kCurveEps, densebox ? plan.super_cap : 0, !densebox,
+                   gplan, densebox ? h->d_info : nullptr, s);
 
   int cur = 0;
   const uint32_t* perm = nullptr;

@@ -83,6 +83,7 @@ struct GridPlan {
   float reach;         // eps / side plus rounding slack, in cell units
   float lo[3];         // the scene's low corner
   int32_t axis_bits[3];  // key bits of each axis (FDbscan's curve: its own for each)
+  float curve_mid[3], curve_log[3];  // where curve_log > 0: the middle, and cells per factor of 2 far from it
   double curve_inv[3];   // FDbscan's curve: 1 / cell side of each axis
   uint64_t supers;     // supers of the grid (a batch: of all its grids)
 };
@@ -162,8 +163,8 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
 // plan->start as 32- or 64-bit words with the identity permutation, and their
 // digits are counted for the sort (hist: 8 x 256 words, cleared by the caller). The key kernel also clears the super table that
 // the grid's index is built into (plan->supers entries, when plan->grid_on).
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
-                      uint32_t* info, hipStream_t s);
+void launch_grid_plan(const float* pts, int64_t n, const uint32_t* bounds, int dim, float eps, int64_t super_cap,
+                      bool curve, GridPlan* plan, uint32_t* info, hipStream_t s);
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
                      void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
                      bool curve, hipStream_t s);

@@ -181,8 +181,11 @@ __device__ __forceinline__ uint32_t quantize(float v, float lo, float scale, uin
 // guard). Neighbours are searched through the grid (grid_on) when its super table
 // fits in super_cap entries and a reach stays within two cells per axis.
 // curve: only an order is wanted (FDbscan), and each axis has its own cells and bits.
+constexpr int kCurveSample = 33;
+constexpr double kCurveLinear = 262144.0;  // cells of the wanted side to either side of the middle
 template <int D>
-__global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int64_t super_cap, bool curve,
+__global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint32_t* __restrict__ bounds, float eps,
+                            int64_t super_cap, bool curve,
                             GridPlan* __restrict__ plan, uint32_t* __restrict__ info) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   constexpr int maxbits = D == 3 ? 21 : 31;
@@ -204,6 +207,7 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
   const float ih = static_cast<float>(1.0 / side);
   int bits = 0;
   GridPlan g;
+  for (int k = 0; k < 3; ++k) g.curve_log[k] = g.curve_mid[k] = 0.0f;
   for (int k = 0; k < 4; ++k) {
     g.inv_h[k] = k < D ? ih : 0.0f;
     uint32_t c = 1;
@@ -237,12 +241,26 @@ __global__ void k_grid_plan(const uint32_t* __restrict__ bounds, float eps, int6
       h[k] = h[k] > 0.0 ? h[k] : 1.0;
       total += g.axis_bits[k] = count(k);
     }
-    while (total > 63) {
-      int w = 0;
-      for (int k = 1; k < D; ++k) w = g.axis_bits[k] > g.axis_bits[w] ? k : w;
-      h[w] *= 2.0;
-      total -= g.axis_bits[w];
-      total += g.axis_bits[w] = count(w);
+    if (total > 63) {
+      // far points on every axis: 21 bits each, cells of the wanted side around the
+      // median of a sample, and farther out, where few points lie, a logarithm of the
+      // distance
+      total = 0;
+      for (int k = 0; k < D; ++k) {
+        float v[kCurveSample];
+        for (int t = 0; t < kCurveSample; ++t) {  // insertion sort
+          float x = pts[((2 * t + 1) * n / (2 * kCurveSample)) * D + k];
+          int at = t;
+          for (; at > 0 && v[at - 1] > x; --at) v[at] = v[at - 1];
+          v[at] = x;
+        }
+        g.curve_mid[k] = v[kCurveSample / 2];
+        h[k] = side0 > 0.0 ? side0 : 1.0e-300;
+        const double most = log2(ext[k] / h[k] / kCurveLinear);
+        g.curve_log[k] = most > 0.0 ? static_cast<float>((1048575.0 - kCurveLinear) / most) : 1.0f;
+        g.ncell[k] = 1u << 21;
+        total += g.axis_bits[k] = 21;
+      }
     }
     for (int k = 0; k < D; ++k) g.curve_inv[k] = 1.0 / h[k];
   }
@@ -341,7 +359,16 @@ __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ p
 #pragma unroll
       for (int k = 0; k < D; ++k) {
         if constexpr (CURVE) {
-          const double u = fmax((static_cast<double>(x[t][k]) - static_cast<double>(lo[k])) * g.curve_inv[k], 0.0);
+          double u;
+          if (g.curve_log[k] > 0.0f) {
+            u = (static_cast<double>(x[t][k]) - static_cast<double>(g.curve_mid[k])) * g.curve_inv[k];
+            const double far = fabs(u);
+            const float out = far > kCurveLinear ? log2f(static_cast<float>(far / kCurveLinear)) * g.curve_log[k] : 0.0f;
+            const double r = fmin(fmin(far, kCurveLinear) + out, 1048575.0);
+            u = u < 0.0 ? 1048575.0 - r : 1048576.0 + r;
+          } else {
+            u = fmax((static_cast<double>(x[t][k]) - static_cast<double>(lo[k])) * g.curve_inv[k], 0.0);
+          }
           c[k] = u >= static_cast<double>(g.ncell[k] - 1) ? g.ncell[k] - 1 : static_cast<uint32_t>(u);
         } else {
           c[k] = quantize(x[t][k], lo[k], g.inv_h[k], g.ncell[k] - 1);
@@ -455,12 +482,12 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
     hipLaunchKernelGGL(k_bounds<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, info);
 }
 
-void launch_grid_plan(const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
+void launch_grid_plan(const float* pts, int64_t n, const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
                       uint32_t* info, hipStream_t s) {
   if (dim == 3)
-    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, curve, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, pts, n, bounds, eps, super_cap, curve, plan, info);
   else
-    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, bounds, eps, super_cap, curve, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, pts, n, bounds, eps, super_cap, curve, plan, info);
 }
 
 template <int D>

@@ -49,12 +49,12 @@ def test_box_of_diagonal_eps(dev, d, grow):  # noqa: F811
 
 
 @pytest.mark.parametrize("d", [2, 3])
-@pytest.mark.parametrize("axes", [1, 2])
+@pytest.mark.parametrize("axes", [1, 2, 3])
 @pytest.mark.parametrize("far", [1.0e4, 1.0e9])
 def test_far_point(dev, d, axes, far):  # noqa: F811
     # one point far out on some axes: the curve's cells there are wider than eps
     pts = clumps(d, 20, 17 * d + axes, noise=3000)
-    pts[5, :axes] = far
+    pts[5, :axes] = far  # (all axes: more than a key holds)
     for min_pts in (2, 10):
         assert_exact(dev, pts, EPS, min_pts, "fdbscan")
 
