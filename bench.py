@@ -43,17 +43,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, GB/s
-# fp32 vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-ops/s for the plain
-# (non-packed, non-fused) v_sub/v_mul/v_add/v_cmp the neighbour test compiles to; packed
-# fp32 would double it (78.6 T) but is disabled in this build. The published 157.3 TFLOP/s
-# counts a packed FMA as 4 flops.
-ALU_PEAK_TOPS = 39.3
-ALU_PEAK_PACKED_TOPS = 78.6
-
-
-def pred_ops(d):
-    """fp32 operations of one neighbour test: d subtractions, d products, d-1 sums, one compare."""
-    return 3 * d
 
 
 def unit_sizes(d):
@@ -143,7 +132,7 @@ def run_leg(fdb, h, name, algos, steps, warmup, scale=1.0, tune=False):
     for a in algos:
         log(f"[bench] {w.name} {a}: warmup {warmup}, steps {steps}")
         r = time_algo(fdb, h, pts, w.eps, w.min_pts, a, steps, warmup)
-        rl, pipe = roofline(a, d, w.n, w.min_pts, r["stages"], r["ms"], r["sizes"], golden, traffic_db)
+        rl, pipe = roofline(a, d, w.n, w.min_pts, r["stages"], r["ms"], r["sizes"], traffic_db)
         ok = None
         if golden is not None:
             ok = (r["k"] == golden["num_clusters"] and
@@ -404,7 +393,7 @@ def time_served(fdb, algo, requests, rates, budget_gib, pool_per_dim, warm_s=1.0
 SINGLE_KERNEL = {
     "densebox": {"core": "k_core_dbx", "main_cells": "k_main_dbx_cells_wave", "main_points": "k_main_dbx_points",
                  "permute": "k_permute", "finalize": "k_finalize"},
-    "fdbscan": {"core": "k_core_fdb", "main": "k_main_fdb_q", "finalize": "k_finalize"},
+    "fdbscan": {"core": "k_core_fdb", "permute": "k_permute", "finalize": "k_finalize"},
 }
 
 
@@ -437,14 +426,13 @@ def stage_bytes(algo, d, n, sizes, min_pts):
                 "main_points": ns * walk,
                 "sort_of_primitives": 2 * m * (C + I)})
     if min_pts > 2:
-        out["core"] = ns * core                           # the isolated-point test and the walks
+        out["core"] = ns * core
     return out
 
 
-def roofline(algo, d, n, min_pts, stages, step_ms, sizes, golden, traffic_db):
-    """The dominant single-kernel stage against its roofline (its algorithmic bytes,
-    or pair tests for the ALU-bound FDbscan walks, over its HIP-event duration), and
-    the whole pipeline's algorithmic bytes over the step time."""
+def roofline(algo, d, n, min_pts, stages, step_ms, sizes, traffic_db):
+    """The dominant single-kernel stage against its roofline (its algorithmic bytes
+    over its HIP-event duration), and the whole pipeline's algorithmic bytes over the step time."""
     sb = stage_bytes(algo, d, n, sizes, min_pts)
     total = sum(sb.values())
     t_roof_ms = total / (HBM_PEAK_GBS * 1e9) * 1e3
@@ -457,24 +445,11 @@ def roofline(algo, d, n, min_pts, stages, step_ms, sizes, golden, traffic_db):
         return None, pipeline
     dom = max(cand, key=cand.get)
     ms = cand[dom]
-    alu = (algo == "fdbscan" and dom in ("main", "core") and golden is not None
-           and "sum_neighbors" in golden)
-    if alu:
-        # one neighbour test per pair in the masked main phase, up to minPts per point in the core pass
-        tests = (golden["sum_neighbors"] - n) // 2 if dom == "main" else golden["sum_min_neighbors_minpts"]
-        ops = tests * pred_ops(d)
-        ach = ops / (ms / 1e3) / 1e12
-        out = {"bound": "alu", "achieved": round(ach, 3), "peak": ALU_PEAK_TOPS, "unit": "TFLOP/s",
-               "frac": round(ach / ALU_PEAK_TOPS, 4), "frac_vs_packed_peak": round(ach / ALU_PEAK_PACKED_TOPS, 4),
-               "kernel": single[dom], "stage": dom, "ms": round(ms, 4),
-               "work": f"{tests} neighbour tests x {pred_ops(d)} fp32 ops"}
-        pipeline["t_roof_alu_ms"] = round(ops / (ALU_PEAK_TOPS * 1e12) * 1e3, 4)
-    else:
-        b = sb.get(dom, 0)
-        ach = b / (ms / 1e3) / 1e9
-        out = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-               "frac": round(ach / HBM_PEAK_GBS, 4), "kernel": single[dom], "stage": dom, "ms": round(ms, 4),
-               "alg_bytes": int(b)}
+    b = sb.get(dom, 0)
+    ach = b / (ms / 1e3) / 1e9
+    out = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(ach / HBM_PEAK_GBS, 4), "kernel": single[dom], "stage": dom, "ms": round(ms, 4),
+           "alg_bytes": int(b)}
     t = (traffic_db or {}).get(f"{algo}:{dom}")
     out["traffic"] = t["bytes"] if t else None  # HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated)
     out["traffic_detail"] = t
