@@ -825,7 +825,6 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   ta.xs = xs;
   ta.n = n;
   ta.eps2 = eps2;
-  ta.packet_ext_eps2 = 9.0f;  // packet when the queries' box is at most 3 eps wide
   ta.packet_leaf = tile;       // buckets of up to `tile` candidates, one per lane
   ta.min_pts = min_pts;
   ta.labels = lab;
@@ -1094,7 +1093,6 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   ta.xs = xs;
   ta.n = n;
   ta.eps2 = 0.0f;
-  ta.packet_ext_eps2 = 9.0f;
   ta.packet_leaf = tile;
   ta.min_pts = 0;
   ta.labels = lab;

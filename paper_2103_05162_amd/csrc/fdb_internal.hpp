@@ -225,8 +225,7 @@ struct TravArgs {
   const float* xs;  // sorted SoA coordinates: x[n], y[n], z[n]
   int64_t n;
   float eps2;
-  float packet_ext_eps2;  // a wavefront walks as one packet if its queries' box extent^2 <= this * eps^2
-  int packet_leaf;    // bucket size of packet walks (<= 64: a bucket is loaded one point per lane)
+  int packet_leaf;    // bucket size of the cliques' walks (a bucket is loaded one point per lane)
   int min_pts;
   int* labels;
   // nonzero = core; FDbscan: kInClique for a point of a listed clique, kCliqueCore for one
