@@ -13,9 +13,9 @@
 // three dependent loads from a query to a candidate. A walk down the hierarchy is a
 // chain of ~80 dependent loads for the same candidates (~1.1 us each), and the
 // hierarchy need not be built. Where the grid has more supers than the table holds
-// (a scene of far outliers, or an eps tiny against the extent), or its cell
-// coordinates round too coarsely, the plan leaves grid_on clear and the walks go
-// through the hierarchy. Measured, hierarchy -> grid: uniform 2M-point set (4
+// (a scene of far outliers, or an eps tiny against the extent), its cell
+// coordinates round too coarsely, or eps^2 leaves the range of fp32 (grid_eps), the plan
+// leaves grid_on clear and the walks go through the hierarchy. Measured, hierarchy -> grid: uniform 2M-point set (4
 // neighbours expected) core pass 0.93 -> 0.27, point main phase 1.06 -> 0.67, border
 // pass 0.79 -> 0.13 ms; 8M dense-clump set core pass (with a filter for isolated points
 // before it) 0.30 -> 0.15, point main phase 0.20 -> 0.12 ms; 370k-point mixture core
@@ -40,6 +40,13 @@ constexpr int kSuperSide = 1 << (2 * kLevelShift<D>);  // cells a super is wide
 // Cells within reach of a query lie within two of its own per axis while reach is
 // below this (a reach is sqrt(d) plus the slack of the largest cell coordinate).
 constexpr double kMaxReach = 1.999;
+// The range of eps in which a pair that passes the test s <= fl32(eps * eps) is at most
+// eps (1 + 2^-16) apart, so that a reach holds all of them: every rounding is then
+// relative (eps^2 in [2^-120, 2^126]; a square that underflows is below 2^-30 of it).
+// Outside it the test passes pairs at other distances (eps = 1e-23: squares and eps^2 are
+// 0 up to 2.6e-23 apart; eps above 1.8e19: all are infinite, every pair passes), and the
+// hierarchy, whose box bounds round as the test does, finds the neighbours.
+__device__ __forceinline__ bool grid_eps(float eps) { return eps >= 0x1p-60f && eps <= 0x1p63f; }
 
 // Empties the super table (a grid-stride share of every thread of the launch).
 __device__ __forceinline__ void clear_supers(uint4* __restrict__ supers, uint64_t count) {

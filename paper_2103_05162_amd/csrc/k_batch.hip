@@ -155,8 +155,9 @@ __global__ __launch_bounds__(kBlock) void k_cloud_bounds(const float* __restrict
 // cloud's box, or DenseBox cells of side eps/sqrt(d), slightly shrunk; the
 // exactness guard covers any rounding). For DenseBox also the cloud's grid for the
 // neighbour search: its reach (as k_grid_plan has it), cells per axis and share of
-// the super table, in whatever order the clouds come; a cloud whose grid is too wide,
-// or a table too small for all of them, sends the whole batch through the hierarchy.
+// the super table, in whatever order the clouds come; a cloud whose grid is too wide or
+// whose eps no reach covers (grid_eps), or a table too small for all of them, sends the
+// whole batch through the hierarchy.
 // A cloud with undefined labels gets no grid. One thread per cloud.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restrict__ off, int num_clouds, int64_t n,
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restri
     uint64_t at = 0;
     if (flags || e <= b) {
       nc[0] = 0;
-    } else if (!(r < kMaxReach) || !(supers <= static_cast<double>(super_cap)) ||
+    } else if (!grid_eps(ec) || !(r < kMaxReach) || !(supers <= static_cast<double>(super_cap)) ||
                !(cmax < static_cast<double>(maxq))) {
       atomicAnd(&plan->grid_on, 0);
       nc[0] = 0;

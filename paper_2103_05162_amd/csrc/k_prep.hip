@@ -179,7 +179,8 @@ __device__ __forceinline__ uint32_t quantize(float v, float lo, float scale, uin
 // cell's extent past h (the exactness guard catches the rest). A grid wider than
 // a 64-bit key holds gets wider cells (every pair in a dense cell still passes the
 // guard). Neighbours are searched through the grid (grid_on) when its super table
-// fits in super_cap entries and a reach stays within two cells per axis.
+// fits in super_cap entries, a reach stays within two cells per axis and eps is one that
+// a reach covers (grid_eps).
 // curve: only an order is wanted (FDbscan), and each axis has its own cells and bits.
 constexpr int kCurveSample = 33;
 constexpr double kCurveLinear = 262144.0;  // cells of the wanted side to either side of the middle
@@ -271,7 +272,7 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
   // reach = eps / side in cell units plus a slack for the rounding of the cell
   // coordinates t = (x - lo) * inv_h: each is within 2^-23 t of exact, so a difference
   // within cmax 2^-22 (times 4 here), and the fp32 test passes pairs up to
-  // eps (1 + 2^-22) apart (2^-16 here)
+  // eps (1 + 2^-22) apart (2^-16 here), for an eps that grid_eps takes
   double cmax = 1.0;
   for (int k = 0; k < D; ++k) cmax = g.ncell[k] > cmax ? g.ncell[k] : cmax;
   const double reach = static_cast<double>(eps) * static_cast<double>(ih) * (1.0 + 1.0 / 65536.0) +
@@ -282,7 +283,7 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
     g.lo[k] = k < D ? ord2f(bounds[k]) : 0.0f;
     if (k < D) supers *= static_cast<double>((static_cast<uint64_t>(g.ncell[k]) + kSuperSide<D> - 1) / kSuperSide<D>);
   }
-  g.grid_on = reach < kMaxReach && supers <= static_cast<double>(super_cap) ? 1 : 0;
+  g.grid_on = grid_eps(eps) && reach < kMaxReach && supers <= static_cast<double>(super_cap) ? 1 : 0;
   g.supers = g.grid_on ? static_cast<uint64_t>(supers) : 0;
   *plan = g;
   if (coarse && info) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
