@@ -816,7 +816,8 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   // The grid is sized on the device (k_grid_plan): nothing waits for the GPU. FDbscan
   // only orders its points by it, and has no index over its cells.
   GridPlan* gplan = at<GridPlan>(ws, plan.gplan);
-  launch_grid_plan(points, n, bounds, dim, densebox ? eps : eps * kCurveEps, densebox ? plan.super_cap : 0, !densebox,
+  float* knots = densebox ? nullptr : at<float>(ws, plan.cut);
+  launch_grid_plan(points, n, bounds, dim, densebox ? eps : eps * kCurveEps, densebox ? plan.super_cap : 0, knots,
                    gplan, densebox ? h->d_info : nullptr, s);
 
   int cur = 0;
@@ -844,7 +845,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     ta.ix = ix;
     st.mark("cell_keys");
     launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist),
-                    ix.supers, false, s);
+                    ix.supers, nullptr, s);
     st.mark("sort");
     radix_sort_planned(keys[0], keys[1], vals[0], vals[1], n, gplan, at<uint32_t>(ws, plan.hist),
                        at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);
@@ -882,7 +883,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   } else {
     st.mark("morton");
     launch_gridkeys(points, n, dim, bounds, gplan, keys[0], keys[1], vals[0], vals[1], at<uint32_t>(ws, plan.hist),
-                    nullptr, true, s);
+                    nullptr, knots, s);
     st.mark("sort");
     radix_sort_planned(keys[0], keys[1], vals[0], vals[1], n, gplan, at<uint32_t>(ws, plan.hist),
                        at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);

@@ -49,6 +49,11 @@ struct Plan {
   int64_t super_cap = 0;  // DenseBox: supers that the node records' buffer holds
 };
 
+// FDbscan's curve over a scene too wide for its keys: floats of a sample per axis, sorted,
+// and where the curve has each (6 kCurveKnots, in the place of TreeView's cut, which FDbscan
+// has no use for).
+constexpr int kCurveKnots = 1024;
+
 Plan make_plan(int64_t n, int dim, int algo, int num_clouds = 0);
 
 // Small device-side scalars kept in the workspace's misc block.
@@ -83,7 +88,7 @@ struct GridPlan {
   float reach;         // eps / side plus rounding slack, in cell units
   float lo[3];         // the scene's low corner
   int32_t axis_bits[3];  // key bits of each axis (FDbscan's curve: its own for each)
-  float curve_mid[3], curve_log[3];  // where curve_log > 0: the middle, and cells per factor of 2 far from it
+  int32_t curve_sampled;  // the curve's cells follow a sample of the points (kCurveKnots)
   double curve_inv[3];   // FDbscan's curve: 1 / cell side of each axis
   uint64_t supers;     // supers of the grid (a batch: of all its grids)
 };
@@ -163,11 +168,12 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
 // plan->start as 32- or 64-bit words with the identity permutation, and their
 // digits are counted for the sort (hist: 8 x 256 words, cleared by the caller). The key kernel also clears the super table that
 // the grid's index is built into (plan->supers entries, when plan->grid_on).
+// knots: FDbscan (its keys are a curve's, and no cells are searched), null for DenseBox.
 void launch_grid_plan(const float* pts, int64_t n, const uint32_t* bounds, int dim, float eps, int64_t super_cap,
-                      bool curve, GridPlan* plan, uint32_t* info, hipStream_t s);
+                      float* knots, GridPlan* plan, uint32_t* info, hipStream_t s);
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan,
                      void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
-                     bool curve, hipStream_t s);
+                     const float* knots, hipStream_t s);
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
                     hipStream_t s);
 

@@ -182,13 +182,23 @@ __device__ __forceinline__ uint32_t quantize(float v, float lo, float scale, uin
 // fits in super_cap entries, a reach stays within two cells per axis and eps is one that
 // a reach covers (grid_eps).
 // curve: only an order is wanted (FDbscan), and each axis has its own cells and bits.
-constexpr int kCurveSample = 33;
-constexpr double kCurveLinear = 262144.0;  // cells of the wanted side to either side of the middle
+//
+// A scene too wide on all its axes for 63 bits has 21 bits an axis, three quarters of the
+// codes laid over the extent evenly, so that no cell is more than 4/3 as wide as an even
+// grid's. The last quarter is laid over a sorted sample, at the wanted cells' side but no
+// more than W of an axis from one sample to the next, W being the widest that still fits: so
+// the gaps between bodies take few codes, wherever the bodies are and however many, and
+// cells in them stay cubes. (Codes by rank alone, W -> 0, give boxes of uneven sides:
+// 1M-point friends-of-friends set 2.05 ms for 1.76.) The n / kCurveKnots or so points
+// between two samples a gap apart, a thin slab, share wide cells on that axis only.
+// Measured, with a fine grid around the median and a logarithm farther out / this (eps 0.002,
+// minPts 10): bodies of 1M and 300k clumped points 2e6 eps apart 36.7 / 1.42 ms, 100 bodies
+// of 10,000 over 2e6 eps 19.4 / 1.18 ms; 1M points and one of them far out 1.41 / 1.44 ms.
+constexpr int kPlanBlock = 256;
+constexpr double kCurveEven = 0.75 * 2097152.0, kCurveSampled = 0.25 * 2097152.0;
 template <int D>
-__global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint32_t* __restrict__ bounds, float eps,
-                            int64_t super_cap, bool curve,
-                            GridPlan* __restrict__ plan, uint32_t* __restrict__ info) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+__device__ __forceinline__ GridPlan grid_plan_of(const uint32_t* __restrict__ bounds, float eps, int64_t super_cap,
+                                                 bool curve) {
   constexpr int maxbits = D == 3 ? 21 : 31;
   const double side0 = static_cast<double>(eps) / sqrt(static_cast<double>(D)) * (1.0 - 1.0 / 1048576.0);
   double ext[3] = {0.0, 0.0, 0.0}, emax = 0.0;
@@ -208,7 +218,7 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
   const float ih = static_cast<float>(1.0 / side);
   int bits = 0;
   GridPlan g;
-  for (int k = 0; k < 3; ++k) g.curve_log[k] = g.curve_mid[k] = 0.0f;
+  g.curve_sampled = 0;
   for (int k = 0; k < 4; ++k) {
     g.inv_h[k] = k < D ? ih : 0.0f;
     uint32_t c = 1;
@@ -225,8 +235,7 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
   int total = D * bits;
   for (int k = 0; k < 3; ++k) g.axis_bits[k] = k < D ? bits : 0;
   if (curve) {
-    // As many bits for each axis as its own extent asks for, up to 31; if they are more
-    // than a key has, the cells of the axis with the most are widened, one bit at a time.
+    // As many bits for each axis as its own extent asks for, up to 31.
     double h[3];
     auto count = [&](int k) {
       const double cells = floor(ext[k] / h[k]) + 1.0;
@@ -243,22 +252,10 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
       total += g.axis_bits[k] = count(k);
     }
     if (total > 63) {
-      // far points on every axis: 21 bits each, cells of the wanted side around the
-      // median of a sample, and farther out, where few points lie, a logarithm of the
-      // distance
+      g.curve_sampled = 1;
       total = 0;
       for (int k = 0; k < D; ++k) {
-        float v[kCurveSample];
-        for (int t = 0; t < kCurveSample; ++t) {  // insertion sort
-          float x = pts[((2 * t + 1) * n / (2 * kCurveSample)) * D + k];
-          int at = t;
-          for (; at > 0 && v[at - 1] > x; --at) v[at] = v[at - 1];
-          v[at] = x;
-        }
-        g.curve_mid[k] = v[kCurveSample / 2];
-        h[k] = side0 > 0.0 ? side0 : 1.0e-300;
-        const double most = log2(ext[k] / h[k] / kCurveLinear);
-        g.curve_log[k] = most > 0.0 ? static_cast<float>((1048575.0 - kCurveLinear) / most) : 1.0f;
+        h[k] = ext[k] / kCurveEven;
         g.ncell[k] = 1u << 21;
         total += g.axis_bits[k] = 21;
       }
@@ -285,8 +282,111 @@ __global__ void k_grid_plan(const float* __restrict__ pts, int64_t n, const uint
   }
   g.grid_on = grid_eps(eps) && reach < kMaxReach && supers <= static_cast<double>(super_cap) ? 1 : 0;
   g.supers = g.grid_on ? static_cast<uint64_t>(supers) : 0;
-  *plan = g;
-  if (coarse && info) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
+  return g;
+}
+
+template <int D>
+__global__ __launch_bounds__(kPlanBlock) void k_grid_plan(const float* __restrict__ pts, int64_t n,
+                                                          const uint32_t* __restrict__ bounds, float eps,
+                                                          int64_t super_cap, float* __restrict__ knots,
+                                                          GridPlan* __restrict__ plan, uint32_t* __restrict__ info) {
+  __shared__ int s_sampled;
+  if (threadIdx.x == 0) {
+    const GridPlan g = grid_plan_of<D>(bounds, eps, super_cap, knots != nullptr);
+    *plan = g;
+    s_sampled = g.curve_sampled;
+    if (g.coarse && info) atomicOr(info, FDB_INFO_DENSEBOX_FALLBACK);
+  }
+  if constexpr (D == 3) {  // (two axes of 31 bits fit a key)
+    if (!knots) return;
+    __shared__ float v[3][kCurveKnots];
+    __syncthreads();
+    if (!s_sampled) return;  // the whole workgroup
+    for (int t = threadIdx.x; t < kCurveKnots; t += kPlanBlock) {
+      // a point of each kCurveKnots-th of the input, not at an even stride: inputs repeat
+      const int64_t b = t * n / kCurveKnots, e = (t + 1) * n / kCurveKnots;
+      const int64_t i = b + (e > b ? (uint32_t(t) * 2654435761u) % static_cast<uint64_t>(e - b) : 0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float x = pts[i * 3 + k];
+        v[k][t] = isfinite(x) ? x : 0.0f;
+      }
+    }
+    __syncthreads();
+    for (int run = 2; run <= kCurveKnots; run <<= 1)  // bitonic sort
+      for (int off = run >> 1; off > 0; off >>= 1) {
+        for (int t = threadIdx.x; t < kCurveKnots; t += kPlanBlock) {
+          const int u = t ^ off;
+          if (u < t) continue;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const float a = v[k][t], b = v[k][u];
+            if ((a > b) == ((t & run) == 0)) {
+              v[k][t] = b;
+              v[k][u] = a;
+            }
+          }
+        }
+        __syncthreads();
+      }
+    // a wavefront per axis, consecutive gaps a lane
+    constexpr int kPer = kCurveKnots / 64;
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (k >= 3) return;
+    double w[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int at = lane * kPer + r;
+      w[r] = at + 1 < kCurveKnots ? static_cast<double>(v[k][at + 1]) - static_cast<double>(v[k][at]) : 0.0;
+    }
+    const double ext = static_cast<double>(v[k][kCurveKnots - 1]) - static_cast<double>(v[k][0]);
+    double h = static_cast<double>(eps) / sqrt(3.0);
+    h = h > ext * 0x1p-60 ? h : ext * 0x1p-60;
+    h = h > 0.0 ? h : 1.0;
+    double lo = h * 0x1p-6, hi = ext > lo ? ext : lo;  // (at lo: 16 cells for all the gaps)
+    for (int it = 0; it < 24; ++it) {
+      const double mid = it ? sqrt(lo * hi) : hi;
+      double sum = 0.0;
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) sum += fmin(w[r], mid);
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+      if (sum <= h * kCurveSampled) lo = mid;
+      else hi = mid;
+    }
+    double part = 0.0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      w[r] = fmin(w[r], lo) / h;
+      part += w[r];
+    }
+    double run = part;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double y = __shfl_up(run, off);
+      if (lane >= off) run += y;
+    }
+    run -= part;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      knots[k * kCurveKnots + lane * kPer + r] = v[k][lane * kPer + r];
+      knots[(3 + k) * kCurveKnots + lane * kPer + r] = static_cast<float>(run);
+      run += w[r];
+    }
+  }
+}
+
+// Where x stands on its axis by the sorted knots, between their places (0 up to
+// kCurveSampled).
+__device__ __forceinline__ double place_of(const float* knots, const float* places, float x) {
+  int at = 0;  // knots at or below x (all: one less)
+#pragma unroll
+  for (int step = kCurveKnots / 2; step > 0; step >>= 1)
+    if (knots[at + step - 1] <= x) at += step;
+  const float a = knots[at > 0 ? at - 1 : 0], b = knots[at];
+  if (!(x > a)) return places[at > 0 ? at - 1 : 0];
+  if (!(x < b)) return places[at];
+  const double t = (static_cast<double>(x) - a) / (static_cast<double>(b) - a);
+  return places[at - 1] + t * (static_cast<double>(places[at]) - places[at - 1]);
 }
 
 constexpr int kGridKeyItems = 4;
@@ -324,16 +424,21 @@ __device__ __forceinline__ uint64_t curve_key(const uint32_t* c, const int32_t* 
 // key is the Morton interleave of the cell coordinates, so equal keys are one cell
 // and cells follow the curve. Written as 32- or 64-bit words as the plan says, into
 // the buffer the plan names, with the identity permutation beside them.
-// CURVE: FDbscan's keys (curve_key), the cells taken in double precision.
+// CURVE: FDbscan's keys (curve_key), the cells taken in double precision; where the plan
+// says so, with the points' places among the knots.
 template <int D, bool CURVE>
 __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ pts, int64_t n,
                                                      const uint32_t* __restrict__ bounds,
                                                      const GridPlan* __restrict__ plan, void* __restrict__ keys0,
                                                      void* __restrict__ keys1, uint32_t* __restrict__ vals0,
                                                      uint32_t* __restrict__ vals1, uint32_t* __restrict__ hist,
-                                                     uint4* __restrict__ supers) {
+                                                     uint4* __restrict__ supers, const float* __restrict__ knots) {
   __shared__ uint32_t s_h[8 * 256];
+  __shared__ float s_knots[CURVE && D == 3 ? 6 * kCurveKnots : 1];
   const GridPlan g = *plan;
+  const bool sampled = CURVE && D == 3 && g.curve_sampled != 0;
+  if (sampled)
+    for (int t = threadIdx.x; t < 6 * kCurveKnots; t += kBlock) s_knots[t] = knots[t];
   clear_supers(supers, g.supers);
   const int passes = g.passes;
   hist_clear(s_h, passes);
@@ -360,16 +465,8 @@ __global__ __launch_bounds__(kBlock) void k_gridkeys(const float* __restrict__ p
 #pragma unroll
       for (int k = 0; k < D; ++k) {
         if constexpr (CURVE) {
-          double u;
-          if (g.curve_log[k] > 0.0f) {
-            u = (static_cast<double>(x[t][k]) - static_cast<double>(g.curve_mid[k])) * g.curve_inv[k];
-            const double far = fabs(u);
-            const float out = far > kCurveLinear ? log2f(static_cast<float>(far / kCurveLinear)) * g.curve_log[k] : 0.0f;
-            const double r = fmin(fmin(far, kCurveLinear) + out, 1048575.0);
-            u = u < 0.0 ? 1048575.0 - r : 1048576.0 + r;
-          } else {
-            u = fmax((static_cast<double>(x[t][k]) - static_cast<double>(lo[k])) * g.curve_inv[k], 0.0);
-          }
+          double u = fmax((static_cast<double>(x[t][k]) - static_cast<double>(lo[k])) * g.curve_inv[k], 0.0);
+          if (sampled) u += place_of(s_knots + k * kCurveKnots, s_knots + (3 + k) * kCurveKnots, x[t][k]);
           c[k] = u >= static_cast<double>(g.ncell[k] - 1) ? g.ncell[k] - 1 : static_cast<uint32_t>(u);
         } else {
           c[k] = quantize(x[t][k], lo[k], g.inv_h[k], g.ncell[k] - 1);
@@ -483,34 +580,35 @@ void launch_bounds(const float* pts, int64_t n, int dim, uint32_t* bounds, uint3
     hipLaunchKernelGGL(k_bounds<2>, dim3(g), dim3(kBlock), 0, s, pts, n, bounds, info);
 }
 
-void launch_grid_plan(const float* pts, int64_t n, const uint32_t* bounds, int dim, float eps, int64_t super_cap, bool curve, GridPlan* plan,
-                      uint32_t* info, hipStream_t s) {
+void launch_grid_plan(const float* pts, int64_t n, const uint32_t* bounds, int dim, float eps, int64_t super_cap,
+                      float* knots, GridPlan* plan, uint32_t* info, hipStream_t s) {
   if (dim == 3)
-    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(64), 0, s, pts, n, bounds, eps, super_cap, curve, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<3>, dim3(1), dim3(knots ? kPlanBlock : 64), 0, s, pts, n, bounds, eps, super_cap,
+                       knots, plan, info);
   else
-    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, pts, n, bounds, eps, super_cap, curve, plan, info);
+    hipLaunchKernelGGL(k_grid_plan<2>, dim3(1), dim3(64), 0, s, pts, n, bounds, eps, super_cap, knots, plan, info);
 }
 
 template <int D>
 static void gridkeys_t(int g, const float* pts, int64_t n, const uint32_t* bounds, const GridPlan* plan, void* keys0,
-                       void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers, bool curve,
-                       hipStream_t s) {
-  if (curve)
+                       void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers,
+                       const float* knots, hipStream_t s) {
+  if (knots)
     hipLaunchKernelGGL((k_gridkeys<D, true>), dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0,
-                       vals1, hist, supers);
+                       vals1, hist, supers, knots);
   else
     hipLaunchKernelGGL((k_gridkeys<D, false>), dim3(g), dim3(kBlock), 0, s, pts, n, bounds, plan, keys0, keys1, vals0,
-                       vals1, hist, supers);
+                       vals1, hist, supers, knots);
 }
 
 void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bounds, const GridPlan* plan, void* keys0,
-                     void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers, bool curve,
+                     void* keys1, uint32_t* vals0, uint32_t* vals1, uint32_t* hist, uint4* supers, const float* knots,
                      hipStream_t s) {
   // A workgroup histogram per 4096+ keys, at most 1024 of them: each flushes up to 2048 bins into the
   // one global histogram, and fewer flushes contend less at L2 than more workgroups gain.
   const int g = grid_for(n, kBlock * 16, 1024);
-  if (dim == 3) gridkeys_t<3>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, curve, s);
-  else gridkeys_t<2>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, curve, s);
+  if (dim == 3) gridkeys_t<3>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, knots, s);
+  else gridkeys_t<2>(g, pts, n, bounds, plan, keys0, keys1, vals0, vals1, hist, supers, knots, s);
 }
 
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
