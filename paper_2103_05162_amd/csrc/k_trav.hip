@@ -264,10 +264,20 @@ __device__ __forceinline__ bool traverse_box(const TreeView& t, int m, const Sco
 // An ancestor of x close to its root: labels followed for up to 16 hops, all
 // lanes of a bucket at once. Equal to a query's root means the two are already
 // in one set (sets only grow); anything else only means "unknown". When the chain
-// had more than one link, x is re-pointed straight at the ancestor found (an
-// ancestor stays an ancestor, so the store is safe however it races): points are
-// visited by many walks, and the next visit takes one load (FDbscan main phase on
-// the 8M set 37.4 -> 35.2 ms).
+// had two links or more to spare, x is re-pointed straight at the ancestor found (an
+// ancestor stays an ancestor, whichever store comes last): points are visited by many
+// walks, and the next visit takes one load.
+//
+// The store is an agent-scope one, as every store to labels is whose word another XCD may
+// store to in the same kernel. Plain ones (up to here the case) left XCDs with different
+// values of the word in the kernels that followed: an XCD whose own L2 had the root passed
+// the word over in the finalisation, the others read a parent of it in the border pass,
+// and border points took ids from slots that hold none (500k points in the plane, minPts
+// 140, FDbscan: 5 calls of 6). Agent-scope stores go to memory, so they are made for longer
+// chains only. Calls with plain stores / none / agent-scope ones for every chain / for
+// longer ones, us: 16,384 points FDbscan 444 / 461 / 465 / 451, 2M friends-of-friends
+// FDbscan 2531 / 2715 / 2728 / 2727, DenseBox 1530 / 1564 / 1597 / 1562, 370k mixture 632 /
+// 658 / 657 / 650, batch of 4,096 clouds 25,591 / 26,369 / 25,986 / 26,085.
 __device__ __forceinline__ int ancestor_compress(int* labels, int x) {
   const int x0 = x;
   int p = labels[x];
@@ -277,7 +287,7 @@ __device__ __forceinline__ int ancestor_compress(int* labels, int x) {
     x = p;
     p = labels[x];
   }
-  if (h > 1) labels[x0] = p;
+  if (h > 2) st_agent(labels + x0, p);
   return p;
 }
 
@@ -461,15 +471,15 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
 
 // True only if `root` is an ancestor of x within a few plain-load hops (then x
 // already is in root's set: sets only grow). False means "unknown". When the
-// chain had intermediate links, x is re-pointed straight at root (an ancestor,
-// so the store is safe however it races) and the next check is one load.
+// chain had two intermediate links or more, x is re-pointed straight at root (see
+// ancestor_compress) and the next check is one load.
 __device__ __forceinline__ bool known_same_set(int* labels, int x, int root) {
   const int x0 = x;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     int p = labels[x];
     if (p == root) {
-      if (h > 0) labels[x0] = root;
+      if (h > 1) st_agent(labels + x0, root);
       return true;
     }
     if (p == x) return false;
