@@ -901,6 +901,8 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     ta.t.d_m = nullptr;
     ta.cliques = at<int>(ws, plan.other);  // the build is done with it
     ta.num_cliques = misc + kMiscNumCliques;
+    ta.boxes = at<int>(ws, plan.gamma);
+    ta.num_boxes = misc + kMiscNumBoxes;
     launch_cliques(ta, dim, s);
   }
 
@@ -914,6 +916,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
   if (!all_core) {
     st.mark("core");
     launch_core(ta, dim, densebox, s);
+    if (!densebox) launch_core_boxes(ta, s);
   }
   if (densebox) {
     st.mark("main_cells");
@@ -1153,6 +1156,8 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
     ta.t.d_m = nullptr;
     ta.cliques = at<int>(ws, plan.other);  // the build is done with it
     ta.num_cliques = misc + kMiscNumCliques;
+    ta.boxes = at<int>(ws, plan.gamma);
+    ta.num_boxes = misc + kMiscNumBoxes;
     launch_cliques(ta, dim, s);
   }
   st.mark("core");
@@ -1163,6 +1168,7 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   ta.brec_nb = at<int>(ws, plan.brec_nb);
   ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per shard
   launch_core(ta, dim, densebox, s);
+  if (!densebox) launch_core_boxes(ta, s);
   if (densebox) {
     st.mark("main_cells");
     launch_main(ta, dim, true, false, first_border, 1, s);

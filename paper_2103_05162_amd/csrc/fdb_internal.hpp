@@ -66,6 +66,7 @@ enum MiscSlot : int {
   kMiscCut = 7,          // entries of the hierarchy's cut (TreeView::cut)
   kMiscNumBricks = 8,    // DenseBox: occupied bricks
   kMiscNumCliques = 9,   // FDbscan: listed cliques
+  kMiscNumBoxes = 10,    // FDbscan: listed boxes of fewer than minPts points
   kMiscCount = 16
 };
 
@@ -239,6 +240,8 @@ struct TravArgs {
   uint8_t* core;
   int* cliques;      // FDbscan: the nodes that are listed cliques, *num_cliques of them
   int* num_cliques;
+  int* boxes;        // FDbscan: boxes that are no cliques before the core pass, *num_boxes of them
+  int* num_boxes;
   uint8_t* lone;  // set by the core pass: 1 = not core and no
                   // neighbour but itself (noise); NULL if no core pass
   // Border work left by the core pass for non-core points with some neighbour
@@ -283,9 +286,11 @@ struct TravArgs {
   int block;
 };
 void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s);
-// FDbscan's cliques (subtrees whose points are pairwise within eps): found, marked in
-// labels and core, listed in cliques; then joined to what is within reach of them.
+// FDbscan's cliques (subtrees of core points pairwise within eps): found, marked in labels
+// and core, listed in cliques, before the core pass and, of fewer than minPts points each,
+// after it; then joined to what is within reach of them.
 void launch_cliques(const TravArgs& a, int dim, hipStream_t s);
+void launch_core_boxes(const TravArgs& a, hipStream_t s);
 void launch_main_cliques(const TravArgs& a, int dim, bool all_core, hipStream_t s);
 void launch_main(const TravArgs& a, int dim, bool densebox, bool all_core, bool first_border, int part,
                  hipStream_t s);

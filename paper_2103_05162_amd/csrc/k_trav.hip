@@ -179,12 +179,13 @@ __device__ __forceinline__ unsigned near_bits(const float* __restrict__ xs, int6
   return bits;
 }
 
-// FDbscan: is the node [first, last] a clique, at least kCliqueMin (and minPts) points
-// in a box of diagonal at most eps? Its points are then pairwise within eps, as the
-// point-by-point test would decide: rounded subtraction, squaring and addition are
-// monotone, so the test of the box's corners bounds every pair's. All of them are core
-// and in one set (k_cliques says so beforehand), whatever part of the tree a walk
-// meets them in.
+// FDbscan's boxes: nodes [first, last] of kCliqueMin points or more in a box of diagonal
+// at most eps. Their points are pairwise within eps, as the point-by-point test would
+// decide: rounded subtraction, squaring and addition are monotone, so the test of the
+// box's corners bounds every pair's. So are those of every node inside a box. A box of
+// minPts points or more is a clique: all its points are core and in one set, whatever part
+// of the tree a walk meets them in (k_cliques says so beforehand). In any other box the
+// core points are in one set, which k_core_boxes says once the core pass knows them.
 constexpr int kCliqueMin = 4;
 // Cliques of this many points search for themselves, a wavefront each; the points of
 // smaller ones search each for itself, as points outside cliques do (but are in one set
@@ -193,10 +194,14 @@ constexpr int kCliqueMin = 4;
 // 175. kCliqueMin 2, 4: alike; 16: 160 us more on the friends-of-friends set.
 constexpr int kCliqueWave = 12;
 template <int D>
-__device__ __forceinline__ bool is_clique(int first, int last, const float4& lo, const float4& hi, const Scope& sc) {
-  const int size = last - first + 1;
-  return size >= kCliqueMin && size >= sc.min_pts &&
-         dist2v<D>(hi.x, hi.y, hi.z, lo.x, lo.y, lo.z) <= sc.eps2;
+__device__ __forceinline__ bool is_box(int first, int last, const float4& lo, const float4& hi, float eps2) {
+  return last - first + 1 >= kCliqueMin && dist2v<D>(hi.x, hi.y, hi.z, lo.x, lo.y, lo.z) <= eps2;
+}
+// A core point of the box [first, last], to stand for them all, or -1 (unknown: neither
+// its first point nor its last is one).
+__device__ __forceinline__ int box_core(const uint8_t* core, int first, int last, int min_pts) {
+  if (last - first + 1 >= min_pts || core[first]) return first;
+  return core[last] ? last : -1;
 }
 
 // Wave-uniform walk for a box query (every point of box [lo,hi]), masked like
@@ -300,18 +305,25 @@ __device__ __forceinline__ int ancestor_compress(int* labels, int x) {
 // once. It visits the same buckets and leaves as traverse_box (in another order:
 // callers only union, which does not depend on it). Children that do not fit on
 // the stack have their subtrees walked with traverse_box instead. SKIP (FDbscan's
-// unions): the walk starts from the escape links above the mask (>= 0), and cliques
-// already in the set of root skip_root (labels skip_labels; the visitor may advance it)
-// are not walked.
+// unions): the walk starts from the escape links above the mask (>= 0), and boxes whose
+// core points (skip_core) are already in the set of root skip_root (labels skip_labels;
+// the visitor may advance it) are not walked.
 constexpr int kWideStack = 512;  // entries per wavefront
 
 template <int D, bool SKIP, typename F>
 __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m, const Scope& sc, const float* lo,
                                                         const float* hi, int mask, int leaf_size, uint32_t* info,
                                                         uint32_t* stack, F&& visit_lanes,
-                                                        int* skip_labels, const int& skip_root) {
+                                                        int* skip_labels, const uint8_t* skip_core,
+                                                        const int& skip_root) {
   if (m <= 0 || mask >= sc.end) return;
   const int lane = lane_id();
+  // is the node a box whose core points are in the set of skip_root?
+  auto known = [&](int first, int last, const float4& na, const float4& nb) {
+    if (!SKIP || skip_root < 0 || !is_box<D>(first, last, na, nb, sc.eps2)) return false;
+    const int c = box_core(skip_core, first, last, sc.min_pts);
+    return c >= 0 && ancestor_compress(skip_labels, c) == skip_root;
+  };
   // a range [s, e] of one lane (wave-uniform arguments), 64 primitives per call
   auto range = [&](int s, int e) {
     for (int b = s; b <= e; b += 64)
@@ -397,8 +409,7 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
         if (last > mask && boxbox_dist2<D>(lo, hi, na.x, na.y, na.z, nb.x, nb.y, nb.z) <= sc.eps2) {
           if (first < 0 || last >= m || g < first || g >= last) {
             atomicOr(info, kInternalBit);
-          } else if (SKIP && skip_root >= 0 && is_clique<D>(first, last, na, nb, sc) &&
-                     ancestor_compress(skip_labels, first) == skip_root) {
+          } else if (known(first, last, na, nb)) {
             // nothing to join
           } else if (last - first < leaf_size) {
             bs = first <= mask ? mask + 1 : first;
@@ -466,7 +477,7 @@ __device__ __forceinline__ void traverse_box_wide_lanes(const TreeView& t, int m
                                                         const float* hi, int mask, int leaf_size, uint32_t* info,
                                                         uint32_t* stack, F&& visit_lanes) {
   const int none = -1;
-  traverse_box_wide_lanes<D, false>(t, m, sc, lo, hi, mask, leaf_size, info, stack, visit_lanes, nullptr, none);
+  traverse_box_wide_lanes<D, false>(t, m, sc, lo, hi, mask, leaf_size, info, stack, visit_lanes, nullptr, nullptr, none);
 }
 
 // True only if `root` is an ancestor of x within a few plain-load hops (then x
@@ -674,73 +685,148 @@ struct Chunks {
   __device__ __forceinline__ int query() const { return slot < 0 ? -1 : static_cast<int>(xcd * chunk + off + slot); }
 };
 
-// Cliques (is_clique) that are in no larger one: a thread takes kCliqueItems nodes in
-// turn and looks at the two children of each that is no clique itself (their records
-// lie side by side). Their points become core and one set; those of kCliqueWave points
-// or more (kInClique, the rest kCliqueCore) are listed for k_main_cliques. A workgroup
-// lists through LDS and reserves once. Bound by the node records: 8M points (80% of them
-// in cliques) 120 us for 268 MB of nodes read up to three times.
+// Cliques, before the core pass: a thread takes kCliqueItems nodes in turn and looks at the
+// two children of each (their records lie side by side). Cliques in no larger one get their
+// points marked: core (kInClique where the node searches for itself, which kCliqueWave
+// points are worth, else kCliqueCore) and one set, their first point's. Boxes of fewer than
+// minPts points in no larger one are listed for k_core_boxes. A workgroup lists through LDS and reserves once.
+// Bound by the node records: 8M points (80% of them in cliques) 120 us for 268 MB of nodes
+// read up to three times.
 constexpr int kCliqueItems = 8;
 
 template <int D, bool B>
 __global__ __launch_bounds__(256) void k_cliques(TravArgs a) {
-  __shared__ int s_list[2 * 256 * kCliqueItems];
-  __shared__ int s_n, s_at;
+  constexpr int kList = 2 * 256 * kCliqueItems;
+  __shared__ int s_list[kList];  // nodes that search from the front, boxes from the back
+  __shared__ int s_n, s_b, s_at, s_bat;
   const int m = tree_m(a.t);
   const int lane = lane_id();
-  if (threadIdx.x == 0) s_n = 0;
+  if (threadIdx.x == 0) s_n = s_b = 0;
   __syncthreads();
-  // node k's range, or first > last where it is no clique
-  auto clique = [&](int k, int& first, int& last, int& g) {
+  struct Node {
+    int first = 0, last = -1, g = -1;
+    bool box = false;
+  };
+  auto load = [&](int k) {
     const float4 lo = a.t.node_a[kNodeStride * size_t(k)], hi = a.t.node_b[kNodeStride * size_t(k)];
     const int o = __float_as_int(lo.w);
-    first = o < k ? o : k;
-    last = o > k ? o : k;
-    g = __float_as_int(hi.w);
-    if (first < 0 || last >= m || g < first || g >= last) {  // not a node: the walks report it
-      g = -1;
-      return false;
+    Node v;
+    v.first = o < k ? o : k;
+    v.last = o > k ? o : k;
+    v.g = __float_as_int(hi.w);
+    if (v.first < 0 || v.last >= m || v.g < v.first || v.g >= v.last) {  // not a node: the walks report it
+      v.g = -1;
+      return v;
     }
-    if (B && cloud_of(a, first) != cloud_of(a, last)) return false;
-    return is_clique<D>(first, last, lo, hi, scope_of<B>(a, m, first));
+    if (B && cloud_of(a, v.first) != cloud_of(a, v.last)) return v;
+    v.box = is_box<D>(v.first, v.last, lo, hi, B ? a.cloud_eps2[cloud_of(a, v.first)] : a.eps2);
+    return v;
   };
   const int64_t base = blockIdx.x * int64_t(256 * kCliqueItems) + threadIdx.x;
   for (int t = 0; t < kCliqueItems; ++t) {
     const int64_t k64 = base + t * 256;
-    int found[2] = {-1, -1}, lo[2] = {0, 0}, hi[2] = {-1, -1};
+    int lo[2] = {0, 0}, hi[2] = {-1, -1};  // ranges to mark
+    bool search[2] = {false, false};
     if (k64 < m - 1) {
       const int k = static_cast<int>(k64);
-      int first, last, g, gc;
-      if (!clique(k, first, last, g)) {
-        if (g >= 0 && first < g && clique(g, lo[0], hi[0], gc)) found[0] = g;
-        if (g >= 0 && last > g + 1 && clique(g + 1, lo[1], hi[1], gc)) found[1] = g + 1;
-      } else if (k == 0) {
-        found[0] = 0;
-        lo[0] = first;
-        hi[0] = last;
+      const Node v = load(k);
+      const int min_pts = v.box ? (B ? a.cloud_minpts[cloud_of(a, v.first)] : a.min_pts) : 0;
+      // node x (a child, or the root) is a box in no larger one
+      auto take = [&](int slot, int x, int first, int last, int cloud_minpts) {
+        const int size = last - first + 1;
+        if (size < cloud_minpts) {
+          s_list[kList - 1 - atomicAdd(&s_b, 1)] = x;
+          return;
+        }
+        lo[slot] = first;
+        hi[slot] = last;
+        search[slot] = size >= kCliqueWave;
+        if (search[slot]) s_list[atomicAdd(&s_n, 1)] = x;
+      };
+      if (k == 0 && v.box) take(0, 0, v.first, v.last, min_pts);
+      if (v.g >= 0 && !v.box) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int x = v.g + c;
+          if (c ? v.last == x : v.first == x) continue;
+          const Node w = load(x);
+          if (w.box) take(c, x, w.first, w.last, B ? a.cloud_minpts[cloud_of(a, w.first)] : a.min_pts);
+        }
       }
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      if (found[c] >= 0 && hi[c] - lo[c] + 1 >= kCliqueWave) s_list[atomicAdd(&s_n, 1)] = found[c];
-      for (uint64_t fm = ballot(found[c] >= 0); fm; fm &= fm - 1) {
+      const int how = search[c] ? kInClique : kCliqueCore;
+      for (uint64_t fm = ballot(hi[c] >= lo[c]); fm; fm &= fm - 1) {
         const int L = __ffsll(static_cast<unsigned long long>(fm)) - 1;
         const int first = __builtin_amdgcn_readlane(lo[c], L), last = __builtin_amdgcn_readlane(hi[c], L);
+        const int flag = __builtin_amdgcn_readlane(how, L);
         for (int i = first + lane; i <= last; i += 64) {
           a.labels[i] = first;
-          a.core[i] = last - first + 1 >= kCliqueWave ? kInClique : kCliqueCore;
+          a.core[i] = static_cast<uint8_t>(flag);
         }
       }
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) s_at = s_n ? atomicAdd(a.num_cliques, s_n) : 0;
+  if (threadIdx.x == 0) {
+    s_at = s_n ? atomicAdd(a.num_cliques, s_n) : 0;
+    s_bat = s_b ? atomicAdd(a.num_boxes, s_b) : 0;
+  }
   __syncthreads();
   for (int k = threadIdx.x; k < s_n; k += 256) a.cliques[s_at + k] = s_list[k];
+  for (int k = threadIdx.x; k < s_b; k += 256) a.boxes[s_bat + k] = s_list[kList - 1 - k];
+}
+
+// The boxes of fewer than minPts points, once the core pass is done, eight lanes each: their
+// core points become one set, and a box of nothing else is a clique from now on. Where an
+// eps-ball holds several times minPts points and a box of diagonal eps fewer than that (it
+// has 1/22 of the ball in three dimensions), there are no other boxes, and the main phase
+// tests every pair without these: 200,000 points in 3D, FDbscan, us, without / with: minPts
+// 100 of 1700 neighbours 7842 / 1227, 1000 of 4000 14,360 / 3690; in 2D 1000 of 4000 9906 /
+// 2155 (walking as packets past whole sets of the hierarchy's cut: 2727, 7842, 3737).
+__global__ __launch_bounds__(256) void k_core_boxes(TravArgs a) {
+  constexpr int G = 8;
+  const int nb = *a.num_boxes;
+  const int sub = threadIdx.x & (G - 1);
+  for (int64_t b0 = blockIdx.x * int64_t(256 / G); b0 < nb; b0 += int64_t(gridDim.x) * (256 / G)) {
+    const int64_t b = b0 + threadIdx.x / G;
+    const int k = b < nb ? a.boxes[b] : 0;
+    const int o = b < nb ? __float_as_int(a.t.node_a[kNodeStride * size_t(k)].w) : 0;
+    const int first = o < k ? o : k, last = b < nb ? (o > k ? o : k) : -1;
+    int rep = 0x7fffffff, cnt = 0;
+    for (int i = first + sub; i <= last; i += G)
+      if (a.core[i]) {
+        rep = min(rep, i);
+        ++cnt;
+      }
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+      rep = min(rep, __shfl_xor(rep, off));
+      cnt += __shfl_xor(cnt, off);
+    }
+    const int size = last - first + 1;
+    const bool all = cnt == size && cnt > 0, search = all && size >= kCliqueWave;
+    const uint8_t flag = search ? kInClique : kCliqueCore;
+    if (cnt > 1)
+      for (int i = first + sub; i <= last; i += G)
+        if (a.core[i]) {
+          a.labels[i] = rep;
+          if (all) a.core[i] = flag;
+        }
+    const uint64_t sm = ballot(search && sub == 0);
+    if (sm) {
+      const int leader = __ffsll(static_cast<unsigned long long>(sm)) - 1;
+      int at = 0;
+      if (lane_id() == leader) at = atomicAdd(a.num_cliques, __popcll(sm));
+      at = __shfl(at, leader);
+      if (search && sub == 0) a.cliques[at + __popcll(sm & lanemask_lt())] = k;
+    }
+  }
 }
 
 // First-claim main phase (the paper's border rule), a lane per point. A core point
-// passes over cliques already in its set, all of whose points are core (with packets of
+// passes over boxes already in its set, if all of their points are core (with packets of
 // near queries instead 1M dense clumps took 23.7 ms a call, with lanes 1.3).
 __device__ __forceinline__ void main_pair_first(const TravArgs& a, int i, bool ci, int j, bool cj, int& root,
                                                 bool& done) {
@@ -776,7 +862,10 @@ __global__ void k_main_fdb_first(TravArgs a) {
       }
     return done;
   }, [&](int first, int last, const float4& lo, const float4& hi) {
-    return ci && is_clique<D>(first, last, lo, hi, sc) && known_same_set(labels, first, root) ? 1 : 0;
+    return ci && is_box<D>(first, last, lo, hi, sc.eps2) &&
+                   (last - first + 1 >= sc.min_pts || a.core[first] >= kCliqueCore) &&
+                   known_same_set(labels, first, root)
+               ? 1 : 0;
   });
 }
 
@@ -809,12 +898,14 @@ __global__ void k_main_fdb(TravArgs a) {
       }
     return false;
   }, [&](int first, int last, const float4& lo, const float4& hi) {
-    return is_clique<D>(first, last, lo, hi, sc) && known_same_set(labels, first, root) ? 1 : 0;
+    if (!is_box<D>(first, last, lo, hi, sc.eps2)) return 0;
+    const int c = ALL_CORE ? first : box_core(a.core, first, last, sc.min_pts);
+    return c >= 0 && known_same_set(labels, c, root) ? 1 : 0;
   });
 }
 
-// Main phase of the cliques of kCliqueWave points or more: one wavefront per clique A walks the tree once with A's
-// box over the points above A. A candidate is a core point within eps of A's box that is
+// Main phase of the cliques that search for themselves: one wavefront per clique A
+// walks the tree once with A's box over the points above A. A candidate is a core point within eps of A's box that is
 // not known to be in A's set, one per lane; it joins the set if some point of A is
 // within eps (the points below A look for A themselves: other points in k_main_fdb,
 // points of cliques here). A wavefront's time is its rounds, each a chain of
@@ -874,7 +965,7 @@ __global__ __launch_bounds__(256) void k_main_cliques(TravArgs a) {
         r = __builtin_amdgcn_readfirstlane(nr);
       }
       return false;
-    }, labels, r);
+    }, labels, a.core, r);
   }
 }
 
@@ -2128,6 +2219,12 @@ static void main_cliques_t(const TravArgs& a, bool all_core, hipStream_t s) {
   if (a.pkeys) hipLaunchKernelGGL((k_main_cliques<D, false, true>), g, b, 0, s, a);
   else if (all_core) hipLaunchKernelGGL((k_main_cliques<D, true, false>), g, b, 0, s, a);
   else hipLaunchKernelGGL((k_main_cliques<D, false, false>), g, b, 0, s, a);
+}
+
+void launch_core_boxes(const TravArgs& a, hipStream_t s) {
+  if (a.n < kCliqueMin || (!a.pkeys && a.min_pts <= kCliqueMin)) return;  // every box is a clique
+  const dim3 g(static_cast<unsigned>(std::min<int64_t>(2048, ceil_div(a.n, 32 * kCliqueMin)))), b(256);
+  hipLaunchKernelGGL(k_core_boxes, g, b, 0, s, a);
 }
 
 void launch_main_cliques(const TravArgs& a, int dim, bool all_core, hipStream_t s) {
