@@ -238,7 +238,7 @@ struct TravArgs {
   // nonzero = core; FDbscan: kInClique for a point of a listed clique, kCliqueCore for one
   // of a smaller clique, 0 elsewhere before the core pass
   uint8_t* core;
-  int* cliques;      // FDbscan: the nodes that are listed cliques, *num_cliques of them
+  int* cliques;      // FDbscan: the nodes (kLeaf | point) that are listed cliques, *num_cliques of them
   int* num_cliques;
   int* boxes;        // FDbscan: boxes that are no cliques before the core pass, *num_boxes of them
   int* num_boxes;

@@ -193,6 +193,14 @@ constexpr int kCliqueMin = 4;
 // set 1812 / 1825 / 1829, 8M-point set 853 / 670 / 743, 16,384 points in 2D 169 / 174 /
 // 175. kCliqueMin 2, 4: alike; 16: 160 us more on the friends-of-friends set.
 constexpr int kCliqueWave = 12;
+// A clique of more points than this (or minPts, if larger) searches as the largest nodes
+// in it that have no more: one wavefront takes a clique, and tests its points against every
+// 64 candidates. Two bodies of 30,000 points, each a clique, whose boxes are within eps
+// though no pair is, took 249 ms as one search each (3.5 when queries walked as packets).
+// With 64 / 128 / 256 / 512 / 1024 at most, call, us: those bodies in 2D 490 / 730 / 920 /
+// 1350 / 1350, in 3D 293 / 570 / 590 / 900 / 7660; 8M-point set 4124 / 3593 / 3306 / 3179 /
+// 3125 (any size: 3343).
+constexpr int kCliqueMost = 512;
 template <int D>
 __device__ __forceinline__ bool is_box(int first, int last, const float4& lo, const float4& hi, float eps2) {
   return last - first + 1 >= kCliqueMin && dist2v<D>(hi.x, hi.y, hi.z, lo.x, lo.y, lo.z) <= eps2;
@@ -686,10 +694,13 @@ struct Chunks {
 };
 
 // Cliques, before the core pass: a thread takes kCliqueItems nodes in turn and looks at the
-// two children of each (their records lie side by side). Cliques in no larger one get their
-// points marked: core (kInClique where the node searches for itself, which kCliqueWave
-// points are worth, else kCliqueCore) and one set, their first point's. Boxes of fewer than
-// minPts points in no larger one are listed for k_core_boxes. A workgroup lists through LDS and reserves once.
+// two children of each (their records lie side by side). Cliques in no larger one, and of
+// larger ones than `most` the largest nodes that are not, get their points marked: core
+// (kInClique where the node searches for itself, which kCliqueWave points in it or a clique
+// above it are worth, else kCliqueCore) and one set, their first point's. A node above them
+// hangs its right child's first point under its own, so a clique of any size is one set and
+// no wavefront marks more than `most` points. Boxes of fewer than minPts points in no
+// larger one are listed for k_core_boxes. A workgroup lists through LDS and reserves once.
 // Bound by the node records: 8M points (80% of them in cliques) 120 us for 268 MB of nodes
 // read up to three times.
 constexpr int kCliqueItems = 8;
@@ -731,26 +742,40 @@ __global__ __launch_bounds__(256) void k_cliques(TravArgs a) {
       const int k = static_cast<int>(k64);
       const Node v = load(k);
       const int min_pts = v.box ? (B ? a.cloud_minpts[cloud_of(a, v.first)] : a.min_pts) : 0;
-      // node x (a child, or the root) is a box in no larger one
-      auto take = [&](int slot, int x, int first, int last, int cloud_minpts) {
+      const int most = max(kCliqueMost, min_pts);
+      const bool large = v.box && v.last - v.first + 1 > most;
+      if (large) a.labels[v.g + 1] = v.first;
+      // node c (a child, or the root) is a box in no larger one, or in a large one
+      auto take = [&](int slot, uint32_t ref, int first, int last, int cloud_minpts, bool inside) {
         const int size = last - first + 1;
-        if (size < cloud_minpts) {
-          s_list[kList - 1 - atomicAdd(&s_b, 1)] = x;
+        if (!inside && size < cloud_minpts) {
+          s_list[kList - 1 - atomicAdd(&s_b, 1)] = static_cast<int>(ref);
           return;
         }
+        if (size > max(kCliqueMost, cloud_minpts)) return;
         lo[slot] = first;
         hi[slot] = last;
-        search[slot] = size >= kCliqueWave;
-        if (search[slot]) s_list[atomicAdd(&s_n, 1)] = x;
+        search[slot] = inside || size >= kCliqueWave;
+        if (search[slot]) s_list[atomicAdd(&s_n, 1)] = static_cast<int>(ref);
       };
-      if (k == 0 && v.box) take(0, 0, v.first, v.last, min_pts);
-      if (v.g >= 0 && !v.box) {
+      if (k == 0 && v.box && !large) take(0, 0u, v.first, v.last, min_pts, false);
+      if (v.g >= 0 && (!v.box || large)) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           const int x = v.g + c;
-          if (c ? v.last == x : v.first == x) continue;
+          const bool leaf = c ? v.last == x : v.first == x;
+          if (leaf) {
+            if (large) take(c, kLeaf | static_cast<uint32_t>(x), x, x, min_pts, true);
+            continue;
+          }
           const Node w = load(x);
-          if (w.box) take(c, x, w.first, w.last, B ? a.cloud_minpts[cloud_of(a, w.first)] : a.min_pts);
+          if (w.g < 0 || !w.box) {
+            // (a child of a large clique is a box unless it is smaller than one)
+            if (large && w.g >= 0) take(c, static_cast<uint32_t>(x), w.first, w.last, min_pts, true);
+            continue;
+          }
+          const int mp = large ? min_pts : (B ? a.cloud_minpts[cloud_of(a, w.first)] : a.min_pts);
+          take(c, static_cast<uint32_t>(x), w.first, w.last, mp, large);
         }
       }
     }
@@ -762,7 +787,7 @@ __global__ __launch_bounds__(256) void k_cliques(TravArgs a) {
         const int first = __builtin_amdgcn_readlane(lo[c], L), last = __builtin_amdgcn_readlane(hi[c], L);
         const int flag = __builtin_amdgcn_readlane(how, L);
         for (int i = first + lane; i <= last; i += 64) {
-          a.labels[i] = first;
+          if (i > first) a.labels[i] = first;  // (the first point's is its own, or a node's above)
           a.core[i] = static_cast<uint8_t>(flag);
         }
       }
@@ -904,8 +929,8 @@ __global__ void k_main_fdb(TravArgs a) {
   });
 }
 
-// Main phase of the cliques that search for themselves: one wavefront per clique A
-// walks the tree once with A's box over the points above A. A candidate is a core point within eps of A's box that is
+// Main phase of the cliques that search for themselves: one wavefront per clique A (a node,
+// or kLeaf | a point of a large one) walks the tree once with A's box over the points above A. A candidate is a core point within eps of A's box that is
 // not known to be in A's set, one per lane; it joins the set if some point of A is
 // within eps (the points below A look for A themselves: other points in k_main_fdb,
 // points of cliques here). A wavefront's time is its rounds, each a chain of
@@ -922,10 +947,20 @@ __global__ __launch_bounds__(256) void k_main_cliques(TravArgs a) {
   const int nwaves = (gridDim.x * blockDim.x) >> 6;
   int* labels = a.labels;
   for (int w = (xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6; w < nq; w += nwaves) {
-    const int k = a.cliques[w];
-    const float4 na = a.t.node_a[kNodeStride * size_t(k)], nb = a.t.node_b[kNodeStride * size_t(k)];
-    const int o = __float_as_int(na.w);
-    const int sa = o < k ? o : k, ea = o > k ? o : k;
+    const uint32_t ref = static_cast<uint32_t>(a.cliques[w]);
+    const int k = static_cast<int>(ref & ~kLeaf);
+    int sa = k, ea = k;
+    float4 na, nb;
+    if (ref & kLeaf) {
+      const Query q = load_point<D>(a.xs, a.n, k);
+      na = nb = make_float4(q.x, q.y, q.z, 0.0f);
+    } else {
+      na = a.t.node_a[kNodeStride * size_t(k)];
+      nb = a.t.node_b[kNodeStride * size_t(k)];
+      const int o = __float_as_int(na.w);
+      sa = o < k ? o : k;
+      ea = o > k ? o : k;
+    }
     const float alo[3] = {na.x, na.y, na.z}, ahi[3] = {nb.x, nb.y, nb.z};
     const Scope sc = scope_of<B>(a, m, sa);
     const float eps2 = sc.eps2;

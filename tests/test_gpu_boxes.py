@@ -1,7 +1,8 @@
 """FDbscan where a box of diagonal eps holds fewer than minPts points but an eps-ball many
-(the box's core points are one set once the core pass is done). Labels equal the oracle's;
-and such a call takes not many times what one with a smaller minPts takes: before boxes of
-core points were joined, every pair was tested."""
+(the box's core points are one set once the core pass is done), and cliques of more points
+than one search takes. Labels equal the oracle's; and such calls take not many times what
+their like take: before boxes of core points were joined, every pair was tested, and a
+clique of any size searched as one."""
 import time
 
 import numpy as np
@@ -53,6 +54,30 @@ def test_boxes_of_a_batch(dev, d):  # noqa: F811
                 assert_tolerance_mode(p, 1.0, lab[s], core[s], rl, rc, oracle.check_border)
 
 
+@pytest.mark.parametrize("d", [2, 3])
+@pytest.mark.parametrize("size", [511, 512, 513, 1025, 3000])
+@pytest.mark.parametrize("single", [False, True])
+def test_large_cliques(dev, d, size, single):  # noqa: F811
+    # a chain of bodies within eps each, some within eps of the next; `single`: one point of a
+    # body stands apart from the others, which are all alike (a leaf beside the rest)
+    rng = np.random.default_rng(size + d)
+    pts = []
+    for b in range(5):
+        p = rng.uniform(0, 0.5, (size, d))
+        if single:
+            p[:] = p[0]
+            p[1] += 0.2
+        pts.append(p + b * rng.uniform(0.6, 1.1))
+    pts.append(rng.uniform(-1, 5, (300, d)))
+    pts = np.concatenate(pts).astype(np.float32)
+    pts = pts[rng.permutation(len(pts))]
+    for min_pts in (2, 5, 513, 600, 2 * size):
+        ref = assert_exact(dev, pts, 1.0, min_pts, "fdbscan")
+        if min_pts > 2:
+            lab, core, _ = run_gpu(dev, pts, 1.0, min_pts, "fdbscan", border="first")
+            assert_tolerance_mode(pts, 1.0, lab, core, ref[0], ref[1], oracle.check_border)
+
+
 def timed(dev, pts, min_pts):
     import torch
     import paper_2103_05162_amd as fdb
@@ -65,6 +90,23 @@ def timed(dev, pts, min_pts):
         torch.cuda.synchronize()
         times.append(time.perf_counter() - t0)
     return lab.cpu().numpy(), k, float(np.median(times[1:]))
+
+
+@pytest.mark.parametrize("d", [2, 3])
+def test_bodies_that_nearly_touch(dev, d):  # noqa: F811
+    # balls of diameter 0.56, each a clique; boxes within 1 of each other but no pair
+    _say(f"[gpu] bodies that nearly touch d={d}")
+    rng = np.random.default_rng(5)
+    n = 30000
+    v = rng.standard_normal((2 * n, d))
+    v *= 0.28 * rng.random((2 * n, 1)) ** (1 / d) / np.linalg.norm(v, axis=1, keepdims=True)
+    v[n:] += 1.57 / np.sqrt(d)
+    v = v.astype(np.float32)
+    alone = timed(dev, v[:n], 10)[2] + timed(dev, v[n:], 10)[2]
+    lab, k, t = timed(dev, v, 10)
+    assert k == 2 and (lab[:n] == 0).all() and (lab[n:] == 1).all()
+    _say(f"[gpu]   {1e6 * t:.0f} us, the bodies alone {1e6 * alone:.0f} us")
+    assert t < 25.0 * alone  # (2 to 3 times; 500 times and more with one search a clique)
 
 
 @pytest.mark.parametrize("d,ball,few,many", [(3, 1700, 10, 100), (2, 4000, 100, 1000)])
