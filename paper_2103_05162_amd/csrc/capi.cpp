@@ -917,6 +917,8 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
     st.mark("core");
     launch_core(ta, dim, densebox, s);
     if (!densebox) launch_core_boxes(ta, s);
+    else launch_cell_sets(ta, dim, at<int>(ws, plan.cell_start), at<uint8_t>(ws, plan.cell_dense),
+                          misc + kMiscNumCells, at<int>(ws, plan.cand), s);
   }
   if (densebox) {
     st.mark("main_cells");
@@ -1169,6 +1171,8 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   ta.brec_cap = static_cast<int>(plan.brec_cap / 8);  // per shard
   launch_core(ta, dim, densebox, s);
   if (!densebox) launch_core_boxes(ta, s);
+  else launch_cell_sets(ta, dim, at<int>(ws, plan.cell_start), at<uint8_t>(ws, plan.cell_dense), misc + kMiscNumCells,
+                        at<int>(ws, plan.cand), s);
   if (densebox) {
     st.mark("main_cells");
     launch_main(ta, dim, true, false, first_border, 1, s);

@@ -347,6 +347,10 @@ __device__ __forceinline__ void lookup_bricks(const CellIndex& ix, const CellGri
   }
 }
 
+// Cells outside dense ones of this many points or more are looked up as sets (TravArgs::
+// cell_sets).
+constexpr int kSetCell = 8;
+
 // The primitives [first, last) of cell c, and whether it is a dense cell (one
 // primitive). cell_prim holds a dense cell's primitive as its complement; the entry
 // after the last cell is the number of primitives.
@@ -403,12 +407,13 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int k) {
 
 // Hands the primitives above `mask` in the box's cells to visit_lanes(r), called on
 // the whole wavefront with a primitive per lane (-1: none); visit_lanes returns true
-// (uniformly) to stop. list: kBoxList ints of the wavefront's LDS.
+// (uniformly) to stop. pass(c), called for a cell of kSetCell primitives or more, says
+// that all of them can be left out. list: kBoxList ints of the wavefront's LDS.
 constexpr int kBoxList = 512;
 
-template <int D, typename F>
+template <int D, typename F, typename P>
 __device__ __forceinline__ void box_candidates(const CellIndex& ix, const CellGrid& g, const CellBox<D>& b, int mask,
-                                               int* list, F&& visit_lanes) {
+                                               int* list, F&& visit_lanes, P&& pass) {
   constexpr int S = kLevelShift<D>;
   const int lane = lane_id();
   int b0[3] = {0, 0, 0}, nb[3] = {1, 1, 1};
@@ -454,7 +459,10 @@ __device__ __forceinline__ void box_candidates(const CellIndex& ix, const CellGr
       for (int q = 0; q < cnt; q += 64) {
         int cur = 0, end = 0;
         bool dense;
-        if (q + lane < cnt) cell_prims(ix, list[q + lane], cur, end, dense);
+        if (q + lane < cnt) {
+          cell_prims(ix, list[q + lane], cur, end, dense);
+          if (end - cur >= kSetCell && pass(list[q + lane])) cur = end;
+        }
         cur = max(cur, mask + 1);
         while (ballot(cur < end)) {
           const int r = cur < end ? cur : -1;
@@ -587,9 +595,10 @@ __device__ __forceinline__ bool cell_walk_done(const CellWalk<D>& w) {
   return w.cur >= w.end && w.left == 0 && w.next >= w.bricks;
 }
 
-// The next primitive of the walk, or -1 (also where a cell has none above the mask).
-template <int D, bool MASKED>
-__device__ __forceinline__ int cell_walk_step(CellWalk<D>& w, const CellIndex& ix, int mask, char* lds) {
+// The next primitive of the walk, or -1 (also where a cell has none above the mask, or
+// pass(c) has it left out, as in box_candidates).
+template <int D, bool MASKED, typename P>
+__device__ __forceinline__ int cell_walk_step(CellWalk<D>& w, const CellIndex& ix, int mask, char* lds, P&& pass) {
   if (w.cur >= w.end) {
     if (w.left == 0 && w.next < w.bricks) {
       w.word = (reinterpret_cast<const uint64_t*>(lds) + lane_id())[64 * w.next];
@@ -602,7 +611,9 @@ __device__ __forceinline__ int cell_walk_step(CellWalk<D>& w, const CellIndex& i
       const uint64_t below = w.left ^ (w.left - 1);  // the lowest bit left and those under it
       w.left &= w.left - 1;
       bool dense;
-      cell_prims(ix, w.base + __popcll(w.word & (below >> 1)), w.cur, w.end, dense);
+      const int c = w.base + __popcll(w.word & (below >> 1));
+      cell_prims(ix, c, w.cur, w.end, dense);
+      if (w.end - w.cur >= kSetCell && pass(c)) w.cur = w.end;
       if (MASKED) w.cur = max(w.cur, mask + 1);
     }
   }

@@ -90,6 +90,7 @@ struct GridPlan {
   float lo[3];         // the scene's low corner
   int32_t axis_bits[3];  // key bits of each axis (FDbscan's curve: its own for each)
   int32_t curve_sampled;  // the curve's cells follow a sample of the points (kCurveKnots)
+  int32_t sets;          // a batch: some cloud's minPts is worth TravArgs::cell_sets
   double curve_inv[3];   // FDbscan's curve: 1 / cell side of each axis
   uint64_t supers;     // supers of the grid (a batch: of all its grids)
 };
@@ -227,6 +228,10 @@ void densebox_cells(const void* sorted_keys, bool key64, const int* d_key64, int
                     int* ends = nullptr, int* minorig = nullptr, int* border_n = nullptr);
 
 // k_trav.hip
+// With minPts up to this a cell that is not dense has too few points for TravArgs::
+// cell_sets to be worth it.
+constexpr int kSetMinPts = 16;
+
 struct TravArgs {
   TreeView t;
   const float* xs;  // sorted SoA coordinates: x[n], y[n], z[n]
@@ -273,6 +278,10 @@ struct TravArgs {
   const int* dense_list;  // dense-cell primitive indices
   const int* d_ndense;    // their number (device)
   CellIndex ix;           // DenseBox: the grid's cells; ix.plan->grid_on says whether the walks go through it
+  // DenseBox, or null: of each cell of kSetCell points or more that is not dense, once the
+  // core pass is done: its first core point, all of them being in one set (kSetWhole added
+  // where all its points are core), -2: it has none, -1: unknown
+  const int* cell_sets;
   // batches (null pkeys = one cloud): cloud of sorted point i = pkeys[i] >> key_shift;
   // per cloud: first node and last primitive of its subtree, eps^2, minPts
   const uint64_t* pkeys;
@@ -286,6 +295,9 @@ struct TravArgs {
   int block;
 };
 void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s);
+// Fills cell_sets (its memory: sets) where minPts makes it worth it, after the core pass.
+void launch_cell_sets(TravArgs& a, int dim, const int* cell_start, const uint8_t* cell_dense, const int* d_cells,
+                      int* sets, hipStream_t s);
 // FDbscan's cliques (subtrees of core points pairwise within eps): found, marked in labels
 // and core, listed in cliques, before the core pass and, of fewer than minPts points each,
 // after it; then joined to what is within reach of them.

@@ -181,6 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restri
   if (flags & (kCloudBadParams | kCloudBadRange)) atomicOr(info, FDB_INFO_BAD_PARAMS);
   cl_eps2[c] = ec * ec;
   cl_minpts[c] = mc;
+  if (densebox && mc > kSetMinPts) atomicOr(&plan->sets, 1);
   const uint32_t maxq = (1u << bpd) - 1u;
   float lo[3] = {0.0f, 0.0f, 0.0f}, hi[3] = {0.0f, 0.0f, 0.0f}, sc[3] = {0.0f, 0.0f, 0.0f};
   for (int k = 0; k < D; ++k) {

@@ -1277,6 +1277,10 @@ __device__ __forceinline__ char* search_lds(char* base) {
   return base + (threadIdx.x >> 6) * kSearchLds<D, G>;
 }
 
+struct EveryCell {
+  __device__ __forceinline__ bool operator()(int) const { return false; }
+};
+
 template <int D, bool B, bool MASKED, bool G, bool NEAR = false>
 struct Walker {
   using State = std::conditional_t<G, CellWalk<D>, Walk>;
@@ -1301,9 +1305,9 @@ struct Walker {
     if constexpr (G) return cell_walk_done(w);
     else return walk_done(w);
   }
-  template <typename QT>
-  __device__ __forceinline__ int step(const TravArgs& a, int m, const QT& q, float eps2, int mask) {
-    if constexpr (G) return cell_walk_step<D, MASKED>(w, a.ix, mask, lds);
+  template <typename QT, typename P = EveryCell>
+  __device__ __forceinline__ int step(const TravArgs& a, int m, const QT& q, float eps2, int mask, P&& pass = P{}) {
+    if constexpr (G) return cell_walk_step<D, MASKED>(w, a.ix, mask, lds, pass);
     else return walk_step<D, MASKED>(w, a.t, m, q, eps2, mask, a.info);
   }
 };
@@ -1458,6 +1462,72 @@ __global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_core_dbx(TravA
     if (blockIdx.x == 0 && threadIdx.x == 0) a.border_n[kWalkShare] = static_cast<int>(c.chunk);
     for (; c.in(); c.next()) core_query<D, B, G>(a, m, c.query(), c.xcd * c.chunk, s_dyn, s_w);
   });
+}
+
+// The core points of a cell are within eps of each other (their tight box passes the test, as
+// a dense cell's does), so they are one set: with a large minPts cells that are not dense
+// hold many, all of which a walk would meet and look up, query by query. Eight lanes a cell.
+// Main
+// phases of 200,000 evenly spread points, us, walked point by point / with sets (as packets
+// through the hierarchy): 3D, minPts 300 of 1500 neighbours 4660 / 1080 (4550), 1000 of 4000
+// 10,910 / 2660 (10,730); 1,000 places of 300 equal points in 2D, minPts 2000, 1580 / 720
+// (348).
+constexpr int kSetWhole = 1 << 30;
+
+template <int D, bool B>
+__global__ __launch_bounds__(256) void k_cell_sets(TravArgs a, const int* __restrict__ cell_start,
+                                                   const uint8_t* __restrict__ dense, const int* __restrict__ d_cells,
+                                                   int* __restrict__ sets) {
+  constexpr int G = 8;
+  if (!a.ix.plan->grid_on || (B && !a.ix.plan->sets)) return;
+  const int ncells = *d_cells;
+  const int sub = threadIdx.x & (G - 1);
+  for (int64_t c0 = blockIdx.x * int64_t(256 / G); c0 < ncells; c0 += int64_t(gridDim.x) * (256 / G)) {
+    const int64_t c = c0 + threadIdx.x / G;
+    const int s = c < ncells ? cell_start[c] : 0, e = c < ncells ? cell_start[c + 1] : 0;
+    if (e - s < kSetCell || dense[c]) continue;  // (a cell's lanes go together)
+    int rep = 0x7fffffff, cnt = 0;
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int i = s + sub; i < e; i += G) {
+      if (!a.core[i]) continue;
+      rep = min(rep, i);
+      ++cnt;
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        const float v = a.xs[k * a.n + i];
+        lo[k] = fminf(lo[k], v);
+        hi[k] = fmaxf(hi[k], v);
+      }
+    }
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+      rep = min(rep, __shfl_xor(rep, off));
+      cnt += __shfl_xor(cnt, off);
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        lo[k] = fminf(lo[k], __shfl_xor(lo[k], off));
+        hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off));
+      }
+    }
+    if (D == 2) lo[2] = hi[2] = 0.0f;
+    const float eps2 = B ? a.cloud_eps2[cloud_of(a, s)] : a.eps2;
+    const bool one = cnt > 0 && dist2v<D>(hi[0], hi[1], hi[2], lo[0], lo[1], lo[2]) <= eps2;
+    if (one)
+      for (int i = s + sub; i < e; i += G)
+        // (a root hangs under the first core point whether that is a root or not)
+        if (i != rep && a.core[i] && cas_agent(a.labels + i, i, rep) != i) uf_union(a.labels, rep, i, a.info);
+    if (sub == 0) sets[c] = cnt == 0 ? -2 : one ? rep + (cnt == e - s ? kSetWhole : 0) : -1;
+  }
+}
+
+// May a core query in the set of root pass over cell c, all of whose core points are in its
+// set (or which has none)? First claim: and which has no others to claim.
+template <bool FIRST, bool B>
+__device__ __forceinline__ bool cell_known(const TravArgs& a, int c, int root) {
+  if (!a.cell_sets || (B && !a.ix.plan->sets)) return false;
+  const int v = a.cell_sets[c];
+  if (v < 0) return !FIRST && v == -2;
+  return !(FIRST && v < kSetWhole) && known_same_set(a.labels, v & (kSetWhole - 1), root);
 }
 
 // Do the dense cells hold kLargeCell points or more on average (m primitives, nd dense
@@ -1623,7 +1693,7 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
         }
       }
       return false;
-    });
+    }, [&](int c) { return common && cell_known<FIRST, B>(a, c, r); });
   };
   const uint64_t mm = ballot(mine);
   if (!mm) return;
@@ -1637,8 +1707,9 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
                                   const int ll = 63 - __clzll(static_cast<unsigned long long>(lanes));
                                   const int pmin = __builtin_amdgcn_readlane(p, fl);
                                   packet(lanes, lo, hi, readlane_f(sc.eps2, fl), __builtin_amdgcn_readlane(p, ll),
-                                         [&](auto&& visit) {
-                                           box_candidates<D>(a.ix, g, box, pmin, reinterpret_cast<int*>(lds), visit);
+                                         [&](auto&& visit, auto&& pass) {
+                                           box_candidates<D>(a.ix, g, box, pmin, reinterpret_cast<int*>(lds), visit,
+                                                             pass);
                                          });
                                 }) >> lane) & 1;
   } else if constexpr (!FIRST && !G) {
@@ -1665,7 +1736,7 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
     const float ext_max = __popcll(mm) <= kPointsFewQueries ? kPointsFewExt : kPointsPacketExt;
     if (!ballot(other_cloud) && ext * ext <= ext_max * ext_max * ps.eps2) {
       uint32_t* stack = s_pstack + (threadIdx.x >> 6) * kWideStack;
-      packet(mm, lo, hi, ps.eps2, __shfl(p, 63), [&](auto&& visit) {
+      packet(mm, lo, hi, ps.eps2, __shfl(p, 63), [&](auto&& visit, auto&&) {
         traverse_box_wide_lanes<D>(a.t, m, ps, lo, hi, pmin, a.t.leaf_size, a.info, stack, visit);
       });
       return;
@@ -1679,7 +1750,7 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
   while (ballot(active)) {
     int pend = -1, pcnt = 0;  // a dense cell to scan: its first point and its size
     if (active) {
-      const int r = w.step(a, m, q, sc.eps2, p);
+      const int r = w.step(a, m, q, sc.eps2, p, [&](int c) { return ci && cell_known<FIRST, B>(a, c, root); });
       if (r >= 0) {
         const float4 lr = a.prim_lo[r];
         const int s = rec_index(lr);
@@ -2226,6 +2297,22 @@ void launch_core(const TravArgs& a, int dim, bool densebox, hipStream_t s) {
     if (B) core_t<2, true>(a, densebox, s);
     else core_t<2, false>(a, densebox, s);
   }
+}
+
+void launch_cell_sets(TravArgs& a, int dim, const int* cell_start, const uint8_t* cell_dense, const int* d_cells,
+                      int* sets, hipStream_t s) {
+  a.cell_sets = nullptr;
+  const bool B = a.pkeys != nullptr;
+  if (a.n < kSetCell || (!B && a.min_pts <= kSetMinPts)) return;
+  const dim3 g(static_cast<unsigned>(std::min<int64_t>(4096, ceil_div(a.n, 256 / 8)))), b(256);
+  if (dim == 3) {
+    if (B) hipLaunchKernelGGL((k_cell_sets<3, true>), g, b, 0, s, a, cell_start, cell_dense, d_cells, sets);
+    else hipLaunchKernelGGL((k_cell_sets<3, false>), g, b, 0, s, a, cell_start, cell_dense, d_cells, sets);
+  } else {
+    if (B) hipLaunchKernelGGL((k_cell_sets<2, true>), g, b, 0, s, a, cell_start, cell_dense, d_cells, sets);
+    else hipLaunchKernelGGL((k_cell_sets<2, false>), g, b, 0, s, a, cell_start, cell_dense, d_cells, sets);
+  }
+  a.cell_sets = sets;
 }
 
 void launch_main(const TravArgs& a, int dim, bool densebox, bool all_core, bool first_border, int part,
