@@ -405,6 +405,34 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int k) {
          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), k));
 }
 
+// Hands each lane's primitives [cur, end) to visit_lanes(r), called on the whole wavefront
+// with a primitive per lane (-1: none); true when visit_lanes said (uniformly) to stop.
+// Lanes step through kStepRange of their own, and what is left of a range goes over all
+// lanes: a cell that is not dense can hold thousands of points (a large minPts, or a scene
+// so wide that the rounding of its cells' edges puts a box past the guard), and the other
+// lanes would wait for it. Dense-cell and point main phases of 500,000 points in 2D, scales
+// log-uniform over six decades, us: 2091 + 2196 by steps alone, 174 + 289 so. (One call
+// of visit_lanes: a second copy of its code cost 2 to 3% of calls that never take it.)
+constexpr int kStepRange = 64;
+template <typename F>
+__device__ __forceinline__ bool visit_ranges(int cur, int end, F&& visit_lanes) {
+  for (int step = 0;; ++step) {
+    const uint64_t left = ballot(cur < end);
+    if (!left) return false;
+    int r = cur < end ? cur : -1;
+    if (step < kStepRange) {
+      ++cur;
+    } else {
+      const int L = __ffsll(static_cast<unsigned long long>(left)) - 1;
+      const int first = __builtin_amdgcn_readlane(cur, L);
+      if (cur == first) cur += 64;  // (lane L alone: ranges are apart)
+      r = first + lane_id();
+      if (r >= __builtin_amdgcn_readlane(end, L)) r = -1;
+    }
+    if (visit_lanes(r)) return true;
+  }
+}
+
 // Hands the primitives above `mask` in the box's cells to visit_lanes(r), called on
 // the whole wavefront with a primitive per lane (-1: none); visit_lanes returns true
 // (uniformly) to stop. pass(c), called for a cell of kSetCell primitives or more, says
@@ -463,12 +491,7 @@ __device__ __forceinline__ void box_candidates(const CellIndex& ix, const CellGr
           cell_prims(ix, list[q + lane], cur, end, dense);
           if (end - cur >= kSetCell && pass(list[q + lane])) cur = end;
         }
-        cur = max(cur, mask + 1);
-        while (ballot(cur < end)) {
-          const int r = cur < end ? cur : -1;
-          ++cur;
-          if (visit_lanes(r)) return;
-        }
+        if (visit_ranges(max(cur, mask + 1), end, visit_lanes)) return;
       }
       cnt = 0;
       if (!todo) break;

@@ -1813,8 +1813,11 @@ __device__ __forceinline__ void points_query(const TravArgs& a, int m, int p, ch
   if (G) hits_join(hits, labels, root, a.info);
 }
 
+// (In 2D the grid's walks fit six wavefronts a SIMD with 80 registers; 81, which the compiler
+// takes when left alone, cost 1% of 1M points.)
 template <int D, bool ALL_CORE, bool FIRST, bool B, int W>
-__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_main_dbx_points(TravArgs a) {
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256, D == 2 && W == kGrid && !B ? 6 : 1) void k_main_dbx_points(
+    TravArgs a) {
   extern __shared__ __align__(16) char s_dyn[];
   with_walk<W>(a, [&](auto grid) {
     constexpr bool G = decltype(grid)::value;
@@ -1889,8 +1892,7 @@ __device__ __forceinline__ void cells_near_box_lanes(const CellIndex& ix, const 
     int cur = 0, end = 0;
     bool dense;
     if (q + lane < cnt) cell_prims(ix, list[q + lane], cur, end, dense);
-    cur = max(cur, A + 1);
-    while (ballot(cur < end)) visit_lanes(cur < end ? cur++ : -1);
+    visit_ranges(max(cur, A + 1), end, visit_lanes);
   }
 }
 
