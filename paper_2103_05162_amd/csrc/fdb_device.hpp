@@ -87,13 +87,6 @@ __device__ __forceinline__ float boxbox_dist2(const float* alo, const float* ahi
   return s;
 }
 
-// Ends the optimiser's knowledge of v. For a value that lanes leave a divergent loop
-// with, before it is tested: this compiler reuses the condition register that the
-// loop's own exit test left, which only holds the lanes of the last iteration (seen
-// with a count that a loop both stopped at and was tested for after: lanes that had
-// left earlier read 0).
-__device__ __forceinline__ void settle(int& v) { asm volatile("" : "+v"(v)); }
-
 // ---- agent-scope atomics -----------------------------------------------------
 // On gfx950 each XCD has its own L2; agent-scope atomic loads and stores bypass it
 // (sc1), so values written by a workgroup on another XCD are seen within the

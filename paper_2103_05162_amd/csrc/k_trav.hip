@@ -1368,7 +1368,6 @@ __device__ __forceinline__ int lane_count_near(const float* __restrict__ xs, int
     for (int u = 0; u < 4; ++u)
       if (j + u < c && dist2v<D>(v[u][0], v[u][1], v[u][2], q.x, q.y, q.z) <= eps2) ++found;
   }
-  settle(found);
   return found;
 }
 
@@ -1383,7 +1382,6 @@ __device__ __forceinline__ bool lane_cells_touch(const float* __restrict__ xs, i
     if (box_dist2<D>(q.x, q.y, q.z, blo.x, blo.y, blo.z, bhi.x, bhi.y, bhi.z) <= eps2)
       hits = cell_within<D>(blo, bhi, q, eps2) ? 1 : lane_count_near<D>(xs, n, sb, nb, q, eps2);
   }
-  settle(hits);
   return hits != 0;
 }
 
