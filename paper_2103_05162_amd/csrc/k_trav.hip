@@ -1449,8 +1449,10 @@ __device__ __forceinline__ void core_query(const TravArgs& a, int m, int p, int6
   core_epilogue(a, mine, i, p, cnt, sc.min_pts, rec, s_w, first);
 }
 
+// (The hierarchy's walks at eight wavefronts a SIMD; seven, which the scalar registers that the
+// compiler takes when left alone allow, took 804 us for 734 on 2M points with a far one.)
 template <int D, bool B, int W>
-__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256) void k_core_dbx(TravArgs a) {
+__global__ __launch_bounds__(W == kHierarchy ? 1024 : 256, W == kHierarchy ? 8 : 1) void k_core_dbx(TravArgs a) {
   __shared__ int s_w[17];
   extern __shared__ __align__(16) char s_dyn[];  // the walk's columns, then neighbour records
   with_walk<W>(a, [&](auto grid) {
