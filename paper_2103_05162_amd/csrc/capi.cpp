@@ -1,13 +1,15 @@
 // C ABI of libfdbscan and the launch sequence of one clustering call.
 //
-// FDbscan (Section 4.1): bounds -> Morton keys -> radix sort -> gather to SoA ->
-// LBVH (Karras hierarchy, ropes, refit) -> core pass if minPts > 2 (early exit
-// at minPts) -> fused masked traversal with union-find -> finalisation ->
-// canonical ids (and the border pass) -> scatter to input order.
-// FDbscan-DenseBox (Section 4.2): bounds (read back once to size the grid) ->
-// grid-cell keys -> radix sort -> gather -> dense cells + mixed primitives ->
-// LBVH over the primitives -> core pass over points outside dense cells ->
-// fused traversal -> the same tail.
+// FDbscan (Section 4.1): bounds -> keys of a curve as fine as eps asks for -> radix sort
+// -> gather to SoA -> LBVH (Karras hierarchy with its boxes, ropes) -> cliques -> core
+// pass if minPts > 2 (early exit at minPts) -> boxes of core points -> fused masked
+// traversal with union-find -> finalisation -> canonical ids (and the border pass) ->
+// scatter to input order.
+// FDbscan-DenseBox (Section 4.2): bounds -> the grid's plan, made on the device ->
+// grid-cell keys -> radix sort -> gather -> dense cells + mixed primitives + the index of
+// occupied cells (or, where the grid is too wide for it, an LBVH over the primitives) ->
+// core pass over points outside dense cells -> sets of core points in cells that are not
+// dense -> fused traversal -> the same tail.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -859,7 +861,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
                    at<float4>(ws, plan.cell_lo), at<float4>(ws, plan.cell_hi), at<int>(ws, plan.pflag),
                    at<int>(ws, plan.prim_start), at<int>(ws, plan.prim_cnt),
                    at<float4>(ws, plan.prim_lo), at<float4>(ws, plan.prim_hi), at<uint64_t>(ws, plan.prim_key),
-                   at<int>(ws, plan.dense_list), lab, core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, ix, 0,
+                   at<int>(ws, plan.dense_list), lab, core, misc, at<int>(ws, plan.bsums), s, ix, 0,
                    nullptr, nullptr, 0, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
   }
   h->last_densebox = densebox;
@@ -869,7 +871,7 @@ fdb_status dbscan_launch(fdb_handle* h, const SingleArgs& args, const fdb_option
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s,
-               at<float4>(ws, plan.cut), misc + kMiscCut, true, kCutDiv, &gplan->grid_on);
+               at<float4>(ws, plan.cut), misc + kMiscCut, true, &gplan->grid_on);
     ta.t.m_cap = static_cast<int>(n);
     ta.t.d_m = misc + kMiscNumPrims;
     ta.t.cut = at<float4>(ws, plan.cut);
@@ -1087,9 +1089,9 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
   batch_keys(points, offsets, num_clouds, n, dim, cl_lo, cl_scale, bpd, shift, static_cast<uint64_t*>(keys[0]),
              vals[0], shift + cb, at<uint32_t>(ws, plan.hist), ix.supers, gplan, s);
   st.mark("sort");
-  const int cur = radix_sort(keys[0], keys[1], vals[0], vals[1], n, true, shift + cb, at<uint32_t>(ws, plan.hist), true,
-                             at<uint32_t>(ws, plan.pass_plan), at<uint32_t>(ws, plan.tilectr),
-                             at<uint64_t>(ws, plan.status), h->d_info, s);
+  const int cur = radix_sort(static_cast<uint64_t*>(keys[0]), static_cast<uint64_t*>(keys[1]), vals[0], vals[1], n,
+                             shift + cb, at<uint32_t>(ws, plan.hist), at<uint32_t>(ws, plan.pass_plan),
+                             at<uint32_t>(ws, plan.tilectr), at<uint64_t>(ws, plan.status), h->d_info, s);
   const uint32_t* perm = vals[cur];
   const uint64_t* pkeys = static_cast<const uint64_t*>(keys[cur]);
   st.mark("permute");
@@ -1128,14 +1130,14 @@ fdb_status batched_launch(fdb_handle* h, const BatchArgs& args, const fdb_option
                    at<float4>(ws, plan.cell_hi), at<int>(ws, plan.pflag),
                    at<int>(ws, plan.prim_start), at<int>(ws, plan.prim_cnt), at<float4>(ws, plan.prim_lo),
                    at<float4>(ws, plan.prim_hi), at<uint64_t>(ws, plan.prim_key), at<int>(ws, plan.dense_list), lab,
-                   core, misc, at<int>(ws, plan.bsums), plan.scan_blocks, s, ix, shift, cl_minpts,
+                   core, misc, at<int>(ws, plan.bsums), s, ix, shift, cl_minpts,
                    cl_eps2, num_clouds, at<int>(ws, plan.ends), at<int>(ws, plan.minorig), at<int>(ws, plan.hist));
     st.mark("lbvh");
     build_lbvh(at<void>(ws, plan.prim_key), nullptr, static_cast<int>(n), dim, xs, n, at<float4>(ws, plan.prim_lo),
                at<float4>(ws, plan.prim_hi), at<float4>(ws, plan.node_a), at<float4>(ws, plan.node_b),
                at<int>(ws, plan.rope), at<int>(ws, plan.leaf_rope), at<int>(ws, plan.ends),
                at<int>(ws, plan.other), at<int>(ws, plan.gamma), misc + kMiscNumPrims, h->d_info, s, nullptr,
-               nullptr, true, kCutDiv, &gplan->grid_on);
+               nullptr, true, &gplan->grid_on);
     batch_roots(offsets, num_clouds, n, at<int>(ws, plan.cand), misc + kMiscNumPrims, at<int>(ws, plan.other),
                 cl_root, cl_end, h->d_info, &gplan->grid_on, s);
     ta.ix = ix;

@@ -11,8 +11,9 @@ struct fdb_handle;
 namespace fdb {
 
 // Keys per thread in a radix pass, by key width (measured: 64-bit keys fit two
-// 6144-key tiles per CU in LDS; 32-bit keys do best at 5120). The workspace
-// sizes the look-back status for the tile taken (sort_status_words).
+// 6144-key tiles per CU in LDS; 32-bit keys do best at 5632, two rounds of the 768
+// tiles resident at once for 8M of them). Small inputs take fewer (k_sort.hip). The
+// workspace sizes the look-back status for the tile taken (sort_status_words).
 template <typename K>
 constexpr int sort_items() { return sizeof(K) == 8 ? 24 : 22; }
 constexpr int kScanItems = 16;                 // items per thread in the device scan
@@ -141,8 +142,9 @@ struct TreeView {
 constexpr int kCutMax = 8192;
 constexpr int kCutDiv = 256;      // the cut holds about kCutDiv to 2 kCutDiv subtrees
 constexpr int kCutUnroll = 4;     // cut entries a lane loads at once
-__host__ __device__ inline int cut_span(int m, int div = kCutDiv) {
-  return (m + div - 1) / div > 64 ? (m + div - 1) / div : 64;
+__host__ __device__ inline int cut_span(int m) {
+  const int span = (m + kCutDiv - 1) / kCutDiv;
+  return span > 64 ? span : 64;
 }
 
 // ---- launch helpers (stream-ordered, asynchronous) --------------------------
@@ -179,15 +181,14 @@ void launch_gridkeys(const float* pts, int64_t n, int dim, const uint32_t* bound
 void launch_permute(const float* pts, int64_t n, int dim, const uint32_t* perm, float* xs, uint32_t* info,
                     hipStream_t s);
 
-// k_sort.hip: LSD radix sort of (key, index) pairs over the low `bits` bits.
-// hist_ready: hist already holds the digit counts of every pass (from the key
-// kernel). pass_plan: 8 words (which passes run: one over a constant digit need not).
-// The tile counters (16 words)
-// and look-back words (sort_status_words) are cleared here unless the caller has
-// (clear = false). Returns which of the two buffers holds the result (0 or 1).
-int radix_sort(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, bool key64, int bits,
-               uint32_t* hist, bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status,
-               uint32_t* info, hipStream_t s, bool clear = true);
+// k_sort.hip: LSD radix sort of (64-bit key, index) pairs over the low `bits` bits (a
+// batch's). hist holds the digit counts of every pass, from the key kernel. pass_plan: 8
+// words (which passes run: one over a constant digit need not). The tile counters (16
+// words) and look-back words (sort_status_words) are cleared here. Returns which of the
+// two buffers holds the result (0 or 1).
+int radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, int bits,
+               const uint32_t* hist, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status, uint32_t* info,
+               hipStream_t s);
 int64_t sort_status_words(int64_t n, bool key64);
 // The same with key width and pass count taken from a GridPlan on the device:
 // passes for both widths are launched and those the plan does not call for exit
@@ -208,8 +209,7 @@ int64_t planned_status_words(int64_t n);
 void build_lbvh(const void* keys, const int* d_key64, int m, int dim, const float* xs, int64_t n_pts,
                 const float4* prim_lo, const float4* prim_hi, float4* node_a, float4* node_b, int* rope,
                 int* leaf_rope, int* ends, int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s,
-                float4* cut = nullptr, int* cut_n = nullptr, bool ends_ready = false, int cut_div = kCutDiv,
-                const int* d_skip = nullptr);
+                float4* cut = nullptr, int* cut_n = nullptr, bool ends_ready = false, const int* d_skip = nullptr);
 
 // k_dense.hip
 // sorted_keys are 64-bit words when key64 (or, with d_key64 set, when *d_key64 on
@@ -223,7 +223,7 @@ void densebox_cells(const void* sorted_keys, bool key64, const int* d_key64, int
                     float eps2, int min_pts, int* cell_id, int* cell_start, int* cand, uint8_t* cell_dense,
                     float4* cell_lo, float4* cell_hi, int* pflag, int* prim_start, int* prim_cnt, float4* prim_lo,
                     float4* prim_hi, uint64_t* prim_key, int* dense_list, int* labels, uint8_t* core, int* misc,
-                    int* bsums, int64_t scan_blocks, hipStream_t s, const CellIndex& ix, int key_shift = 0,
+                    int* bsums, hipStream_t s, const CellIndex& ix, int key_shift = 0,
                     const int* cl_minpts = nullptr, const float* cl_eps2 = nullptr, int num_clouds = 0,
                     int* ends = nullptr, int* minorig = nullptr, int* border_n = nullptr);
 
@@ -325,8 +325,7 @@ void launch_core_from_sets(const int* labels, uint8_t* core, int64_t n, int min_
 void launch_check_forest(const int* labels, const uint8_t* core, int64_t n, uint32_t* bad, uint32_t* info,
                          hipStream_t s);
 // Canonical cluster ids (ids 0..K-1 in increasing order of each cluster's
-// smallest core input index). bits: ceil(n/32) leader words followed by as many
-// ints of scratch (fits the n-int lflag array); wpre: ceil(n/32) ints.
+// smallest core input index). bits: ceil(n/32) leader words; wpre: ceil(n/32) ints.
 // minorig_ready: launch_finalize already filled minorig and cleared the leader words.
 void canonical_ids(const int* labels, const uint8_t* core, const uint32_t* perm, int64_t n, int* minorig,
                    uint32_t* bits, int* wpre, int* bsums, int* cid, int* d_k, hipStream_t s,

@@ -501,14 +501,14 @@ __global__ __launch_bounds__(kBlock) void k_bricks(KeyIn keys, CloudParams cp, c
 }
 
 // Tight box of each listed cell of more than kSmallCell points, a wavefront per
-// cell (G = 64 lanes), then the guard.
-
-template <int D, int G>
+// cell, then the guard.
+template <int D>
 __global__ __launch_bounds__(kBlock) void k_cell_boxes(const float* __restrict__ xs, int64_t n,
                                                        const int* __restrict__ cell_start, const int* __restrict__ cand,
                                                        const int* __restrict__ num_cand, float eps2_all,
                                                        CloudParams cp, uint8_t* __restrict__ dense,
                                                        float4* __restrict__ cell_lo, float4* __restrict__ cell_hi) {
+  constexpr int G = 64;
   const int sub = threadIdx.x & (G - 1);
   const int grp = (blockIdx.x * kBlock + threadIdx.x) / G;
   const int ngrp = (gridDim.x * kBlock) / G;
@@ -516,7 +516,6 @@ __global__ __launch_bounds__(kBlock) void k_cell_boxes(const float* __restrict__
   for (int w = grp; w < ncand; w += ngrp) {
     const int c = cand[w];
     const int s = cell_start[c], e = cell_start[c + 1];
-    if ((e - s > kSmallCell) != (G == 64)) continue;  // the other launch takes it
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     // four G-point chunks per trip: their loads are in flight together
     for (int j0 = s + sub; j0 < e; j0 += 4 * G) {
@@ -555,9 +554,8 @@ __global__ __launch_bounds__(kBlock) void k_cell_boxes(const float* __restrict__
 void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2, int min_pts, int* cell_id,
              int* cell_start, int* cand, uint8_t* dense, float4* cell_lo, float4* cell_hi, int* pflag,
              int* prim_start, int* prim_cnt, float4* prim_lo, float4* prim_hi, uint64_t* prim_key, int* dense_list,
-             int* labels, uint8_t* core, int* misc, int* bsums, int64_t scan_blocks, const CloudParams& cp,
+             int* labels, uint8_t* core, int* misc, int* bsums, const CloudParams& cp,
              hipStream_t s, int* ends, int* minorig, int* border_n, const CellIndex& ix, int num_clouds) {
-  (void)scan_blocks;
   int* d_cells = misc + kMiscNumCells;
   int* d_big = misc + kMiscNumCand;  // candidate cells of more than kSmallCell points
   int* d_prims = misc + kMiscNumPrims;
@@ -579,12 +577,12 @@ void cells_t(const KeyIn& keys, int64_t n, int dim, const float* xs, float eps2,
   if (dim == 3) {
     hipLaunchKernelGGL(k_cells_small<3>, dim3(gs), dim3(kBlock), 0, s, xs, n, cell_start, d_cells, min_pts, eps2, cp,
                        dense, cell_lo, cell_hi, big, d_big);
-    hipLaunchKernelGGL((k_cell_boxes<3, 64>), dim3(gb), dim3(kBlock), 0, s, xs, n, cell_start, big, d_big, eps2, cp,
+    hipLaunchKernelGGL(k_cell_boxes<3>, dim3(gb), dim3(kBlock), 0, s, xs, n, cell_start, big, d_big, eps2, cp,
                        dense, cell_lo, cell_hi);
   } else {
     hipLaunchKernelGGL(k_cells_small<2>, dim3(gs), dim3(kBlock), 0, s, xs, n, cell_start, d_cells, min_pts, eps2, cp,
                        dense, cell_lo, cell_hi, big, d_big);
-    hipLaunchKernelGGL((k_cell_boxes<2, 64>), dim3(gb), dim3(kBlock), 0, s, xs, n, cell_start, big, d_big, eps2, cp,
+    hipLaunchKernelGGL(k_cell_boxes<2>, dim3(gb), dim3(kBlock), 0, s, xs, n, cell_start, big, d_big, eps2, cp,
                        dense, cell_lo, cell_hi);
   }
   // a batch reads every point's primitive index afterwards (in cand, which the
@@ -616,13 +614,13 @@ void densebox_cells(const void* sorted_keys, bool key64, const int* d_key64, int
                     float eps2, int min_pts, int* cell_id, int* cell_start, int* cand, uint8_t* cell_dense,
                     float4* cell_lo, float4* cell_hi, int* pflag, int* prim_start, int* prim_cnt, float4* prim_lo,
                     float4* prim_hi, uint64_t* prim_key, int* dense_list, int* labels, uint8_t* core, int* misc,
-                    int* bsums, int64_t scan_blocks, hipStream_t s, const CellIndex& ix, int key_shift,
+                    int* bsums, hipStream_t s, const CellIndex& ix, int key_shift,
                     const int* cl_minpts, const float* cl_eps2, int num_clouds, int* ends, int* minorig, int* border_n) {
   // per-cloud parameters come with batches, whose keys are always 64-bit
   CloudParams cp{static_cast<const uint64_t*>(sorted_keys), key_shift, cl_minpts, cl_eps2};
   const KeyIn keys{sorted_keys, d_key64, key64 ? 1 : 0};
   cells_t(keys, n, dim, xs, eps2, min_pts, cell_id, cell_start, cand, cell_dense, cell_lo, cell_hi, pflag, prim_start,
-          prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels, core, misc, bsums, scan_blocks, cp, s, ends,
+          prim_cnt, prim_lo, prim_hi, prim_key, dense_list, labels, core, misc, bsums, cp, s, ends,
           minorig, border_n, ix, num_clouds);
 }
 

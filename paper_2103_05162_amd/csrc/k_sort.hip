@@ -3,8 +3,8 @@
 // the keys sorted with equal keys left in index order, which a stable LSD sort
 // started from the identity permutation gives.
 //
-// Design (after Merrill & Adinets' "onesweep"): one kernel builds the histograms
-// of every pass at once; then in each pass a workgroup ranks a tile (5632 32-bit
+// Design (after Merrill & Adinets' "onesweep"): the key kernels count the digits of
+// every pass at once; then in each pass a workgroup ranks a tile (5632 32-bit
 // or 6144 64-bit keys) with wavefront ballots and scatters it through LDS, so that
 // writes are contiguous per digit. A tile learns its global offsets in one of two
 // ways. Look-back: a decoupled look-back over earlier tiles (four status words per
@@ -38,23 +38,6 @@ __device__ __forceinline__ uint64_t pack_status(uint32_t epoch, uint64_t flag, u
 template <typename K>
 __device__ __forceinline__ uint32_t digit_of(K key, int shift) {
   return static_cast<uint32_t>(key >> shift) & 0xffu;
-}
-
-// Histogram of every pass's digit over all keys.
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_hist(const K* __restrict__ keys, int64_t n, int passes,
-                                                 uint32_t* __restrict__ hist) {
-  __shared__ uint32_t s_h[8 * kRadix];
-  hist_clear(s_h, passes);
-  const int64_t stride = int64_t(gridDim.x) * kBlock;
-  // every lane of a wavefront runs the same trip count so ballots see all lanes
-  const int64_t base0 = blockIdx.x * int64_t(kBlock) + (threadIdx.x & ~63);
-  for (int64_t base = base0; base < n; base += stride) {
-    int64_t i = base + (threadIdx.x & 63);
-    bool valid = i < n;
-    hist_add(valid ? keys[i] : K(0), valid, passes, s_h);
-  }
-  hist_flush(s_h, passes, hist);
 }
 
 // Passes of a host-sequenced sort that need not run, as a bit mask: a pass whose digit
@@ -488,23 +471,17 @@ void launch_sort_all_planned(void* keys0, void* keys1, uint32_t* vals0, uint32_t
                      0, s, keys0, keys1, vals0, vals1, n, plan, hist, tilectr, tilectr + 8, status, info);
 }
 
-template <typename K>
-int radix_sort_t(K* keys0, K* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, int bits, uint32_t* hist,
-                 bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status, uint32_t* info,
-                 hipStream_t s, bool clear) {
+}  // namespace
+
+int radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, int bits,
+               const uint32_t* hist, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status, uint32_t* info,
+               hipStream_t s) {
+  using K = uint64_t;
   const int passes = (bits + 7) / 8;
   if (n <= 1 || passes == 0) return 0;
   const int64_t tiles = ceil_div(n, 256 * sort_items<K>());
-  if (clear) {
-    fill_u32(tilectr, 0, 16, s);
-    fill_u32(reinterpret_cast<uint32_t*>(status), 0, sort_status_words(n, sizeof(K) == 8), s);
-  }
-  if (!hist_ready) {
-    fill_u32(hist, 0, passes * kRadix, s);
-    int hg = static_cast<int>(ceil_div(n, kBlock * 16));
-    if (hg > 2048) hg = 2048;
-    hipLaunchKernelGGL(k_hist<K>, dim3(hg), dim3(kBlock), 0, s, keys0, n, passes, hist);
-  }
+  fill_u32(tilectr, 0, 16, s);
+  fill_u32(reinterpret_cast<uint32_t*>(status), 0, sort_status_words(n, true), s);
   if (n <= kSortAllUnplanned) {
     if (n <= kSort4Max)
       launch_sort_all<K, 4>(keys0, keys1, vals0, vals1, n, passes, nullptr, hist, tilectr, status, info, s);
@@ -528,8 +505,6 @@ int radix_sort_t(K* keys0, K* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n
   }
   return cur;
 }
-
-}  // namespace
 
 int64_t sort_status_words(int64_t n, bool key64) {
   return ceil_div(n, key64 ? sort_tile<uint64_t>(n) : sort_tile<uint32_t>(n)) * kRadix * 2;
@@ -575,16 +550,6 @@ void radix_sort_planned(void* keys0, void* keys1, uint32_t* vals0, uint32_t* val
                          k64[0], k64[1], vals0, vals1, n, p, plan, static_cast<const uint32_t*>(nullptr), hist, tilectr,
                          status, static_cast<const uint32_t*>(nullptr), int64_t(0), info);
   }
-}
-
-int radix_sort(void* keys0, void* keys1, uint32_t* vals0, uint32_t* vals1, int64_t n, bool key64, int bits,
-               uint32_t* hist, bool hist_ready, uint32_t* pass_plan, uint32_t* tilectr, uint64_t* status,
-               uint32_t* info, hipStream_t s, bool clear) {
-  if (key64)
-    return radix_sort_t(static_cast<uint64_t*>(keys0), static_cast<uint64_t*>(keys1), vals0, vals1, n, bits, hist,
-                        hist_ready, pass_plan, tilectr, status, info, s, clear);
-  return radix_sort_t(static_cast<uint32_t*>(keys0), static_cast<uint32_t*>(keys1), vals0, vals1, n, bits, hist,
-                      hist_ready, pass_plan, tilectr, status, info, s, clear);
 }
 
 }  // namespace fdb

@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(KeyIn keys, int m_cap,
                                                      int64_t n, LeafSrc ls, int* __restrict__ other,
                                                      int* __restrict__ gamma, int* __restrict__ ends, float4* node_a,
                                                      float4* node_b, uint32_t* __restrict__ info,
-                                                     float4* __restrict__ cut, int* __restrict__ cut_n, int cut_div,
+                                                     float4* __restrict__ cut, int* __restrict__ cut_n,
                                                      const int* __restrict__ d_skip) {
   if (d_skip && *d_skip) return;
   constexpr int E = kRefitBlock + 1;  // edges L0-1 .. L0+255
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(KeyIn keys, int m_cap,
     if (cut) {
       // a child of at most span primitives under a larger parent is a cut node
       const int a0 = left ? i : far, a1 = sp, b0 = sp + 1, b1 = left ? far : j;
-      const int span = cut_span(m, cut_div);
+      const int span = cut_span(m);
       if (b1 - a0 + 1 > span) {
         if (a1 - a0 + 1 <= span)
           cut_add(cut, cut_n, a0 == a1 ? (kLeaf | static_cast<uint32_t>(a1)) : static_cast<uint32_t>(a1), a1,
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_build_up(KeyIn keys, int m_cap,
 // ends: m_cap words, the far-end exchange of meetings across workgroups.
 void build_t(const KeyIn& keys, int m_cap, const int* d_m, int dim, const float* xs, int64_t n_pts,
              const LeafSrc& ls, float4* node_a, float4* node_b, int* rope, int* leaf_rope, int* ends, int* other,
-             int* gamma, uint32_t* info, hipStream_t s, float4* cut, int* cut_n, bool ends_ready, int cut_div,
+             int* gamma, uint32_t* info, hipStream_t s, float4* cut, int* cut_n, bool ends_ready,
              const int* d_skip) {
   if (m_cap <= 0) return;
   int g = static_cast<int>(ceil_div(m_cap, kBlock));
@@ -330,16 +330,16 @@ void build_t(const KeyIn& keys, int m_cap, const int* d_m, int dim, const float*
     const dim3 rg(static_cast<unsigned>(ceil_div(m_cap, kRefitBlock))), rb(kRefitBlock);
     if (dim == 3 && buf)
       hipLaunchKernelGGL((k_build_up<3, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
+                         node_a, node_b, info, cut, cut_n, d_skip);
     else if (dim == 3)
       hipLaunchKernelGGL((k_build_up<3, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
+                         node_a, node_b, info, cut, cut_n, d_skip);
     else if (buf)
       hipLaunchKernelGGL((k_build_up<2, true>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
+                         node_a, node_b, info, cut, cut_n, d_skip);
     else
       hipLaunchKernelGGL((k_build_up<2, false>), rg, rb, 0, s, keys, m_cap, d_m, xs, n_pts, ls, other, gamma, ends,
-                         node_a, node_b, info, cut, cut_n, cut_div, d_skip);
+                         node_a, node_b, info, cut, cut_n, d_skip);
   }
   hipLaunchKernelGGL(k_ropes, dim3(g), dim3(kBlock), 0, s, other, m_cap, d_m, rope, leaf_rope, d_skip);
 }
@@ -349,9 +349,9 @@ void build_t(const KeyIn& keys, int m_cap, const int* d_m, int dim, const float*
 void build_lbvh(const void* keys, const int* d_key64, int m, int dim, const float* xs, int64_t n_pts,
                 const float4* prim_lo, const float4* prim_hi, float4* node_a, float4* node_b, int* rope,
                 int* leaf_rope, int* ends, int* other, int* gamma, const int* d_m, uint32_t* info, hipStream_t s,
-                float4* cut, int* cut_n, bool ends_ready, int cut_div, const int* d_skip) {
+                float4* cut, int* cut_n, bool ends_ready, const int* d_skip) {
   build_t(KeyIn{keys, d_key64, 1}, m, d_m, dim, xs, n_pts, LeafSrc{prim_lo, prim_hi}, node_a, node_b, rope, leaf_rope,
-          ends, other, gamma, info, s, cut, cut_n, ends_ready, cut_div, d_skip);
+          ends, other, gamma, info, s, cut, cut_n, ends_ready, d_skip);
 }
 
 }  // namespace fdb
